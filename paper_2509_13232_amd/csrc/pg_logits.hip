@@ -1,6 +1,6 @@
 // Logits-in form of the clipped policy-gradient loss: the [T x V] logits already
 // exist and are streamed once (forward) or read once and written once
-// (backward).  Pure HBM streaming; one workgroup per token row, 16-byte accesses.
+// (backward).  Pure HBM streaming, 16 bytes per lane and access.
 #include <algorithm>
 
 #include "pg_common.hpp"
@@ -8,13 +8,26 @@
 
 namespace spo {
 
+// What bounds both kernels is memory, and how many separate streams of addresses are open at once:
+// a workgroup per row of 304 KB keeps 2048 rows open (8192 x 151936 bf16: forward 451 us, backward
+// 968 us = 5.5 and 5.1 TB/s).  So a row is cut into short segments, neighbouring workgroups work on
+// neighbouring segments, and the chip sweeps the array nearly in order (350 us = 7.1 TB/s and
+// 772 us = 6.4 TB/s).  The forward takes two rounds of kLseGroup 16-byte loads per thread (a third of
+// the partial results of one round; with four 368 us), the second on its way while the first is worked
+// on; the backward has nothing to carry along and takes one round of kGradGroup (four per thread:
+// 806 us, two rounds of four 842 us).
+// Arrays that no cache can hold are read and written with the non-temporal hint: the forward of the
+// next pass then finds no modified lines of the gradients to drain first (forward 437 -> 350 us).
 constexpr int kRowThreads = 256;
+constexpr int kLseGroup = 4, kLseRounds = 2, kGradGroup = 2;
+constexpr int64_t kStreamBytes = int64_t(256) << 20;  // the Infinity Cache
 
+// 16 bytes of a row as floats and back
 template <typename T> struct Vec;
 template <> struct Vec<bf16_t> {
     static constexpr int N = 8;
-    __device__ static __forceinline__ void load(const bf16_t *p, float (&x)[8]) {
-        const uint4 u = *reinterpret_cast<const uint4 *>(p);
+    static constexpr uint32_t kNegInf = 0xff80ff80u;  // a pair of -inf
+    __device__ static __forceinline__ void unpack(const uint4 &u, float (&x)[8]) {
         const uint32_t w[4] = {u.x, u.y, u.z, u.w};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -22,138 +35,230 @@ template <> struct Vec<bf16_t> {
             x[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
         }
     }
-    __device__ static __forceinline__ void store(bf16_t *p, const float (&x)[8]) {
-        uint4 u;
-        u.x = pack_bf16x2(x[0], x[1]); u.y = pack_bf16x2(x[2], x[3]);
-        u.z = pack_bf16x2(x[4], x[5]); u.w = pack_bf16x2(x[6], x[7]);
-        *reinterpret_cast<uint4 *>(p) = u;
+    __device__ static __forceinline__ uint4 pack(const float (&x)[8]) {
+        return make_uint4(pack_bf16x2_rn(x[0], x[1]), pack_bf16x2_rn(x[2], x[3]), pack_bf16x2_rn(x[4], x[5]),
+                          pack_bf16x2_rn(x[6], x[7]));
     }
     __device__ static __forceinline__ float get(const bf16_t *p) { return bf16_to_f32(*p); }
     __device__ static __forceinline__ void put(bf16_t *p, float v) { *p = f32_to_bf16(v); }
 };
 template <> struct Vec<float> {
     static constexpr int N = 4;
-    __device__ static __forceinline__ void load(const float *p, float (&x)[4]) {
-        const float4 u = *reinterpret_cast<const float4 *>(p);
-        x[0] = u.x; x[1] = u.y; x[2] = u.z; x[3] = u.w;
+    static constexpr uint32_t kNegInf = 0xff800000u;
+    __device__ static __forceinline__ void unpack(const uint4 &u, float (&x)[4]) {
+        x[0] = __uint_as_float(u.x); x[1] = __uint_as_float(u.y); x[2] = __uint_as_float(u.z); x[3] = __uint_as_float(u.w);
     }
-    __device__ static __forceinline__ void store(float *p, const float (&x)[4]) {
-        *reinterpret_cast<float4 *>(p) = make_float4(x[0], x[1], x[2], x[3]);
+    __device__ static __forceinline__ uint4 pack(const float (&x)[4]) {
+        return make_uint4(__float_as_uint(x[0]), __float_as_uint(x[1]), __float_as_uint(x[2]), __float_as_uint(x[3]));
     }
     __device__ static __forceinline__ float get(const float *p) { return *p; }
     __device__ static __forceinline__ void put(float *p, float v) { *p = v; }
 };
 
-// running (max, sum of exp(x - max)) with one more value / merged with another pair
+// 16 bytes from an address that may only be aligned to the element (the hardware takes it), and to a
+// 16-byte boundary; Stream: with the non-temporal hint
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+template <typename T> struct Unaligned16;
+template <> struct Unaligned16<bf16_t> { typedef u32x4_t V __attribute__((aligned(2))); };
+template <> struct Unaligned16<float> { typedef u32x4_t V __attribute__((aligned(4))); };
+
+template <bool Stream, typename T>
+__device__ __forceinline__ uint4 load16(const T *p) {
+    const auto *q = reinterpret_cast<const typename Unaligned16<T>::V *>(p);
+    const u32x4_t v = Stream ? __builtin_nontemporal_load(q) : *q;
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+template <bool Stream>
+__device__ __forceinline__ void store16(uint4 *p, const uint4 &u) {
+    const u32x4_t v = {u.x, u.y, u.z, u.w};
+    if (Stream) __builtin_nontemporal_store(v, reinterpret_cast<u32x4_t *>(p));
+    else *reinterpret_cast<u32x4_t *>(p) = v;
+}
+
+// Elements [0, n) of a row segment as: a head of single elements up to the first 16-byte boundary,
+// whole vectors, a tail of single elements.
+struct Span {
+    int head, nvec, tail;  // a segment has fewer than 2^31 elements
+    template <typename T>
+    __device__ __forceinline__ Span(const T *p, int n) {
+        const int off = static_cast<int>((16 - reinterpret_cast<uintptr_t>(p) % 16) % 16 / sizeof(T));
+        head = off < n ? off : n;
+        nvec = (n - head) / Vec<T>::N;
+        tail = n - head - nvec * Vec<T>::N;
+    }
+};
+
+// Which part of which row a group of threads works on: `unit` counts (row, segment) pairs, the
+// segments of a row next to each other.
+struct RowGrid {
+    int64_t rows, seg_len;  // elements per segment
+    int nseg, per_wg;       // segments per row, (row, segment) pairs per workgroup
+    __host__ __device__ uint32_t units() const { return static_cast<uint32_t>(rows * nseg); }  // < 2^32: a grid's limit
+    __host__ unsigned blocks() const { return static_cast<unsigned>(ceil_div(rows * nseg, per_wg)); }
+};
+
+// running (max, sum of exp(x - max)) merged with another pair
 __device__ __forceinline__ void lse_merge(float &m, float &s, float om, float os) {
     const float nm = fmaxf(m, om);
     s = s * __builtin_amdgcn_exp2f((m - nm) * kLog2e) + os * __builtin_amdgcn_exp2f((om - nm) * kLog2e);
     m = nm;
 }
 
-// One row per workgroup: (max, sum-exp) of the row and the target's logit.
-template <typename T, bool kVector>
+// (max, sum-exp) of one segment of a row, by TR threads (a workgroup or one wavefront of it), and the
+// target's logit.  part_max / part_sum [segment][row].
+template <typename T, int TR, bool Stream>
 __global__ void __launch_bounds__(kRowThreads)
-logits_row_lse_kernel(const T *__restrict__ logits, int64_t V, const int32_t *__restrict__ target,
-                      float *__restrict__ row_max, float *__restrict__ row_sum, float *__restrict__ z_target) {
-    __shared__ float sm[kRowThreads / kWave], ss[kRowThreads / kWave];
-    constexpr int N = Vec<T>::N;
-    const int64_t t = blockIdx.x;
-    const T *row = logits + t * V;
+logits_row_lse_kernel(const T *__restrict__ logits, int64_t V, RowGrid grid, const int32_t *__restrict__ target,
+                      float *__restrict__ part_max, float *__restrict__ part_sum, float *__restrict__ z_target) {
+    constexpr int N = Vec<T>::N, U = kLseGroup;
+    const uint32_t unit = blockIdx.x * (kRowThreads / TR) + threadIdx.x / TR;
+    const int tid = threadIdx.x % TR;
+    if (unit >= grid.units()) return;  // TR < kRowThreads only: no barrier below in that case
+    const uint32_t seg = unit % static_cast<uint32_t>(grid.nseg);
+    const int64_t t = unit / static_cast<uint32_t>(grid.nseg), e0 = seg * grid.seg_len;
+    const T *p = logits + t * V + e0;
+    const Span sp(p, static_cast<int>(V - e0 < grid.seg_len ? V - e0 : grid.seg_len));
+    float zt = 0.0f;
+    if (seg == 0 && tid == 0) {
+        const int64_t y = target[t];  // an id outside [0, V) gives NaN instead of a read out of bounds
+        zt = (y >= 0 && y < V) ? Vec<T>::get(logits + t * V + y) : __builtin_nanf("");
+    }
+    // the few elements outside the whole vectors, one per thread
     float m = kNegBig, s = 0.0f;
-    if (kVector) {
-        // four independent 16-byte loads in flight per thread before any of them is used
-        constexpr int U = 4;
-        const int64_t step = static_cast<int64_t>(kRowThreads) * N;
-        for (int64_t v0 = static_cast<int64_t>(threadIdx.x) * N; v0 < V; v0 += U * step) {
-            float x[U][N];
+    if (tid < sp.head + sp.tail) {
+        const float x = Vec<T>::get(p + (tid < sp.head ? tid : tid + sp.nvec * N));
+        m = fmaxf(m, x);
+        s = __builtin_amdgcn_exp2f((x - m) * kLog2e);
+    }
+    const T *body = p + sp.head;
+    auto request = [&](uint4 (&v)[U], int i0) {
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (v0 + u * step < V) Vec<T>::load(row + v0 + u * step, x[u]);
-            // one new maximum and one rescaling of the running sum for the whole group of loads
-            float mx = m;
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (v0 + u * step >= V) break;
-#pragma unroll
-                for (int i = 0; i < N; ++i) mx = fmaxf(mx, x[u][i]);
-            }
-            const float nm2 = -mx * kLog2e;
-            float a = 0.0f;
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (v0 + u * step >= V) break;
-#pragma unroll
-                for (int i = 0; i < N; ++i) a += __builtin_amdgcn_exp2f(fmaf(x[u][i], kLog2e, nm2));
-            }
-            s = s * __builtin_amdgcn_exp2f((m - mx) * kLog2e) + a;
-            m = mx;
+        for (int u = 0; u < U; ++u) {
+            const int i = i0 + u * TR;
+            v[u] = make_uint4(Vec<T>::kNegInf, Vec<T>::kNegInf, Vec<T>::kNegInf, Vec<T>::kNegInf);  // counts as nothing
+            if (i < sp.nvec) v[u] = load16<Stream>(body + i * N);
         }
-    } else {
-        for (int64_t v = threadIdx.x; v < V; v += kRowThreads) lse_merge(m, s, Vec<T>::get(row + v), 1.0f);
+    };
+    uint4 cur[U], nxt[U];
+    request(cur, tid);
+    for (int i0 = tid; i0 < sp.nvec; i0 += U * TR) {
+        request(nxt, i0 + U * TR);
+        // one new maximum and one rescaling of the running sum for the whole group
+        float x[U][N], mx = m;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            Vec<T>::unpack(cur[u], x[u]);
+#pragma unroll
+            for (int i = 0; i < N; ++i) mx = fmaxf(mx, x[u][i]);
+        }
+        const float nm2 = -mx * kLog2e;
+        float a[U] = {};
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int i = 0; i < N; ++i) a[u] += __builtin_amdgcn_exp2f(fmaf(x[u][i], kLog2e, nm2));
+        s = s * __builtin_amdgcn_exp2f((m - mx) * kLog2e) + ((a[0] + a[1]) + (a[2] + a[3]));
+        m = mx;
+#pragma unroll
+        for (int u = 0; u < U; ++u) cur[u] = nxt[u];
     }
 #pragma unroll
     for (int o = kWave / 2; o > 0; o >>= 1) lse_merge(m, s, __shfl_xor(m, o, kWave), __shfl_xor(s, o, kWave));
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (lane == 0) { sm[wave] = m; ss[wave] = s; }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        float M = sm[0], S = ss[0];
-        for (int w = 1; w < kRowThreads / kWave; ++w) lse_merge(M, S, sm[w], ss[w]);
-        row_max[t] = M;
-        row_sum[t] = S;
-        const int64_t y = target[t];  // an id outside [0, V) gives NaN instead of a read out of bounds
-        z_target[t] = (y >= 0 && y < V) ? Vec<T>::get(row + y) : __builtin_nanf("");
+    if constexpr (TR > kWave) {
+        __shared__ float sm[TR / kWave], ss[TR / kWave];
+        const int wave = threadIdx.x >> 6;
+        if ((threadIdx.x & 63) == 0) { sm[wave] = m; ss[wave] = s; }
+        __syncthreads();
+        m = sm[0];
+        s = ss[0];
+        for (int w = 1; w < TR / kWave; ++w) lse_merge(m, s, sm[w], ss[w]);
+    }
+    if (tid == 0) {
+        part_max[seg * grid.rows + t] = m;
+        part_sum[seg * grid.rows + t] = s;
+        if (seg == 0) z_target[t] = zt;
     }
 }
 
-// d_logits[t][v] = g[t] * ([v == target[t]] - exp(z[t][v] - lse[t])); rows whose
-// scale is zero are written as zeros without being read.
-template <typename T, bool kVector>
+// d_logits[t][v] = g[t] * ([v == target[t]] - exp(z[t][v] - lse[t])) of one segment of a row (at most
+// kGradGroup vectors per thread); rows whose scale is zero are written as zeros without being read.
+// Vectors are aligned on the output side; the input's (the same boundaries unless the two arrays are
+// offset against each other) may be unaligned.
+template <typename T, int TR, bool Stream>
 __global__ void __launch_bounds__(kRowThreads)
-logits_row_grad_kernel(const T *__restrict__ logits, int64_t V, const int32_t *__restrict__ target,
+logits_row_grad_kernel(const T *__restrict__ logits, int64_t V, RowGrid grid, const int32_t *__restrict__ target,
                        const float *__restrict__ lse, const float *__restrict__ g, T *__restrict__ d_logits) {
-    constexpr int N = Vec<T>::N;
-    const int64_t t = blockIdx.x;
-    const T *row = logits + t * V;
-    T *out = d_logits + t * V;
-    const float gt = g[t], nl = -lse[t] * kLog2e;
-    const int64_t y = target[t];
-    if (kVector) {
-        constexpr int U = 4;
-        const int64_t step = static_cast<int64_t>(kRowThreads) * N;
-        for (int64_t v0 = static_cast<int64_t>(threadIdx.x) * N; v0 < V; v0 += U * step) {
-            float x[U][N];
-            if (gt != 0.0f) {
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-                    if (v0 + u * step < V) Vec<T>::load(row + v0 + u * step, x[u]);
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int64_t v = v0 + u * step;
-                if (v >= V) break;
-                if (gt != 0.0f) {
-#pragma unroll
-                    for (int i = 0; i < N; ++i)
-                        x[u][i] = (v + i == y ? gt : 0.0f) - gt * __builtin_amdgcn_exp2f(fmaf(x[u][i], kLog2e, nl));
-                } else {
-#pragma unroll
-                    for (int i = 0; i < N; ++i) x[u][i] = 0.0f;
-                }
-                Vec<T>::store(out + v, x[u]);
-            }
-        }
-    } else {
-        for (int64_t v = threadIdx.x; v < V; v += kRowThreads) {
-            float x = 0.0f;
-            if (gt != 0.0f) x = (v == y ? gt : 0.0f) - gt * __builtin_amdgcn_exp2f(fmaf(Vec<T>::get(row + v), kLog2e, nl));
-            Vec<T>::put(out + v, x);
-        }
+    constexpr int N = Vec<T>::N, U = kGradGroup;
+    const uint32_t unit = blockIdx.x * (kRowThreads / TR) + threadIdx.x / TR;
+    const int tid = threadIdx.x % TR;
+    if (unit >= grid.units()) return;
+    const uint32_t nseg = static_cast<uint32_t>(grid.nseg);
+    const int64_t t = unit / nseg, e0 = (unit % nseg) * grid.seg_len;
+    const T *p = logits + t * V + e0;
+    T *out = d_logits + t * V + e0;
+    const Span sp(out, static_cast<int>(V - e0 < grid.seg_len ? V - e0 : grid.seg_len));
+    const float gt = g[t], ng = -gt, nl = -lse[t] * kLog2e;
+    const int64_t yl = static_cast<int64_t>(target[t]) - e0;  // target's place in the segment
+    const int y = yl >= 0 && yl < grid.seg_len ? static_cast<int>(yl) : -1;
+    auto grad = [&](float x) { return ng * __builtin_amdgcn_exp2f(fmaf(x, kLog2e, nl)); };
+    if (tid < sp.head + sp.tail) {
+        const int e = tid < sp.head ? tid : tid + sp.nvec * N;
+        Vec<T>::put(out + e, gt != 0.0f ? grad(Vec<T>::get(p + e)) + (e == y ? gt : 0.0f) : 0.0f);
     }
+    const T *body = p + sp.head;
+    uint4 *dst = reinterpret_cast<uint4 *>(out + sp.head);
+    if (gt == 0.0f) {
+        for (int i = tid; i < sp.nvec; i += TR) store16<Stream>(dst + i, make_uint4(0u, 0u, 0u, 0u));
+        return;
+    }
+    const int yv = y >= sp.head ? (y - sp.head) / N : -1, yr = y >= sp.head ? (y - sp.head) % N : 0;
+    uint4 v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (tid + u * TR < sp.nvec) v[u] = load16<Stream>(body + (tid + u * TR) * N);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int iv = tid + u * TR;
+        if (iv >= sp.nvec) break;
+        float x[N];
+        Vec<T>::unpack(v[u], x);
+#pragma unroll
+        for (int i = 0; i < N; ++i) x[i] = grad(x[i]);
+        if (iv == yv) {
+#pragma unroll
+            for (int i = 0; i < N; ++i)
+                if (i == yr) x[i] += gt;
+        }
+        store16<Stream>(dst + iv, Vec<T>::pack(x));
+    }
+}
+
+// How the rows are cut: segments of `rounds` rounds of `group` vectors per thread.  Rows that give a
+// workgroup less than half a round go to single wavefronts, four to a workgroup.
+static RowGrid row_grid(const spo_pg_desc *d, int group, int rounds) {
+    const int64_t n = d->dtype == SPO_FP32 ? 4 : 8;  // elements per vector
+    RowGrid g;
+    g.rows = d->T;
+    const bool narrow = d->V * 2 <= kRowThreads * group * n;
+    g.per_wg = narrow ? kRowThreads / kWave : 1;
+    g.seg_len = (narrow ? kWave : kRowThreads) * group * n * rounds;
+    g.nseg = static_cast<int>(ceil_div(d->V, g.seg_len));
+    return g;
+}
+
+// the forward goes down to one round per segment where two would leave compute units without their
+// eight workgroups (256 x 151936 bf16: 17.4 against 18.0 us)
+static RowGrid lse_grid(const spo_pg_desc *d) {
+    const RowGrid g = row_grid(d, kLseGroup, kLseRounds);
+    return g.units() >= 2048 ? g : row_grid(d, kLseGroup, 1);
+}
+
+static bool streams(const spo_pg_desc *d) {
+    return d->T * d->V * (d->dtype == SPO_FP32 ? 4 : 2) > kStreamBytes;
 }
 
 struct LogitsFwdPlan {
+    RowGrid grid;
     float *row_max, *row_sum, *z_target;
     FwdPartial *partials;
     int64_t nblk_tok;
@@ -164,18 +269,40 @@ static LogitsFwdPlan plan_logits_fwd(const spo_pg_desc *d, void *ws) {
     LogitsFwdPlan p;
     const int64_t Tn = std::max<int64_t>(d->T, 1);
     p.nblk_tok = ceil_div(Tn, kTokThreads);
+    p.grid = lse_grid(d);
     Arena a(ws);
-    p.row_max = a.take<float>(Tn);
-    p.row_sum = a.take<float>(Tn);
+    p.row_max = a.take<float>(Tn * p.grid.nseg);
+    p.row_sum = a.take<float>(Tn * p.grid.nseg);
     p.z_target = a.take<float>(Tn);
     p.partials = a.take<FwdPartial>(p.nblk_tok);
     p.bytes = a.used;
     return p;
 }
 
+template <typename T, int TR, bool Stream>
+static void launch_row_lse(const spo_pg_desc *d, const LogitsFwdPlan &p, hipStream_t s) {
+    logits_row_lse_kernel<T, TR, Stream><<<p.grid.blocks(), kRowThreads, 0, s>>>(
+        static_cast<const T *>(d->logits), d->V, p.grid, d->target, p.row_max, p.row_sum, p.z_target);
+}
 template <typename T>
-static bool vector_ok(const void *p, int64_t V) {
-    return V % Vec<T>::N == 0 && reinterpret_cast<uintptr_t>(p) % 16 == 0;
+static void launch_row_lse(const spo_pg_desc *d, const LogitsFwdPlan &p, hipStream_t s) {
+    if (p.grid.per_wg > 1) launch_row_lse<T, kWave, false>(d, p, s);
+    else if (streams(d)) launch_row_lse<T, kRowThreads, true>(d, p, s);
+    else launch_row_lse<T, kRowThreads, false>(d, p, s);
+}
+
+template <typename T, int TR, bool Stream>
+static void launch_row_grad(const spo_pg_desc *d, const RowGrid &grid, const float *lse, const float *g, void *d_logits,
+                            hipStream_t s) {
+    logits_row_grad_kernel<T, TR, Stream><<<grid.blocks(), kRowThreads, 0, s>>>(
+        static_cast<const T *>(d->logits), d->V, grid, d->target, lse, g, static_cast<T *>(d_logits));
+}
+template <typename T>
+static void launch_row_grad(const spo_pg_desc *d, const float *lse, const float *g, void *d_logits, hipStream_t s) {
+    const RowGrid grid = row_grid(d, kGradGroup, 1);
+    if (grid.per_wg > 1) launch_row_grad<T, kWave, false>(d, grid, lse, g, d_logits, s);
+    else if (streams(d)) launch_row_grad<T, kRowThreads, true>(d, grid, lse, g, d_logits, s);
+    else launch_row_grad<T, kRowThreads, false>(d, grid, lse, g, d_logits, s);
 }
 
 int logits_fwd_workspace(const spo_pg_desc *d, size_t *bytes) {
@@ -188,24 +315,12 @@ int logits_fwd(const spo_pg_desc *d, float *loss, float *logp, float *lse, float
     const LogitsFwdPlan p = plan_logits_fwd(d, ws);
     if (ws_bytes < p.bytes) return SPO_EWORKSPACE;
     if (d->T > 0) {
-        const unsigned rows = static_cast<unsigned>(d->T);
         ScopedKernelTimer timer(kTimeLogitsFwd, s);
-        if (d->dtype == SPO_BF16) {
-            const bf16_t *lg = static_cast<const bf16_t *>(d->logits);
-            if (vector_ok<bf16_t>(lg, d->V))
-                logits_row_lse_kernel<bf16_t, true><<<rows, kRowThreads, 0, s>>>(lg, d->V, d->target, p.row_max, p.row_sum, p.z_target);
-            else
-                logits_row_lse_kernel<bf16_t, false><<<rows, kRowThreads, 0, s>>>(lg, d->V, d->target, p.row_max, p.row_sum, p.z_target);
-        } else {
-            const float *lg = static_cast<const float *>(d->logits);
-            if (vector_ok<float>(lg, d->V))
-                logits_row_lse_kernel<float, true><<<rows, kRowThreads, 0, s>>>(lg, d->V, d->target, p.row_max, p.row_sum, p.z_target);
-            else
-                logits_row_lse_kernel<float, false><<<rows, kRowThreads, 0, s>>>(lg, d->V, d->target, p.row_max, p.row_sum, p.z_target);
-        }
+        if (d->dtype == SPO_BF16) launch_row_lse<bf16_t>(d, p, s);
+        else launch_row_lse<float>(d, p, s);
     }
     token_loss_kernel<<<static_cast<unsigned>(p.nblk_tok), kTokThreads, 0, s>>>(
-        p.row_max, p.row_sum, 1, 0, p.z_target, d->T, d->old_logp, d->mask, d->adv_norm, d->cu_seqlens, d->B,
+        p.row_max, p.row_sum, p.grid.nseg, d->T, p.z_target, d->T, d->old_logp, d->mask, d->adv_norm, d->cu_seqlens, d->B,
         d->eps_low, d->eps_high, logp, lse, p.partials);
     loss_finalize_kernel<<<1, kTokThreads, 0, s>>>(p.partials, p.nblk_tok, loss, stats);
     return launch_status();
@@ -241,23 +356,9 @@ int logits_bwd(const spo_pg_desc *d, const float *logp, const float *lse, float 
     grad_scale_kernel<<<static_cast<unsigned>(ceil_div(d->T, kTokThreads)), kTokThreads, 0, s>>>(
         logp, d->old_logp, d->mask, d->adv_norm, d->cu_seqlens, d->B, d->T, d->T, d->eps_low, d->eps_high, grad_loss,
         p.count, p.g);
-    const unsigned rows = static_cast<unsigned>(d->T);
     ScopedKernelTimer timer(kTimeLogitsBwd, s);
-    if (d->dtype == SPO_BF16) {
-        const bf16_t *lg = static_cast<const bf16_t *>(d->logits);
-        bf16_t *dl = static_cast<bf16_t *>(d_logits);
-        if (vector_ok<bf16_t>(lg, d->V) && vector_ok<bf16_t>(dl, d->V))
-            logits_row_grad_kernel<bf16_t, true><<<rows, kRowThreads, 0, s>>>(lg, d->V, d->target, lse, p.g, dl);
-        else
-            logits_row_grad_kernel<bf16_t, false><<<rows, kRowThreads, 0, s>>>(lg, d->V, d->target, lse, p.g, dl);
-    } else {
-        const float *lg = static_cast<const float *>(d->logits);
-        float *dl = static_cast<float *>(d_logits);
-        if (vector_ok<float>(lg, d->V) && vector_ok<float>(dl, d->V))
-            logits_row_grad_kernel<float, true><<<rows, kRowThreads, 0, s>>>(lg, d->V, d->target, lse, p.g, dl);
-        else
-            logits_row_grad_kernel<float, false><<<rows, kRowThreads, 0, s>>>(lg, d->V, d->target, lse, p.g, dl);
-    }
+    if (d->dtype == SPO_BF16) launch_row_grad<bf16_t>(d, lse, p.g, d_logits, s);
+    else launch_row_grad<float>(d, lse, p.g, d_logits, s);
     return launch_status();
 }
 

@@ -439,6 +439,42 @@ def test_logits_in_matches_oracle(spo, oracle, dtype, V):
     assert not dl[torch.as_tensor(case.mask == 0)].any()
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("T,V,offset", [
+    (5, 1, 0), (5, 7, 0), (9, 9, 3),              # rows shorter than one 16-byte vector, or just longer
+    (7, 1024, 0), (7, 1025, 0), (6, 4097, 1),     # a row to a wavefront, and the first rows past that
+    (3, 16384, 0), (3, 33001, 5),                 # segments of one round, whole and ragged, and rows off a 16-byte boundary
+    (2100, 2055, 1)])                             # enough rows for two rounds per segment
+def test_logits_in_row_edges(spo, oracle, dtype, T, V, offset):
+    say(f"logits-in {dtype} T={T} V={V} offset={offset}")
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator().manual_seed(T * 131 + V)
+    logits = (torch.randn((T, V), generator=g) * 3.0).to(tdt)
+    rng = np.random.default_rng([T, V])
+    tg = rng.integers(0, V, T).astype(np.int32)
+    adv = np.array([0.7, -1.3], np.float32)
+    cu = np.array([0, T // 2, T], np.int32)
+    lg64 = f64(logits)
+    logp = oracle.pg_loss_fwd(None, None, tg, np.zeros(T), None, adv.astype(np.float64), cu, 0.2, 0.28, logits=lg64)["logp"]
+    old = (logp + rng.choice([-0.1, 0.1, 0.5], T)).astype(np.float32)     # ratios 1.105, 0.905, 0.61: off the bounds
+    ref = oracle.pg_loss_fwd(None, None, tg, old.astype(np.float64), None, adv.astype(np.float64), cu, 0.2, 0.28, logits=lg64)
+    rb = oracle.pg_loss_bwd(None, None, tg, old.astype(np.float64), None, adv.astype(np.float64), cu, 0.2, 0.28, logits=lg64)
+    buf = torch.zeros(T * V + offset, dtype=tdt, device="cuda")
+    buf[offset:] = logits.cuda().flatten()
+    t = lambda x: torch.as_tensor(x).cuda()
+    desc = spo.make_desc(None, None, t(tg), t(old), None, t(adv), t(cu), 0.2, 0.28, logits=buf[offset:].view(T, V))
+    loss, lp, lse, _ = spo.spo_pg_loss_fwd(desc)
+    dl = spo.spo_pg_loss_bwd(desc, lp, lse, 1.0)
+    torch.cuda.synchronize()
+    # fp32 sums of at most 33001 exponentials: a few 1e-7 relative
+    np.testing.assert_allclose(f64(lse), ref["lse"], atol=1e-5, rtol=0)
+    np.testing.assert_allclose(f64(lp), ref["logp"], atol=1e-5, rtol=0)
+    assert abs(loss.item() - ref["loss"]) <= 1e-5
+    if V > 1:   # entry by entry: one rounding to the storage type (bf16: 2^-9), differences near zero against the row's scale
+        scale = np.abs(rb["d_logits"]) + 1e-3 * np.abs(rb["d_logits"]).max(axis=1, keepdims=True)
+        assert (np.abs(f64(dl) - rb["d_logits"]) <= (2e-4 if dtype == "fp32" else 5e-3) * scale).all()
+
+
 def test_target_id_out_of_range_gives_nan_not_garbage(spo, oracle):
     # sampled-token ids are not validated on the host; an id outside [0, V) must neither read out of
     # bounds nor leave a stale number behind: the token's log-prob is NaN, all other tokens are untouched
