@@ -10,7 +10,6 @@ namespace spo {
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kNegBig = -1.0e30f;  // finite stand-in for -inf in running maxima
-constexpr int kTokThreads = 256;
 
 struct Surrogate {
     float ratio, obj;
@@ -28,59 +27,160 @@ __device__ __forceinline__ Surrogate surrogate(float logp, float old_logp, float
     return r;
 }
 
-// Per-block partial sums of the forward, reduced later in block order.
+// Per-block partial sums of the forward, added in block order by the last block to finish.
 struct FwdPartial {
     double sum_obj, count, clipped, sum_ratio;
 };
 
-// One thread per token: merges the per-split (running max, sum of exponentials)
-// pairs into lse, forms logp and the surrogate, and reduces this block's masked
-// sums.  z_target[t] is the logit of the sampled token.  The per-token arrays start at token
-// t_base of the batch (a multiple of the block size; 0 unless the batch is walked in pieces).
-static __global__ void __launch_bounds__(kTokThreads)
-token_loss_kernel(const float *__restrict__ part_max, const float *__restrict__ part_sum, int nsplit,
-                  int64_t split_stride, const float *__restrict__ z_target, int64_t T,
-                  const float *__restrict__ old_logp, const uint8_t *__restrict__ mask,
-                  const float *__restrict__ adv_norm, const int32_t *__restrict__ cu, int B, float eps_low,
-                  float eps_high, float *__restrict__ logp_out, float *__restrict__ lse_out,
-                  FwdPartial *__restrict__ partials, int64_t t_base = 0) {
-    __shared__ double scratch[kTokThreads / kWave];
-    const int64_t t = static_cast<int64_t>(blockIdx.x) * kTokThreads + threadIdx.x;
-    double so = 0.0, cnt = 0.0, clp = 0.0, sr = 0.0;
-    if (t < T) {
-        float mx = kNegBig;
-        for (int i = 0; i < nsplit; ++i) mx = fmaxf(mx, part_max[i * split_stride + t]);
-        float s = 0.0f;
-        for (int i = 0; i < nsplit; ++i) s += part_sum[i * split_stride + t] * expf(part_max[i * split_stride + t] - mx);
-        const float lse = mx + logf(s);
-        const float logp = z_target[t] - lse;
-        lse_out[t] = lse;
-        logp_out[t] = logp;
-        if (!mask || mask[t]) {
-            const float adv = adv_norm[response_of_token(cu, B, t_base + t)];
-            const Surrogate r = surrogate(logp, old_logp[t], adv, eps_low, eps_high);
-            so = logp == logp ? r.obj : logp;  // a NaN log-prob (target id outside the vocabulary) reaches the loss
-            cnt = 1.0;
-            clp = r.active ? 0.0 : 1.0;
-            sr = r.ratio;
-        }
-    }
-    so = block_sum(so, scratch);
-    cnt = block_sum(cnt, scratch);
-    clp = block_sum(clp, scratch);
-    sr = block_sum(sr, scratch);
-    if (threadIdx.x == 0) partials[blockIdx.x] = FwdPartial{so, cnt, clp, sr};
+// Response offsets a token workgroup keeps in LDS (a binary search through global memory is seven
+// dependent loads for 128 responses).
+constexpr int kCuStaged = 1024;
+
+// cu - or, where B + 1 offsets fit, a copy of it in LDS - for response_of_token.  A barrier follows before it is read.
+__device__ __forceinline__ const int32_t *stage_offsets(const int32_t *cu, int B, int32_t *lds) {
+    if (B >= kCuStaged) return cu;
+    for (int i = threadIdx.x; i <= B; i += blockDim.x) lds[i] = cu[i];
+    return lds;
 }
 
-// One workgroup sums the block partials in a fixed order and writes the loss.
-static __global__ void __launch_bounds__(kTokThreads)
-loss_finalize_kernel(const FwdPartial *__restrict__ partials, int64_t nblocks, float *__restrict__ loss,
-                     float *__restrict__ stats) {
-    __shared__ double scratch[kTokThreads / kWave];
+// What the per-token kernels of a call read; every per-token array starts at token t_base of the batch.
+struct TokenInputs {
+    const float *old_logp;
+    const uint8_t *mask;      // NULL: all ones
+    const float *adv_norm;
+    const int32_t *cu;
+    int B;
+    float eps_low, eps_high;
+    int64_t T, t_base;
+};
+
+static inline TokenInputs token_inputs(const spo_pg_desc *d, int64_t t0, int64_t T) {
+    return TokenInputs{d->old_logp + t0, d->mask ? d->mask + t0 : nullptr, d->adv_norm, d->cu_seqlens, d->B,
+                       d->eps_low, d->eps_high, T, t0};
+}
+
+// What a piece of the batch needs for its backward, where the weight of the loss is known beforehand:
+// g[t] (see grad_factor; zero for T <= t < T_pad), and for batches without a mask what turns stored
+// scaled probabilities into operands of the contractions (see the one-call form): c[t] and one entry
+// of Q per token.
+struct TokenGrad {
+    float *g;                // NULL: forward only
+    int64_t T_pad;
+    const double *count;     // number of unmasked tokens
+    float grad_loss;
+    float *c;                // NULL: no scaled probabilities
+    uint16_t *Q;
+    int64_t q_blk, V;
+    const int32_t *target;
+};
+
+// -(mask / M) * A * ratio * [unclipped branch is the minimum] * grad_loss
+__device__ __forceinline__ float grad_factor(const Surrogate &r, float adv, double M, float grad_loss) {
+    return r.active ? -(adv * r.ratio * grad_loss) / static_cast<float>(M) : 0.0f;
+}
+
+// One lane per token, 64 tokens per workgroup.  The (running max, sum of exponentials) pairs of the
+// vocabulary splits are merged by all wavefronts of the workgroup together (1191 tokens x 408 splits
+// by one thread per token, a load at a time: 312 us); the first wavefront forms lse, logp, the
+// surrogate and, where asked for, the gradient factors.  z_target[t] is the logit of the sampled
+// token.  The workgroup that finishes last (counted in *done, zero beforehand, over all launches of
+// the call: total_blocks) adds the partial sums in order and writes the loss.
+constexpr int kTokThreads = kWave;  // tokens per workgroup
+
+static __global__ void __launch_bounds__(1024)
+token_loss_kernel(const float *__restrict__ part_max, const float *__restrict__ part_sum, int nsplit,
+                  int64_t split_stride, const float *__restrict__ z_target, TokenInputs in, float *__restrict__ logp_out,
+                  float *__restrict__ lse_out, FwdPartial *__restrict__ partials, TokenGrad gr, int64_t total_blocks,
+                  uint32_t *__restrict__ done, float *__restrict__ loss, float *__restrict__ stats) {
+    __shared__ float sm[16][kWave], ss[16][kWave];
+    __shared__ int32_t cu_lds[kCuStaged];
+    __shared__ double scratch[16];
+    __shared__ int last;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwave = blockDim.x >> 6;
+    const int64_t t = static_cast<int64_t>(blockIdx.x) * kTokThreads + lane;
+    const int32_t *cu = stage_offsets(in.cu, in.B, cu_lds);
+    float m = kNegBig, s = 0.0f;
+    if (t < in.T) {
+        constexpr int U = 8;  // pairs requested at a time
+        for (int i0 = wave; i0 < nsplit; i0 += U * nwave) {
+            float pm[U], ps[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = i0 + u * nwave;
+                pm[u] = i < nsplit ? part_max[i * split_stride + t] : kNegBig;
+                ps[u] = i < nsplit ? part_sum[i * split_stride + t] : 0.0f;
+            }
+            float nm = m;
+#pragma unroll
+            for (int u = 0; u < U; ++u) nm = fmaxf(nm, pm[u]);
+            s *= expf(m - nm);
+#pragma unroll
+            for (int u = 0; u < U; ++u) s += ps[u] * expf(pm[u] - nm);
+            m = nm;
+        }
+    }
+    sm[wave][lane] = m;
+    ss[wave][lane] = s;
+    __syncthreads();
     double so = 0.0, cnt = 0.0, clp = 0.0, sr = 0.0;
-    for (int64_t i = threadIdx.x; i < nblocks; i += kTokThreads) {
-        const FwdPartial p = partials[i];
-        so += p.sum_obj; cnt += p.count; clp += p.clipped; sr += p.sum_ratio;
+    if (wave == 0) {
+        float g = 0.0f, c = 0.0f;
+        if (t < in.T) {
+            for (int w = 1; w < nwave; ++w) m = fmaxf(m, sm[w][lane]);
+            s = 0.0f;
+            for (int w = 0; w < nwave; ++w) s += ss[w][lane] * expf(sm[w][lane] - m);
+            const float lse = m + logf(s);
+            const float logp = z_target[t] - lse;
+            lse_out[t] = lse;
+            logp_out[t] = logp;
+            if (!in.mask || in.mask[t]) {
+                const float adv = in.adv_norm[response_of_token(cu, in.B, in.t_base + t)];
+                const float old = in.old_logp[t];
+                const Surrogate r = surrogate(logp, old, adv, in.eps_low, in.eps_high);
+                so = logp == logp ? r.obj : logp;  // a NaN log-prob (target id outside the vocabulary) reaches the loss
+                cnt = 1.0;
+                clp = r.active ? 0.0 : 1.0;
+                sr = r.ratio;
+                if (gr.g) g = grad_factor(r, adv, *gr.count, gr.grad_loss);
+                if (gr.c && g != 0.0f) {
+                    c = -g * r.ratio;  // the ratio is finite and positive where g != 0
+                    const int64_t y = gr.target[t];
+                    if (y >= 0 && y < gr.V)
+                        gr.Q[(y / 64) * gr.q_blk + t * 64 + y % 64] = f32_to_bf16(expf(old) - 1.0f / r.ratio);
+                }
+            }
+        }
+        if (gr.g && t < gr.T_pad) {
+            gr.g[t] = g;
+            if (gr.c) gr.c[t] = c;
+        }
+        so = wave_sum(so);
+        cnt = wave_sum(cnt);
+        clp = wave_sum(clp);
+        sr = wave_sum(sr);
+        if (lane == 0) {
+            // Seen by the last workgroup on whatever XCD it runs: stores and loads that act beyond the
+            // L2 caches of the XCDs (agent scope), and the count goes up when the stores have arrived.
+            auto put = [](double *p, double v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+            FwdPartial *p = partials + in.t_base / kTokThreads + blockIdx.x;
+            put(&p->sum_obj, so);
+            put(&p->count, cnt);
+            put(&p->clipped, clp);
+            put(&p->sum_ratio, sr);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            last = total_blocks == 1 ||
+                   __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == total_blocks - 1;
+        }
+    }
+    __syncthreads();
+    if (!last) return;
+    so = cnt = clp = sr = 0.0;
+    auto get = [](const double *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    for (int64_t i = threadIdx.x; i < total_blocks; i += blockDim.x) {
+        so += get(&partials[i].sum_obj);
+        cnt += get(&partials[i].count);
+        clp += get(&partials[i].clipped);
+        sr += get(&partials[i].sum_ratio);
     }
     so = block_sum(so, scratch);
     cnt = block_sum(cnt, scratch);
@@ -97,37 +197,73 @@ loss_finalize_kernel(const FwdPartial *__restrict__ partials, int64_t nblocks, f
     }
 }
 
-// count[0] = number of unmasked tokens.  One workgroup, fixed order.
-static __global__ void __launch_bounds__(1024)
-mask_count_kernel(const uint8_t *__restrict__ mask, int64_t T, double *__restrict__ count) {
-    __shared__ double scratch[1024 / kWave];
-    double c = 0.0;
-    if (mask) {
-        for (int64_t t = threadIdx.x; t < T; t += 1024) c += mask[t] ? 1.0 : 0.0;
-        c = block_sum(c, scratch);
-    } else {
-        c = static_cast<double>(T);
-    }
-    if (threadIdx.x == 0) count[0] = c;
+// Wavefronts per workgroup of token_loss_kernel: four splits each, or enough to add many workgroups' partial sums.
+static inline unsigned token_threads(int nsplit, int64_t total_blocks) {
+    unsigned w = 1;
+    while (w < 16 && (static_cast<int>(w) * 4 < nsplit || static_cast<int64_t>(w) * 512 < total_blocks)) w *= 2;
+    return w * kWave;
 }
 
-// g[t] = -(mask_t / M) * A * ratio_t * [unclipped branch is the minimum] * grad_loss;
-// entries T <= t < T_pad are zero so that padded tokens contribute nothing.  t_base as above.
-static __global__ void __launch_bounds__(kTokThreads)
-grad_scale_kernel(const float *__restrict__ logp, const float *__restrict__ old_logp,
-                  const uint8_t *__restrict__ mask, const float *__restrict__ adv_norm,
-                  const int32_t *__restrict__ cu, int B, int64_t T, int64_t T_pad, float eps_low, float eps_high,
-                  float grad_loss, const double *__restrict__ count, float *__restrict__ g, int64_t t_base = 0) {
-    const int64_t t = static_cast<int64_t>(blockIdx.x) * kTokThreads + threadIdx.x;
+// Number of set entries of mask[0..T), by one workgroup of up to 1024 threads; every thread receives it.
+__device__ __forceinline__ int64_t count_mask(const uint8_t *__restrict__ mask, int64_t T, int *scratch) {
+    auto set_bytes = [](uint32_t x) {  // bytes that are not zero
+        x |= x >> 4;
+        x |= x >> 2;
+        x |= x >> 1;
+        return __popc(x & 0x01010101u);
+    };
+    const int64_t off = (16 - reinterpret_cast<uintptr_t>(mask) % 16) % 16, head = off < T ? off : T;
+    const int64_t nvec = (T - head) / 16, tail0 = head + nvec * 16;
+    const uint4 *v = reinterpret_cast<const uint4 *>(mask + head);
+    int c = 0;
+    if (threadIdx.x < head) c += mask[threadIdx.x] != 0;
+    if (tail0 + threadIdx.x < T) c += mask[tail0 + threadIdx.x] != 0;
+#pragma unroll 4
+    for (int64_t i = threadIdx.x; i < nvec; i += blockDim.x) {
+        const uint4 u = v[i];
+        c += set_bytes(u.x) + set_bytes(u.y) + set_bytes(u.z) + set_bytes(u.w);
+    }
+    return block_sum(c, scratch);  // T < 2^31
+}
+
+// count[0] = number of unmasked tokens.  One workgroup.
+static __global__ void __launch_bounds__(1024)
+mask_count_kernel(const uint8_t *__restrict__ mask, int64_t T, double *__restrict__ count) {
+    __shared__ int scratch[1024 / kWave];
+    const int64_t c = mask ? count_mask(mask, T, scratch) : T;
+    if (threadIdx.x == 0) count[0] = static_cast<double>(c);
+}
+
+// g[t] (see grad_factor) from the forward's log-probs; entries T <= t < T_pad are zero so that padded
+// tokens contribute nothing.  count == NULL: every workgroup counts the mask itself (kCountInline).
+constexpr int kGradThreads = 256;
+constexpr int64_t kCountInline = 32768;  // tokens: 8 loads per thread; above, one workgroup counts for all
+
+static __global__ void __launch_bounds__(kGradThreads)
+grad_scale_kernel(const float *__restrict__ logp, TokenInputs in, int64_t T_pad, float grad_loss,
+                  const double *__restrict__ count, float *__restrict__ g) {
+    __shared__ int32_t cu_lds[kCuStaged];
+    __shared__ int scratch[kGradThreads / kWave];
+    const int64_t t = static_cast<int64_t>(blockIdx.x) * kGradThreads + threadIdx.x;
+    const int32_t *cu = stage_offsets(in.cu, in.B, cu_lds);
+    const double M = count ? count[0] : static_cast<double>(in.mask ? count_mask(in.mask, in.T, scratch) : in.T);
+    __syncthreads();
     if (t >= T_pad) return;
     float out = 0.0f;
-    const double M = count[0];
-    if (t < T && M > 0.0 && (!mask || mask[t])) {
-        const float adv = adv_norm[response_of_token(cu, B, t_base + t)];
-        const Surrogate r = surrogate(logp[t], old_logp[t], adv, eps_low, eps_high);
-        if (r.active) out = -(adv * r.ratio * grad_loss) / static_cast<float>(M);
+    if (t < in.T && (!in.mask || in.mask[t])) {
+        const float adv = in.adv_norm[response_of_token(cu, in.B, in.t_base + t)];
+        out = grad_factor(surrogate(logp[t], in.old_logp[t], adv, in.eps_low, in.eps_high), adv, M, grad_loss);
     }
     g[t] = out;
+}
+
+// The gradient factors of a whole batch; `count` is scratch for batches with a long mask.
+static inline void launch_grad_scale(const spo_pg_desc *d, const float *logp, int64_t T_pad, float grad_loss,
+                                     double *count, float *g, hipStream_t s) {
+    const bool apart = d->mask && d->T > kCountInline;
+    if (apart) mask_count_kernel<<<1, 1024, 0, s>>>(d->mask, d->T, count);
+    grad_scale_kernel<<<static_cast<unsigned>(ceil_div(T_pad, kGradThreads)), kGradThreads, 0, s>>>(
+        logp, token_inputs(d, 0, d->T), T_pad, grad_loss, apart ? count : nullptr, g);
 }
 
 // Host-side checks common to forward and backward.

@@ -232,8 +232,9 @@ __device__ __forceinline__ float dot8(const uint4 a, const uint4 b) {
 template <typename T_>
 __global__ void __launch_bounds__(256)
 target_logit_kernel(const T_ *__restrict__ X, const T_ *__restrict__ Wvh, int64_t H, int64_t V, int64_t T,
-                    const int32_t *__restrict__ target, float *__restrict__ z_target) {
+                    const int32_t *__restrict__ target, float *__restrict__ z_target, uint32_t *__restrict__ done) {
     const int64_t t = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *done = 0u;  // counts the workgroups of the token kernel
     const int lane = threadIdx.x & 63;
     if (t >= T) return;
     const int64_t y = target[t];
@@ -1004,10 +1005,10 @@ dz_from_logits_kernel(const uint16_t *__restrict__ Z, int64_t z_blk, const float
 
 // ref2[t] = r_t * log2(e); 0 where the token has no valid target logit, where old_logp is not
 // finite, and for the padding rows Tv <= t < Tzp (their stored rows stay finite and are multiplied by 0).
-__global__ void __launch_bounds__(kTokThreads)
+__global__ void __launch_bounds__(256)
 probs_reference_kernel(const float *__restrict__ z_target, const float *__restrict__ old_logp, int64_t Tv, int64_t Tzp,
                        float *__restrict__ ref2) {
-    const int64_t t = static_cast<int64_t>(blockIdx.x) * kTokThreads + threadIdx.x;
+    const int64_t t = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
     if (t >= Tzp) return;
     float r = 0.0f;
     if (t < Tv) {
@@ -1015,24 +1016,6 @@ probs_reference_kernel(const float *__restrict__ z_target, const float *__restri
         if (!(fabsf(r) < 3.0e38f)) r = 0.0f;  // NaN or infinite
     }
     ref2[t] = r;
-}
-
-// c[t] = -g[t] * ratio_t (0 for tokens without a gradient and for the padding rows), and for the
-// tokens with a gradient Q[t][y_t] = exp(old_logp_t) - 1 / ratio_t.
-__global__ void __launch_bounds__(kTokThreads)
-probs_patch_kernel(const float *__restrict__ g, const float *__restrict__ logp, const float *__restrict__ old_logp,
-                   const int32_t *__restrict__ target, int64_t V, int64_t Tv, int64_t Tzp, uint16_t *__restrict__ Q,
-                   int64_t q_blk, float *__restrict__ c) {
-    const int64_t t = static_cast<int64_t>(blockIdx.x) * kTokThreads + threadIdx.x;
-    if (t >= Tzp) return;
-    float ct = 0.0f;
-    if (t < Tv && g[t] != 0.0f) {
-        const float ratio = expf(logp[t] - old_logp[t]);  // as in the surrogate: finite and positive where g != 0
-        ct = -g[t] * ratio;
-        const int64_t y = target[t];
-        if (y >= 0 && y < V) Q[(y / kBlockK) * q_blk + t * kBlockK + y % kBlockK] = f32_to_bf16(expf(old_logp[t]) - 1.0f / ratio);
-    }
-    c[t] = ct;
 }
 
 // dst[t][:] = bf16(c[t] * src[t][:]) for t < rows_pad (c is 0 from the last valid row on: zeros).
@@ -1094,6 +1077,7 @@ struct FwdPlan {
     // workspace
     float *part_max, *part_sum, *z_target;
     FwdPartial *partials;
+    uint32_t *done;
     bf16_t *Xs, *Ws, *Wvh;  // split-expanded operands (fp32), [V,H] copy (HV layout)
     float *W32;             // [V,H] copy of an fp32 head given as [H,V]
     size_t bytes;
@@ -1112,6 +1096,7 @@ static FwdPlan plan_fwd(const spo_pg_desc *d, void *ws) {
     p.part_sum = a.take<float>(static_cast<size_t>(p.nsplit) * p.T_pad);
     p.z_target = a.take<float>(p.T_pad);
     p.partials = a.take<FwdPartial>(p.nblk_tok);
+    p.done = a.take<uint32_t>(1);
     p.Xs = p.Ws = p.Wvh = nullptr;
     p.W32 = nullptr;
     if (d->dtype == SPO_FP32) {
@@ -1174,16 +1159,15 @@ int fused_fwd(const spo_pg_desc *d, float *loss, float *logp, float *lse, float 
         if (d->dtype == SPO_FP32)
             target_logit_kernel<float><<<grid1(d->T, 4), 256, 0, s>>>(
                 static_cast<const float *>(d->hidden), d->w_layout == SPO_W_HV ? p.W32 : static_cast<const float *>(d->W),
-                d->H, d->V, d->T, d->target, p.z_target);
+                d->H, d->V, d->T, d->target, p.z_target, p.done);
         else
             target_logit_kernel<bf16_t><<<grid1(d->T, 4), 256, 0, s>>>(
                 static_cast<const bf16_t *>(d->hidden), d->w_layout == SPO_W_HV ? p.Wvh : static_cast<const bf16_t *>(d->W),
-                d->H, d->V, d->T, d->target, p.z_target);
+                d->H, d->V, d->T, d->target, p.z_target, p.done);
     }
-    token_loss_kernel<<<static_cast<unsigned>(p.nblk_tok), kTokThreads, 0, s>>>(
-        p.part_max, p.part_sum, p.nsplit, p.T_pad, p.z_target, d->T, d->old_logp, d->mask, d->adv_norm,
-        d->cu_seqlens, d->B, d->eps_low, d->eps_high, logp, lse, p.partials);
-    loss_finalize_kernel<<<1, kTokThreads, 0, s>>>(p.partials, p.nblk_tok, loss, stats);
+    token_loss_kernel<<<static_cast<unsigned>(p.nblk_tok), token_threads(p.nsplit, p.nblk_tok), 0, s>>>(
+        p.part_max, p.part_sum, p.nsplit, p.T_pad, p.z_target, token_inputs(d, 0, d->T), logp, lse, p.partials,
+        TokenGrad{}, p.nblk_tok, p.done, loss, stats);
     return launch_status();
 }
 
@@ -1306,10 +1290,7 @@ int fused_bwd(const spo_pg_desc *d, const float *logp, const float *lse, float g
         }
         return launch_status();
     }
-    mask_count_kernel<<<1, 1024, 0, s>>>(d->mask, T, p.count);
-    grad_scale_kernel<<<grid1(p.T_pad, kTokThreads), kTokThreads, 0, s>>>(
-        logp, d->old_logp, d->mask, d->adv_norm, d->cu_seqlens, d->B, T, p.T_pad, d->eps_low, d->eps_high, grad_loss,
-        p.count, p.g);
+    launch_grad_scale(d, logp, p.T_pad, grad_loss, p.count, p.g, s);
     // vocabulary-major head for the recompute, hidden-major head for dHidden
     const bf16_t *Wk;
     if (d->dtype == SPO_FP32) {
@@ -1406,6 +1387,7 @@ struct FbPlan {
     float *g, *z_target, *part_max, *part_sum, *offs, *dW_acc, *W32, *dx_part, *dw_tail, *cscale;
     bool dense;  // no loss mask: the sweep stores what the contractions read (see probs_reference_kernel)
     FwdPartial *partials;
+    uint32_t *done;
     int32_t *act_idx, *n_act;
     float4 *tok;
     uint16_t *Z;
@@ -1449,6 +1431,7 @@ static FbPlan plan_fb(const spo_pg_desc *d, int64_t chunk_tokens, void *ws, bool
     p.g = a.take<float>(p.T_pad);
     p.z_target = a.take<float>(p.T_pad);
     p.partials = a.take<FwdPartial>(p.nblk_tok);
+    p.done = a.take<uint32_t>(1);
     p.part_max = a.take<float>(static_cast<size_t>(p.nsplit) * p.Tz);
     p.part_sum = a.take<float>(static_cast<size_t>(p.nsplit) * p.Tz);
     p.dense = d->mask == nullptr;
@@ -1502,10 +1485,11 @@ int fused_fwd_bwd(const spo_pg_desc *d, float grad_loss, float *loss, float *log
             const int64_t words = d_W_dtype == SPO_FP32 ? V * H : V * H / 2;
             fill_zero_kernel<<<grid1(words), 256, 0, s>>>(static_cast<uint32_t *>(d_W), words);
         }
-        loss_finalize_kernel<<<1, kTokThreads, 0, s>>>(p.partials, 0, loss, stats);
+        token_loss_kernel<<<1, kTokThreads, 0, s>>>(nullptr, nullptr, 0, 0, nullptr, token_inputs(d, 0, 0), logp, lse,
+                                                    p.partials, TokenGrad{}, 1, p.done, loss, stats);
         return launch_status();
     }
-    mask_count_kernel<<<1, 1024, 0, s>>>(d->mask, T, p.count);
+    mask_count_kernel<<<1, d->mask ? 1024 : kWave, 0, s>>>(d->mask, T, p.count);
     // the head as the kernels read it: one row per vocabulary entry for the logits, one row per
     // hidden unit (blocked over the vocabulary) for dHidden
     const char *Wk;
@@ -1519,7 +1503,7 @@ int fused_fwd_bwd(const spo_pg_desc *d, float grad_loss, float *loss, float *log
         Wk = reinterpret_cast<const char *>(p.Ws);
         if (d_hidden) launch_transpose(w32, V, H, H, p.WT, p.V_blk, H, 0, s);
         target_logit_kernel<float><<<grid1(T, 4), 256, 0, s>>>(static_cast<const float *>(d->hidden), w32, H, V, T,
-                                                               d->target, p.z_target);
+                                                               d->target, p.z_target, p.done);
     } else {
         const bf16_t *Wvh = static_cast<const bf16_t *>(d->W);
         if (d->w_layout == SPO_W_HV) {
@@ -1529,7 +1513,7 @@ int fused_fwd_bwd(const spo_pg_desc *d, float grad_loss, float *loss, float *log
         Wk = reinterpret_cast<const char *>(Wvh);
         if (d_hidden) launch_transpose(Wvh, V, H, H, p.WT, p.V_blk, H, 0, s);
         target_logit_kernel<bf16_t><<<grid1(T, 4), 256, 0, s>>>(static_cast<const bf16_t *>(d->hidden), Wvh, H, V, T,
-                                                                d->target, p.z_target);
+                                                                d->target, p.z_target, p.done);
     }
     if (d_hidden && !p.dense) {  // rows of tokens without a gradient stay zero (without a mask every row is written)
         const int64_t words = T * H / (d_hidden_dtype == SPO_FP32 ? 1 : 2);
@@ -1545,7 +1529,7 @@ int fused_fwd_bwd(const spo_pg_desc *d, float grad_loss, float *loss, float *log
             Xk = reinterpret_cast<const char *>(p.Xs);
         }
         const SweepMap map(Tzp / TL::BN, p.nVt, p.nsplit);
-        if (p.dense) probs_reference_kernel<<<grid1(Tzp, kTokThreads), kTokThreads, 0, s>>>(p.z_target + t0, d->old_logp + t0, Tv, Tzp, p.offs);
+        if (p.dense) probs_reference_kernel<<<grid1(Tzp), 256, 0, s>>>(p.z_target + t0, d->old_logp + t0, Tv, Tzp, p.offs);
         {
             ScopedKernelTimer timer(kTimeFwdSweep, s);
             if (p.dense)
@@ -1557,18 +1541,20 @@ int fused_fwd_bwd(const spo_pg_desc *d, float grad_loss, float *loss, float *log
                     Wk, p.Kc * 2, V, Xk, p.Kc * 2, Tv, static_cast<int>(p.Kc / kBK), map.nsplit, map.nTt, map.nVt, Tzp,
                     p.part_max, p.part_sum, p.Z, Tzp * kBlockK, p.offs);
         }
-        token_loss_kernel<<<grid1(Tv, kTokThreads), kTokThreads, 0, s>>>(
-            p.part_max, p.part_sum, map.nsplit, Tzp, p.z_target + t0, Tv, d->old_logp + t0, d->mask ? d->mask + t0 : nullptr,
-            d->adv_norm, d->cu_seqlens, d->B, d->eps_low, d->eps_high, logp + t0, lse + t0, p.partials + t0 / kTokThreads,
-            t0);
-        if (!d_hidden && !d_W) continue;
-        grad_scale_kernel<<<grid1(Tzp, kTokThreads), kTokThreads, 0, s>>>(
-            logp + t0, d->old_logp + t0, d->mask ? d->mask + t0 : nullptr, d->adv_norm, d->cu_seqlens, d->B, Tv, Tzp,
-            d->eps_low, d->eps_high, grad_loss, p.count, p.g + t0, t0);
+        const bool back = d_hidden || d_W;
+        TokenGrad gr{};
+        if (back) gr = TokenGrad{p.g + t0, Tzp, p.count, grad_loss, nullptr, nullptr, 0, V, d->target + t0};
+        if (back && p.dense) {
+            gr.c = p.cscale;
+            gr.Q = p.Z;
+            gr.q_blk = Tzp * kBlockK;
+        }
+        token_loss_kernel<<<grid1(back ? Tzp : Tv, kTokThreads), token_threads(map.nsplit, p.nblk_tok), 0, s>>>(
+            p.part_max, p.part_sum, map.nsplit, Tzp, p.z_target + t0, token_inputs(d, t0, Tv), logp + t0, lse + t0,
+            p.partials, gr, back ? ceil_div(p.T_pad, kTokThreads) : ceil_div(T, kTokThreads), p.done, loss, stats);
+        if (!back) continue;
         if (p.dense) {
             // the contractions run on what the sweep stored: every row of the piece, scaled by c_t
-            probs_patch_kernel<<<grid1(Tzp, kTokThreads), kTokThreads, 0, s>>>(
-                p.g + t0, logp + t0, d->old_logp + t0, d->target + t0, V, Tv, Tzp, p.Z, Tzp * kBlockK, p.cscale);
             const bf16_t *Q = p.Z;
             if (d_hidden) {
                 ScopedKernelTimer timer(kTimeDHidden, s);
@@ -1636,7 +1622,6 @@ int fused_fwd_bwd(const spo_pg_desc *d, float grad_loss, float *loss, float *log
                                   0, Tzp * kBlockK, s, 1, nullptr, p.dw_tail);
         }
     }
-    loss_finalize_kernel<<<1, kTokThreads, 0, s>>>(p.partials, ceil_div(T, kTokThreads), loss, stats);
     if (need_acc) f32_to_bf16_kernel<<<grid1(V * H), 256, 0, s>>>(p.dW_acc, static_cast<bf16_t *>(d_W), V * H);
     return launch_status();
 }

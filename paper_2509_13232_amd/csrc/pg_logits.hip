@@ -105,14 +105,16 @@ __device__ __forceinline__ void lse_merge(float &m, float &s, float om, float os
 }
 
 // (max, sum-exp) of one segment of a row, by TR threads (a workgroup or one wavefront of it), and the
-// target's logit.  part_max / part_sum [segment][row].
+// target's logit.  part_max / part_sum [segment][row].  Also clears *done.
 template <typename T, int TR, bool Stream>
 __global__ void __launch_bounds__(kRowThreads)
 logits_row_lse_kernel(const T *__restrict__ logits, int64_t V, RowGrid grid, const int32_t *__restrict__ target,
-                      float *__restrict__ part_max, float *__restrict__ part_sum, float *__restrict__ z_target) {
+                      float *__restrict__ part_max, float *__restrict__ part_sum, float *__restrict__ z_target,
+                      uint32_t *__restrict__ done) {
     constexpr int N = Vec<T>::N, U = kLseGroup;
     const uint32_t unit = blockIdx.x * (kRowThreads / TR) + threadIdx.x / TR;
     const int tid = threadIdx.x % TR;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *done = 0u;  // for the kernel that follows
     if (unit >= grid.units()) return;  // TR < kRowThreads only: no barrier below in that case
     const uint32_t seg = unit % static_cast<uint32_t>(grid.nseg);
     const int64_t t = unit / static_cast<uint32_t>(grid.nseg), e0 = seg * grid.seg_len;
@@ -261,6 +263,7 @@ struct LogitsFwdPlan {
     RowGrid grid;
     float *row_max, *row_sum, *z_target;
     FwdPartial *partials;
+    uint32_t *done;
     int64_t nblk_tok;
     size_t bytes;
 };
@@ -275,6 +278,7 @@ static LogitsFwdPlan plan_logits_fwd(const spo_pg_desc *d, void *ws) {
     p.row_sum = a.take<float>(Tn * p.grid.nseg);
     p.z_target = a.take<float>(Tn);
     p.partials = a.take<FwdPartial>(p.nblk_tok);
+    p.done = a.take<uint32_t>(1);
     p.bytes = a.used;
     return p;
 }
@@ -282,7 +286,8 @@ static LogitsFwdPlan plan_logits_fwd(const spo_pg_desc *d, void *ws) {
 template <typename T, int TR, bool Stream>
 static void launch_row_lse(const spo_pg_desc *d, const LogitsFwdPlan &p, hipStream_t s) {
     logits_row_lse_kernel<T, TR, Stream><<<p.grid.blocks(), kRowThreads, 0, s>>>(
-        static_cast<const T *>(d->logits), d->V, p.grid, d->target, p.row_max, p.row_sum, p.z_target);
+        static_cast<const T *>(d->logits), d->V, p.grid, d->target, p.row_max, p.row_sum, p.z_target,
+        p.done);
 }
 template <typename T>
 static void launch_row_lse(const spo_pg_desc *d, const LogitsFwdPlan &p, hipStream_t s) {
@@ -319,10 +324,9 @@ int logits_fwd(const spo_pg_desc *d, float *loss, float *logp, float *lse, float
         if (d->dtype == SPO_BF16) launch_row_lse<bf16_t>(d, p, s);
         else launch_row_lse<float>(d, p, s);
     }
-    token_loss_kernel<<<static_cast<unsigned>(p.nblk_tok), kTokThreads, 0, s>>>(
-        p.row_max, p.row_sum, p.grid.nseg, d->T, p.z_target, d->T, d->old_logp, d->mask, d->adv_norm, d->cu_seqlens, d->B,
-        d->eps_low, d->eps_high, logp, lse, p.partials);
-    loss_finalize_kernel<<<1, kTokThreads, 0, s>>>(p.partials, p.nblk_tok, loss, stats);
+    token_loss_kernel<<<static_cast<unsigned>(p.nblk_tok), token_threads(p.grid.nseg, p.nblk_tok), 0, s>>>(
+        p.row_max, p.row_sum, p.grid.nseg, d->T, p.z_target, token_inputs(d, 0, d->T), logp, lse, p.partials,
+        TokenGrad{}, p.nblk_tok, p.done, loss, stats);
     return launch_status();
 }
 
@@ -352,10 +356,7 @@ int logits_bwd(const spo_pg_desc *d, const float *logp, const float *lse, float 
     const LogitsBwdPlan p = plan_logits_bwd(d, ws);
     if (ws_bytes < p.bytes) return SPO_EWORKSPACE;
     if (d->T == 0) return SPO_OK;
-    mask_count_kernel<<<1, 1024, 0, s>>>(d->mask, d->T, p.count);
-    grad_scale_kernel<<<static_cast<unsigned>(ceil_div(d->T, kTokThreads)), kTokThreads, 0, s>>>(
-        logp, d->old_logp, d->mask, d->adv_norm, d->cu_seqlens, d->B, d->T, d->T, d->eps_low, d->eps_high, grad_loss,
-        p.count, p.g);
+    launch_grad_scale(d, logp, d->T, grad_loss, p.count, p.g, s);
     ScopedKernelTimer timer(kTimeLogitsBwd, s);
     if (d->dtype == SPO_BF16) launch_row_grad<bf16_t>(d, lse, p.g, d_logits, s);
     else launch_row_grad<float>(d, lse, p.g, d_logits, s);

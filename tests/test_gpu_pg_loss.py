@@ -475,6 +475,39 @@ def test_logits_in_row_edges(spo, oracle, dtype, T, V, offset):
         assert (np.abs(f64(dl) - rb["d_logits"]) <= (2e-4 if dtype == "fp32" else 5e-3) * scale).all()
 
 
+@pytest.mark.parametrize("T,B,offset", [
+    (63, 3, 0), (64, 3, 1), (65, 1, 15),            # one workgroup of tokens, whole and one more; masks off 16-byte boundaries
+    (5000, 1023, 3), (5000, 1024, 0),               # response offsets kept in LDS, and too many for it
+    (32768, 5, 7), (32769, 5, 2)])                  # longest mask that every workgroup counts, and the next
+def test_token_kernels_edges(spo, oracle, T, B, offset):
+    say(f"per-token kernels T={T} B={B} mask offset={offset}")
+    V = 8
+    rng = np.random.default_rng([T, B])
+    logits = (rng.standard_normal((T, V)) * 2).astype(np.float32)
+    tg = rng.integers(0, V, T).astype(np.int32)
+    adv = rng.standard_normal(B).astype(np.float32)
+    cu = np.concatenate([[0], np.sort(rng.integers(0, T + 1, B - 1)), [T]]).astype(np.int32)   # some responses empty
+    mask = (rng.random(T) < 0.7).astype(np.uint8)
+    o = lambda old: oracle.pg_loss_fwd(None, None, tg, old, mask, adv.astype(np.float64), cu, 0.2, 0.28, logits=logits.astype(np.float64))
+    old = (o(np.zeros(T))["logp"] + rng.choice([-0.1, 0.1, 0.5], T)).astype(np.float32)
+    ref = o(old.astype(np.float64))
+    rb = oracle.pg_loss_bwd(None, None, tg, old.astype(np.float64), mask, adv.astype(np.float64), cu, 0.2, 0.28,
+                            logits=logits.astype(np.float64))
+    t = lambda x: torch.as_tensor(x).cuda()
+    buf = torch.ones(T + offset, dtype=torch.uint8, device="cuda")
+    buf[offset:] = t(mask)
+    desc = spo.make_desc(None, None, t(tg), t(old), buf[offset:], t(adv), t(cu), 0.2, 0.28, logits=t(logits))
+    loss, lp, lse, stats = spo.spo_pg_loss_fwd(desc)
+    dl = spo.spo_pg_loss_bwd(desc, lp, lse, 1.0)
+    torch.cuda.synchronize()
+    np.testing.assert_allclose(f64(lp), ref["logp"], atol=1e-5, rtol=0)
+    st = f64(stats)
+    m = mask.astype(bool)
+    assert st[0] == ref["M"] and abs(st[1] - (1 - ref["active"][m].mean())) < 1e-6 and abs(st[2] - ref["ratio"][m].mean()) < 1e-4
+    assert abs(loss.item() - ref["loss"]) <= 1e-5
+    assert rel_l2(f64(dl), rb["d_logits"]) < 1e-5 and not dl[t(mask) == 0].any()
+
+
 def test_target_id_out_of_range_gives_nan_not_garbage(spo, oracle):
     # sampled-token ids are not validated on the host; an id outside [0, V) must neither read out of
     # bounds nor leave a stale number behind: the token's log-prob is NaN, all other tokens are untouched
