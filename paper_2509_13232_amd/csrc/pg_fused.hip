@@ -263,8 +263,56 @@ target_logit_kernel(const T_ *__restrict__ X, const T_ *__restrict__ Wvh, int64_
 // Tile rows (m) are vocabulary entries, tile columns (n) are tokens, so that each
 // lane owns FN tokens and reduces over the vocabulary inside its own registers.
 
-// Workgroup -> (token tile, vocabulary split) of the two kernels that form logits (the forward
-// sweep and the backward's recompute): a workgroup keeps its token tile and walks the vocabulary
+// Vocabulary splits of the two kernels that form logits (the forward sweep and the backward's
+// recompute).  A launch lasts about (rounds of workgroups on the chip) x (vocabulary tiles of the
+// longest workgroup), so among the multiples of 8 the count with the smallest product is taken (the
+// smallest such count: longer workgroups).  67 token tiles x 594 vocabulary tiles in 16 splits are
+// 5 rounds x 38 tiles = 190, in 40 splits 11 x 15 = 165, of 155.5 that the work divided by 256 units
+// comes to.  Fewer tiles than units: a workgroup each.
+template <typename U>
+__host__ __device__ static inline U sweep_cost(U nTt, U nVt, U ns) {
+    return (nTt * ns + kChipCUs - 1) / kChipCUs * ((nVt + ns - 1) / ns);
+}
+// Candidates: the multiples of 8 in [sweep_splits_lo, sweep_splits_hi].  From 16 token tiles on at least
+// 16 splits (workgroups that share lines drift apart on longer runs), at most about 4096 workgroups
+// (more gain nothing in balance and grow the partial results).
+__host__ __device__ static inline uint32_t sweep_splits_lo(uint32_t nTt) { return nTt >= 16 ? kSweepSplits : 8; }
+__host__ __device__ static inline uint32_t sweep_splits_hi(uint32_t nTt, uint32_t nVt, uint32_t cap) {
+    uint32_t hi = 4096 / nTt;
+    hi = hi < static_cast<uint32_t>(kSweepSplits) ? kSweepSplits : (hi > 512 ? 512 : hi);
+    hi = hi < nVt ? hi : nVt;
+    return hi < cap ? hi : cap;
+}
+constexpr uint32_t kNoSplitCap = 512;
+// cap: the most splits the caller has room for (at least kSweepSplits)
+static int sweep_splits(int64_t token_tiles, int64_t vocab_tiles, uint32_t cap = kNoSplitCap) {
+    const uint64_t nTt = token_tiles > 0 ? token_tiles : 1, nVt = vocab_tiles;
+    if (nTt * nVt <= kChipCUs && nVt <= cap) return static_cast<int>(nVt);
+    const uint64_t hi = sweep_splits_hi(static_cast<uint32_t>(nTt), static_cast<uint32_t>(nVt), cap);
+    uint64_t best = 0;
+    for (uint64_t ns = sweep_splits_lo(static_cast<uint32_t>(nTt)); ns <= hi; ns += 8)
+        if (!best || sweep_cost(nTt, nVt, ns) < sweep_cost(nTt, nVt, best)) best = ns;
+    return static_cast<int>(best ? best : hi);
+}
+// The same choice by a wavefront, one candidate per lane, where the number of token tiles is known on the
+// device only (the tiles of a chunk's gradients fit the memory: costs stay far below 2^22).
+__device__ __forceinline__ int sweep_splits_wave(uint32_t nTt, uint32_t nVt) {
+    if (nTt * nVt <= kChipCUs) return static_cast<int>(nVt);
+    const uint32_t hi = sweep_splits_hi(nTt, nVt, kNoSplitCap), ns = sweep_splits_lo(nTt) + 8 * (threadIdx.x & 63);
+    uint32_t key = ns <= hi ? sweep_cost(nTt, nVt, ns) << 10 | ns : 0xffffffffu;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const uint32_t k = __shfl_xor(key, o, kWave);
+        key = k < key ? k : key;
+    }
+    return __builtin_amdgcn_readfirstlane(static_cast<int>(key == 0xffffffffu ? hi : key & 1023u));
+}
+// The most workgroups (ids of SweepMap) that any number of token tiles up to nTt can ask for.
+static int64_t sweep_blocks_max(int64_t nTt, int64_t nVt) {
+    return std::min(nTt * std::min<int64_t>(nVt, kNoSplitCap), std::max<int64_t>(4096, nTt * kSweepSplits)) + 8;
+}
+
+// Workgroup -> (token tile, vocabulary split): a workgroup keeps its token tile and walks the vocabulary
 // tiles of its split.  Ids equal mod 8 run on the same XCD and share its L2: there, 32
 // consecutive workgroups are a patch of 4 token tiles x 8 splits (each hidden-state panel feeds
 // 8 of them, each head tile 4), and the eight XCDs work on the same splits of different token
@@ -272,36 +320,44 @@ target_logit_kernel(const T_ *__restrict__ X, const T_ *__restrict__ Wvh, int64_
 // the Infinity Cache.  (A 4 x 8 patch of tiles walked along the vocabulary, every head tile used by
 // one XCD only, made the recompute 3.6 % slower.)  More than 8 splits shorten a workgroup's
 // sweep: workgroups that share lines then have less time to drift apart.
+// Token tiles left over when their number is no multiple of 8 would give some XCDs a tile more than
+// others (5 tiles: three XCDs idle): those few are divided by splits instead, each XCD an eighth of the
+// vocabulary of all of them (1191 tokens at H = 4096, V = 151936: 1960 us -> 1196 us with the choice of splits).
 struct SweepMap {
-    int nsplit;
-    int64_t nTt, nVt, per_xcd;
-    // splits = 0: chosen here; otherwise the caller's number (kept when it is a multiple of 8 or below 8)
-    __host__ __device__ SweepMap(int64_t token_tiles, int64_t vocab_tiles, int splits = 0)
-        : nTt(token_tiles), nVt(vocab_tiles) {
-        int64_t ns = (2048 + (nTt > 0 ? nTt : 1) - 1) / (nTt > 0 ? nTt : 1);  // small batches: more splits fill the chip
-        ns = ns < kSweepSplits ? kSweepSplits : ns;
-        if (splits > 0) ns = splits;
-        ns = ns < nVt ? ns : nVt;
-        nsplit = static_cast<int>(ns >= 8 ? ns / 8 * 8 : ns);  // whole groups of 8 splits whenever there are 8
-        const int64_t x = (nTt + 7) / 8;
-        per_xcd = nsplit % 8 == 0 ? (x + 3) / 4 * 4 : x;  // whole patches of 4 when the splits come in groups of 8
-    }
-    __host__ __device__ int64_t blocks() const { return per_xcd * 8 * nsplit; }
-    // token tile jt and split of workgroup bid; false past the last token tile
-    __device__ bool tile(int64_t bid, int &split, int64_t &jt) const {
-        const int64_t xcd = bid & 7, q = bid >> 3;
-        if (nsplit % 8 == 0) {
-            const int groups = nsplit / 8, w = static_cast<int>(q & 31);
-            const int64_t patch = q >> 5;
-            split = static_cast<int>(patch % groups) * 8 + (w & 7);
-            jt = ((patch / groups) * 4 + (w >> 3)) * 8 + xcd;
-        } else {  // small problems: all splits of a token tile side by side
-            split = static_cast<int>(q % nsplit);
-            jt = (q / nsplit) * 8 + xcd;
+    uint32_t ns;
+    int64_t nTt, nVt, main_tt;  // tiles; token tiles that belong to one XCD each
+    __host__ __device__ SweepMap(int64_t token_tiles, int64_t vocab_tiles, int splits)
+        : ns(static_cast<uint32_t>(splits)), nTt(token_tiles), nVt(vocab_tiles), main_tt(token_tiles / 8 * 8) {}
+    __host__ __device__ int64_t blocks() const { return main_tt * ns + ((nTt - main_tt) * ns + 7) / 8 * 8; }
+    // token tile jt and split of workgroup bid; false for ids without work
+    __device__ bool tile(uint32_t bid, int &split, int64_t &jt) const {
+        const uint32_t xcd = bid & 7, q = bid >> 3, x = static_cast<uint32_t>(main_tt / 8);
+        if (q >= x * ns) {
+            const uint32_t r = static_cast<uint32_t>(nTt - main_tt), i = q - x * ns;
+            if (ns % 8 == 0) {  // token tiles side by side share the head tiles of a split
+                if (i >= r * (ns / 8)) return false;
+                split = static_cast<int>(xcd * (ns / 8) + i / r);
+                jt = main_tt + i % r;
+                return true;
+            }
+            const uint32_t j = i * 8 + xcd;
+            if (j >= r * ns) return false;
+            split = static_cast<int>(j % ns);
+            jt = main_tt + j / ns;
+            return true;
         }
-        return jt < nTt;
+        if (ns % 8 == 0) {  // rows of patches of 4 token tiles (the last row: what is left) x 8 splits
+            const uint32_t row = q / (4 * ns), i = q - row * 4 * ns, h = x - 4 * row < 4 ? x - 4 * row : 4;
+            const uint32_t g = i / (8 * h), w = i - g * 8 * h;
+            split = static_cast<int>(g * 8 + (w & 7));
+            jt = static_cast<int64_t>(row * 4 + (w >> 3)) * 8 + xcd;
+        } else {  // small vocabularies: all splits of a token tile side by side
+            split = static_cast<int>(q % ns);
+            jt = static_cast<int64_t>(q / ns) * 8 + xcd;
+        }
+        return true;
     }
-    __host__ __device__ int64_t first_tile(int split) const { return split * nVt / nsplit; }
+    __host__ __device__ int64_t first_tile(int split) const { return split * nVt / ns; }
 };
 
 constexpr int kSweepLds = TL::LDS_BYTES + TL::NT * 32;       // operand stages + the per-thread running state
@@ -525,16 +581,18 @@ fwd_sweep_kernel(const char *__restrict__ W, int64_t ldw_bytes, int64_t V, const
 __global__ void __launch_bounds__(TL::NT)
 recompute_dz_kernel(const char *__restrict__ W, int64_t ldw_bytes, int64_t V,
                     const char *__restrict__ X, int64_t ldx_bytes, int64_t T_valid, int KT,
-                    const float4 *__restrict__ tok, int64_t nVt, int64_t nTt, bf16_t *__restrict__ dZ,
+                    const float4 *__restrict__ tok, int64_t nVt, bf16_t *__restrict__ dZ,
                     int64_t dz_blk, const int32_t *__restrict__ n_act, int64_t row_base) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     static_assert(TL::BM % kBlockK == 0 && kBlockK == 4 * TL::MI && TL::FM % 4 == 0,
                   "a block of dZ is four MFMA blocks of vocabulary rows");
     const int act = static_cast<int>(active_rows(n_act, row_base, T_valid));
-    const SweepMap map(nTt, nVt);
+    if (act == 0) return;
+    const uint32_t act_tt = static_cast<uint32_t>((act + TL::BN - 1) / TL::BN);
+    const SweepMap map(act_tt, nVt, sweep_splits_wave(act_tt, static_cast<uint32_t>(nVt)));
     int split;
     int64_t jt;
-    if (!map.tile(blockIdx.x, split, jt) || jt * TL::BN >= act) return;  // past the last active token
+    if (!map.tile(blockIdx.x, split, jt)) return;
     const int tn = static_cast<int>(jt);
     const int vt0 = static_cast<int>(map.first_tile(split)), vt1 = static_cast<int>(map.first_tile(split + 1));
     auto tile_ops = [&](int tile_m, int tile_n) {
@@ -1088,7 +1146,7 @@ static FwdPlan plan_fwd(const spo_pg_desc *d, void *ws) {
     p.nTt = ceil_div(d->T, TL::BN);
     p.nVt = ceil_div(d->V, TL::BM);
     p.T_pad = p.nTt * TL::BN;
-    p.nsplit = SweepMap(p.nTt, p.nVt).nsplit;
+    p.nsplit = sweep_splits(p.nTt, p.nVt);
     p.Kc = d->dtype == SPO_FP32 ? kSplitTerms * d->H : d->H;
     p.nblk_tok = ceil_div(std::max<int64_t>(d->T, 1), kTokThreads);
     Arena a(ws);
@@ -1149,7 +1207,7 @@ int fused_fwd(const spo_pg_desc *d, float *loss, float *logp, float *lse, float 
                 W = static_cast<const char *>(d->W);
             }
         }
-        const int64_t blocks = SweepMap(p.nTt, p.nVt).blocks();
+        const int64_t blocks = SweepMap(p.nTt, p.nVt, p.nsplit).blocks();
         ScopedKernelTimer timer(kTimeFwdSweep, s);
         fwd_sweep_kernel<kEmitNone><<<static_cast<unsigned>(blocks), TL::NT, kSweepLds, s>>>(
             W, p.Kc * 2, d->V, X, p.Kc * 2, d->T, static_cast<int>(p.Kc / kBK), p.nsplit, p.nTt, p.nVt, p.T_pad,
@@ -1340,12 +1398,11 @@ int fused_bwd(const spo_pg_desc *d, const float *logp, const float *lse, float g
             Xk = Xrows = xc;
         }
         {
-            const SweepMap map(Tcp / TL::BN, nVt);
-            const int64_t wgs = map.blocks();
+            const int64_t wgs = sweep_blocks_max(Tcp / TL::BN, nVt);
             ScopedKernelTimer timer(kTimeRecompute, s);
             recompute_dz_kernel<<<static_cast<unsigned>(wgs), TL::NT, TL::LDS_BYTES, s>>>(
                 reinterpret_cast<const char *>(Wk), p.Kc * 2, V, reinterpret_cast<const char *>(Xk), p.Kc * 2,
-                Tcp, static_cast<int>(p.Kc / kBK), p.tok, nVt, Tcp / TL::BN, p.dZ, Tcp * kBlockK, p.n_act, t0);
+                Tcp, static_cast<int>(p.Kc / kBK), p.tok, nVt, p.dZ, Tcp * kBlockK, p.n_act, t0);
         }
         if (d_hidden) {
             ScopedKernelTimer timer(kTimeDHidden, s);
@@ -1410,20 +1467,7 @@ static FbPlan plan_fb(const spo_pg_desc *d, int64_t chunk_tokens, void *ws, bool
     int64_t tz = chunk_tokens > 0 ? round_up(chunk_tokens, TL::BN) : kDzBudgetBytes / (2 * p.V_blk) / 4096 * 4096;
     if (tz < TL::BN) tz = TL::BN;
     p.Tz = std::min(tz, p.T_pad);
-    // Vocabulary splits of a piece's sweep: a launch lasts (rounds of workgroups on the chip) x
-    // (tiles of the longest workgroup); among the multiples of 8 that fill the chip the count
-    // with the shortest launch, else what the sweep chooses for small problems.
-    p.nsplit = 0;
-    const int64_t nTz = p.Tz / TL::BN;
-    int64_t best = 0;
-    for (int ns = kSweepSplits; ns <= 64 && ns <= p.nVt && nTz * kSweepSplits >= kChipCUs; ns += 8) {
-        const int64_t cost = ceil_div(nTz * ns, kChipCUs) * ceil_div(p.nVt, ns);
-        if (!p.nsplit || cost < best) {
-            best = cost;
-            p.nsplit = ns;
-        }
-    }
-    p.nsplit = SweepMap(nTz, p.nVt, p.nsplit).nsplit;
+    p.nsplit = sweep_splits(p.Tz / TL::BN, p.nVt);
     p.nblk_tok = p.T_pad / kTokThreads;
     static_assert(TL::BN % kTokThreads == 0, "pieces start at a block of the per-token kernels");
     Arena a(ws);
@@ -1528,17 +1572,19 @@ int fused_fwd_bwd(const spo_pg_desc *d, float grad_loss, float *loss, float *log
             split_expand_kernel<<<grid1(Tv * H), 256, 0, s>>>(reinterpret_cast<const float *>(Xpiece), Tv, H, p.Xs, 1);
             Xk = reinterpret_cast<const char *>(p.Xs);
         }
-        const SweepMap map(Tzp / TL::BN, p.nVt, p.nsplit);
+        // the last piece may be shorter: its own choice of splits, within the room for partial results
+        const SweepMap map(Tzp / TL::BN, p.nVt,
+                           Tzp == p.Tz ? p.nsplit : sweep_splits(Tzp / TL::BN, p.nVt, static_cast<uint32_t>(std::min<int64_t>(p.nsplit * p.Tz / Tzp, kNoSplitCap))));
         if (p.dense) probs_reference_kernel<<<grid1(Tzp), 256, 0, s>>>(p.z_target + t0, d->old_logp + t0, Tv, Tzp, p.offs);
         {
             ScopedKernelTimer timer(kTimeFwdSweep, s);
             if (p.dense)
                 fwd_sweep_kernel<kEmitProbs><<<static_cast<unsigned>(map.blocks()), TL::NT, kSweepLdsProbs, s>>>(
-                    Wk, p.Kc * 2, V, Xk, p.Kc * 2, Tv, static_cast<int>(p.Kc / kBK), map.nsplit, map.nTt, map.nVt, Tzp,
+                    Wk, p.Kc * 2, V, Xk, p.Kc * 2, Tv, static_cast<int>(p.Kc / kBK), map.ns, map.nTt, map.nVt, Tzp,
                     p.part_max, p.part_sum, p.Z, Tzp * kBlockK, p.offs);
             else
                 fwd_sweep_kernel<kEmitLogits><<<static_cast<unsigned>(map.blocks()), TL::NT, kSweepLds, s>>>(
-                    Wk, p.Kc * 2, V, Xk, p.Kc * 2, Tv, static_cast<int>(p.Kc / kBK), map.nsplit, map.nTt, map.nVt, Tzp,
+                    Wk, p.Kc * 2, V, Xk, p.Kc * 2, Tv, static_cast<int>(p.Kc / kBK), map.ns, map.nTt, map.nVt, Tzp,
                     p.part_max, p.part_sum, p.Z, Tzp * kBlockK, p.offs);
         }
         const bool back = d_hidden || d_W;
@@ -1549,8 +1595,8 @@ int fused_fwd_bwd(const spo_pg_desc *d, float grad_loss, float *loss, float *log
             gr.Q = p.Z;
             gr.q_blk = Tzp * kBlockK;
         }
-        token_loss_kernel<<<grid1(back ? Tzp : Tv, kTokThreads), token_threads(map.nsplit, p.nblk_tok), 0, s>>>(
-            p.part_max, p.part_sum, map.nsplit, Tzp, p.z_target + t0, token_inputs(d, t0, Tv), logp + t0, lse + t0,
+        token_loss_kernel<<<grid1(back ? Tzp : Tv, kTokThreads), token_threads(map.ns, p.nblk_tok), 0, s>>>(
+            p.part_max, p.part_sum, map.ns, Tzp, p.z_target + t0, token_inputs(d, t0, Tv), logp + t0, lse + t0,
             p.partials, gr, back ? ceil_div(p.T_pad, kTokThreads) : ceil_div(T, kTokThreads), p.done, loss, stats);
         if (!back) continue;
         if (p.dense) {

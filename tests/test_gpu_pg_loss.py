@@ -314,6 +314,23 @@ def test_backward_runs_over_active_tokens_only(spo, oracle, keep, chunk, one_cal
     assert not dx[torch.as_tensor(zero_rows, device="cuda")].any()
 
 
+@pytest.mark.parametrize("T,V,chunk", [
+    (1000, 17900, 0),      # 4 token tiles, all divided by splits (a multiple of 8)
+    (2304, 10200, 0),      # 9: eight by token tile, one by splits
+    (4700, 3000, 0),       # 19 over 12 vocabulary tiles: more token tiles than splits, splits no multiple of 8
+    (8900, 4000, 6144)])   # 35 in pieces of 24 and 11, each with its own splits; the masked ones run on fewer
+def test_token_tiles_and_splits_over_the_chip(spo, oracle, T, V, chunk, one_call):
+    say(f"fused bf16 T={T} H=64 V={V} chunk={chunk} one_call={one_call}: token tiles x splits")
+    case = Case(wl.scaled(MID, name="splits", H=64, V=V), [T // 3, T - T // 3], mask_frac=0.3 if T > 4000 else None)
+    case.set_old_from_oracle(oracle)
+    fwd, dx, dw = run_fwd_bwd(spo, case, chunk_tokens=chunk, one_call=one_call)
+    check_forward(case, oracle, fwd)
+    rb = oracle.pg_loss_bwd(*case.oracle_inputs(), *case.eps)
+    assert rel_l2(f64(dx), rb["d_hidden"]) < GRAD_TOL and rel_l2(f64(dw), rb["d_W"]) < GRAD_TOL
+    per_row = np.linalg.norm(f64(dx) - rb["d_hidden"], axis=1)
+    assert (per_row <= 2 * GRAD_TOL * np.linalg.norm(rb["d_hidden"], axis=1) + 1e-12).all()
+
+
 def test_cu_seqlens_may_start_anywhere(spo, oracle):
     # a mini-batch cut out of a packed batch keeps the batch's offsets: only differences count
     say("fused bf16 mid, cu_seqlens shifted by a constant")
