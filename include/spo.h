@@ -167,8 +167,8 @@ int spo_advantage_diagnostics(const float *adv_raw, const float *reward, int32_t
  * ids_unique   1: the caller guarantees that idx holds no repeated id (one
  *              response per prompt).  0: repeated ids are applied one after the
  *              other in batch order, as if the responses arrived in sequence
- *              (needs ws); the cost is one pass over the batch per repeat of the
- *              most repeated id, in a single workgroup.
+ *              (needs ws); updates of one id are a serial chain, different ids are
+ *              worked on side by side.
  * n_obs        optional uint32[N] visit counters, incremented per observation.
  * v_prev_out   optional [B]: tracker mean right before observation k.
  * info         optional int32[1], bits: 1 = some idx[k] lies outside [0, N) (that

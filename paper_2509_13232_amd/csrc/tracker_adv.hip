@@ -1,7 +1,7 @@
 // Beta value tracker (update, initialisation) and single-stream advantages.
 // Method, "A KL-Adaptive Value Tracker" and "Advantage Estimation and Policy
 // Optimization".  Plain ALU work on B <= a few thousand scattered entries:
-// launch-latency bound, one small launch each.
+// launch-latency bound.
 #include "common.hpp"
 
 namespace spo {
@@ -83,82 +83,121 @@ tracker_update_unique_kernel(float *__restrict__ alpha, float *__restrict__ beta
     if (n_obs) n_obs[i] += 1u;
 }
 
-// Repeated ids, applied one after the other in batch order.  One workgroup works in rounds: every
-// pending observation files its number under its id with an atomic minimum (slot table, all
-// kNoOwner on entry and again on exit); the observation that finds its own number there is the
-// earliest pending one of its id and is applied, by one thread, with no other thread touching that
-// entry in this round.  The number of rounds is the largest number of repeats of an id (8 for
-// batches that sample every prompt 8 times), the work per round the batch size; a batch larger
-// than 32768 observations is taken in windows of that many, in order.  The minimum does not
-// depend on the order of the atomics: the result is the same on every run.  Tracker entries and
-// slots are read and written with L2-coherent accesses, since a later round's thread must see
-// what an earlier round's thread wrote.
-constexpr int kRoundThreads = 1024, kRoundPer = 32;
+// Repeated ids, applied one after the other in batch order.  Every id belongs to one workgroup (a hash of
+// the id), which reads the whole list of ids, keeps its own observations in LDS, sorts them by (id,
+// place in the batch) and lets one thread per id walk that id's run: the state passes through
+// registers from one observation to the next, and neither a table over the prompts nor an atomic
+// on memory is needed.  (One workgroup filing claims in a table and applying the earliest pending
+// observation of every id per round: 952 us for a prompt step of 40000 responses to 20000 prompts,
+// 109 us this way.)  A list that might overflow is applied and restarted: the ids are read in
+// batch order, so what is applied earlier is earlier in the batch.
+constexpr int kOwnThreads = 512, kOwnCap = 4096, kOwnStep = 2 * kOwnThreads;
+constexpr int kOwnSpan = 2048;          // sorted observations whose rewards and discounts are in LDS at a time
+constexpr int kOwnGroups = 256;         // most workgroups: one per compute unit
+constexpr int kOwnPerGroup = 128;       // observations per workgroup below that
 
 template <bool Ema>
-__global__ void __launch_bounds__(kRoundThreads)
-tracker_update_rounds_kernel(float *__restrict__ alpha, float *__restrict__ beta, int64_t N,
-                             const int32_t *__restrict__ idx, const float *__restrict__ reward,
-                             const float *__restrict__ kl, int B, double d_half, double rho_min,
-                             double rho_max, uint32_t *__restrict__ n_obs, float *__restrict__ v_prev,
-                             int32_t *__restrict__ info, int32_t *__restrict__ slot) {
-    __shared__ int pending_flag[2];
-    auto ld = [](const float *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
-    auto st = [](float *p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
-    if (threadIdx.x == 0) { pending_flag[0] = 0; pending_flag[1] = 0; }
-    __syncthreads();
-    for (int64_t w0 = 0; w0 < B; w0 += static_cast<int64_t>(kRoundThreads) * kRoundPer) {
-        // observation j of this thread in the window: k = w0 + j * kRoundThreads + tid
-        uint32_t pending = 0;
-        for (int j = 0; j < kRoundPer; ++j) {
-            const int64_t k = w0 + static_cast<int64_t>(j) * kRoundThreads + threadIdx.x;
-            if (k >= B) break;
-            const int64_t i = idx[k];
-            if (i < 0 || i >= N) {
-                if (info) atomicOr(&info[0], kInfoRange);
-                if (v_prev) v_prev[k] = __builtin_nanf("");
-            } else {
-                pending |= 1u << j;
+__global__ void __launch_bounds__(kOwnThreads)
+tracker_update_owned_kernel(float *__restrict__ alpha, float *__restrict__ beta, int64_t N,
+                            const int32_t *__restrict__ idx, const float *__restrict__ reward,
+                            const float *__restrict__ kl, int B, double d_half, double rho_min,
+                            double rho_max, uint32_t *__restrict__ n_obs, float *__restrict__ v_prev,
+                            int32_t *__restrict__ info, int shift) {
+    __shared__ uint64_t key[kOwnCap];  // id << 32 | place in the batch
+    __shared__ double rho[kOwnSpan];
+    __shared__ float rew[kOwnSpan];
+    __shared__ int count;
+    const int tid = threadIdx.x;
+    // applies the n observations in key[] (n is the same in every thread)
+    auto apply_list = [&](int n) {
+        int P = 1;
+        while (P < n) P <<= 1;
+        for (int i = n + tid; i < P; i += kOwnThreads) key[i] = ~0ull;
+        __syncthreads();
+        for (int k = 2; k <= P; k <<= 1)
+            for (int j = k >> 1; j > 0; j >>= 1) {
+                for (int t = tid; t < P / 2; t += kOwnThreads) {
+                    const int i = 2 * t - (t & (j - 1));
+                    const uint64_t x = key[i], y = key[i + j];
+                    if ((x > y) == ((i & k) == 0)) {
+                        key[i] = y;
+                        key[i + j] = x;
+                    }
+                }
+                __syncthreads();
+            }
+        for (int w0 = 0; w0 < n; w0 += kOwnSpan) {
+            const int w1 = n - w0 < kOwnSpan ? n : w0 + kOwnSpan;
+            for (int i = w0 + tid; i < w1; i += kOwnThreads) {
+                const int k = static_cast<int>(static_cast<uint32_t>(key[i]));
+                rew[i - w0] = reward[k];
+                rho[i - w0] = discount(kl[k], d_half, rho_min, rho_max);
+            }
+            __syncthreads();
+            for (int i = w0 + tid; i < w1; i += kOwnThreads) {
+                const uint32_t id = static_cast<uint32_t>(key[i] >> 32);
+                if (i > w0 && static_cast<uint32_t>(key[i - 1] >> 32) == id) continue;  // not the first of its run
+                float a = alpha[id], b = beta[id];
+                int j = i;
+                do {
+                    if (v_prev) v_prev[static_cast<uint32_t>(key[j])] = mean_of<Ema>(a, b);
+                    apply<Ema>(a, b, rew[j - w0], rho[j - w0]);
+                    ++j;
+                } while (j < w1 && static_cast<uint32_t>(key[j] >> 32) == id);
+                alpha[id] = a;
+                beta[id] = b;
+                if (n_obs) n_obs[id] += static_cast<uint32_t>(j - i);
+            }
+            __syncthreads();  // the state is written, rew / rho / key may be overwritten
+        }
+    };
+    if (tid == 0) count = 0;
+    int bound = 0;  // the list holds at most this many
+    constexpr int AHEAD = 4;
+    for (int64_t base = 0; base < B; base += AHEAD * kOwnStep) {
+        int32_t id[AHEAD][2];
+#pragma unroll
+        for (int c = 0; c < AHEAD; ++c)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const int64_t k = base + (2 * c + e) * kOwnThreads + tid;
+                id[c][e] = k < B ? idx[k] : 0;
+            }
+#pragma unroll
+        for (int c = 0; c < AHEAD; ++c) {
+            if (base + c * kOwnStep >= B) break;
+            if (bound + kOwnStep > kOwnCap) {
+                __syncthreads();
+                bound = count;
+                __syncthreads();
+                if (bound + kOwnStep > kOwnCap) {
+                    apply_list(bound);
+                    if (tid == 0) count = 0;
+                    bound = 0;
+                }
+            }
+            __syncthreads();  // the count is set
+            bound += kOwnStep;
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const int64_t k = base + (2 * c + e) * kOwnThreads + tid;
+                if (k >= B) continue;
+                const int32_t i = id[c][e];
+                if (i < 0 || i >= N) {
+                    if (blockIdx.x == 0) {
+                        if (info) atomicOr(&info[0], kInfoRange);
+                        if (v_prev) v_prev[k] = __builtin_nanf("");
+                    }
+                    continue;
+                }
+                const uint64_t owner = static_cast<uint64_t>(static_cast<uint32_t>(i) * 0x9E3779B1u) >> shift;
+                if (owner == blockIdx.x)
+                    key[atomicAdd(&count, 1)] = static_cast<uint64_t>(i) << 32 | static_cast<uint32_t>(k);
             }
         }
-        for (int round = 0;; ++round) {
-            for (int j = 0; j < kRoundPer; ++j)
-                if (pending >> j & 1u) {
-                    const int k = static_cast<int>(w0 + static_cast<int64_t>(j) * kRoundThreads + threadIdx.x);
-                    atomicMin(&slot[idx[k]], k);
-                }
-            __threadfence();
-            __syncthreads();  // every claim of this round is filed
-            uint32_t won = 0;
-            for (int j = 0; j < kRoundPer; ++j)
-                if (pending >> j & 1u) {
-                    const int k = static_cast<int>(w0 + static_cast<int64_t>(j) * kRoundThreads + threadIdx.x);
-                    if (__hip_atomic_load(&slot[idx[k]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == k) won |= 1u << j;
-                }
-            __syncthreads();  // every claim has been read
-            for (int j = 0; j < kRoundPer; ++j)
-                if (won >> j & 1u) {
-                    const int k = static_cast<int>(w0 + static_cast<int64_t>(j) * kRoundThreads + threadIdx.x);
-                    const int32_t i = idx[k];
-                    __hip_atomic_store(&slot[i], kNoOwner, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    float a = ld(&alpha[i]), b = ld(&beta[i]);
-                    if (v_prev) v_prev[k] = mean_of<Ema>(a, b);
-                    apply<Ema>(a, b, reward[k], discount(kl[k], d_half, rho_min, rho_max));
-                    st(&alpha[i], a);
-                    st(&beta[i], b);
-                    if (n_obs) atomicAdd(&n_obs[i], 1u);
-                }
-            pending &= ~won;
-            int *flag = &pending_flag[round & 1];
-            if (pending) *flag = 1;
-            __threadfence();
-            __syncthreads();  // the slots are clear again, the updates are visible, the flag is complete
-            const bool again = *flag != 0;
-            if (threadIdx.x == 0) pending_flag[(round + 1) & 1] = 0;
-            __syncthreads();
-            if (!again) break;
-        }
     }
+    __syncthreads();
+    apply_list(count);
 }
 
 __global__ void __launch_bounds__(256)
@@ -347,14 +386,16 @@ static int tracker_update_launch(float *alpha, float *beta, int64_t N, const int
     hipStream_t s = as_stream(stream);
     int32_t *slot = static_cast<int32_t *>(ws);
     if (info) clear_info_kernel<<<1, 1, 0, s>>>(info);
-    if (slot) fill_slots_kernel<<<static_cast<unsigned>(ceil_div(N, 256)), 256, 0, s>>>(slot, N);
     if (ids_unique) {
+        if (slot) fill_slots_kernel<<<static_cast<unsigned>(ceil_div(N, 256)), 256, 0, s>>>(slot, N);
         const int threads = 256, blocks = (B + threads - 1) / threads;
         tracker_update_unique_kernel<Ema><<<blocks, threads, 0, s>>>(alpha, beta, N, idx, reward, kl, B, d_half, rho_min,
                                                                       rho_max, n_obs, v_prev_out, info, slot);
     } else {
-        tracker_update_rounds_kernel<Ema><<<1, kRoundThreads, 0, s>>>(alpha, beta, N, idx, reward, kl, B, d_half, rho_min,
-                                                                       rho_max, n_obs, v_prev_out, info, slot);
+        int bits = 0;
+        while (1 << bits < kOwnGroups && (static_cast<int64_t>(kOwnPerGroup) << bits) < B) ++bits;
+        tracker_update_owned_kernel<Ema><<<1u << bits, kOwnThreads, 0, s>>>(alpha, beta, N, idx, reward, kl, B, d_half, rho_min,
+                                                                            rho_max, n_obs, v_prev_out, info, 32 - bits);
     }
     return launch_status();
 }

@@ -132,6 +132,40 @@ def test_tracker_update_of_batches_that_repeat_every_prompt(spo, oracle, B, G, N
         assert info.item() == 0
 
 
+@pytest.mark.parametrize("B,n_ids,bad", [
+    (1, 1, 0), (128, 5, 3), (129, 129, 1),          # one workgroup, and one observation more
+    (1024, 1, 0), (1025, 2, 7),                     # one step of the list, and one more
+    (4096, 1, 0), (9000, 1, 11),                    # one id fills the list; the list is applied and restarted
+    (33000, 7, 100)])                               # a few long runs over many workgroups and restarts
+def test_tracker_update_runs_of_one_id(spo, oracle, B, n_ids, bad):
+    # an id's observations form a serial chain wherever the list they are collected in ends; ids outside the
+    # table (bad of them) are skipped, flagged and get a NaN baseline
+    N = 300
+    say(f"tracker_update B={B}, {n_ids} ids, {bad} out of range")
+    rng = np.random.default_rng([B, n_ids])
+    idx = rng.choice(rng.choice(N, n_ids, replace=False), B).astype(np.int32)
+    out = rng.choice(B, bad, replace=False)
+    idx[out] = rng.choice([-1, N, 2 ** 31 - 1, -2 ** 31], bad)
+    ok = np.ones(B, bool)
+    ok[out] = False
+    a, b = (rng.uniform(0.5, 50, N).astype(np.float32) for _ in range(2))
+    r = (rng.random(B) < 0.4).astype(np.float32)
+    kl = rng.exponential(0.02, B).astype(np.float32)
+    ea, eb, ev, _ = oracle.tracker_update(a, b, idx[ok], r[ok], kl[ok], 0.25, 0.875, 0.96)
+    ga, gb = dev(a), dev(b)
+    nobs = torch.zeros(N, dtype=torch.int32, device="cuda")
+    info = torch.full((1,), 7, dtype=torch.int32, device="cuda")
+    gv = spo.spo_tracker_update(ga, gb, dev(idx), dev(r), dev(kl), 0.25, 0.875, 0.96, ids_unique=False, n_obs=nobs,
+                                want_v_prev=True, info=info)
+    torch.cuda.synchronize()
+    # the state is rounded to fp32 after every observation on both sides; a discount forgets old roundings
+    np.testing.assert_allclose(ga.cpu().numpy(), ea, rtol=RTOL)
+    np.testing.assert_allclose(gb.cpu().numpy(), eb, rtol=RTOL)
+    np.testing.assert_allclose(gv.cpu().numpy()[ok], ev, rtol=RTOL)
+    assert np.isnan(gv.cpu().numpy()[~ok]).all() and info.item() == (1 if bad else 0)
+    assert np.array_equal(nobs.cpu().numpy(), np.bincount(idx[ok], minlength=N))
+
+
 def test_ids_out_of_range_or_repeated_are_flagged_not_followed(spo, oracle):
     say("tracker_update / advantages: ids outside the table, repeats under ids_unique")
     N, B = 1000, 64
