@@ -159,28 +159,21 @@ token_loss_kernel(const float *__restrict__ part_max, const float *__restrict__ 
         clp = wave_sum(clp);
         sr = wave_sum(sr);
         if (lane == 0) {
-            // Seen by the last workgroup on whatever XCD it runs: stores and loads that act beyond the
-            // L2 caches of the XCDs (agent scope), and the count goes up when the stores have arrived.
-            auto put = [](double *p, double v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
-            FwdPartial *p = partials + in.t_base / kTokThreads + blockIdx.x;
-            put(&p->sum_obj, so);
-            put(&p->count, cnt);
-            put(&p->clipped, clp);
-            put(&p->sum_ratio, sr);
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            partials[in.t_base / kTokThreads + blockIdx.x] = FwdPartial{so, cnt, clp, sr};
+            // the count releases this workgroup's sums to whichever ends last, and acquires theirs
             last = total_blocks == 1 ||
-                   __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == total_blocks - 1;
+                   __hip_atomic_fetch_add(done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == total_blocks - 1;
         }
     }
     __syncthreads();
     if (!last) return;
     so = cnt = clp = sr = 0.0;
-    auto get = [](const double *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // for the wavefronts that did not count
     for (int64_t i = threadIdx.x; i < total_blocks; i += blockDim.x) {
-        so += get(&partials[i].sum_obj);
-        cnt += get(&partials[i].count);
-        clp += get(&partials[i].clipped);
-        sr += get(&partials[i].sum_ratio);
+        so += partials[i].sum_obj;
+        cnt += partials[i].count;
+        clp += partials[i].clipped;
+        sr += partials[i].sum_ratio;
     }
     so = block_sum(so, scratch);
     cnt = block_sum(cnt, scratch);
