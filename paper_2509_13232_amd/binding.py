@@ -165,7 +165,7 @@ def spo_sample_prompts(alpha, beta, B, eps_explore=0.05, seed=0, iteration=0, re
     _want(alpha, torch.float32, "alpha")
     _want(beta, torch.float32, "beta", N)
     idx = torch.empty(B, dtype=torch.int32, device=alpha.device)
-    info = torch.zeros(2, dtype=torch.int32, device=alpha.device)
+    info = torch.empty(2, dtype=torch.int32, device=alpha.device)
     nbytes = lib().spo_sample_prompts_workspace_bytes(N, B)
     ws = _workspace(nbytes, alpha.device, workspace)
     _check(lib().spo_sample_prompts(_ptr(alpha), _ptr(beta), N, B, float(eps_explore), int(seed),
@@ -182,7 +182,7 @@ def spo_sample_prompts_static(alpha, beta, B, eps_explore=0.05, seed=0, iteratio
     _want(alpha, torch.float32, "alpha")
     _want(beta, torch.float32, "beta", N)
     idx = torch.empty(B, dtype=torch.int32, device=alpha.device) if idx_out is None else idx_out
-    info = torch.zeros(2, dtype=torch.int32, device=alpha.device) if info_out is None else info_out
+    info = torch.empty(2, dtype=torch.int32, device=alpha.device) if info_out is None else info_out
     _want(idx, torch.int32, "idx_out", B)
     _want(info, torch.int32, "info_out", 2)
     _check(lib().spo_sample_prompts_static(_ptr(alpha), _ptr(beta), N, B, float(eps_explore), int(seed),

@@ -302,6 +302,38 @@ def test_sampler_indices_are_bit_exact(spo, oracle, name, B, seed, replace):
             assert len(set(eidx.tolist())) == B
 
 
+@pytest.mark.parametrize("N,B,replace", [
+    (1, 1, False), (1, 300, True), (64, 64, False), (65, 65, False), (257, 250, False),   # one workgroup of 1, 1, 2, 2 wavefronts
+    (4095, 3000, False), (4096, 3500, False), (4096, 4096, True),                          # its largest tables
+    (4096, 4097, True), (4097, 3500, False), (8193, 2000, True),                           # tables in memory, two and three blocks
+    (16384, 12000, False),                                                                 # long chains of displaced slots
+    (4096 * 1024, 500, False), (4096 * 1024 + 1, 500, False)])                             # most blocks that add up sums themselves, one more
+def test_sampler_table_sizes(spo, oracle, N, B, replace):
+    say(f"sample_prompts N={N} B={B} replace={replace}")
+    rng = np.random.default_rng([N, B])
+    a, b = (rng.uniform(0.5, 50, N).astype(np.float32) for _ in range(2))
+    eidx, eatt = oracle.sample_prompts(a, b, B, 0.05, 3, 1 << 33, replace, return_attempts=True)
+    for _ in range(2):
+        gidx, info = spo.spo_sample_prompts(dev(a), dev(b), B, 0.05, 3, 1 << 33, replace, return_info=True)
+        torch.cuda.synchronize()
+        assert np.array_equal(gidx.cpu().numpy(), eidx) and info.cpu().tolist() == [0, int(eatt.max())]
+
+
+def test_sampler_exhausted_attempts_over_many_workgroups(spo, oracle):
+    # 5000 prompts, all weight on a few: a slot that finds none of them free within 3 attempts gets -1, the
+    # others keep what the sequential draw gives them (slots that fail hold nothing)
+    say("sample_prompts exhausted attempts N=5000 B=200")
+    rng = np.random.default_rng(8)
+    a, b = np.zeros(5000, np.float32), np.ones(5000, np.float32)
+    a[rng.choice(5000, 150, replace=False)] = 1.0
+    gidx, info = spo.spo_sample_prompts(dev(a), dev(b), 200, 0.0, 4, 2, False, max_attempts=3, return_info=True)
+    first = spo.spo_sample_prompts(dev(a), dev(b), 1, 0.0, 4, 2, True)
+    torch.cuda.synchronize()
+    out = gidx.cpu().numpy()
+    assert out[0] == first.item() and (a[out[out >= 0]] > 0).all() and len(set(out[out >= 0].tolist())) == (out >= 0).sum()
+    assert info.cpu().tolist() == [1, 3] and (out == -1).sum() >= 50
+
+
 def test_sampler_reports_exhausted_attempts(spo, oracle):
     # one prompt holds nearly all the weight: later slots cannot find a free id in 2 attempts
     say("sample_prompts exhausted attempts")
