@@ -275,6 +275,38 @@ def test_advantages_of_large_batches_over_many_workgroups(spo, oracle, B, ddof, 
         assert info.item() == 1 and torch.isnan(raw[B // 2]) and torch.isnan(nrm).all()
 
 
+@pytest.mark.parametrize("B", [1, 64, 65, 1024, 1025, 4096, 4097, 16383, 16385])   # responses per thread: 1, 4, 16, any
+@pytest.mark.parametrize("beta", [True, False])
+def test_advantages_kept_in_registers(spo, oracle, B, beta):
+    say(f"advantages in one workgroup, B={B} beta={beta}")
+    rng = np.random.default_rng([B, 3])
+    N = 5000
+    a, b = (rng.uniform(0.5, 50, N).astype(np.float32) for _ in range(2))
+    v = a / (a + b) if not beta else None
+    idx = rng.integers(0, N, B).astype(np.int32)
+    r = (rng.random(B) < 0.4).astype(np.float32)
+    base = a.astype(np.float64)[idx] / (a.astype(np.float64) + b.astype(np.float64))[idx] if beta else v.astype(np.float64)[idx]
+    raw64 = r.astype(np.float64) - base
+    info = torch.full((1,), 7, dtype=torch.int32, device="cuda")
+    state = (dev(a), dev(b)) if beta else (dev(v), None)
+    raw, nrm, st = spo.spo_advantages(*state, dev(idx), dev(r), info=info)
+    diag = spo.spo_advantage_diagnostics(raw, dev(r), 0.1, 0.3)
+    torch.cuda.synchronize()
+    sd = raw64.std()
+    assert info.item() == 0
+    np.testing.assert_allclose(raw.cpu().numpy(), raw64, rtol=1e-6, atol=1e-7)
+    np.testing.assert_allclose(st.cpu().numpy(), [raw64.mean(), sd], rtol=1e-6, atol=1e-9)
+    np.testing.assert_allclose(nrm.cpu().numpy(), (raw64 - raw64.mean()) / sd if sd else 0 * raw64, rtol=1e-5, atol=1e-6)
+    raw32 = raw.cpu().numpy().astype(np.float64)
+    np.testing.assert_allclose(diag.cpu().numpy(), [(np.abs(raw32) <= np.float32(0.1)).mean(), (np.abs(raw32) <= np.float32(0.3)).mean(),
+                                                    raw32.var(), r.var()], rtol=1e-5, atol=1e-9)
+    bad = idx.copy()
+    bad[B - 1] = -1
+    raw, nrm, _ = spo.spo_advantages(*state, dev(bad), dev(r), info=info)
+    torch.cuda.synchronize()
+    assert info.item() == 1 and torch.isnan(raw[B - 1]) and torch.isnan(nrm).all() and not torch.isnan(raw[:B - 1]).any()
+
+
 def test_advantages_degenerate_batch(spo):
     say("advantages all-equal")
     a = dev(np.ones(4, np.float32))
