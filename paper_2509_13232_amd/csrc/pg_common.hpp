@@ -219,11 +219,19 @@ __device__ __forceinline__ int64_t count_mask(const uint8_t *__restrict__ mask, 
     return block_sum(c, scratch);  // T < 2^31
 }
 
+// Gradient factor of token t from the forward's log-prob; cu: see stage_offsets, M: number of unmasked tokens.
+__device__ __forceinline__ float token_grad(const float *__restrict__ logp, const TokenInputs &in, const int32_t *cu, double M,
+                                            float grad_loss, int64_t t) {
+    if (in.mask && !in.mask[t]) return 0.0f;
+    const float adv = in.adv_norm[response_of_token(cu, in.B, in.t_base + t)];
+    return grad_factor(surrogate(logp[t], in.old_logp[t], adv, in.eps_low, in.eps_high), adv, M, grad_loss);
+}
+
 // count[0] = number of unmasked tokens.  One workgroup.
 static __global__ void __launch_bounds__(1024)
 mask_count_kernel(const uint8_t *__restrict__ mask, int64_t T, double *__restrict__ count) {
     __shared__ int scratch[1024 / kWave];
-    const int64_t c = mask ? count_mask(mask, T, scratch) : T;
+    const int64_t c = count_mask(mask, T, scratch);
     if (threadIdx.x == 0) count[0] = static_cast<double>(c);
 }
 
@@ -242,12 +250,7 @@ grad_scale_kernel(const float *__restrict__ logp, TokenInputs in, int64_t T_pad,
     const double M = count ? count[0] : static_cast<double>(in.mask ? count_mask(in.mask, in.T, scratch) : in.T);
     __syncthreads();
     if (t >= T_pad) return;
-    float out = 0.0f;
-    if (t < in.T && (!in.mask || in.mask[t])) {
-        const float adv = in.adv_norm[response_of_token(cu, in.B, in.t_base + t)];
-        out = grad_factor(surrogate(logp[t], in.old_logp[t], adv, in.eps_low, in.eps_high), adv, M, grad_loss);
-    }
-    g[t] = out;
+    g[t] = t < in.T ? token_grad(logp, in, cu, M, grad_loss, t) : 0.0f;
 }
 
 // The gradient factors of a whole batch; `count` is scratch for batches with a long mask.

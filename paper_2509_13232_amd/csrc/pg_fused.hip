@@ -56,64 +56,170 @@ static int64_t default_chunk_tokens(int64_t H, int64_t V_blk) {
 // operand preparation
 // ----------------------------------------------------------------------------
 
-// dst[r][j*K + k] = part_{sel(j)}(src[r][k]) with sel = {0,0,1,0,2,1} (side 0) or
-// {0,1,0,2,0,1} (side 1): sum_j dst0[.][jK+k] * dst1[.][jK+k] keeps the products
-// x0y0, x0y1, x1y0, x0y2, x2y0, x1y1 of the three-part bf16 splits of x and y.
-__global__ void __launch_bounds__(256)
-split_expand_kernel(const float *__restrict__ src, int64_t rows, int64_t K, bf16_t *__restrict__ dst, int side) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (i >= rows * K) return;
-    const int64_t r = i / K, k = i % K;
-    const float x = src[i];
-    const bf16_t p0 = f32_to_bf16(x);
-    const float r1 = x - bf16_to_f32(p0);
-    const bf16_t p1 = f32_to_bf16(r1);
-    const bf16_t p2 = f32_to_bf16(r1 - bf16_to_f32(p1));
-    bf16_t *o = dst + r * (kSplitTerms * K) + k;
-    if (side == 0) {
-        o[0] = p0; o[K] = p0; o[2 * K] = p1; o[3 * K] = p0; o[4 * K] = p2; o[5 * K] = p1;
-    } else {
-        o[0] = p0; o[K] = p1; o[2 * K] = p0; o[3 * K] = p2; o[4 * K] = p0; o[5 * K] = p1;
+// The three-part bf16 split of eight values, laid out along the contraction index: part j of value k at
+// o[j*K + k] is part_{sel(j)} with sel = {0,0,1,0,2,1} (Side 0) or {0,1,0,2,0,1} (Side 1), so that
+// sum_j side0[jK+k] * side1[jK+k] keeps the products x0y0, x0y1, x1y0, x0y2, x2y0, x1y1.
+template <int Side>
+__device__ __forceinline__ void store_split(bf16_t *o, int64_t K, const float (&x)[8]) {
+    uint32_t part[3][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        uint32_t two[2][3];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const float v = x[2 * i + h];
+            const bf16_t p0 = f32_to_bf16(v);
+            const float r1 = v - bf16_to_f32(p0);
+            const bf16_t p1 = f32_to_bf16(r1);
+            two[h][0] = p0;
+            two[h][1] = p1;
+            two[h][2] = f32_to_bf16(r1 - bf16_to_f32(p1));
+        }
+#pragma unroll
+        for (int j = 0; j < 3; ++j) part[j][i] = two[0][j] | two[1][j] << 16;
+    }
+    constexpr int sel[2][kSplitTerms] = {{0, 0, 1, 0, 2, 1}, {0, 1, 0, 2, 0, 1}};
+#pragma unroll
+    for (int j = 0; j < kSplitTerms; ++j) {
+        const uint32_t(&q)[4] = part[sel[Side][j]];
+        *reinterpret_cast<uint4 *>(o + j * K) = make_uint4(q[0], q[1], q[2], q[3]);
     }
 }
 
-__device__ __forceinline__ bf16_t load_as_bf16(const bf16_t *p) { return *p; }
-__device__ __forceinline__ bf16_t load_as_bf16(const float *p) { return f32_to_bf16(*p); }
-
-// dst[c][r] = bf16(src[r][c]) for r < R, c < C; dst[c][r] = 0 for R <= r < R_pad and
-// for C <= c < C_pad (all r < R_pad).  dst has leading dimension ld_dst >= R_pad, or with
-// ld_dst == 0 it is stored in blocks of kBlockK values of r (the layout the main loop reads
-// as a k-blocked operand): dst[c][r] at (r / kBlockK) * C_pad * kBlockK + c * kBlockK + r % kBlockK.
-template <typename SrcT>
-__global__ void __launch_bounds__(256)
-transpose_to_bf16_kernel(const SrcT *__restrict__ src, int64_t R, int64_t C, int64_t ld_src,
-                         bf16_t *__restrict__ dst, int64_t R_pad, int64_t C_pad, int64_t ld_dst) {
-    __shared__ bf16_t tile[64][66];
-    const int64_t r0 = static_cast<int64_t>(blockIdx.x) * 64, c0 = static_cast<int64_t>(blockIdx.y) * 64;
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-    for (int i = ty; i < 64; i += 4) {
-        const int64_t r = r0 + i, c = c0 + tx;
-        tile[i][tx] = (r < R && c < C) ? load_as_bf16(src + r * ld_src + c) : bf16_t(0);
-    }
-    __syncthreads();
-    for (int i = ty; i < 64; i += 4) {
-        const int64_t c = c0 + i, r = r0 + tx;
-        if (c < C_pad && r < R_pad)
-            dst[ld_dst ? c * ld_dst + r : (r / kBlockK) * (C_pad * kBlockK) + c * kBlockK + r % kBlockK] = tile[tx][i];
-    }
+__device__ __forceinline__ void load8(const float *p, float (&x)[8]) {
+    const float4 a = reinterpret_cast<const float4 *>(p)[0], b = reinterpret_cast<const float4 *>(p)[1];
+    x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w; x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
 }
 
-// dst[c][r] = src[r][c] (fp32, R x C -> C x R), 64 x 64 tiles through LDS.
-__global__ void __launch_bounds__(256)
-transpose_f32_kernel(const float *__restrict__ src, int64_t R, int64_t C, float *__restrict__ dst) {
-    __shared__ float tile[64][65];
-    const int64_t r0 = static_cast<int64_t>(blockIdx.x) * 64, c0 = static_cast<int64_t>(blockIdx.y) * 64;
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-    for (int i = ty; i < 64; i += 4)
-        if (r0 + i < R && c0 + tx < C) tile[i][tx] = src[(r0 + i) * C + c0 + tx];
+__device__ __forceinline__ uint4 round8(const float (&x)[8]) {
+    return make_uint4(pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]), pack_bf16x2(x[6], x[7]));
+}
+
+// 1-D grids may be longer than a launch's 2^32 threads per dimension: they are folded into two
+static dim3 fold_grid(int64_t blocks) {
+    constexpr int64_t kRow = int64_t(1) << 22;
+    return blocks <= kRow ? dim3(static_cast<unsigned>(blocks)) : dim3(static_cast<unsigned>(kRow), static_cast<unsigned>(ceil_div(blocks, kRow)));
+}
+__device__ __forceinline__ int64_t flat_block() { return static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x; }
+
+// Everything that the loss's and the gradients' kernels need beforehand and that depends on the inputs
+// alone, in one launch: jobs of different kinds share a grid (small batches are bound by the number of
+// launches: an fp32 step of 512 tokens went through 17, now 10: 152 -> 137 us).
+//   head     the head W [V,H] or [H,V], read once, in every form that is asked for (NULL: not):
+//            Wvh  [V][H] as it is (for a head given as [H,V]),
+//            Ws   [V][6H] three-part split (fp32),
+//            WT   bf16 in blocks of kBlockK vocabulary entries, [V_blk / 64][H][64], zero past V;
+//   rows     the three-part split Xs [T][6H] of fp32 hidden states;
+//   target   z_target[t] and, with ref2, the reference of every token (see probs_reference);
+//   mask     count[0] = number of unmasked tokens, by one workgroup;
+//   grad     the gradient factors g of the batch and the list of its active tokens, by one workgroup (up
+//            to kPrepGradTokens tokens; above, grad_scale_kernel and compact_active_kernel).
+// `head` and `target` may not be in one launch where the head is given as [H,V] (target reads Wvh).
+struct PrepJobs {
+    int64_t H, V, T;
+    const void *W;
+    void *Wvh;
+    bf16_t *Ws, *WT;
+    int64_t head_blocks;          // tiles of 64 x 64
+    const void *X;
+    bf16_t *Xs;
+    int64_t rows, row_blocks;     // rows of Xs; 256 groups of eight values per workgroup
+    const void *Wrows;            // the head with one row per vocabulary entry
+    const int32_t *target;
+    const float *old_logp;
+    float *z_target, *ref2;
+    int64_t T_ref;                // entries of ref2
+    uint32_t *done;
+    int64_t target_blocks;        // four tokens each
+    const uint8_t *mask;
+    double *count;                // NULL: not counted
+    float *g;                     // NULL: no gradient factors
+    const float *logp;
+    TokenInputs in;
+    float grad_loss;
+    int32_t *act_idx, *n_act;
+    int64_t blocks() const { return head_blocks + row_blocks + target_blocks + (count ? 1 : 0) + (g ? 1 : 0); }
+};
+
+// One workgroup takes 1024 tokens per round, some 3 us; four rounds pass beside the smallest head's tiles.
+constexpr int64_t kPrepGradTokens = 4096;
+
+constexpr int kPrepTile = 64;
+template <typename T_> constexpr int kPrepPitch = sizeof(T_) == 2 ? 66 : 65;
+
+// One 64 x 64 tile of the head.  Bound by memory: sixteen bytes per lane in and out, rows of 128 bytes
+// in, whole 8 KiB pieces of WT out (151936 x 4096: 443 us = 5.6 TB/s).
+template <typename T_, bool HV>
+__device__ __forceinline__ void prep_head_tile(const PrepJobs &j, int64_t tile_id, T_ *tile) {
+    constexpr int P = kPrepPitch<T_>, N = 16 / sizeof(T_);  // N values per 16-byte load
+    const int64_t nh = j.H / kPrepTile;
+    const int64_t v0 = tile_id / nh * kPrepTile, h0 = tile_id % nh * kPrepTile;
+    const T_ *W = static_cast<const T_ *>(j.W);
+    const int nv = static_cast<int>(j.V - v0 < kPrepTile ? j.V - v0 : kPrepTile);  // may be <= 0: only padding of WT
+    const int tid = threadIdx.x;
+    // tile[r][c], r the source's row: v (h of an [H,V] head), c its contiguous index
+    constexpr int per_row = kPrepTile / N, rows_at_once = 256 / per_row;
+    const bool whole = HV ? nv == kPrepTile && j.V % N == 0 : true;
+    if (whole) {
+#pragma unroll
+        for (int r = tid / per_row; r < kPrepTile; r += rows_at_once) {
+            const int c = tid % per_row * N;
+            uint4 u = make_uint4(0u, 0u, 0u, 0u);
+            if (HV) u = *reinterpret_cast<const uint4 *>(W + (h0 + r) * j.V + v0 + c);
+            else if (r < nv) u = *reinterpret_cast<const uint4 *>(W + (v0 + r) * j.H + h0 + c);
+            const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if constexpr (sizeof(T_) == 2) *reinterpret_cast<uint32_t *>(tile + r * P + c + 2 * i) = w[i];
+                else tile[r * P + c + i] = __uint_as_float(w[i]);
+        }
+    } else {  // an [H,V] head whose rows end or start off 16-byte boundaries
+        for (int i = tid; i < kPrepTile * kPrepTile; i += 256) {
+            const int r = i / kPrepTile, c = i % kPrepTile;
+            tile[r * P + c] = c < nv ? W[(h0 + r) * j.V + v0 + c] : T_(0);
+        }
+    }
     __syncthreads();
-    for (int i = ty; i < 64; i += 4)
-        if (c0 + i < C && r0 + tx < R) dst[(c0 + i) * R + r0 + tx] = tile[tx][i];
+    auto at = [&](int v, int h) { return HV ? tile[h * P + v] : tile[v * P + h]; };
+    constexpr int G = kPrepTile / 8;  // groups of eight values per row
+#pragma unroll
+    for (int i = tid; i < kPrepTile * G; i += 256) {
+        const int r = i / G, c = i % G * 8;
+        if (j.WT) {  // r: hidden unit, c: vocabulary
+            uint4 u;
+            if constexpr (sizeof(T_) == 2) {
+                uint32_t w[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) w[k] = at(c + 2 * k, r) | static_cast<uint32_t>(at(c + 2 * k + 1, r)) << 16;
+                u = make_uint4(w[0], w[1], w[2], w[3]);
+            } else {
+                float x[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) x[k] = at(c + k, r);
+                u = round8(x);
+            }
+            *reinterpret_cast<uint4 *>(j.WT + (v0 * j.H + (h0 + r) * kBlockK + c)) = u;
+        }
+        if (r < nv && (j.Wvh || j.Ws)) {  // r: vocabulary, c: hidden unit
+            T_ x[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) x[k] = at(r, c + k);
+            if (j.Wvh) {
+                T_ *o = static_cast<T_ *>(j.Wvh) + (v0 + r) * j.H + h0 + c;
+                if constexpr (sizeof(T_) == 2) {
+                    uint32_t w[4];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) w[k] = x[2 * k] | static_cast<uint32_t>(x[2 * k + 1]) << 16;
+                    *reinterpret_cast<uint4 *>(o) = make_uint4(w[0], w[1], w[2], w[3]);
+                } else {
+                    reinterpret_cast<float4 *>(o)[0] = make_float4(x[0], x[1], x[2], x[3]);
+                    reinterpret_cast<float4 *>(o)[1] = make_float4(x[4], x[5], x[6], x[7]);
+                }
+            }
+            if constexpr (sizeof(T_) == 4)
+                if (j.Ws) store_split<0>(j.Ws + (v0 + r) * (kSplitTerms * j.H) + h0 + c, j.H, x);
+        }
+    }
 }
 
 __global__ void __launch_bounds__(256)
@@ -134,24 +240,23 @@ __global__ void __launch_bounds__(256) fill_zero_kernel(uint32_t *__restrict__ p
 // advantage have g = 0: their rows of dZ vanish, so the backward contractions run
 // over the remaining ("active") tokens only, in their original order.
 
-// act_idx[j] = index of the j-th token with g != 0; n_act[0] = their number.
-// One workgroup walks the tokens 4096 at a time (order-preserving, deterministic).
-__global__ void __launch_bounds__(1024)
-compact_active_kernel(const float *__restrict__ g, int64_t T, int32_t *__restrict__ act_idx,
-                      int32_t *__restrict__ n_act) {
-    __shared__ int wave_cnt[16];
+// act_idx[j] = index of the j-th token t < T with g_at(t) != 0 (called once per token); n_act[0] = their
+// number.  One workgroup of NT threads walks the tokens 4 * NT at a time (order-preserving, deterministic).
+template <int NT, typename G>
+__device__ __forceinline__ void compact_tokens(int64_t T, G g_at, int32_t *__restrict__ act_idx, int32_t *__restrict__ n_act,
+                                               int *wave_cnt) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int base = 0;
-    for (int64_t t0 = 0; t0 < T; t0 += 4096) {
+    for (int64_t t0 = 0; t0 < T; t0 += 4 * NT) {
         const int64_t t = t0 + threadIdx.x * 4;
         bool on[4];
         int mine = 0;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            on[i] = t + i < T && g[t + i] != 0.0f;
+            on[i] = t + i < T && g_at(t + i) != 0.0f;
             mine += on[i] ? 1 : 0;
         }
-        // exclusive prefix of `mine` over the wavefront, then over the 16 wavefronts
+        // exclusive prefix of `mine` over the wavefront, then over the wavefronts
         int incl = mine;
 #pragma unroll
         for (int d = 1; d < kWave; d <<= 1) {
@@ -162,7 +267,7 @@ compact_active_kernel(const float *__restrict__ g, int64_t T, int32_t *__restric
         __syncthreads();
         int off = 0, tot = 0;
 #pragma unroll
-        for (int w = 0; w < 16; ++w) {
+        for (int w = 0; w < NT / kWave; ++w) {
             const int c = wave_cnt[w];
             off += w < wave ? c : 0;
             tot += c;
@@ -177,33 +282,56 @@ compact_active_kernel(const float *__restrict__ g, int64_t T, int32_t *__restric
     if (threadIdx.x == 0) n_act[0] = base;
 }
 
+__global__ void __launch_bounds__(1024)
+compact_active_kernel(const float *__restrict__ g, int64_t T, int32_t *__restrict__ act_idx,
+                      int32_t *__restrict__ n_act) {
+    __shared__ int wave_cnt[1024 / kWave];
+    compact_tokens<1024>(T, [&](int64_t t) { return g[t]; }, act_idx, n_act, wave_cnt);
+}
+
 // Number of active tokens that fall into rows [row_base, row_base + cap) of the compact order.
 __device__ __forceinline__ int64_t active_rows(const int32_t *n_act, int64_t row_base, int64_t cap) {
     const int64_t n = static_cast<int64_t>(*n_act) - row_base;
     return n < 0 ? 0 : (n > cap ? cap : n);
 }
 
-// Rows [row_base, row_base + rows) of the compact order as contiguous copies: the hidden
-// states (Xc[r] = X[act_idx[row_base + r]]) and, packed into one 16-byte record per row, the
+// Rows [row_base, row_base + rows) of the compact order: their hidden states X[act_idx[row_base + r]] as
+// bf16 rows Xc (NULL: not) and, of fp32 ones, as the three-part split Xs (NULL: not); and, packed into
+// one 16-byte record per row, the
 // per-token scalars the recompute needs: tok[r] = (|g|, log2|g| - lse * log2(e), target with the
 // sign of g in the top bit (set: g > 0), 0): the gradient's softmax part -g * p is then
 // -sign(g) * exp2(z * log2(e) + tok.y), one multiply-add and one exponential per logit.
 // Rows past the last active token are filled with zeros and (0, -inf, no target): every
-// exponential underflows to an exact zero.  One workgroup per row.
+// exponential underflows to an exact zero.  A wavefront per row.  The first zero_rows rows of `zero`, of
+// zero_bytes each, are cleared on the way (d_hidden: rows of tokens without a gradient stay zero).
 template <typename T_>
 __global__ void __launch_bounds__(256)
 gather_chunk_kernel(const T_ *__restrict__ X, int64_t H, const int32_t *__restrict__ act_idx,
                     const int32_t *__restrict__ n_act, int64_t row_base, int64_t rows,
                     const int32_t *__restrict__ target, const float *__restrict__ lse, const float *__restrict__ g,
-                    T_ *__restrict__ Xc, float4 *__restrict__ tok) {
-    const int64_t r = blockIdx.x;
+                    bf16_t *__restrict__ Xc, bf16_t *__restrict__ Xs, float4 *__restrict__ tok, char *__restrict__ zero,
+                    int64_t zero_rows, int64_t zero_bytes) {
+    const int64_t r = flat_block() * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (r < zero_rows) {
+        uint4 *z = reinterpret_cast<uint4 *>(zero + r * zero_bytes);  // a multiple of 128 bytes
+        for (int i = lane; i < zero_bytes / 16; i += kWave) z[i] = make_uint4(0u, 0u, 0u, 0u);
+    }
+    if (r >= rows) return;
     const bool live = r < active_rows(n_act, row_base, rows);
     const int64_t src = live ? act_idx[row_base + r] : 0;
-    const int n16 = static_cast<int>(H * sizeof(T_) / 16);  // H is a multiple of 64
-    const uint4 *in = reinterpret_cast<const uint4 *>(X + src * H);
-    uint4 *out = reinterpret_cast<uint4 *>(Xc + r * H);
-    for (int i = threadIdx.x; i < n16; i += 256) out[i] = live ? in[i] : make_uint4(0u, 0u, 0u, 0u);
-    if (threadIdx.x == 0) {
+    for (int i = lane; i < H / 8; i += kWave) {  // H is a multiple of 64
+        if constexpr (sizeof(T_) == 2) {
+            reinterpret_cast<uint4 *>(Xc + r * H)[i] =
+                live ? reinterpret_cast<const uint4 *>(X + src * H)[i] : make_uint4(0u, 0u, 0u, 0u);
+        } else {
+            float x[8] = {};
+            if (live) load8(X + src * H + i * 8, x);
+            if (Xc) reinterpret_cast<uint4 *>(Xc + r * H)[i] = round8(x);
+            if (Xs) store_split<1>(Xs + r * (kSplitTerms * H) + i * 8, H, x);
+        }
+    }
+    if (lane == 0) {
         const float gs = live ? g[src] : 0.0f;
         const uint32_t ts = live ? (static_cast<uint32_t>(target[src]) & 0x7fffffffu) | (gs > 0.0f ? 0x80000000u : 0u)
                                  : 0x7fffffffu;
@@ -230,18 +358,9 @@ __device__ __forceinline__ float dot8(const uint4 a, const uint4 b) {
 }
 
 template <typename T_>
-__global__ void __launch_bounds__(256)
-target_logit_kernel(const T_ *__restrict__ X, const T_ *__restrict__ Wvh, int64_t H, int64_t V, int64_t T,
-                    const int32_t *__restrict__ target, float *__restrict__ z_target, uint32_t *__restrict__ done) {
-    const int64_t t = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
-    if (blockIdx.x == 0 && threadIdx.x == 0) *done = 0u;  // counts the workgroups of the token kernel
-    const int lane = threadIdx.x & 63;
-    if (t >= T) return;
-    const int64_t y = target[t];
-    if (y < 0 || y >= V) {
-        if (lane == 0) z_target[t] = __builtin_nanf("");
-        return;
-    }
+__device__ __forceinline__ float target_logit(const T_ *__restrict__ X, const T_ *__restrict__ Wvh, int64_t H, int64_t V,
+                                              int64_t y, int64_t t, int lane) {
+    if (y < 0 || y >= V) return __builtin_nanf("");
     float s = 0.0f;
     if constexpr (sizeof(T_) == 2) {
         const uint4 *x = reinterpret_cast<const uint4 *>(X + t * H), *w = reinterpret_cast<const uint4 *>(Wvh + y * H);
@@ -253,8 +372,112 @@ target_logit_kernel(const T_ *__restrict__ X, const T_ *__restrict__ Wvh, int64_
             s = fmaf(a.x, b.x, s); s = fmaf(a.y, b.y, s); s = fmaf(a.z, b.z, s); s = fmaf(a.w, b.w, s);
         }
     }
-    s = wave_sum(s);
-    if (lane == 0) z_target[t] = s;
+    return wave_sum(s);
+}
+
+// The reference of a token whose logits are stored as scaled probabilities (see below, one-call form without
+// a loss mask), times log2(e); 0 where the token has no valid target logit or old_logp is not finite (its
+// stored row stays finite and is multiplied by 0).
+__device__ __forceinline__ float probs_reference(float z_target, float old_logp) {
+    const float r = (z_target - old_logp) * kLog2e;
+    return fabsf(r) < 3.0e38f ? r : 0.0f;  // not NaN, not infinite
+}
+
+template <typename T_, bool HV>
+__global__ void __launch_bounds__(256) prep_kernel(PrepJobs j) {
+    __shared__ __attribute__((aligned(16))) T_ tile[kPrepTile * kPrepPitch<T_>];
+    __shared__ int scratch[256 / kWave];
+    int64_t b = flat_block();
+    if (b == 0 && threadIdx.x == 0 && j.done) *j.done = 0u;  // counts the workgroups of the token kernel
+    if (b < j.head_blocks) return prep_head_tile<T_, HV>(j, b, tile);
+    b -= j.head_blocks;
+    if (b < j.row_blocks) {
+        if constexpr (sizeof(T_) == 4) {
+            const int64_t i = (b * 256 + threadIdx.x) * 8, r = i / j.H, k = i % j.H;  // H is a multiple of 64
+            if (r >= j.rows) return;
+            float x[8];
+            load8(static_cast<const float *>(j.X) + i, x);
+            store_split<1>(j.Xs + r * (kSplitTerms * j.H) + k, j.H, x);
+        }
+        return;
+    }
+    b -= j.row_blocks;
+    if (b < j.target_blocks) {
+        const int64_t t = b * 4 + (threadIdx.x >> 6);
+        const int lane = threadIdx.x & 63;
+        float ref = 0.0f;
+        if (t < j.T) {
+            const float z = target_logit(static_cast<const T_ *>(j.X), static_cast<const T_ *>(j.Wrows), j.H, j.V,
+                                         j.target[t], t, lane);
+            if (lane == 0) j.z_target[t] = z;
+            if (j.ref2) ref = probs_reference(z, j.old_logp[t]);
+        }
+        if (j.ref2 && t < j.T_ref && lane == 0) j.ref2[t] = ref;
+        return;
+    }
+    b -= j.target_blocks;
+    if (b == 0 && j.count) {
+        const int64_t c = j.mask ? count_mask(j.mask, j.T, scratch) : j.T;
+        if (threadIdx.x == 0) j.count[0] = static_cast<double>(c);
+        return;
+    }
+    if (b == (j.count ? 1 : 0) && j.g) {
+        __shared__ int32_t cu_lds[kCuStaged];
+        const int32_t *cu = stage_offsets(j.in.cu, j.in.B, cu_lds);
+        const double M = static_cast<double>(j.in.mask ? count_mask(j.in.mask, j.in.T, scratch) : j.in.T);
+        __syncthreads();
+        compact_tokens<256>(j.in.T, [&](int64_t t) { return j.g[t] = token_grad(j.logp, j.in, cu, M, j.grad_loss, t); }, j.act_idx,
+                            j.n_act, scratch);
+    }
+}
+
+// The jobs that make the head's forms; those of the hidden rows X[0..rows) where they are fp32.
+static PrepJobs prep_head_jobs(const spo_pg_desc *d, void *Wvh, bf16_t *Ws, bf16_t *WT) {
+    PrepJobs j{};
+    j.H = d->H;
+    j.V = d->V;
+    j.T = d->T;
+    j.W = d->W;
+    j.Wvh = Wvh;
+    j.Ws = Ws;
+    j.WT = WT;
+    if (Wvh || Ws || WT) j.head_blocks = ceil_div(d->V, WT ? TL::BM : kPrepTile) * (WT ? TL::BM / kPrepTile : 1) * (d->H / kPrepTile);
+    return j;
+}
+static void prep_rows(PrepJobs &j, const spo_pg_desc *d, const void *X, int64_t rows, bf16_t *Xs) {
+    if (d->dtype != SPO_FP32) return;
+    j.X = X;
+    j.Xs = Xs;
+    j.rows = rows;
+    j.row_blocks = ceil_div(rows * (d->H / 8), 256);
+}
+static void launch_prep(const spo_pg_desc *d, const PrepJobs &j, hipStream_t s) {
+    if (j.blocks() == 0) return;
+    const bool hv = d->w_layout == SPO_W_HV;
+    auto *kernel = d->dtype == SPO_FP32 ? (hv ? prep_kernel<float, true> : prep_kernel<float, false>)
+                                        : (hv ? prep_kernel<bf16_t, true> : prep_kernel<bf16_t, false>);
+    kernel<<<fold_grid(j.blocks()), 256, 0, s>>>(j);
+}
+// The jobs of `j` and the target logits: in one launch, unless the latter read a form of the head that the former make.
+static void launch_prep_with_targets(const spo_pg_desc *d, PrepJobs j, float *z_target, float *ref2, int64_t T_ref,
+                                     uint32_t *done, hipStream_t s) {
+    if (j.Wvh) {
+        launch_prep(d, j, s);
+        const void *Wvh = j.Wvh;
+        j = prep_head_jobs(d, nullptr, nullptr, nullptr);
+        j.Wrows = Wvh;
+    } else {
+        j.Wrows = d->W;
+    }
+    j.X = d->hidden;
+    j.target = d->target;
+    j.old_logp = d->old_logp;
+    j.z_target = z_target;
+    j.ref2 = ref2;
+    j.T_ref = T_ref;
+    j.done = done;
+    j.target_blocks = ceil_div(ref2 ? T_ref : d->T, 4);
+    launch_prep(d, j, s);
 }
 
 // ----------------------------------------------------------------------------
@@ -1061,21 +1284,6 @@ dz_from_logits_kernel(const uint16_t *__restrict__ Z, int64_t z_blk, const float
 // the price is that rows of tokens without a gradient (c_t = 0) are multiplied like the others,
 // which is why this form serves batches without a loss mask.
 
-// ref2[t] = r_t * log2(e); 0 where the token has no valid target logit, where old_logp is not
-// finite, and for the padding rows Tv <= t < Tzp (their stored rows stay finite and are multiplied by 0).
-__global__ void __launch_bounds__(256)
-probs_reference_kernel(const float *__restrict__ z_target, const float *__restrict__ old_logp, int64_t Tv, int64_t Tzp,
-                       float *__restrict__ ref2) {
-    const int64_t t = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (t >= Tzp) return;
-    float r = 0.0f;
-    if (t < Tv) {
-        r = (z_target[t] - old_logp[t]) * kLog2e;
-        if (!(fabsf(r) < 3.0e38f)) r = 0.0f;  // NaN or infinite
-    }
-    ref2[t] = r;
-}
-
 // dst[t][:] = bf16(c[t] * src[t][:]) for t < rows_pad (c is 0 from the last valid row on: zeros).
 // One workgroup per row; H is a multiple of 64.
 template <typename T_>
@@ -1136,10 +1344,17 @@ struct FwdPlan {
     float *part_max, *part_sum, *z_target;
     FwdPartial *partials;
     uint32_t *done;
-    bf16_t *Xs, *Ws, *Wvh;  // split-expanded operands (fp32), [V,H] copy (HV layout)
-    float *W32;             // [V,H] copy of an fp32 head given as [H,V]
+    bf16_t *Xs, *Ws;  // split-expanded operands (fp32)
+    void *Wvh;        // [V,H] copy of a head given as [H,V]
     size_t bytes;
 };
+
+// room for the [V,H] copy of a head given as [H,V]
+static void *take_head_copy(Arena &a, const spo_pg_desc *d) {
+    if (d->w_layout != SPO_W_HV) return nullptr;
+    char *p = a.take<char>(static_cast<size_t>(d->V) * d->H * (d->dtype == SPO_FP32 ? 4 : 2));
+    return p;
+}
 
 static FwdPlan plan_fwd(const spo_pg_desc *d, void *ws) {
     FwdPlan p;
@@ -1155,15 +1370,12 @@ static FwdPlan plan_fwd(const spo_pg_desc *d, void *ws) {
     p.z_target = a.take<float>(p.T_pad);
     p.partials = a.take<FwdPartial>(p.nblk_tok);
     p.done = a.take<uint32_t>(1);
-    p.Xs = p.Ws = p.Wvh = nullptr;
-    p.W32 = nullptr;
+    p.Xs = p.Ws = nullptr;
     if (d->dtype == SPO_FP32) {
         p.Xs = a.take<bf16_t>(static_cast<size_t>(std::max<int64_t>(d->T, 1)) * p.Kc);
         p.Ws = a.take<bf16_t>(static_cast<size_t>(d->V) * p.Kc);
-        if (d->w_layout == SPO_W_HV) p.W32 = a.take<float>(static_cast<size_t>(d->V) * d->H);
-    } else if (d->w_layout == SPO_W_HV) {
-        p.Wvh = a.take<bf16_t>(static_cast<size_t>(d->V) * d->H);
     }
+    p.Wvh = take_head_copy(a, d);
     p.bytes = a.used;
     return p;
 }
@@ -1186,42 +1398,17 @@ int fused_fwd(const spo_pg_desc *d, float *loss, float *logp, float *lse, float 
     if (ws_bytes < p.bytes) return SPO_EWORKSPACE;
     if ((rc = set_lds_limit())) return rc;
     if (d->T > 0) {
-        const char *X, *W;
-        if (d->dtype == SPO_FP32) {
-            split_expand_kernel<<<grid1(d->T * d->H), 256, 0, s>>>(static_cast<const float *>(d->hidden), d->T, d->H, p.Xs, 1);
-            const float *w32 = static_cast<const float *>(d->W);
-            if (d->w_layout == SPO_W_HV) {
-                transpose_f32_kernel<<<dim3(grid1(d->H, 64), grid1(d->V, 64)), 256, 0, s>>>(w32, d->H, d->V, p.W32);
-                w32 = p.W32;
-            }
-            split_expand_kernel<<<grid1(d->V * d->H), 256, 0, s>>>(w32, d->V, d->H, p.Ws, 0);
-            X = reinterpret_cast<const char *>(p.Xs);
-            W = reinterpret_cast<const char *>(p.Ws);
-        } else {
-            X = static_cast<const char *>(d->hidden);
-            if (d->w_layout == SPO_W_HV) {
-                transpose_to_bf16_kernel<bf16_t><<<dim3(grid1(d->H, 64), grid1(d->V, 64)), 256, 0, s>>>(
-                    static_cast<const bf16_t *>(d->W), d->H, d->V, d->V, p.Wvh, d->H, d->V, d->H);
-                W = reinterpret_cast<const char *>(p.Wvh);
-            } else {
-                W = static_cast<const char *>(d->W);
-            }
-        }
+        const bool fp32 = d->dtype == SPO_FP32;
+        PrepJobs jobs = prep_head_jobs(d, p.Wvh, p.Ws, nullptr);
+        prep_rows(jobs, d, d->hidden, d->T, p.Xs);
+        launch_prep_with_targets(d, jobs, p.z_target, nullptr, 0, p.done, s);
+        const char *X = fp32 ? reinterpret_cast<const char *>(p.Xs) : static_cast<const char *>(d->hidden);
+        const char *W = fp32 ? reinterpret_cast<const char *>(p.Ws) : static_cast<const char *>(p.Wvh ? p.Wvh : d->W);
         const int64_t blocks = SweepMap(p.nTt, p.nVt, p.nsplit).blocks();
         ScopedKernelTimer timer(kTimeFwdSweep, s);
         fwd_sweep_kernel<kEmitNone><<<static_cast<unsigned>(blocks), TL::NT, kSweepLds, s>>>(
             W, p.Kc * 2, d->V, X, p.Kc * 2, d->T, static_cast<int>(p.Kc / kBK), p.nsplit, p.nTt, p.nVt, p.T_pad,
             p.part_max, p.part_sum, nullptr, 0, nullptr);
-    }
-    if (d->T > 0) {
-        if (d->dtype == SPO_FP32)
-            target_logit_kernel<float><<<grid1(d->T, 4), 256, 0, s>>>(
-                static_cast<const float *>(d->hidden), d->w_layout == SPO_W_HV ? p.W32 : static_cast<const float *>(d->W),
-                d->H, d->V, d->T, d->target, p.z_target, p.done);
-        else
-            target_logit_kernel<bf16_t><<<grid1(d->T, 4), 256, 0, s>>>(
-                static_cast<const bf16_t *>(d->hidden), d->w_layout == SPO_W_HV ? p.Wvh : static_cast<const bf16_t *>(d->W),
-                d->H, d->V, d->T, d->target, p.z_target, p.done);
     }
     token_loss_kernel<<<static_cast<unsigned>(p.nblk_tok), token_threads(p.nsplit, p.nblk_tok), 0, s>>>(
         p.part_max, p.part_sum, p.nsplit, p.T_pad, p.z_target, token_inputs(d, 0, d->T), logp, lse, p.partials,
@@ -1233,14 +1420,13 @@ struct BwdPlan {
     int64_t Tc, V_pad, V_blk, Kc, T_pad;  // V rounded up to a k-step (64) and to whole tiles (256)
     double *count;
     float *g, *dW_acc;
-    bf16_t *WT, *Xb, *dZ, *Xs, *Ws, *Wvh;  // Xb: bf16 copy of the gathered rows of an fp32 hidden
-    float *W32;  // [V,H] copy of an fp32 head given as [H,V]
+    bf16_t *WT, *Xc, *dZ, *Xs, *Ws;  // Xc: the gathered rows in bf16
+    void *Wvh;                 // [V,H] copy of a head given as [H,V]
     int32_t *act_idx, *n_act;  // active-token list, its length
     float4 *tok;               // per-chunk records (g, -lse*log2e, target) of the gathered rows
     int dx_split;              // parts the dHidden contraction is cut into (1: not split)
     float *dx_part;            // their fp32 partial results [dx_split][Tc][H]
     float *dw_tail;            // partial tiles of a contraction's short last round (see launch_gemm)
-    void *Xc;
     size_t bytes;
 };
 
@@ -1264,20 +1450,17 @@ static BwdPlan plan_bwd(const spo_pg_desc *d, int64_t chunk_tokens, void *ws, bo
     const int64_t dx_tiles = (p.Tc / TL::BN) * ceil_div(d->H, TL::BM);
     p.dx_split = dx_tiles * 4 < kChipCUs * 3 ? static_cast<int>(std::min<int64_t>(8, kChipCUs / dx_tiles)) : 1;
     p.dx_part = p.dx_split > 1 ? a.take<float>(static_cast<size_t>(p.dx_split) * p.Tc * d->H) : nullptr;
-    p.Xc = a.take<char>(static_cast<size_t>(p.Tc) * d->H * (d->dtype == SPO_FP32 ? 4 : 2));
+    p.Xc = a.take<bf16_t>(static_cast<size_t>(p.Tc) * d->H);
     p.WT = a.take<bf16_t>(static_cast<size_t>(d->H) * p.V_blk);   // [V_blk / 64][H][64]
     p.dZ = a.take<bf16_t>(static_cast<size_t>(p.Tc) * p.V_blk);  // [V_blk / 64][rows of the chunk][64]
-    p.Xb = p.Xs = p.Ws = p.Wvh = nullptr;
+    p.Xs = p.Ws = nullptr;
     p.dW_acc = nullptr;
-    p.W32 = nullptr;
     if (d->dtype == SPO_FP32) {
-        p.Xb = a.take<bf16_t>(static_cast<size_t>(p.Tc) * d->H);
         p.Xs = a.take<bf16_t>(static_cast<size_t>(p.Tc) * p.Kc);
         p.Ws = a.take<bf16_t>(static_cast<size_t>(d->V) * p.Kc);
-        if (d->w_layout == SPO_W_HV) p.W32 = a.take<float>(static_cast<size_t>(d->V) * d->H);
-    } else if (d->w_layout == SPO_W_HV) {
-        p.Wvh = a.take<bf16_t>(static_cast<size_t>(d->V) * d->H);
     }
+    // the logits of a bf16 head are formed from rows per vocabulary entry; an fp32 head is split from any layout
+    p.Wvh = d->dtype == SPO_BF16 ? take_head_copy(a, d) : nullptr;
     if (need_dw_acc) p.dW_acc = a.take<float>(static_cast<size_t>(d->V) * d->H);
     p.dw_tail = a.take<float>(static_cast<size_t>(kTailTiles) * TL::BM * TL::BN);
     p.bytes = a.used;
@@ -1288,13 +1471,6 @@ int fused_bwd_workspace(const spo_pg_desc *d, int64_t chunk_tokens, size_t *byte
     // sized for the larger case (bf16 d_W needs an fp32 accumulator)
     *bytes = plan_bwd(d, chunk_tokens, nullptr, true).bytes;
     return SPO_OK;
-}
-
-template <typename SrcT>
-static void launch_transpose(const SrcT *src, int64_t R, int64_t C, int64_t ld_src, bf16_t *dst, int64_t R_pad,
-                             int64_t C_pad, int64_t ld_dst, hipStream_t s) {
-    transpose_to_bf16_kernel<SrcT><<<dim3(grid1(R_pad, 64), grid1(C_pad, 64)), 256, 0, s>>>(src, R, C, ld_src, dst,
-                                                                                         R_pad, C_pad, ld_dst);
 }
 
 // `tail`: room for kTailTiles fp32 tiles; with it a short last round of tiles is cut along the
@@ -1329,6 +1505,23 @@ static void launch_gemm(const bf16_t *A, int64_t lda, int64_t M, const bf16_t *B
     }
 }
 
+// The gathered rows of a chunk (see gather_chunk_kernel), and d_hidden[0..zero_rows) (NULL: not) cleared.
+static void launch_gather(const spo_pg_desc *d, const void *X, const int32_t *act_idx, const int32_t *n_act, int64_t row_base,
+                          int64_t rows, const int32_t *target, const float *lse, const float *g, bf16_t *Xc, bf16_t *Xs,
+                          float4 *tok, void *d_hidden, int d_hidden_dtype, int64_t zero_rows, hipStream_t s) {
+    if (!d_hidden) zero_rows = 0;
+    const dim3 grid = fold_grid(ceil_div(std::max(rows, zero_rows), 4));
+    const int64_t zero_bytes = d->H * (d_hidden_dtype == SPO_FP32 ? 4 : 2);
+    if (d->dtype == SPO_FP32)
+        gather_chunk_kernel<float><<<grid, 256, 0, s>>>(static_cast<const float *>(X), d->H, act_idx, n_act, row_base, rows,
+                                                        target, lse, g, Xc, Xs, tok, static_cast<char *>(d_hidden), zero_rows,
+                                                        zero_bytes);
+    else
+        gather_chunk_kernel<bf16_t><<<grid, 256, 0, s>>>(static_cast<const bf16_t *>(X), d->H, act_idx, n_act, row_base, rows,
+                                                         target, lse, g, Xc, Xs, tok, static_cast<char *>(d_hidden), zero_rows,
+                                                         zero_bytes);
+}
+
 int fused_bwd(const spo_pg_desc *d, const float *logp, const float *lse, float grad_loss, void *d_hidden,
               int d_hidden_dtype, void *d_W, int d_W_dtype, int accumulate_dW, int64_t chunk_tokens, void *ws,
               size_t ws_bytes, hipStream_t s) {
@@ -1348,55 +1541,33 @@ int fused_bwd(const spo_pg_desc *d, const float *logp, const float *lse, float g
         }
         return launch_status();
     }
-    launch_grad_scale(d, logp, p.T_pad, grad_loss, p.count, p.g, s);
-    // vocabulary-major head for the recompute, hidden-major head for dHidden
-    const bf16_t *Wk;
-    if (d->dtype == SPO_FP32) {
-        const float *w32 = static_cast<const float *>(d->W);
-        if (d->w_layout == SPO_W_HV) {
-            transpose_f32_kernel<<<dim3(grid1(H, 64), grid1(V, 64)), 256, 0, s>>>(w32, H, V, p.W32);
-            w32 = p.W32;
-        }
-        split_expand_kernel<<<grid1(V * H), 256, 0, s>>>(w32, V, H, p.Ws, 0);
-        Wk = p.Ws;
-        if (d_hidden) launch_transpose(w32, V, H, H, p.WT, p.V_blk, H, 0, s);
-    } else {
-        const bf16_t *Wvh = static_cast<const bf16_t *>(d->W);
-        if (d->w_layout == SPO_W_HV) {
-            launch_transpose(static_cast<const bf16_t *>(d->W), H, V, V, p.Wvh, H, V, H, s);
-            Wvh = p.Wvh;
-        }
-        Wk = Wvh;
-        if (d_hidden) launch_transpose(Wvh, V, H, H, p.WT, p.V_blk, H, 0, s);
+    // vocabulary-major head for the recompute, hidden-major head for dHidden; the gradient factors and the
+    // tokens that carry one, in order: the chunks below run over this list
+    PrepJobs jobs = prep_head_jobs(d, p.Wvh, p.Ws, d_hidden ? p.WT : nullptr);
+    const bool grad_inside = T <= kPrepGradTokens;
+    if (grad_inside) {
+        jobs.g = p.g;
+        jobs.logp = logp;
+        jobs.in = token_inputs(d, 0, T);
+        jobs.grad_loss = grad_loss;
+        jobs.act_idx = p.act_idx;
+        jobs.n_act = p.n_act;
     }
-    // the tokens that carry a gradient, in order; the chunks below run over this list
-    compact_active_kernel<<<1, 1024, 0, s>>>(p.g, T, p.act_idx, p.n_act);
-    if (d_hidden) {  // rows of the other tokens stay zero
-        const int64_t words = T * H / (d_hidden_dtype == SPO_FP32 ? 1 : 2);
-        fill_zero_kernel<<<grid1(words), 256, 0, s>>>(static_cast<uint32_t *>(d_hidden), words);
+    launch_prep(d, jobs, s);
+    if (!grad_inside) {
+        launch_grad_scale(d, logp, p.T_pad, grad_loss, p.count, p.g, s);
+        compact_active_kernel<<<1, 1024, 0, s>>>(p.g, T, p.act_idx, p.n_act);
     }
+    const void *Wk = d->dtype == SPO_FP32 ? p.Ws : (p.Wvh ? p.Wvh : d->W);
     const int64_t nVt = ceil_div(V, TL::BM);
     for (int64_t t0 = 0, c = 0; t0 < T; t0 += p.Tc, ++c) {
         // rows [t0, t0 + Tcp) of the compact order; how many of them exist is known on the
         // device only, so every launch is sized for the most there can be and trims itself
         const int64_t Tcp = round_up(std::min(p.Tc, T - t0), TL::BN);
-        const bf16_t *Xk, *Xrows;  // operand of the recompute; the rows as plain bf16 (operand of dW)
-        if (d->dtype == SPO_FP32) {
-            float *xc = static_cast<float *>(p.Xc);
-            gather_chunk_kernel<float><<<static_cast<unsigned>(Tcp), 256, 0, s>>>(
-                static_cast<const float *>(d->hidden), H, p.act_idx, p.n_act, t0, Tcp, d->target, lse, p.g, xc,
-                p.tok);
-            split_expand_kernel<<<grid1(Tcp * H), 256, 0, s>>>(xc, Tcp, H, p.Xs, 1);
-            Xk = p.Xs;
-            if (d_W) f32_to_bf16_kernel<<<grid1(Tcp * H), 256, 0, s>>>(xc, p.Xb, Tcp * H);
-            Xrows = p.Xb;
-        } else {
-            bf16_t *xc = static_cast<bf16_t *>(p.Xc);
-            gather_chunk_kernel<bf16_t><<<static_cast<unsigned>(Tcp), 256, 0, s>>>(
-                static_cast<const bf16_t *>(d->hidden), H, p.act_idx, p.n_act, t0, Tcp, d->target, lse, p.g, xc,
-                p.tok);
-            Xk = Xrows = xc;
-        }
+        // (the first chunk's launch also clears d_hidden: later ones would clear what earlier ones wrote)
+        launch_gather(d, d->hidden, p.act_idx, p.n_act, t0, Tcp, d->target, lse, p.g, d->dtype == SPO_BF16 || d_W ? p.Xc : nullptr,
+                      p.Xs, p.tok, c == 0 ? d_hidden : nullptr, d_hidden_dtype, T, s);
+        const bf16_t *Xk = d->dtype == SPO_FP32 ? p.Xs : p.Xc, *Xrows = p.Xc;  // operands of the recompute and of dW
         {
             const int64_t wgs = sweep_blocks_max(Tcp / TL::BN, nVt);
             ScopedKernelTimer timer(kTimeRecompute, s);
@@ -1436,20 +1607,20 @@ int fused_bwd(const spo_pg_desc *d, const float *logp, const float *lse, float g
 // gradients, and the two contractions follow: three products of size T x V x H instead of four.
 // By default a piece's stored logits stay within kDzBudgetBytes, and so do its gradients.
 // Without a loss mask the pass over the stored logits is left out as well: the sweep stores
-// bf16 scaled probabilities that the contractions read as they are (probs_reference_kernel).
+// bf16 scaled probabilities that the contractions read as they are (probs_reference).
 struct FbPlan {
     int64_t Tz, T_pad, V_pad, V_blk, Kc, nVt, nblk_tok;
     int nsplit;
     double *count;
-    float *g, *z_target, *part_max, *part_sum, *offs, *dW_acc, *W32, *dx_part, *dw_tail, *cscale;
-    bool dense;  // no loss mask: the sweep stores what the contractions read (see probs_reference_kernel)
+    float *g, *z_target, *part_max, *part_sum, *offs, *dW_acc, *dx_part, *dw_tail, *cscale;
+    bool dense;  // no loss mask: the sweep stores what the contractions read; offs: the references of all tokens
     FwdPartial *partials;
     uint32_t *done;
     int32_t *act_idx, *n_act;
     float4 *tok;
     uint16_t *Z;
-    bf16_t *dZ, *WT, *Xb, *Xs, *Ws, *Wvh;
-    void *Xc;
+    bf16_t *dZ, *WT, *Xc, *Xs, *Ws;
+    void *Wvh;
     int dx_split;
     size_t bytes;
 };
@@ -1479,7 +1650,7 @@ static FbPlan plan_fb(const spo_pg_desc *d, int64_t chunk_tokens, void *ws, bool
     p.part_max = a.take<float>(static_cast<size_t>(p.nsplit) * p.Tz);
     p.part_sum = a.take<float>(static_cast<size_t>(p.nsplit) * p.Tz);
     p.dense = d->mask == nullptr;
-    p.offs = a.take<float>(p.dense ? p.Tz : static_cast<size_t>(p.nVt) * TL::WGM * p.Tz);
+    p.offs = a.take<float>(p.dense ? p.T_pad : static_cast<size_t>(p.nVt) * TL::WGM * p.Tz);
     p.cscale = p.dense ? a.take<float>(p.Tz) : nullptr;
     p.act_idx = a.take<int32_t>(p.Tz);
     p.n_act = a.take<int32_t>(1);
@@ -1487,20 +1658,17 @@ static FbPlan plan_fb(const spo_pg_desc *d, int64_t chunk_tokens, void *ws, bool
     const int64_t dx_tiles = (p.Tz / TL::BN) * ceil_div(d->H, TL::BM);
     p.dx_split = want_dx && dx_tiles * 4 < kChipCUs * 3 ? static_cast<int>(std::min<int64_t>(8, kChipCUs / dx_tiles)) : 1;
     p.dx_part = p.dx_split > 1 ? a.take<float>(static_cast<size_t>(p.dx_split) * p.Tz * d->H) : nullptr;
-    p.Xc = a.take<char>(static_cast<size_t>(p.Tz) * d->H * (d->dtype == SPO_FP32 ? 4 : 2));
+    p.Xc = a.take<bf16_t>(static_cast<size_t>(p.Tz) * d->H);
     p.WT = want_dx ? a.take<bf16_t>(static_cast<size_t>(d->H) * p.V_blk) : nullptr;
     p.Z = a.take<uint16_t>(static_cast<size_t>(p.Tz) * p.V_blk);
     p.dZ = p.dense ? nullptr : a.take<bf16_t>(static_cast<size_t>(p.Tz) * p.V_blk);
-    p.Xb = p.Xs = p.Ws = p.Wvh = nullptr;
-    p.dW_acc = p.W32 = nullptr;
+    p.Xs = p.Ws = nullptr;
+    p.dW_acc = nullptr;
     if (d->dtype == SPO_FP32) {
-        p.Xb = a.take<bf16_t>(static_cast<size_t>(p.Tz) * d->H);
         p.Xs = a.take<bf16_t>(static_cast<size_t>(p.Tz) * p.Kc);
         p.Ws = a.take<bf16_t>(static_cast<size_t>(d->V) * p.Kc);
-        if (d->w_layout == SPO_W_HV) p.W32 = a.take<float>(static_cast<size_t>(d->V) * d->H);
-    } else if (d->w_layout == SPO_W_HV) {
-        p.Wvh = a.take<bf16_t>(static_cast<size_t>(d->V) * d->H);
     }
+    p.Wvh = take_head_copy(a, d);
     if (need_dw_acc) p.dW_acc = a.take<float>(static_cast<size_t>(d->V) * d->H);
     p.dw_tail = a.take<float>(static_cast<size_t>(kTailTiles) * TL::BM * TL::BN);
     p.bytes = a.used;
@@ -1533,55 +1701,36 @@ int fused_fwd_bwd(const spo_pg_desc *d, float grad_loss, float *loss, float *log
                                                     p.partials, TokenGrad{}, 1, p.done, loss, stats);
         return launch_status();
     }
-    mask_count_kernel<<<1, d->mask ? 1024 : kWave, 0, s>>>(d->mask, T, p.count);
     // the head as the kernels read it: one row per vocabulary entry for the logits, one row per
-    // hidden unit (blocked over the vocabulary) for dHidden
-    const char *Wk;
-    if (d->dtype == SPO_FP32) {
-        const float *w32 = static_cast<const float *>(d->W);
-        if (d->w_layout == SPO_W_HV) {
-            transpose_f32_kernel<<<dim3(grid1(H, 64), grid1(V, 64)), 256, 0, s>>>(w32, H, V, p.W32);
-            w32 = p.W32;
-        }
-        split_expand_kernel<<<grid1(V * H), 256, 0, s>>>(w32, V, H, p.Ws, 0);
-        Wk = reinterpret_cast<const char *>(p.Ws);
-        if (d_hidden) launch_transpose(w32, V, H, H, p.WT, p.V_blk, H, 0, s);
-        target_logit_kernel<float><<<grid1(T, 4), 256, 0, s>>>(static_cast<const float *>(d->hidden), w32, H, V, T,
-                                                               d->target, p.z_target, p.done);
-    } else {
-        const bf16_t *Wvh = static_cast<const bf16_t *>(d->W);
-        if (d->w_layout == SPO_W_HV) {
-            launch_transpose(static_cast<const bf16_t *>(d->W), H, V, V, p.Wvh, H, V, H, s);
-            Wvh = p.Wvh;
-        }
-        Wk = reinterpret_cast<const char *>(Wvh);
-        if (d_hidden) launch_transpose(Wvh, V, H, H, p.WT, p.V_blk, H, 0, s);
-        target_logit_kernel<bf16_t><<<grid1(T, 4), 256, 0, s>>>(static_cast<const bf16_t *>(d->hidden), Wvh, H, V, T,
-                                                                d->target, p.z_target, p.done);
-    }
-    if (d_hidden && !p.dense) {  // rows of tokens without a gradient stay zero (without a mask every row is written)
-        const int64_t words = T * H / (d_hidden_dtype == SPO_FP32 ? 1 : 2);
-        fill_zero_kernel<<<grid1(words), 256, 0, s>>>(static_cast<uint32_t *>(d_hidden), words);
-    }
+    // hidden unit (blocked over the vocabulary) for dHidden; the first piece's rows; the target logits
+    PrepJobs jobs = prep_head_jobs(d, p.Wvh, p.Ws, d_hidden ? p.WT : nullptr);
+    prep_rows(jobs, d, d->hidden, std::min(p.Tz, T), p.Xs);
+    jobs.mask = d->mask;
+    jobs.count = p.count;
+    launch_prep_with_targets(d, jobs, p.z_target, p.dense ? p.offs : nullptr, p.T_pad, p.done, s);
+    const char *Wk = static_cast<const char *>(d->dtype == SPO_FP32 ? p.Ws : (p.Wvh ? p.Wvh : d->W));
     const size_t x_elt = d->dtype == SPO_FP32 ? 4 : 2, dx_elt = d_hidden_dtype == SPO_FP32 ? 4 : 2;
     for (int64_t t0 = 0, c = 0; t0 < T; t0 += p.Tz, ++c) {
         const int64_t Tv = std::min(p.Tz, T - t0), Tzp = round_up(Tv, TL::BN);
         const char *Xpiece = static_cast<const char *>(d->hidden) + t0 * H * x_elt;
         const char *Xk = Xpiece;
         if (d->dtype == SPO_FP32) {
-            split_expand_kernel<<<grid1(Tv * H), 256, 0, s>>>(reinterpret_cast<const float *>(Xpiece), Tv, H, p.Xs, 1);
+            if (c > 0) {
+                jobs = prep_head_jobs(d, nullptr, nullptr, nullptr);
+                prep_rows(jobs, d, Xpiece, Tv, p.Xs);
+                launch_prep(d, jobs, s);
+            }
             Xk = reinterpret_cast<const char *>(p.Xs);
         }
         // the last piece may be shorter: its own choice of splits, within the room for partial results
         const SweepMap map(Tzp / TL::BN, p.nVt,
                            Tzp == p.Tz ? p.nsplit : sweep_splits(Tzp / TL::BN, p.nVt, static_cast<uint32_t>(std::min<int64_t>(p.nsplit * p.Tz / Tzp, kNoSplitCap))));
-        if (p.dense) probs_reference_kernel<<<grid1(Tzp), 256, 0, s>>>(p.z_target + t0, d->old_logp + t0, Tv, Tzp, p.offs);
         {
             ScopedKernelTimer timer(kTimeFwdSweep, s);
             if (p.dense)
                 fwd_sweep_kernel<kEmitProbs><<<static_cast<unsigned>(map.blocks()), TL::NT, kSweepLdsProbs, s>>>(
                     Wk, p.Kc * 2, V, Xk, p.Kc * 2, Tv, static_cast<int>(p.Kc / kBK), map.ns, map.nTt, map.nVt, Tzp,
-                    p.part_max, p.part_sum, p.Z, Tzp * kBlockK, p.offs);
+                    p.part_max, p.part_sum, p.Z, Tzp * kBlockK, p.offs + t0);
             else
                 fwd_sweep_kernel<kEmitLogits><<<static_cast<unsigned>(map.blocks()), TL::NT, kSweepLds, s>>>(
                     Wk, p.Kc * 2, V, Xk, p.Kc * 2, Tv, static_cast<int>(p.Kc / kBK), map.ns, map.nTt, map.nVt, Tzp,
@@ -1609,7 +1758,7 @@ int fused_fwd_bwd(const spo_pg_desc *d, float grad_loss, float *loss, float *log
                                    p.dx_part, p.dw_tail, p.cscale);
             }
             if (d_W) {
-                bf16_t *Xc = d->dtype == SPO_FP32 ? p.Xb : static_cast<bf16_t *>(p.Xc);  // c_t x_t, the rows past the piece zero
+                bf16_t *Xc = p.Xc;  // c_t x_t, the rows past the piece zero
                 if (d->dtype == SPO_FP32)
                     scale_rows_kernel<float><<<static_cast<unsigned>(Tzp), 256, 0, s>>>(
                         reinterpret_cast<const float *>(Xpiece), p.cscale, Tv, H, Xc);
@@ -1628,21 +1777,10 @@ int fused_fwd_bwd(const spo_pg_desc *d, float grad_loss, float *loss, float *log
             continue;
         }
         compact_active_kernel<<<1, 1024, 0, s>>>(p.g + t0, Tv, p.act_idx, p.n_act);
-        const bf16_t *Xrows;
-        if (d->dtype == SPO_FP32) {
-            float *xc = static_cast<float *>(p.Xc);
-            gather_chunk_kernel<float><<<static_cast<unsigned>(Tzp), 256, 0, s>>>(
-                reinterpret_cast<const float *>(Xpiece), H, p.act_idx, p.n_act, 0, Tzp, d->target + t0, lse + t0, p.g + t0,
-                xc, p.tok);
-            if (d_W) f32_to_bf16_kernel<<<grid1(Tzp * H), 256, 0, s>>>(xc, p.Xb, Tzp * H);
-            Xrows = p.Xb;
-        } else {
-            bf16_t *xc = static_cast<bf16_t *>(p.Xc);
-            gather_chunk_kernel<bf16_t><<<static_cast<unsigned>(Tzp), 256, 0, s>>>(
-                reinterpret_cast<const bf16_t *>(Xpiece), H, p.act_idx, p.n_act, 0, Tzp, d->target + t0, lse + t0,
-                p.g + t0, xc, p.tok);
-            Xrows = xc;
-        }
+        launch_gather(d, Xpiece, p.act_idx, p.n_act, 0, Tzp, d->target + t0, lse + t0, p.g + t0,
+                      d->dtype == SPO_BF16 || d_W ? p.Xc : nullptr, nullptr, p.tok,
+                      d_hidden ? static_cast<char *>(d_hidden) + t0 * H * dx_elt : nullptr, d_hidden_dtype, Tv, s);
+        const bf16_t *Xrows = p.Xc;
         {
             constexpr int per_wg = 8;
             const int64_t n_blk = p.V_blk / kBlockK;

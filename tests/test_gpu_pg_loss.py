@@ -331,6 +331,26 @@ def test_token_tiles_and_splits_over_the_chip(spo, oracle, T, V, chunk, one_call
     assert (per_row <= 2 * GRAD_TOL * np.linalg.norm(rb["d_hidden"], axis=1) + 1e-12).all()
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("w_layout", [0, 1])
+@pytest.mark.parametrize("T,H,V,mask_frac", [
+    (1, 64, 1, None), (3, 64, 63, None),          # less than a tile of the head
+    (257, 128, 1032, None),                       # a head of whole tiles and one vector, rows on 16-byte boundaries
+    (300, 64, 1001, 0.3),                         # rows off 16-byte boundaries
+    (4096, 64, 320, 0.2), (4097, 64, 320, 0.2)])  # most tokens whose factors are formed beside the head, and the next
+def test_inputs_prepared_in_one_launch(spo, oracle, dtype, w_layout, T, H, V, mask_frac, one_call):
+    say(f"prepared inputs {dtype} T={T} H={H} V={V} layout={w_layout} mask={mask_frac} one_call={one_call}")
+    case = Case(wl.scaled(MID, name="prep", H=H, V=V, dtype=dtype), [T] if T < 3 else [T // 3, T - T // 3], mask_frac=mask_frac)
+    case.set_old_from_oracle(oracle)
+    fwd, dx, dw = run_fwd_bwd(spo, case, w_layout=w_layout, one_call=one_call)
+    check_forward(case, oracle, fwd)
+    rb = oracle.pg_loss_bwd(*case.oracle_inputs(), *case.eps)
+    # a vocabulary of one: the softmax is 1 and every gradient 0, in fp32 up to the rounding of one exponential
+    tol = lambda ref: GRAD_TOL * np.linalg.norm(ref) + (1e-5 if V == 1 else 0.0)
+    assert np.linalg.norm(f64(dx) - rb["d_hidden"]) <= tol(rb["d_hidden"])
+    assert np.linalg.norm(f64(dw) - rb["d_W"]) <= tol(rb["d_W"])
+
+
 def test_cu_seqlens_may_start_anywhere(spo, oracle):
     # a mini-batch cut out of a packed batch keeps the batch's offsets: only differences count
     say("fused bf16 mid, cu_seqlens shifted by a constant")
