@@ -148,7 +148,8 @@ constexpr int kPrepTile = 64;
 template <typename T_> constexpr int kPrepPitch = sizeof(T_) == 2 ? 66 : 65;
 
 // One 64 x 64 tile of the head.  Bound by memory: sixteen bytes per lane in and out, rows of 128 bytes
-// in, whole 8 KiB pieces of WT out (151936 x 4096: 443 us = 5.6 TB/s).
+// in, whole 8 KiB pieces of WT out (151936 x 4096: 952 -> 443 us = 5.6 TB/s;
+// one element per lane was 2.6).
 template <typename T_, bool HV>
 __device__ __forceinline__ void prep_head_tile(const PrepJobs &j, int64_t tile_id, T_ *tile) {
     constexpr int P = kPrepPitch<T_>, N = 16 / sizeof(T_);  // N values per 16-byte load
@@ -916,12 +917,15 @@ recompute_dz_kernel(const char *__restrict__ W, int64_t ldw_bytes, int64_t V,
 // before it run as they are, in whole rounds, and the `rem` tiles after them are each cut along the
 // contraction into `parts` runs whose partial results are added in a fixed order afterwards.  Host
 // and device code ask the same function, so the number of tiles may be known on the device only.
+// k_steps: the contraction's length before it is limited on the device.  Where the short round is all there
+// is, the extra launch has to be worth it (kCutSteps).
+constexpr int kCutSteps = 8;
 struct TailCut {
     int64_t whole;  // tiles that run in whole rounds (all of them when nothing is cut)
     int rem, parts;
-    __host__ __device__ explicit TailCut(int64_t tiles) : whole(tiles), rem(0), parts(1) {
+    __host__ __device__ TailCut(int64_t tiles, int64_t k_steps) : whole(tiles), rem(0), parts(1) {
         const int r = static_cast<int>(tiles % kChipCUs);
-        if (tiles > kChipCUs && r > 0 && r <= kChipCUs / 2) {
+        if (r > 0 && r <= kChipCUs / 2 && (tiles > kChipCUs || k_steps >= kCutSteps)) {
             whole = tiles - r;
             rem = r;
             parts = kChipCUs / r < 8 ? kChipCUs / r : 8;
@@ -975,7 +979,7 @@ gemm_store_kernel(const char *__restrict__ A, int64_t lda_bytes, int64_t M, cons
     if (n_act && limit == kLimitRows) m_end = active_rows(n_act, row_base, M);
     // kTailWhole: the launch of the whole rounds; kTailCut: the launch of the cut tiles (workgroup
     // i * parts + p takes part p of tile whole + i of the row-major order); both see the same cut
-    const TailCut cut(tail == kTailNone ? 0 : ceil_div(m_end, TL::BM) * tiles_n);
+    const TailCut cut(tail == kTailNone ? 0 : ceil_div(m_end, TL::BM) * tiles_n, KT);
     int64_t tm, tn;
     int part;
     if (tail == kTailCut) {
@@ -985,10 +989,13 @@ gemm_store_kernel(const char *__restrict__ A, int64_t lda_bytes, int64_t M, cons
         tm = t / tiles_n;
         tn = t % tiles_n;
     } else {
-        const TileOrder ord(ceil_div(M, TL::BM), tiles_n);
-        const int64_t per_part = ord.blocks();
-        part = static_cast<int>(blockIdx.x / per_part);
-        if (!ord.tile(blockIdx.x % per_part, tm, tn)) return;
+        // (rows that are not there, known on the device only, leave the ids at the end without a tile)
+        const TileOrder ord(ceil_div(m_end, TL::BM), tiles_n);
+        const uint32_t tiles = static_cast<uint32_t>(ord.tiles());
+        uint32_t i;
+        if (!TileOrder::item(blockIdx.x, tiles * nsplit, i)) return;
+        part = static_cast<int>(i / tiles);
+        ord.at(i % tiles, tm, tn);
         if (tail == kTailWhole && tm * tiles_n + tn >= cut.whole) return;  // left to the launch of the cut tiles
     }
     const int64_t m0 = tm * TL::BM, n0 = tn * TL::BN;
@@ -1161,13 +1168,13 @@ reduce_split_kernel(const float *__restrict__ partials, int nsplit, int64_t M, i
 // sized for the most tiles a cut can have; n_act (with limit == kLimitRows), row_map and row_scale
 // may be NULL.  Four values per thread.
 __global__ void __launch_bounds__(256)
-reduce_tail_kernel(const float *__restrict__ partials, int64_t M, int64_t N, const int32_t *__restrict__ n_act,
+reduce_tail_kernel(const float *__restrict__ partials, int64_t M, int64_t N, int64_t KT, const int32_t *__restrict__ n_act,
                    int64_t row_base, int limit, const int32_t *__restrict__ row_map, void *__restrict__ out, int64_t ldo,
                    int out_dtype, int accumulate, const float *__restrict__ row_scale) {
     constexpr int64_t per_tile = TL::BM * TL::BN / 4;
     const int64_t m_end = n_act && limit == kLimitRows ? active_rows(n_act, row_base, M) : M;
     const int64_t tiles_n = ceil_div(N, TL::BN);
-    const TailCut cut(ceil_div(m_end, TL::BM) * tiles_n);
+    const TailCut cut(ceil_div(m_end, TL::BM) * tiles_n, KT);
     const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
     const int64_t tl = i / per_tile, r = (i % per_tile) / (TL::BN / 4), c = (i % (TL::BN / 4)) * 4;
     if (tl >= cut.rem) return;
@@ -1484,24 +1491,28 @@ static void launch_gemm(const bf16_t *A, int64_t lda, int64_t M, const bf16_t *B
                         int limit, const int32_t *row_map, int64_t a_blk_elems, int64_t b_blk_elems, hipStream_t s,
                         int nsplit = 1, float *partials = nullptr, float *tail = nullptr,
                         const float *row_scale = nullptr) {
-    const TileOrder ord(ceil_div(M, TL::BM), ceil_div(N, TL::BN));
+    const int64_t tiles = ceil_div(M, TL::BM) * ceil_div(N, TL::BN);
     const bool rows_on_device = n_act && limit == kLimitRows;
-    const bool cut = tail && nsplit == 1 && (rows_on_device ? ord.nM * ord.nN > kChipCUs : TailCut(ord.nM * ord.nN).rem > 0);
-    gemm_store_kernel<KMajor><<<static_cast<unsigned>(ord.blocks() * nsplit), TL::NT, TL::LDS_BYTES, s>>>(
-        reinterpret_cast<const char *>(A), lda * 2, M, reinterpret_cast<const char *>(B), ldb * 2, N,
-        static_cast<int>(K / kBK), out, ldo, out_dtype, accumulate, n_act, row_base, limit, row_map, a_blk_elems * 2,
-        b_blk_elems * 2, nsplit, partials, cut ? kTailWhole : kTailNone, row_scale);
+    const TailCut host_cut(tiles, K / kBK);
+    const bool cut = tail && nsplit == 1 && (rows_on_device ? tiles > kChipCUs : host_cut.rem > 0);
+    if (!cut || rows_on_device || host_cut.whole > 0)
+        gemm_store_kernel<KMajor><<<static_cast<unsigned>(TileOrder::blocks(tiles * nsplit)), TL::NT, TL::LDS_BYTES, s>>>(
+            reinterpret_cast<const char *>(A), lda * 2, M, reinterpret_cast<const char *>(B), ldb * 2, N,
+            static_cast<int>(K / kBK), out, ldo, out_dtype, accumulate, n_act, row_base, limit, row_map, a_blk_elems * 2,
+            b_blk_elems * 2, nsplit, partials, cut ? kTailWhole : kTailNone, row_scale);
     if (nsplit > 1)
         reduce_split_kernel<<<grid1(M * (N / 4)), 256, 0, s>>>(partials, nsplit, M, N, n_act, row_base, row_map, out, ldo,
                                                                out_dtype, row_scale);
     if (cut) {
-        // sized for the most a cut can be: half of the units' worth of tiles, as many part-tiles as units
-        gemm_store_kernel<KMajor><<<kChipCUs, TL::NT, TL::LDS_BYTES, s>>>(
+        // (on the device: sized for the most a cut can be, half of the units' worth of tiles, as many part-tiles as units)
+        const int part_tiles = rows_on_device ? kChipCUs : host_cut.rem * host_cut.parts;
+        gemm_store_kernel<KMajor><<<part_tiles, TL::NT, TL::LDS_BYTES, s>>>(
             reinterpret_cast<const char *>(A), lda * 2, M, reinterpret_cast<const char *>(B), ldb * 2, N,
             static_cast<int>(K / kBK), out, ldo, out_dtype, accumulate, n_act, row_base, limit, row_map, a_blk_elems * 2,
             b_blk_elems * 2, 1, tail, kTailCut, nullptr);
-        reduce_tail_kernel<<<grid1((kChipCUs / 2) * (TL::BM * TL::BN / 4)), 256, 0, s>>>(
-            tail, M, N, n_act, row_base, limit, row_map, out, ldo, out_dtype, accumulate, row_scale);
+        const int rem_most = rows_on_device ? kChipCUs / 2 : host_cut.rem;
+        reduce_tail_kernel<<<grid1(rem_most * (TL::BM * TL::BN / 4)), 256, 0, s>>>(
+            tail, M, N, K / kBK, n_act, row_base, limit, row_map, out, ldo, out_dtype, accumulate, row_scale);
     }
 }
 

@@ -351,6 +351,29 @@ def test_inputs_prepared_in_one_launch(spo, oracle, dtype, w_layout, T, H, V, ma
     assert np.linalg.norm(f64(dw) - rb["d_W"]) <= tol(rb["d_W"])
 
 
+@pytest.mark.parametrize("w_layout", [0, 1])
+@pytest.mark.parametrize("T,H,V", [
+    (440, 1344, 2500),     # 10 x 6 tiles of d_W: bands of 4, 4, 2 tile rows, patches 6 wide; 7 steps: not cut
+    (700, 1344, 2500),     # the same, cut into parts
+    (300, 2368, 8000)])    # 32 x 10: a round of the chip and 64 tiles, patches 8 and 2 wide
+def test_every_tile_of_dW_is_written(spo, oracle, T, H, V, w_layout, one_call):
+    say(f"tiles of d_W, T={T} H={H} V={V} layout={w_layout} one_call={one_call}")
+    case = Case(wl.scaled(MID, name="tiles", H=H, V=V), [T // 3, T - T // 3])
+    case.set_old_from_oracle(oracle)
+    desc = case.to_gpu(spo, w_layout)
+    dw = torch.full((V, H) if w_layout == 0 else (H, V), float("nan"), device="cuda")
+    if one_call:
+        dx = spo.spo_pg_loss_fwd_bwd(desc, 1.0, d_hidden_dtype=torch.float32, d_W=dw)[4]
+    else:
+        _, logp, lse, _ = spo.spo_pg_loss_fwd(desc)
+        dx, _ = spo.spo_pg_loss_bwd(desc, logp, lse, 1.0, d_hidden_dtype=torch.float32, d_W=dw)
+    torch.cuda.synchronize()
+    rb = oracle.pg_loss_bwd(*case.oracle_inputs(), *case.eps)
+    got = f64(dw.t() if w_layout else dw)
+    np.testing.assert_allclose(got, rb["d_W"], atol=2e-2 * np.abs(rb["d_W"]).max(), rtol=0)
+    assert rel_l2(got, rb["d_W"]) < GRAD_TOL and rel_l2(f64(dx), rb["d_hidden"]) < GRAD_TOL
+
+
 def test_cu_seqlens_may_start_anywhere(spo, oracle):
     # a mini-batch cut out of a packed batch keeps the batch's offsets: only differences count
     say("fused bf16 mid, cu_seqlens shifted by a constant")
