@@ -39,7 +39,7 @@ constexpr int kSweepSplits = 16;  // vocabulary splits of the forward sweep on l
 // at H = 4096, V = 151936 the step takes about 1 % longer with 8 GiB than with 40 GB.
 constexpr int64_t kDzBudgetBytes = int64_t(8) << 30;
 constexpr int kChipCUs = 256;
-constexpr int kTailTiles = kChipCUs;  // fp32 tiles of room for the parts of a short last round of tiles (see TailCut)
+constexpr int kTailTiles = kChipCUs;  // fp32 tiles of room for the parts of cut contractions (see launch_gemm)
 
 static int64_t gcd64(int64_t a, int64_t b) { return b ? gcd64(b, a % b) : a; }
 
@@ -1146,9 +1146,17 @@ reduce_split_kernel(const float *__restrict__ partials, int nsplit, int64_t M, i
     const int64_t per_row = N / 4, m = i / per_row, n = (i % per_row) * 4;
     if (m >= (n_act ? active_rows(n_act, row_base, M) : M)) return;
     float4 s = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    for (int p = 0; p < nsplit; ++p) {
-        const float4 v = *reinterpret_cast<const float4 *>(partials + (static_cast<int64_t>(p) * M + m) * N + n);
-        s = make_float4(s.x + v.x, s.y + v.y, s.z + v.z, s.w + v.w);
+    constexpr int U = 8;  // parts requested at a time
+    for (int p0 = 0; p0 < nsplit; p0 += U) {
+        float4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int p = p0 + u < nsplit ? p0 + u : nsplit - 1;  // always a load, none of them behind a branch
+            v[u] = *reinterpret_cast<const float4 *>(partials + (static_cast<int64_t>(p) * M + m) * N + n);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (p0 + u < nsplit) s = make_float4(s.x + v[u].x, s.y + v[u].y, s.z + v[u].z, s.w + v[u].w);
     }
     if (row_scale) {
         const float sc = row_scale[m];
@@ -1423,6 +1431,19 @@ int fused_fwd(const spo_pg_desc *d, float *loss, float *logp, float *lse, float 
     return launch_status();
 }
 
+// Parts that the contraction of dHidden over the vocabulary is cut into, for a chunk of Tc tokens: its
+// (Tc / 256) * ceil(H / 256) tiles leave more than a quarter of the chip idle.  A part takes some 1.4 us per
+// step of 64 entries and adds its tile to what reduce_split_kernel reads (64 MB for a chip full of parts,
+// some 20 us): up to eight parts in any case, more while a part keeps kPartSteps steps.  (Loss then gradients
+// of 17 tokens at 896 x 151936, 4 tiles, 2374 steps: 948 us in 8 parts, 642 in 64; of 85 tokens at
+// 3264 x 15635, 13 tiles, 245 steps: 19 parts gain what 8 leave of the chip idle.)
+constexpr int64_t kPartSteps = 16;
+static int dhidden_parts(int64_t Tc, int64_t H, int64_t V_pad) {
+    const int64_t tiles = Tc / TL::BN * ceil_div(H, TL::BM);
+    if (tiles * 4 >= kChipCUs * 3) return 1;
+    return static_cast<int>(std::min<int64_t>(kChipCUs / tiles, std::max<int64_t>(8, V_pad / kBK / kPartSteps)));
+}
+
 struct BwdPlan {
     int64_t Tc, V_pad, V_blk, Kc, T_pad;  // V rounded up to a k-step (64) and to whole tiles (256)
     double *count;
@@ -1432,8 +1453,7 @@ struct BwdPlan {
     int32_t *act_idx, *n_act;  // active-token list, its length
     float4 *tok;               // per-chunk records (g, -lse*log2e, target) of the gathered rows
     int dx_split;              // parts the dHidden contraction is cut into (1: not split)
-    float *dx_part;            // their fp32 partial results [dx_split][Tc][H]
-    float *dw_tail;            // partial tiles of a contraction's short last round (see launch_gemm)
+    float *part_tiles;         // room for kTailTiles fp32 tiles: partial results of a cut contraction (see launch_gemm)
     size_t bytes;
 };
 
@@ -1452,11 +1472,7 @@ static BwdPlan plan_bwd(const spo_pg_desc *d, int64_t chunk_tokens, void *ws, bo
     p.act_idx = a.take<int32_t>(p.T_pad);
     p.n_act = a.take<int32_t>(1);
     p.tok = a.take<float4>(p.Tc);
-    // dHidden has (Tc / 256) * ceil(H / 256) tiles; below three quarters of the chip's compute
-    // units the contraction over the vocabulary is cut into parts (H a multiple of 4 is given)
-    const int64_t dx_tiles = (p.Tc / TL::BN) * ceil_div(d->H, TL::BM);
-    p.dx_split = dx_tiles * 4 < kChipCUs * 3 ? static_cast<int>(std::min<int64_t>(8, kChipCUs / dx_tiles)) : 1;
-    p.dx_part = p.dx_split > 1 ? a.take<float>(static_cast<size_t>(p.dx_split) * p.Tc * d->H) : nullptr;
+    p.dx_split = dhidden_parts(p.Tc, d->H, p.V_pad);
     p.Xc = a.take<bf16_t>(static_cast<size_t>(p.Tc) * d->H);
     p.WT = a.take<bf16_t>(static_cast<size_t>(d->H) * p.V_blk);   // [V_blk / 64][H][64]
     p.dZ = a.take<bf16_t>(static_cast<size_t>(p.Tc) * p.V_blk);  // [V_blk / 64][rows of the chunk][64]
@@ -1469,7 +1485,7 @@ static BwdPlan plan_bwd(const spo_pg_desc *d, int64_t chunk_tokens, void *ws, bo
     // the logits of a bf16 head are formed from rows per vocabulary entry; an fp32 head is split from any layout
     p.Wvh = d->dtype == SPO_BF16 ? take_head_copy(a, d) : nullptr;
     if (need_dw_acc) p.dW_acc = a.take<float>(static_cast<size_t>(d->V) * d->H);
-    p.dw_tail = a.take<float>(static_cast<size_t>(kTailTiles) * TL::BM * TL::BN);
+    p.part_tiles = a.take<float>(static_cast<size_t>(kTailTiles) * TL::BM * TL::BN);
     p.bytes = a.used;
     return p;
 }
@@ -1480,7 +1496,8 @@ int fused_bwd_workspace(const spo_pg_desc *d, int64_t chunk_tokens, size_t *byte
     return SPO_OK;
 }
 
-// `tail`: room for kTailTiles fp32 tiles; with it a short last round of tiles is cut along the
+// `partials`: room for kTailTiles fp32 tiles: the parts of a contraction cut nsplit times (at most as many part
+// tiles as the chip has units), or those of a short last round of tiles, which is cut along the
 // contraction (TailCut): 9504 tiles of dW on 256 units take 37 rounds and an eighth instead of 38,
 // and a dHidden launch whose number of active rows leaves a round nearly empty loses a fifth of a
 // round instead of a whole one.  Where the tile count depends on n_act the two extra launches
@@ -1489,12 +1506,11 @@ template <bool KMajor>
 static void launch_gemm(const bf16_t *A, int64_t lda, int64_t M, const bf16_t *B, int64_t ldb, int64_t N, int64_t K,
                         void *out, int64_t ldo, int out_dtype, int accumulate, const int32_t *n_act, int64_t row_base,
                         int limit, const int32_t *row_map, int64_t a_blk_elems, int64_t b_blk_elems, hipStream_t s,
-                        int nsplit = 1, float *partials = nullptr, float *tail = nullptr,
-                        const float *row_scale = nullptr) {
+                        int nsplit, float *partials, const float *row_scale = nullptr) {
     const int64_t tiles = ceil_div(M, TL::BM) * ceil_div(N, TL::BN);
     const bool rows_on_device = n_act && limit == kLimitRows;
     const TailCut host_cut(tiles, K / kBK);
-    const bool cut = tail && nsplit == 1 && (rows_on_device ? tiles > kChipCUs : host_cut.rem > 0);
+    const bool cut = nsplit == 1 && (rows_on_device ? tiles > kChipCUs : host_cut.rem > 0);
     if (!cut || rows_on_device || host_cut.whole > 0)
         gemm_store_kernel<KMajor><<<static_cast<unsigned>(TileOrder::blocks(tiles * nsplit)), TL::NT, TL::LDS_BYTES, s>>>(
             reinterpret_cast<const char *>(A), lda * 2, M, reinterpret_cast<const char *>(B), ldb * 2, N,
@@ -1509,10 +1525,10 @@ static void launch_gemm(const bf16_t *A, int64_t lda, int64_t M, const bf16_t *B
         gemm_store_kernel<KMajor><<<part_tiles, TL::NT, TL::LDS_BYTES, s>>>(
             reinterpret_cast<const char *>(A), lda * 2, M, reinterpret_cast<const char *>(B), ldb * 2, N,
             static_cast<int>(K / kBK), out, ldo, out_dtype, accumulate, n_act, row_base, limit, row_map, a_blk_elems * 2,
-            b_blk_elems * 2, 1, tail, kTailCut, nullptr);
+            b_blk_elems * 2, 1, partials, kTailCut, nullptr);
         const int rem_most = rows_on_device ? kChipCUs / 2 : host_cut.rem;
         reduce_tail_kernel<<<grid1(rem_most * (TL::BM * TL::BN / 4)), 256, 0, s>>>(
-            tail, M, N, K / kBK, n_act, row_base, limit, row_map, out, ldo, out_dtype, accumulate, row_scale);
+            partials, M, N, K / kBK, n_act, row_base, limit, row_map, out, ldo, out_dtype, accumulate, row_scale);
     }
 }
 
@@ -1590,7 +1606,7 @@ int fused_bwd(const spo_pg_desc *d, const float *logp, const float *lse, float g
             ScopedKernelTimer timer(kTimeDHidden, s);
             // both operands k-blocked over the vocabulary: a stage of a tile is 32 KiB contiguous
             launch_gemm<false>(p.dZ, kBlockK, Tcp, p.WT, kBlockK, H, p.V_pad, d_hidden, H, d_hidden_dtype, 0, p.n_act, t0,
-                               kLimitRows, p.act_idx + t0, Tcp * kBlockK, H * kBlockK, s, p.dx_split, p.dx_part, p.dw_tail);
+                               kLimitRows, p.act_idx + t0, Tcp * kBlockK, H * kBlockK, s, p.dx_split, p.part_tiles);
         }
         if (d_W) {
             const int acc = (c > 0 || accumulate_dW) ? 1 : 0;
@@ -1598,10 +1614,10 @@ int fused_bwd(const spo_pg_desc *d, const float *logp, const float *lse, float g
             // contraction over the chunk's tokens, the row index of both dZ and the gathered hidden rows
             if (d->w_layout == SPO_W_VH)
                 launch_gemm<true>(p.dZ, kBlockK, V, Xrows, H, H, Tcp, dW32, H, SPO_FP32, acc, p.n_act, t0, kLimitK, nullptr,
-                                  Tcp * kBlockK, 0, s, 1, nullptr, p.dw_tail);
+                                  Tcp * kBlockK, 0, s, 1, p.part_tiles);
             else
                 launch_gemm<true>(Xrows, H, H, p.dZ, kBlockK, V, Tcp, dW32, V, SPO_FP32, acc, p.n_act, t0, kLimitK, nullptr,
-                                  0, Tcp * kBlockK, s, 1, nullptr, p.dw_tail);
+                                  0, Tcp * kBlockK, s, 1, p.part_tiles);
         }
     }
     if (need_acc) f32_to_bf16_kernel<<<grid1(V * H), 256, 0, s>>>(p.dW_acc, static_cast<bf16_t *>(d_W), V * H);
@@ -1623,7 +1639,7 @@ struct FbPlan {
     int64_t Tz, T_pad, V_pad, V_blk, Kc, nVt, nblk_tok;
     int nsplit;
     double *count;
-    float *g, *z_target, *part_max, *part_sum, *offs, *dW_acc, *dx_part, *dw_tail, *cscale;
+    float *g, *z_target, *part_max, *part_sum, *offs, *dW_acc, *part_tiles, *cscale;
     bool dense;  // no loss mask: the sweep stores what the contractions read; offs: the references of all tokens
     FwdPartial *partials;
     uint32_t *done;
@@ -1666,9 +1682,7 @@ static FbPlan plan_fb(const spo_pg_desc *d, int64_t chunk_tokens, void *ws, bool
     p.act_idx = a.take<int32_t>(p.Tz);
     p.n_act = a.take<int32_t>(1);
     p.tok = a.take<float4>(p.Tz);
-    const int64_t dx_tiles = (p.Tz / TL::BN) * ceil_div(d->H, TL::BM);
-    p.dx_split = want_dx && dx_tiles * 4 < kChipCUs * 3 ? static_cast<int>(std::min<int64_t>(8, kChipCUs / dx_tiles)) : 1;
-    p.dx_part = p.dx_split > 1 ? a.take<float>(static_cast<size_t>(p.dx_split) * p.Tz * d->H) : nullptr;
+    p.dx_split = want_dx ? dhidden_parts(p.Tz, d->H, p.V_pad) : 1;
     p.Xc = a.take<bf16_t>(static_cast<size_t>(p.Tz) * d->H);
     p.WT = want_dx ? a.take<bf16_t>(static_cast<size_t>(d->H) * p.V_blk) : nullptr;
     p.Z = a.take<uint16_t>(static_cast<size_t>(p.Tz) * p.V_blk);
@@ -1681,7 +1695,7 @@ static FbPlan plan_fb(const spo_pg_desc *d, int64_t chunk_tokens, void *ws, bool
     }
     p.Wvh = take_head_copy(a, d);
     if (need_dw_acc) p.dW_acc = a.take<float>(static_cast<size_t>(d->V) * d->H);
-    p.dw_tail = a.take<float>(static_cast<size_t>(kTailTiles) * TL::BM * TL::BN);
+    p.part_tiles = a.take<float>(static_cast<size_t>(kTailTiles) * TL::BM * TL::BN);
     p.bytes = a.used;
     return p;
 }
@@ -1766,7 +1780,7 @@ int fused_fwd_bwd(const spo_pg_desc *d, float grad_loss, float *loss, float *log
                 ScopedKernelTimer timer(kTimeDHidden, s);
                 launch_gemm<false>(Q, kBlockK, Tv, p.WT, kBlockK, H, p.V_pad, static_cast<char *>(d_hidden) + t0 * H * dx_elt, H,
                                    d_hidden_dtype, 0, nullptr, 0, 0, nullptr, Tzp * kBlockK, H * kBlockK, s, p.dx_split,
-                                   p.dx_part, p.dw_tail, p.cscale);
+                                   p.part_tiles, p.cscale);
             }
             if (d_W) {
                 bf16_t *Xc = p.Xc;  // c_t x_t, the rows past the piece zero
@@ -1780,10 +1794,10 @@ int fused_fwd_bwd(const spo_pg_desc *d, float grad_loss, float *loss, float *log
                 ScopedKernelTimer timer(kTimeDW, s);
                 if (d->w_layout == SPO_W_VH)
                     launch_gemm<true>(Q, kBlockK, V, Xc, H, H, Tzp, dW32, H, SPO_FP32, acc, nullptr, 0, 0, nullptr,
-                                      Tzp * kBlockK, 0, s, 1, nullptr, p.dw_tail);
+                                      Tzp * kBlockK, 0, s, 1, p.part_tiles);
                 else
                     launch_gemm<true>(Xc, H, H, Q, kBlockK, V, Tzp, dW32, V, SPO_FP32, acc, nullptr, 0, 0, nullptr, 0,
-                                      Tzp * kBlockK, s, 1, nullptr, p.dw_tail);
+                                      Tzp * kBlockK, s, 1, p.part_tiles);
             }
             continue;
         }
@@ -1804,17 +1818,17 @@ int fused_fwd_bwd(const spo_pg_desc *d, float grad_loss, float *loss, float *log
             ScopedKernelTimer timer(kTimeDHidden, s);
             launch_gemm<false>(p.dZ, kBlockK, Tzp, p.WT, kBlockK, H, p.V_pad, static_cast<char *>(d_hidden) + t0 * H * dx_elt, H,
                                d_hidden_dtype, 0, p.n_act, 0, kLimitRows, p.act_idx, Tzp * kBlockK, H * kBlockK, s,
-                               p.dx_split, p.dx_part, p.dw_tail);
+                               p.dx_split, p.part_tiles);
         }
         if (d_W) {
             const int acc = (c > 0 || accumulate_dW) ? 1 : 0;
             ScopedKernelTimer timer(kTimeDW, s);
             if (d->w_layout == SPO_W_VH)
                 launch_gemm<true>(p.dZ, kBlockK, V, Xrows, H, H, Tzp, dW32, H, SPO_FP32, acc, p.n_act, 0, kLimitK, nullptr,
-                                  Tzp * kBlockK, 0, s, 1, nullptr, p.dw_tail);
+                                  Tzp * kBlockK, 0, s, 1, p.part_tiles);
             else
                 launch_gemm<true>(Xrows, H, H, p.dZ, kBlockK, V, Tzp, dW32, V, SPO_FP32, acc, p.n_act, 0, kLimitK, nullptr,
-                                  0, Tzp * kBlockK, s, 1, nullptr, p.dw_tail);
+                                  0, Tzp * kBlockK, s, 1, p.part_tiles);
         }
     }
     if (need_acc) f32_to_bf16_kernel<<<grid1(V * H), 256, 0, s>>>(p.dW_acc, static_cast<bf16_t *>(d_W), V * H);

@@ -374,6 +374,22 @@ def test_every_tile_of_dW_is_written(spo, oracle, T, H, V, w_layout, one_call):
     assert rel_l2(got, rb["d_W"]) < GRAD_TOL and rel_l2(f64(dx), rb["d_hidden"]) < GRAD_TOL
 
 
+@pytest.mark.parametrize("T,H,V,mask_frac", [
+    (20, 64, 20000, None),     # 1 tile of d_hidden, 313 steps: 19 parts, the last ones shorter or empty
+    (290, 448, 16500, 0.2),    # 4 tiles, 258 steps: 16 parts
+    (700, 4096, 8300, None)])  # 48 tiles: five parts, what the chip has room for
+def test_dHidden_in_parts_along_the_vocabulary(spo, oracle, T, H, V, mask_frac, one_call):
+    say(f"parts of d_hidden, T={T} H={H} V={V} mask={mask_frac} one_call={one_call}")
+    case = Case(wl.scaled(MID, name="parts", H=H, V=V), [T // 3, T - T // 3], mask_frac=mask_frac)
+    case.set_old_from_oracle(oracle)
+    fwd, dx, dw = run_fwd_bwd(spo, case, one_call=one_call)
+    rb = oracle.pg_loss_bwd(*case.oracle_inputs(), *case.eps)
+    got, scale = f64(dx), np.linalg.norm(rb["d_hidden"], axis=1)
+    assert rel_l2(got, rb["d_hidden"]) < GRAD_TOL and rel_l2(f64(dw), rb["d_W"]) < GRAD_TOL
+    assert (np.linalg.norm(got - rb["d_hidden"], axis=1) <= 2 * GRAD_TOL * scale + 1e-12).all()
+    assert not got[scale == 0].any()
+
+
 def test_cu_seqlens_may_start_anywhere(spo, oracle):
     # a mini-batch cut out of a packed batch keeps the batch's offsets: only differences count
     say("fused bf16 mid, cu_seqlens shifted by a constant")
