@@ -223,10 +223,14 @@ __device__ __forceinline__ void prep_head_tile(const PrepJobs &j, int64_t tile_i
     }
 }
 
+// n a multiple of 64; both arrays on 16-byte boundaries
 __global__ void __launch_bounds__(256)
 f32_to_bf16_kernel(const float *__restrict__ src, bf16_t *__restrict__ dst, int64_t n) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (i < n) dst[i] = f32_to_bf16(src[i]);
+    const int64_t i = (static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x) * 8;
+    if (i >= n) return;
+    float x[8];
+    load8(src + i, x);
+    *reinterpret_cast<uint4 *>(dst + i) = round8(x);
 }
 
 __global__ void __launch_bounds__(256) fill_zero_kernel(uint32_t *__restrict__ p, int64_t n_words) {
@@ -1484,7 +1488,7 @@ static BwdPlan plan_bwd(const spo_pg_desc *d, int64_t chunk_tokens, void *ws, bo
     }
     // the logits of a bf16 head are formed from rows per vocabulary entry; an fp32 head is split from any layout
     p.Wvh = d->dtype == SPO_BF16 ? take_head_copy(a, d) : nullptr;
-    if (need_dw_acc) p.dW_acc = a.take<float>(static_cast<size_t>(d->V) * d->H);
+    if (need_dw_acc && d->T > p.Tc) p.dW_acc = a.take<float>(static_cast<size_t>(d->V) * d->H);
     p.part_tiles = a.take<float>(static_cast<size_t>(kTailTiles) * TL::BM * TL::BN);
     p.bytes = a.used;
     return p;
@@ -1555,12 +1559,15 @@ int fused_bwd(const spo_pg_desc *d, const float *logp, const float *lse, float g
     int rc = check_fused(d);
     if (rc) return rc;
     if (accumulate_dW && d_W && d_W_dtype != SPO_FP32) return SPO_EINVAL;
-    const bool need_acc = d_W && d_W_dtype == SPO_BF16;
-    const BwdPlan p = plan_bwd(d, chunk_tokens, ws, need_acc);
+    const BwdPlan p = plan_bwd(d, chunk_tokens, ws, d_W && d_W_dtype == SPO_BF16);
+    // a bf16 d_W is summed in fp32 beside it, unless one chunk holds all tokens: its tiles are rounded as they are stored
+    // (an fp32 d_W of 151936 x 4096 written, read and rounded again: 2 ms)
+    const bool need_acc = p.dW_acc != nullptr;
     if (ws_bytes < p.bytes) return SPO_EWORKSPACE;
     if ((rc = set_lds_limit())) return rc;
     const int64_t H = d->H, V = d->V, T = d->T;
-    float *dW32 = need_acc ? p.dW_acc : static_cast<float *>(d_W);
+    void *dW_sum = need_acc ? p.dW_acc : d_W;
+    const int dW_sum_dtype = need_acc ? SPO_FP32 : d_W_dtype;
     if (T == 0) {
         if (d_W && !accumulate_dW) {
             const int64_t words = d_W_dtype == SPO_FP32 ? V * H : V * H / 2;
@@ -1613,14 +1620,14 @@ int fused_bwd(const spo_pg_desc *d, const float *logp, const float *lse, float g
             ScopedKernelTimer timer(kTimeDW, s);
             // contraction over the chunk's tokens, the row index of both dZ and the gathered hidden rows
             if (d->w_layout == SPO_W_VH)
-                launch_gemm<true>(p.dZ, kBlockK, V, Xrows, H, H, Tcp, dW32, H, SPO_FP32, acc, p.n_act, t0, kLimitK, nullptr,
+                launch_gemm<true>(p.dZ, kBlockK, V, Xrows, H, H, Tcp, dW_sum, H, dW_sum_dtype, acc, p.n_act, t0, kLimitK, nullptr,
                                   Tcp * kBlockK, 0, s, 1, p.part_tiles);
             else
-                launch_gemm<true>(Xrows, H, H, p.dZ, kBlockK, V, Tcp, dW32, V, SPO_FP32, acc, p.n_act, t0, kLimitK, nullptr,
+                launch_gemm<true>(Xrows, H, H, p.dZ, kBlockK, V, Tcp, dW_sum, V, dW_sum_dtype, acc, p.n_act, t0, kLimitK, nullptr,
                                   0, Tcp * kBlockK, s, 1, p.part_tiles);
         }
     }
-    if (need_acc) f32_to_bf16_kernel<<<grid1(V * H), 256, 0, s>>>(p.dW_acc, static_cast<bf16_t *>(d_W), V * H);
+    if (need_acc) f32_to_bf16_kernel<<<grid1(V * H / 8), 256, 0, s>>>(p.dW_acc, static_cast<bf16_t *>(d_W), V * H);
     return launch_status();
 }
 
@@ -1694,7 +1701,7 @@ static FbPlan plan_fb(const spo_pg_desc *d, int64_t chunk_tokens, void *ws, bool
         p.Ws = a.take<bf16_t>(static_cast<size_t>(d->V) * p.Kc);
     }
     p.Wvh = take_head_copy(a, d);
-    if (need_dw_acc) p.dW_acc = a.take<float>(static_cast<size_t>(d->V) * d->H);
+    if (need_dw_acc && d->T > p.Tz) p.dW_acc = a.take<float>(static_cast<size_t>(d->V) * d->H);
     p.part_tiles = a.take<float>(static_cast<size_t>(kTailTiles) * TL::BM * TL::BN);
     p.bytes = a.used;
     return p;
@@ -1711,12 +1718,13 @@ int fused_fwd_bwd(const spo_pg_desc *d, float grad_loss, float *loss, float *log
     int rc = check_fused(d);
     if (rc) return rc;
     if (accumulate_dW && d_W && d_W_dtype != SPO_FP32) return SPO_EINVAL;
-    const bool need_acc = d_W && d_W_dtype == SPO_BF16;
-    const FbPlan p = plan_fb(d, chunk_tokens, ws, need_acc, d_hidden != nullptr);
+    const FbPlan p = plan_fb(d, chunk_tokens, ws, d_W && d_W_dtype == SPO_BF16, d_hidden != nullptr);
+    const bool need_acc = p.dW_acc != nullptr;  // a bf16 d_W of several pieces (see fused_bwd)
     if (ws_bytes < p.bytes) return SPO_EWORKSPACE;
     if ((rc = set_lds_limit())) return rc;
     const int64_t H = d->H, V = d->V, T = d->T;
-    float *dW32 = need_acc ? p.dW_acc : static_cast<float *>(d_W);
+    void *dW_sum = need_acc ? p.dW_acc : d_W;
+    const int dW_sum_dtype = need_acc ? SPO_FP32 : d_W_dtype;
     if (T == 0) {
         if (d_W && !accumulate_dW) {
             const int64_t words = d_W_dtype == SPO_FP32 ? V * H : V * H / 2;
@@ -1793,10 +1801,10 @@ int fused_fwd_bwd(const spo_pg_desc *d, float grad_loss, float *loss, float *log
                 const int acc = (c > 0 || accumulate_dW) ? 1 : 0;
                 ScopedKernelTimer timer(kTimeDW, s);
                 if (d->w_layout == SPO_W_VH)
-                    launch_gemm<true>(Q, kBlockK, V, Xc, H, H, Tzp, dW32, H, SPO_FP32, acc, nullptr, 0, 0, nullptr,
+                    launch_gemm<true>(Q, kBlockK, V, Xc, H, H, Tzp, dW_sum, H, dW_sum_dtype, acc, nullptr, 0, 0, nullptr,
                                       Tzp * kBlockK, 0, s, 1, p.part_tiles);
                 else
-                    launch_gemm<true>(Xc, H, H, Q, kBlockK, V, Tzp, dW32, V, SPO_FP32, acc, nullptr, 0, 0, nullptr, 0,
+                    launch_gemm<true>(Xc, H, H, Q, kBlockK, V, Tzp, dW_sum, V, dW_sum_dtype, acc, nullptr, 0, 0, nullptr, 0,
                                       Tzp * kBlockK, s, 1, p.part_tiles);
             }
             continue;
@@ -1824,14 +1832,14 @@ int fused_fwd_bwd(const spo_pg_desc *d, float grad_loss, float *loss, float *log
             const int acc = (c > 0 || accumulate_dW) ? 1 : 0;
             ScopedKernelTimer timer(kTimeDW, s);
             if (d->w_layout == SPO_W_VH)
-                launch_gemm<true>(p.dZ, kBlockK, V, Xrows, H, H, Tzp, dW32, H, SPO_FP32, acc, p.n_act, 0, kLimitK, nullptr,
+                launch_gemm<true>(p.dZ, kBlockK, V, Xrows, H, H, Tzp, dW_sum, H, dW_sum_dtype, acc, p.n_act, 0, kLimitK, nullptr,
                                   Tzp * kBlockK, 0, s, 1, p.part_tiles);
             else
-                launch_gemm<true>(Xrows, H, H, p.dZ, kBlockK, V, Tzp, dW32, V, SPO_FP32, acc, p.n_act, 0, kLimitK, nullptr,
+                launch_gemm<true>(Xrows, H, H, p.dZ, kBlockK, V, Tzp, dW_sum, V, dW_sum_dtype, acc, p.n_act, 0, kLimitK, nullptr,
                                   0, Tzp * kBlockK, s, 1, p.part_tiles);
         }
     }
-    if (need_acc) f32_to_bf16_kernel<<<grid1(V * H), 256, 0, s>>>(p.dW_acc, static_cast<bf16_t *>(d_W), V * H);
+    if (need_acc) f32_to_bf16_kernel<<<grid1(V * H / 8), 256, 0, s>>>(p.dW_acc, static_cast<bf16_t *>(d_W), V * H);
     return launch_status();
 }
 

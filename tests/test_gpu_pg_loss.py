@@ -390,6 +390,21 @@ def test_dHidden_in_parts_along_the_vocabulary(spo, oracle, T, H, V, mask_frac, 
     assert not got[scale == 0].any()
 
 
+@pytest.mark.parametrize("w_layout", [0, 1])
+@pytest.mark.parametrize("T,H,V,chunk", [
+    (300, 64, 1001, 0), (700, 1344, 2500, 0),    # one chunk: rounded as it is stored, rows off 8-byte boundaries; cut tiles
+    (700, 64, 1001, 256)])                       # three chunks: summed in fp32 first
+def test_bf16_dW_is_the_fp32_one_rounded(spo, oracle, T, H, V, chunk, w_layout, one_call):
+    say(f"bf16 d_W, T={T} H={H} V={V} chunk={chunk} layout={w_layout} one_call={one_call}")
+    case = Case(wl.scaled(MID, name="dw16", H=H, V=V), [T // 3, T - T // 3], mask_frac=0.2)
+    case.set_old_from_oracle(oracle)
+    _, _, dw32 = run_fwd_bwd(spo, case, w_layout, chunk_tokens=chunk, one_call=one_call)
+    _, _, dw16 = run_fwd_bwd(spo, case, w_layout, chunk_tokens=chunk, one_call=one_call, dw_dtype=torch.bfloat16)
+    assert torch.equal(dw16, dw32.to(torch.bfloat16))
+    rb = oracle.pg_loss_bwd(*case.oracle_inputs(), *case.eps)
+    assert rel_l2(f64(dw16), rb["d_W"]) < GRAD_TOL
+
+
 def test_cu_seqlens_may_start_anywhere(spo, oracle):
     # a mini-batch cut out of a packed batch keeps the batch's offsets: only differences count
     say("fused bf16 mid, cu_seqlens shifted by a constant")
