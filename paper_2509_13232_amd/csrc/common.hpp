@@ -62,6 +62,13 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
     return static_cast<uint32_t>(f32_to_bf16(lo)) | (static_cast<uint32_t>(f32_to_bf16(hi)) << 16);
 }
 
+// 1-D grids may be longer than a launch's 2^32 threads per dimension: they are folded into two
+static inline dim3 fold_grid(int64_t blocks) {
+    constexpr int64_t kRow = int64_t(1) << 22;
+    return blocks <= kRow ? dim3(static_cast<unsigned>(blocks)) : dim3(static_cast<unsigned>(kRow), static_cast<unsigned>(ceil_div(blocks, kRow)));
+}
+__device__ __forceinline__ int64_t flat_block() { return static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x; }
+
 // Sum over the 64 lanes of a wavefront; every lane receives the total.
 template <typename T>
 __device__ __forceinline__ T wave_sum(T v) {
@@ -83,6 +90,25 @@ __device__ __forceinline__ T block_sum(T v, T *scratch) {
     T total = T(0);
     for (int w = 0; w < nwave; ++w) total += scratch[w];
     return total;
+}
+
+// The same for M sums in one exchange; scratch holds M T's per wavefront.
+template <int M, typename T>
+__device__ __forceinline__ void block_sums(T (&v)[M], T *scratch) {
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int nwave = (blockDim.x + kWave - 1) / kWave;
+#pragma unroll
+    for (int m = 0; m < M; ++m) v[m] = wave_sum(v[m]);
+    __syncthreads();  // scratch may still be read by a previous reduction
+    if (lane == 0)
+#pragma unroll
+        for (int m = 0; m < M; ++m) scratch[wave * M + m] = v[m];
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < M; ++m) v[m] = T(0);
+    for (int w = 0; w < nwave; ++w)
+#pragma unroll
+        for (int m = 0; m < M; ++m) v[m] += scratch[w * M + m];
 }
 
 // Response that holds token t: largest b with cu[b]-cu[0] <= t (cu has B+1 entries).

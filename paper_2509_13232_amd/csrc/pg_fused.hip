@@ -95,13 +95,6 @@ __device__ __forceinline__ uint4 round8(const float (&x)[8]) {
     return make_uint4(pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]), pack_bf16x2(x[6], x[7]));
 }
 
-// 1-D grids may be longer than a launch's 2^32 threads per dimension: they are folded into two
-static dim3 fold_grid(int64_t blocks) {
-    constexpr int64_t kRow = int64_t(1) << 22;
-    return blocks <= kRow ? dim3(static_cast<unsigned>(blocks)) : dim3(static_cast<unsigned>(kRow), static_cast<unsigned>(ceil_div(blocks, kRow)));
-}
-__device__ __forceinline__ int64_t flat_block() { return static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x; }
-
 // Everything that the loss's and the gradients' kernels need beforehand and that depends on the inputs
 // alone, in one launch: jobs of different kinds share a grid (small batches are bound by the number of
 // launches: an fp32 step of 512 tokens went through 17, now 10: 152 -> 137 us).

@@ -93,8 +93,8 @@ struct Span {
 struct RowGrid {
     int64_t rows, seg_len;  // elements per segment
     int nseg, per_wg;       // segments per row, (row, segment) pairs per workgroup
-    __host__ __device__ uint32_t units() const { return static_cast<uint32_t>(rows * nseg); }  // < 2^32: a grid's limit
-    __host__ unsigned blocks() const { return static_cast<unsigned>(ceil_div(rows * nseg, per_wg)); }
+    __host__ __device__ uint32_t units() const { return static_cast<uint32_t>(rows * nseg); }  // < 2^32: of 4 KB segments, 16 TB
+    __host__ dim3 blocks() const { return fold_grid(ceil_div(rows * nseg, per_wg)); }
 };
 
 // running (max, sum of exp(x - max)) merged with another pair
@@ -112,12 +112,12 @@ logits_row_lse_kernel(const T *__restrict__ logits, int64_t V, RowGrid grid, con
                       float *__restrict__ part_max, float *__restrict__ part_sum, float *__restrict__ z_target,
                       uint32_t *__restrict__ done) {
     constexpr int N = Vec<T>::N, U = kLseGroup;
-    const uint32_t unit = blockIdx.x * (kRowThreads / TR) + threadIdx.x / TR;
+    const int64_t unit = flat_block() * (kRowThreads / TR) + threadIdx.x / TR;
     const int tid = threadIdx.x % TR;
-    if (blockIdx.x == 0 && threadIdx.x == 0) *done = 0u;  // for the kernel that follows
+    if (unit == 0 && threadIdx.x == 0) *done = 0u;  // for the kernel that follows
     if (unit >= grid.units()) return;  // TR < kRowThreads only: no barrier below in that case
-    const uint32_t seg = unit % static_cast<uint32_t>(grid.nseg);
-    const int64_t t = unit / static_cast<uint32_t>(grid.nseg), e0 = seg * grid.seg_len;
+    const uint32_t seg = static_cast<uint32_t>(unit) % static_cast<uint32_t>(grid.nseg);
+    const int64_t t = static_cast<uint32_t>(unit) / static_cast<uint32_t>(grid.nseg), e0 = seg * grid.seg_len;
     const T *p = logits + t * V + e0;
     const Span sp(p, static_cast<int>(V - e0 < grid.seg_len ? V - e0 : grid.seg_len));
     float zt = 0.0f;
@@ -191,11 +191,11 @@ __global__ void __launch_bounds__(kRowThreads)
 logits_row_grad_kernel(const T *__restrict__ logits, int64_t V, RowGrid grid, const int32_t *__restrict__ target,
                        const float *__restrict__ lse, const float *__restrict__ g, T *__restrict__ d_logits) {
     constexpr int N = Vec<T>::N, U = kGradGroup;
-    const uint32_t unit = blockIdx.x * (kRowThreads / TR) + threadIdx.x / TR;
+    const int64_t unit = flat_block() * (kRowThreads / TR) + threadIdx.x / TR;
     const int tid = threadIdx.x % TR;
     if (unit >= grid.units()) return;
     const uint32_t nseg = static_cast<uint32_t>(grid.nseg);
-    const int64_t t = unit / nseg, e0 = (unit % nseg) * grid.seg_len;
+    const int64_t t = static_cast<uint32_t>(unit) / nseg, e0 = (static_cast<uint32_t>(unit) % nseg) * grid.seg_len;
     const T *p = logits + t * V + e0;
     T *out = d_logits + t * V + e0;
     const Span sp(out, static_cast<int>(V - e0 < grid.seg_len ? V - e0 : grid.seg_len));
