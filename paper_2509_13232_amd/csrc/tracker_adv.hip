@@ -95,6 +95,9 @@ constexpr int kOwnThreads = 512, kOwnCap = 4096, kOwnStep = 2 * kOwnThreads;
 constexpr int kOwnSpan = 2048;          // sorted observations whose rewards and discounts are in LDS at a time
 constexpr int kOwnGroups = 256;         // most workgroups: one per compute unit
 constexpr int kOwnPerGroup = 128;       // observations per workgroup below that
+// Up to here a list is sorted by ranks, n broadcast reads per thread and two barriers, instead of the 36 rounds
+// with a barrier each that a bitonic sort of 256 keys takes; a round costs about as much as 30 reads.
+constexpr int kOwnRank = 256;
 
 template <bool Ema>
 __global__ void __launch_bounds__(kOwnThreads)
@@ -110,22 +113,34 @@ tracker_update_owned_kernel(float *__restrict__ alpha, float *__restrict__ beta,
     const int tid = threadIdx.x;
     // applies the n observations in key[] (n is the same in every thread)
     auto apply_list = [&](int n) {
-        int P = 1;
-        while (P < n) P <<= 1;
-        for (int i = n + tid; i < P; i += kOwnThreads) key[i] = ~0ull;
-        __syncthreads();
-        for (int k = 2; k <= P; k <<= 1)
-            for (int j = k >> 1; j > 0; j >>= 1) {
-                for (int t = tid; t < P / 2; t += kOwnThreads) {
-                    const int i = 2 * t - (t & (j - 1));
-                    const uint64_t x = key[i], y = key[i + j];
-                    if ((x > y) == ((i & k) == 0)) {
-                        key[i] = y;
-                        key[i + j] = x;
+        if (n <= kOwnRank) {  // every key counts the smaller ones (keys are distinct)
+            __syncthreads();
+            const uint64_t mine = tid < n ? key[tid] : 0;
+            int rank = 0;
+            if (tid < n)
+#pragma unroll 8
+                for (int i = 0; i < n; ++i) rank += key[i] < mine;
+            __syncthreads();
+            if (tid < n) key[rank] = mine;
+            __syncthreads();
+        } else {
+            int P = 1;
+            while (P < n) P <<= 1;
+            for (int i = n + tid; i < P; i += kOwnThreads) key[i] = ~0ull;
+            __syncthreads();
+            for (int k = 2; k <= P; k <<= 1)
+                for (int j = k >> 1; j > 0; j >>= 1) {
+                    for (int t = tid; t < P / 2; t += kOwnThreads) {
+                        const int i = 2 * t - (t & (j - 1));
+                        const uint64_t x = key[i], y = key[i + j];
+                        if ((x > y) == ((i & k) == 0)) {
+                            key[i] = y;
+                            key[i + j] = x;
+                        }
                     }
+                    __syncthreads();
                 }
-                __syncthreads();
-            }
+        }
         for (int w0 = 0; w0 < n; w0 += kOwnSpan) {
             const int w1 = n - w0 < kOwnSpan ? n : w0 + kOwnSpan;
             for (int i = w0 + tid; i < w1; i += kOwnThreads) {
@@ -389,7 +404,7 @@ constexpr int kDiagAhead = 8;
 __global__ void __launch_bounds__(kAdvThreads)
 advantage_diagnostics_kernel(const float *__restrict__ adv_raw, const float *__restrict__ reward, int B,
                              float tau_tight, float tau_loose, float *__restrict__ diag) {
-    __shared__ double scratch[kAdvThreads / kWave];
+    __shared__ double scratch[4 * kAdvThreads / kWave];
     auto each = [&](auto f) {  // f(advantage, reward) for this thread's responses, in order
         for (int64_t k0 = threadIdx.x; k0 < B; k0 += kDiagAhead * kAdvThreads) {
             float a[kDiagAhead], r[kDiagAhead];
@@ -404,29 +419,27 @@ advantage_diagnostics_kernel(const float *__restrict__ adv_raw, const float *__r
                 if (k0 + i * kAdvThreads < B) f(a[i], r[i]);
         }
     };
-    double nt = 0.0, nl = 0.0, sa = 0.0, sr = 0.0;
+    double s[4] = {};  // within tau_tight, within tau_loose, advantages, rewards
     each([&](float a, float r) {
-        nt += fabsf(a) <= tau_tight ? 1.0 : 0.0;
-        nl += fabsf(a) <= tau_loose ? 1.0 : 0.0;
-        sa += static_cast<double>(a);
-        sr += static_cast<double>(r);
+        s[0] += fabsf(a) <= tau_tight ? 1.0 : 0.0;
+        s[1] += fabsf(a) <= tau_loose ? 1.0 : 0.0;
+        s[2] += static_cast<double>(a);
+        s[3] += static_cast<double>(r);
     });
-    nt = block_sum(nt, scratch);
-    nl = block_sum(nl, scratch);
-    const double ma = block_sum(sa, scratch) / B, mr = block_sum(sr, scratch) / B;
-    double va = 0.0, vr = 0.0;
+    block_sums(s, scratch);
+    const double ma = s[2] / B, mr = s[3] / B;
+    double v[2] = {};
     each([&](float a, float r) {
         const double da = static_cast<double>(a) - ma, dr = static_cast<double>(r) - mr;
-        va += da * da;
-        vr += dr * dr;
+        v[0] += da * da;
+        v[1] += dr * dr;
     });
-    va = block_sum(va, scratch);
-    vr = block_sum(vr, scratch);
+    block_sums(v, scratch);
     if (threadIdx.x == 0) {
-        diag[0] = static_cast<float>(nt / B);
-        diag[1] = static_cast<float>(nl / B);
-        diag[2] = static_cast<float>(va / B);
-        diag[3] = static_cast<float>(vr / B);
+        diag[0] = static_cast<float>(s[0] / B);
+        diag[1] = static_cast<float>(s[1] / B);
+        diag[2] = static_cast<float>(v[0] / B);
+        diag[3] = static_cast<float>(v[1] / B);
     }
 }
 

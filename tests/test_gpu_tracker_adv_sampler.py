@@ -134,6 +134,7 @@ def test_tracker_update_of_batches_that_repeat_every_prompt(spo, oracle, B, G, N
 
 @pytest.mark.parametrize("B,n_ids,bad", [
     (1, 1, 0), (128, 5, 3), (129, 129, 1),          # one workgroup, and one observation more
+    (256, 1, 0), (257, 1, 0), (257, 90, 2),         # the longest list sorted by ranks, and one more
     (1024, 1, 0), (1025, 2, 7),                     # one step of the list, and one more
     (4096, 1, 0), (9000, 1, 11),                    # one id fills the list; the list is applied and restarted
     (33000, 7, 100)])                               # a few long runs over many workgroups and restarts
