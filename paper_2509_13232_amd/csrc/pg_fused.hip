@@ -134,7 +134,8 @@ struct PrepJobs {
     int64_t blocks() const { return head_blocks + row_blocks + target_blocks + (count ? 1 : 0) + (g ? 1 : 0); }
 };
 
-// One workgroup takes 1024 tokens per round, some 3 us; four rounds pass beside the smallest head's tiles.
+// One workgroup takes 1024 tokens per round; four rounds save two launches and pass beside the head's tiles (512
+// tokens: the whole launch 6 us).
 constexpr int64_t kPrepGradTokens = 4096;
 
 constexpr int kPrepTile = 64;
@@ -1431,7 +1432,7 @@ int fused_fwd(const spo_pg_desc *d, float *loss, float *logp, float *lse, float 
 // Parts that the contraction of dHidden over the vocabulary is cut into, for a chunk of Tc tokens: its
 // (Tc / 256) * ceil(H / 256) tiles leave more than a quarter of the chip idle.  A part takes some 1.4 us per
 // step of 64 entries and adds its tile to what reduce_split_kernel reads (64 MB for a chip full of parts,
-// some 20 us): up to eight parts in any case, more while a part keeps kPartSteps steps.  (Loss then gradients
+// 15 us): up to eight parts in any case, more while a part keeps kPartSteps steps.  (Loss then gradients
 // of 17 tokens at 896 x 151936, 4 tiles, 2374 steps: 948 us in 8 parts, 642 in 64; of 85 tokens at
 // 3264 x 15635, 13 tiles, 245 steps: 19 parts gain what 8 leave of the chip idle.)
 constexpr int64_t kPartSteps = 16;

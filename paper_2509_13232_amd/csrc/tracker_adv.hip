@@ -89,14 +89,15 @@ tracker_update_unique_kernel(float *__restrict__ alpha, float *__restrict__ beta
 // registers from one observation to the next, and neither a table over the prompts nor an atomic
 // on memory is needed.  (One workgroup filing claims in a table and applying the earliest pending
 // observation of every id per round: 952 us for a prompt step of 40000 responses to 20000 prompts,
-// 109 us this way.)  A list that might overflow is applied and restarted: the ids are read in
+// 84 us now, 30 of them here before the lists were sorted by ranks.)  A list that might overflow is applied and restarted: the ids are read in
 // batch order, so what is applied earlier is earlier in the batch.
 constexpr int kOwnThreads = 512, kOwnCap = 4096, kOwnStep = 2 * kOwnThreads;
 constexpr int kOwnSpan = 2048;          // sorted observations whose rewards and discounts are in LDS at a time
 constexpr int kOwnGroups = 256;         // most workgroups: one per compute unit
 constexpr int kOwnPerGroup = 128;       // observations per workgroup below that
 // Up to here a list is sorted by ranks, n broadcast reads per thread and two barriers, instead of the 36 rounds
-// with a barrier each that a bitonic sort of 256 keys takes; a round costs about as much as 30 reads.
+// with a barrier each that a bitonic sort of 256 keys takes (that step, with the diagnostics' shorter reductions:
+// 88 -> 84 us).  The reads grow with n * n: longer lists keep the bitonic sort.
 constexpr int kOwnRank = 256;
 
 template <bool Ema>
@@ -285,8 +286,8 @@ __device__ __forceinline__ void raw_advantages(const float *__restrict__ alpha, 
 //
 // Bound by the latency of id -> (alpha, beta): each of the three passes waited for both loads, one
 // response per thread after the other.  Up to PER responses per thread are now requested
-// together and stay in registers for all passes (4096 responses of 2^20 prompts: 17 -> 7 us); PER = 0
-// is the form without a limit.
+// together and stay in registers for all passes (a step of 4096 responses to 2^20 prompts: 57 -> 48 us);
+// PER = 0 is the form without a limit.
 constexpr int kAdvThreads = 1024;
 
 template <int PER>
