@@ -80,12 +80,11 @@ const char *spo_status_string(int status);
  *               and every v_i is 0 or 1) nothing can be drawn: all entries are
  *               -1 and info[0] = 1.
  * max_attempts  bound on attempts per slot (0 selects 65536).  Without replacement the
- *               draw runs in one workgroup, one sweep over the B slots per attempt
- *               level (about 2 us each): a batch that takes most of the prompts
- *               with non-zero weight needs many levels for its last slots (about
- *               N ln N draws to collect the last of N equal weights), so such a
- *               call can take max_attempts sweeps before it gives up; info[0] and
- *               info[1] tell.
+ *               slots draw side by side, a thread each, some 3 us per attempt (less for
+ *               N <= 4096): a batch that takes most of the prompts with non-zero weight
+ *               needs many attempts for its last slots (about N ln N draws to collect
+ *               the last of N equal weights), so such a call can take max_attempts of
+ *               them in a row before it gives up; info[0] and info[1] tell.
  * ws            spo_sample_prompts_workspace_bytes(N, B) bytes, 256-byte aligned.
  * Limits: 1 <= N < 2^31, 1 <= B <= 16384 (replace = 0) or B < 2^31 (replace = 1).
  * ------------------------------------------------------------------------- */
@@ -131,9 +130,9 @@ int spo_sample_prompts_static(const float *alpha, const float *beta, int64_t N, 
  *              id is never used as an index: its advantage is NaN, and so are the
  *              batch statistics and every normalised value.
  * ws           optional, spo_advantages_workspace_bytes(B) bytes, 256-byte aligned.
- *              Without it one workgroup does all the work (three passes over the
- *              batch: right for the batches of the paper, slow beyond ~10^5
- *              responses); with it, batches of 16384 responses or more are spread
+ *              Without it one workgroup does all the work (right for the batches
+ *              of the paper; from 16385 responses on it reads the batch three times, slow
+ *              beyond ~10^5 responses); with it, batches of 16384 responses or more are spread
  *              over the chip (partial sums of 4096 responses each, added in a fixed
  *              order).  Both forms are bitwise reproducible; between them the
  *              statistics agree to fp64 rounding.
@@ -176,8 +175,8 @@ int spo_advantage_diagnostics(const float *adv_raw, const float *reward, int32_t
  *              NaN); 2 = ids_unique = 1 but an id repeats (only looked for when ws is
  *              given; the entry of such an id then holds one of its updates).
  * ws           spo_tracker_update_workspace_bytes(N) bytes, 256-byte aligned: a table
- *              of one int32 per prompt.  Required for ids_unique = 0; with
- *              ids_unique = 1 it is optional and only serves the repeat check.
+ *              of one int32 per prompt.  Optional with ids_unique = 1, where it serves
+ *              the repeat check; required with ids_unique = 0, though not written.
  * Arithmetic: rho and the products are formed in fp64 and rounded once to fp32,
  * so rho_min = rho_max = 1 reproduces Beta posterior counts exactly.
  * Limits: 1 <= B < 2^31.
