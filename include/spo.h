@@ -261,6 +261,8 @@ typedef struct {
  * stats optional fp32[4]: M, share of unmasked tokens whose clipped branch is the
  *       minimum, mean ratio over unmasked tokens, sum_t mask_t*obj_t.
  * Reductions run in a fixed order: results are bitwise reproducible.
+ * The workspace size never shrinks with T or V (nor with H): one that serves the largest
+ * batch of a program serves its smaller ones.
  * Requirements (fused form): H a multiple of 64, H <= 65536, pointers 16-byte
  * aligned.  T = 0 is allowed (loss = 0, the per-token
  * pointers may then be NULL). */

@@ -529,10 +529,14 @@ __device__ __forceinline__ int sweep_splits_wave(uint32_t nTt, uint32_t nVt) {
     }
     return __builtin_amdgcn_readfirstlane(static_cast<int>(key == 0xffffffffu ? hi : key & 1023u));
 }
-// The most workgroups (ids of SweepMap) that any number of token tiles up to nTt can ask for.
-static int64_t sweep_blocks_max(int64_t nTt, int64_t nVt) {
-    return std::min(nTt * std::min<int64_t>(nVt, kNoSplitCap), std::max<int64_t>(4096, nTt * kSweepSplits)) + 8;
+// The most (token tile, split) pairs that any number of token tiles up to nTt can ask for.  The number of splits
+// jumps with that of the token tiles; this grows with both sizes, so room sized by it for the longest batch serves
+// every shorter one.
+static int64_t sweep_pairs_max(int64_t nTt, int64_t nVt) {
+    return std::min(nTt * std::min<int64_t>(nVt, kNoSplitCap), std::max<int64_t>(4096, nTt * kSweepSplits));
 }
+// The most workgroups (ids of SweepMap) for them: what is left over by eight XCDs is rounded up.
+static int64_t sweep_blocks_max(int64_t nTt, int64_t nVt) { return sweep_pairs_max(nTt, nVt) + 8; }
 
 // Workgroup -> (token tile, vocabulary split): a workgroup keeps its token tile and walks the vocabulary
 // tiles of its split.  Ids equal mod 8 run on the same XCD and share its L2: there, 32
@@ -1378,8 +1382,9 @@ static FwdPlan plan_fwd(const spo_pg_desc *d, void *ws) {
     p.Kc = d->dtype == SPO_FP32 ? kSplitTerms * d->H : d->H;
     p.nblk_tok = ceil_div(std::max<int64_t>(d->T, 1), kTokThreads);
     Arena a(ws);
-    p.part_max = a.take<float>(static_cast<size_t>(p.nsplit) * p.T_pad);
-    p.part_sum = a.take<float>(static_cast<size_t>(p.nsplit) * p.T_pad);
+    const size_t room = static_cast<size_t>(sweep_pairs_max(p.nTt, p.nVt)) * TL::BN;  // [nsplit][T_pad] and more
+    p.part_max = a.take<float>(room);
+    p.part_sum = a.take<float>(room);
     p.z_target = a.take<float>(p.T_pad);
     p.partials = a.take<FwdPartial>(p.nblk_tok);
     p.done = a.take<uint32_t>(1);

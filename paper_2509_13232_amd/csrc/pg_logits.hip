@@ -274,8 +274,11 @@ static LogitsFwdPlan plan_logits_fwd(const spo_pg_desc *d, void *ws) {
     p.nblk_tok = ceil_div(Tn, kTokThreads);
     p.grid = lse_grid(d);
     Arena a(ws);
-    p.row_max = a.take<float>(Tn * p.grid.nseg);
-    p.row_sum = a.take<float>(Tn * p.grid.nseg);
+    // room for rows of T and V cut into the shortest segments of either type (0.4 % of the logits' bytes): the segments
+    // in use get longer with T and V, and room sized for the largest batch is to serve every smaller one
+    const size_t room = static_cast<size_t>(Tn * ceil_div(d->V, kWave * kLseGroup * Vec<float>::N));
+    p.row_max = a.take<float>(room);
+    p.row_sum = a.take<float>(room);
     p.z_target = a.take<float>(Tn);
     p.partials = a.take<FwdPartial>(p.nblk_tok);
     p.done = a.take<uint32_t>(1);

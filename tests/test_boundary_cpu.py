@@ -119,3 +119,37 @@ def test_host_side_argument_checks(L):
     fb0 = L.spo_pg_loss_fwd_bwd_workspace_bytes(C.byref(d), 0)
     fb8k = L.spo_pg_loss_fwd_bwd_workspace_bytes(C.byref(d), 8192)
     assert fb8k < fb0 < 24 << 30 and fb8k > big8k
+
+
+def _pg_desc(T, V, H=0, dtype=1, w_layout=0, mask=False):
+    """A descriptor for the workspace queries, which read sizes only (H = 0: logits-in)."""
+    from paper_2509_13232_amd.binding import PgDesc
+    d = PgDesc()
+    d.struct_size = C.sizeof(PgDesc)
+    d.dtype, d.w_layout, d.T, d.H, d.V, d.B = dtype, w_layout, T, H, V, 1
+    d.eps_low = d.eps_high = 0.2
+    for f in ("target", "old_logp", "adv_norm", "cu_seqlens") + (("hidden", "W") if H else ("logits",)):
+        setattr(d, f, 256)
+    d.mask = 256 if mask else None
+    return C.byref(d)
+
+
+def _never_shrinks(sizes):
+    return all(a <= b for a, b in zip(sizes, sizes[1:]))
+
+
+TOKENS = sorted({0, 1, 255, 257} | {int(1.13 ** i) for i in range(1, 110)} | set(range(256, 34000, 256)))
+VOCABS = sorted({1, 4096, 4097, 8192, 8193, 151936} | {int(1.3 ** i) for i in range(1, 47)})
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("H,w_layout", [(0, 0), (64, 0), (64, 1)])
+def test_forward_workspace_of_the_largest_batch_serves_smaller_ones(L, dtype, H, w_layout):
+    # how a batch is cut jumps with its sizes; what a program reserves for its largest one must not fall short
+    size = lambda T, V: L.spo_pg_loss_fwd_workspace_bytes(_pg_desc(T, V, H, dtype, w_layout))
+    for V in VOCABS:
+        assert _never_shrinks([size(T, V) for T in TOKENS]), V
+    for T in TOKENS[::5]:
+        assert _never_shrinks([size(T, V) for V in VOCABS]), T
+    if not H:   # the logits-in forward keeps a few numbers per row: its size does not depend on their type
+        assert size(300, 50000) == L.spo_pg_loss_fwd_workspace_bytes(_pg_desc(300, 50000, 0, 1 - dtype))
