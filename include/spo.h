@@ -287,6 +287,8 @@ int spo_pg_loss_fwd(const spo_pg_desc *d, float *loss, float *logp, float *lse, 
  *               choose: as many tokens as keep that buffer within 8 GiB (24576 at
  *               V = 151936, H = 4096).  Fewer, larger chunks cost workspace and save
  *               passes over d_W, which is read and rewritten once per chunk.
+ * The workspace size never shrinks with T or chunk_tokens: one queried for a long batch
+ * and long chunks serves shorter ones (so does that of spo_pg_loss_fwd_bwd).
  * Tokens whose gradient factor is zero (masked, on the clipped branch, or in a
  * response with zero advantage) are left out of the recompute and of both
  * contractions: the cost of the backward follows the number of remaining tokens,

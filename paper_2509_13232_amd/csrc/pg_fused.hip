@@ -1493,9 +1493,17 @@ static BwdPlan plan_bwd(const spo_pg_desc *d, int64_t chunk_tokens, void *ws, bo
     return p;
 }
 
+// What a query adds where its chunk holds all tokens and the fp32 sum of a bf16 d_W is left out: a call with
+// shorter chunks needs the sum, and a workspace that serves long chunks serves short ones.  (Up to a tile of tokens
+// every choice is one chunk.)
+static size_t room_for_shorter_chunks(const spo_pg_desc *d, int64_t chunk) {
+    return d->T > TL::BN && d->T <= chunk ? align_up(static_cast<size_t>(d->V) * d->H * sizeof(float), 256) : 0;
+}
+
 int fused_bwd_workspace(const spo_pg_desc *d, int64_t chunk_tokens, size_t *bytes) {
     // sized for the larger case (bf16 d_W needs an fp32 accumulator)
-    *bytes = plan_bwd(d, chunk_tokens, nullptr, true).bytes;
+    const BwdPlan p = plan_bwd(d, chunk_tokens, nullptr, true);
+    *bytes = p.bytes + room_for_shorter_chunks(d, p.Tc);
     return SPO_OK;
 }
 
@@ -1707,7 +1715,8 @@ static FbPlan plan_fb(const spo_pg_desc *d, int64_t chunk_tokens, void *ws, bool
 }
 
 int fused_fwd_bwd_workspace(const spo_pg_desc *d, int64_t chunk_tokens, size_t *bytes) {
-    *bytes = plan_fb(d, chunk_tokens, nullptr, true, true).bytes;  // sized for the larger case
+    const FbPlan p = plan_fb(d, chunk_tokens, nullptr, true, true);  // sized for the larger case
+    *bytes = p.bytes + room_for_shorter_chunks(d, p.Tz);
     return SPO_OK;
 }
 

@@ -153,3 +153,19 @@ def test_forward_workspace_of_the_largest_batch_serves_smaller_ones(L, dtype, H,
         assert _never_shrinks([size(T, V) for V in VOCABS]), T
     if not H:   # the logits-in forward keeps a few numbers per row: its size does not depend on their type
         assert size(300, 50000) == L.spo_pg_loss_fwd_workspace_bytes(_pg_desc(300, 50000, 0, 1 - dtype))
+
+
+@pytest.mark.parametrize("mask", [False, True])
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_gradient_workspace_of_long_chunks_serves_short_ones(L, dtype, mask):
+    def sizes(T, V, H, chunks):
+        d = _pg_desc(T, V, H, dtype, 0, mask)
+        return [[q(d, c) for c in chunks] for q in (L.spo_pg_loss_bwd_workspace_bytes, L.spo_pg_loss_fwd_bwd_workspace_bytes)]
+    for T in (1, 256, 257, 700, 3000, 9000):
+        for V, H in ((300, 64), (3000, 1024), (30000, 4096)):
+            # these heads' default (0) is one chunk
+            assert all(map(_never_shrinks, sizes(T, V, H, [*range(256, 10000, 256), 0]))), (T, V, H)
+    for V, H in ((300, 64), (3000, 1024), (151936, 4096)):   # nor does it shrink with the batch
+        for chunk in (0, 256, 4096):
+            by_T = [[s[0] for s in sizes(T, V, H, [chunk])] for T in TOKENS]
+            assert all(_never_shrinks([s[i] for s in by_T]) for i in (0, 1)), (V, H, chunk)
