@@ -79,34 +79,53 @@ __device__ __forceinline__ float grad_factor(const Surrogate &r, float adv, doub
     return r.active ? -(adv * r.ratio * grad_loss) / static_cast<float>(M) : 0.0f;
 }
 
-// One lane per token, 64 tokens per workgroup.  The (running max, sum of exponentials) pairs of the
-// vocabulary splits are merged by all wavefronts of the workgroup together (1191 tokens x 408 splits
-// by one thread per token, a load at a time: 312 us); the first wavefront forms lse, logp, the
-// surrogate and, where asked for, the gradient factors.  z_target[t] is the logit of the sampled
-// token.  The workgroup that finishes last (counted in *done, zero beforehand, over all launches of
-// the call: total_blocks) adds the partial sums in order and writes the loss.
-constexpr int kTokThreads = kWave;  // tokens per workgroup
+// One lane per token, a block of 64 tokens per `ways` wavefronts.  These merge the (running max, sum of
+// exponentials) pairs of the vocabulary splits together (1191 tokens x 408 splits by one thread per token, a load
+// at a time: 312 us); their first one forms lse, logp, the surrogate and, where asked for, the gradient factors.
+// z_target[t] is the logit of the sampled token.  The workgroup that finishes last (counted in *done in blocks,
+// zero beforehand, over all launches of the call: total_blocks) adds the partial sums in order and writes the loss.
+constexpr int kTokThreads = kWave;  // tokens per block
+constexpr int kTokWaves = 16;       // most wavefronts per workgroup
 
-static __global__ void __launch_bounds__(1024)
-token_loss_kernel(const float *__restrict__ part_max, const float *__restrict__ part_sum, int nsplit,
+// How a launch over n_blocks blocks is cut: four splits for each of `ways` wavefronts while the blocks alone do not
+// fill the chip (kTokChipWaves), and several blocks per workgroup, more where there would be more than kTokChipGroups
+// workgroups: their counts meet at one address, 11 ns apart.  (200000 tokens of two splits: 19 us, 27 with four blocks
+// per workgroup and 71 with one, of 16 wavefronts.)
+constexpr int kTokChipWaves = 2048, kTokChipGroups = 512;
+struct TokenShape {
+    unsigned blocks, threads;
+    int ways;
+};
+static inline TokenShape token_shape(int nsplit, int64_t n_blocks) {
+    int ways = 1;
+    while (ways < kTokWaves && ways * 4 < nsplit && ways * n_blocks < kTokChipWaves) ways *= 2;
+    int waves = ways;
+    while (waves < 4 ? waves / ways < n_blocks : waves < kTokWaves && n_blocks * ways / waves > kTokChipGroups) waves *= 2;
+    return TokenShape{static_cast<unsigned>(ceil_div(n_blocks, waves / ways)), static_cast<unsigned>(waves * kWave), ways};
+}
+
+static __global__ void __launch_bounds__(kTokWaves * kWave)
+token_loss_kernel(const float *__restrict__ part_max, const float *__restrict__ part_sum, int nsplit, int ways,
                   int64_t split_stride, const float *__restrict__ z_target, TokenInputs in, float *__restrict__ logp_out,
-                  float *__restrict__ lse_out, FwdPartial *__restrict__ partials, TokenGrad gr, int64_t total_blocks,
-                  uint32_t *__restrict__ done, float *__restrict__ loss, float *__restrict__ stats) {
-    __shared__ float sm[16][kWave], ss[16][kWave];
+                  float *__restrict__ lse_out, FwdPartial *__restrict__ partials, TokenGrad gr, int64_t n_blocks,
+                  int64_t total_blocks, uint32_t *__restrict__ done, float *__restrict__ loss, float *__restrict__ stats) {
+    __shared__ float sm[kTokWaves][kWave], ss[kTokWaves][kWave];
     __shared__ int32_t cu_lds[kCuStaged];
-    __shared__ double scratch[16];
+    __shared__ double scratch[4 * kTokWaves];
+    __shared__ FwdPartial block_part[kTokWaves];
     __shared__ int last;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwave = blockDim.x >> 6;
-    const int64_t t = static_cast<int64_t>(blockIdx.x) * kTokThreads + lane;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, way = wave % ways;
+    const int per_wg = static_cast<int>(blockDim.x >> 6) / ways;  // blocks per workgroup
+    const int64_t first = static_cast<int64_t>(blockIdx.x) * per_wg, t = (first + wave / ways) * kTokThreads + lane;
     const int32_t *cu = stage_offsets(in.cu, in.B, cu_lds);
     float m = kNegBig, s = 0.0f;
     if (t < in.T) {
         constexpr int U = 8;  // pairs requested at a time
-        for (int i0 = wave; i0 < nsplit; i0 += U * nwave) {
+        for (int i0 = way; i0 < nsplit; i0 += U * ways) {
             float pm[U], ps[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int i = i0 + u * nwave;
+                const int i = i0 + u * ways;
                 pm[u] = i < nsplit ? part_max[i * split_stride + t] : kNegBig;
                 ps[u] = i < nsplit ? part_sum[i * split_stride + t] : 0.0f;
             }
@@ -123,12 +142,12 @@ token_loss_kernel(const float *__restrict__ part_max, const float *__restrict__ 
     ss[wave][lane] = s;
     __syncthreads();
     double so = 0.0, cnt = 0.0, clp = 0.0, sr = 0.0;
-    if (wave == 0) {
+    if (way == 0) {
         float g = 0.0f, c = 0.0f;
         if (t < in.T) {
-            for (int w = 1; w < nwave; ++w) m = fmaxf(m, sm[w][lane]);
+            for (int w = 1; w < ways; ++w) m = fmaxf(m, sm[wave + w][lane]);
             s = 0.0f;
-            for (int w = 0; w < nwave; ++w) s += ss[w][lane] * expf(sm[w][lane] - m);
+            for (int w = 0; w < ways; ++w) s += ss[wave + w][lane] * expf(sm[wave + w][lane] - m);
             const float lse = m + logf(s);
             const float logp = z_target[t] - lse;
             lse_out[t] = lse;
@@ -158,43 +177,49 @@ token_loss_kernel(const float *__restrict__ part_max, const float *__restrict__ 
         cnt = wave_sum(cnt);
         clp = wave_sum(clp);
         sr = wave_sum(sr);
-        if (lane == 0) {
-            partials[in.t_base / kTokThreads + blockIdx.x] = FwdPartial{so, cnt, clp, sr};
-            // the count releases this workgroup's sums to whichever ends last, and acquires theirs
-            last = total_blocks == 1 ||
-                   __hip_atomic_fetch_add(done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == total_blocks - 1;
-        }
+        if (lane == 0) block_part[wave / ways] = FwdPartial{so, cnt, clp, sr};
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const int mine = static_cast<int>(n_blocks - first < per_wg ? n_blocks - first : per_wg);
+        for (int b = 0; b < mine; ++b) partials[in.t_base / kTokThreads + first + b] = block_part[b];
+        // the count releases this thread's stores to whichever workgroup ends last, and acquires theirs
+        last = total_blocks == mine ||
+               __hip_atomic_fetch_add(done, static_cast<uint32_t>(mine), __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) ==
+                   static_cast<uint32_t>(total_blocks - mine);
     }
     __syncthreads();
     if (!last) return;
-    so = cnt = clp = sr = 0.0;
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // for the wavefronts that did not count
-    for (int64_t i = threadIdx.x; i < total_blocks; i += blockDim.x) {
-        so += partials[i].sum_obj;
-        cnt += partials[i].count;
-        clp += partials[i].clipped;
-        sr += partials[i].sum_ratio;
-    }
-    so = block_sum(so, scratch);
-    cnt = block_sum(cnt, scratch);
-    clp = block_sum(clp, scratch);
-    sr = block_sum(sr, scratch);
-    if (threadIdx.x == 0) {
-        loss[0] = cnt > 0.0 ? static_cast<float>(-so / cnt) : 0.0f;
-        if (stats) {
-            stats[0] = static_cast<float>(cnt);
-            stats[1] = cnt > 0.0 ? static_cast<float>(clp / cnt) : 0.0f;
-            stats[2] = cnt > 0.0 ? static_cast<float>(sr / cnt) : 0.0f;
-            stats[3] = static_cast<float>(so);
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // for the threads that did not count
+    double v[4] = {};  // objective, unmasked, clipped, ratios
+    constexpr int A = 4;  // partial sums requested at a time
+    for (int64_t i0 = threadIdx.x; i0 < total_blocks; i0 += A * blockDim.x) {
+        FwdPartial p[A];
+#pragma unroll
+        for (int a = 0; a < A; ++a) {
+            const int64_t i = i0 + a * static_cast<int64_t>(blockDim.x);
+            p[a] = partials[i < total_blocks ? i : total_blocks - 1];  // always a load, none of them behind a branch
+        }
+#pragma unroll
+        for (int a = 0; a < A; ++a) {
+            if (i0 + a * static_cast<int64_t>(blockDim.x) >= total_blocks) break;
+            v[0] += p[a].sum_obj;
+            v[1] += p[a].count;
+            v[2] += p[a].clipped;
+            v[3] += p[a].sum_ratio;
         }
     }
-}
-
-// Wavefronts per workgroup of token_loss_kernel: four splits each, or enough to add many workgroups' partial sums.
-static inline unsigned token_threads(int nsplit, int64_t total_blocks) {
-    unsigned w = 1;
-    while (w < 16 && (static_cast<int>(w) * 4 < nsplit || static_cast<int64_t>(w) * 512 < total_blocks)) w *= 2;
-    return w * kWave;
+    block_sums(v, scratch);
+    if (threadIdx.x == 0) {
+        cnt = v[1];
+        loss[0] = cnt > 0.0 ? static_cast<float>(-v[0] / cnt) : 0.0f;
+        if (stats) {
+            stats[0] = static_cast<float>(cnt);
+            stats[1] = cnt > 0.0 ? static_cast<float>(v[2] / cnt) : 0.0f;
+            stats[2] = cnt > 0.0 ? static_cast<float>(v[3] / cnt) : 0.0f;
+            stats[3] = static_cast<float>(v[0]);
+        }
+    }
 }
 
 // Number of set entries of mask[0..T), by one workgroup of up to 1024 threads; every thread receives it.

@@ -1428,9 +1428,10 @@ int fused_fwd(const spo_pg_desc *d, float *loss, float *logp, float *lse, float 
             W, p.Kc * 2, d->V, X, p.Kc * 2, d->T, static_cast<int>(p.Kc / kBK), p.nsplit, p.nTt, p.nVt, p.T_pad,
             p.part_max, p.part_sum, nullptr, 0, nullptr);
     }
-    token_loss_kernel<<<static_cast<unsigned>(p.nblk_tok), token_threads(p.nsplit, p.nblk_tok), 0, s>>>(
-        p.part_max, p.part_sum, p.nsplit, p.T_pad, p.z_target, token_inputs(d, 0, d->T), logp, lse, p.partials,
-        TokenGrad{}, p.nblk_tok, p.done, loss, stats);
+    const TokenShape tok = token_shape(p.nsplit, p.nblk_tok);
+    token_loss_kernel<<<tok.blocks, tok.threads, 0, s>>>(
+        p.part_max, p.part_sum, p.nsplit, tok.ways, p.T_pad, p.z_target, token_inputs(d, 0, d->T), logp, lse, p.partials,
+        TokenGrad{}, p.nblk_tok, p.nblk_tok, p.done, loss, stats);
     return launch_status();
 }
 
@@ -1738,8 +1739,8 @@ int fused_fwd_bwd(const spo_pg_desc *d, float grad_loss, float *loss, float *log
             const int64_t words = d_W_dtype == SPO_FP32 ? V * H : V * H / 2;
             fill_zero_kernel<<<grid1(words), 256, 0, s>>>(static_cast<uint32_t *>(d_W), words);
         }
-        token_loss_kernel<<<1, kTokThreads, 0, s>>>(nullptr, nullptr, 0, 0, nullptr, token_inputs(d, 0, 0), logp, lse,
-                                                    p.partials, TokenGrad{}, 1, p.done, loss, stats);
+        token_loss_kernel<<<1, kTokThreads, 0, s>>>(nullptr, nullptr, 0, 1, 0, nullptr, token_inputs(d, 0, 0), logp, lse,
+                                                    p.partials, TokenGrad{}, 1, 1, p.done, loss, stats);
         return launch_status();
     }
     // the head as the kernels read it: one row per vocabulary entry for the logits, one row per
@@ -1785,9 +1786,11 @@ int fused_fwd_bwd(const spo_pg_desc *d, float grad_loss, float *loss, float *log
             gr.Q = p.Z;
             gr.q_blk = Tzp * kBlockK;
         }
-        token_loss_kernel<<<grid1(back ? Tzp : Tv, kTokThreads), token_threads(map.ns, p.nblk_tok), 0, s>>>(
-            p.part_max, p.part_sum, map.ns, Tzp, p.z_target + t0, token_inputs(d, t0, Tv), logp + t0, lse + t0,
-            p.partials, gr, back ? ceil_div(p.T_pad, kTokThreads) : ceil_div(T, kTokThreads), p.done, loss, stats);
+        const int64_t n_blocks = ceil_div(back ? Tzp : Tv, kTokThreads);
+        const TokenShape tok = token_shape(static_cast<int>(map.ns), n_blocks);
+        token_loss_kernel<<<tok.blocks, tok.threads, 0, s>>>(
+            p.part_max, p.part_sum, map.ns, tok.ways, Tzp, p.z_target + t0, token_inputs(d, t0, Tv), logp + t0, lse + t0,
+            p.partials, gr, n_blocks, back ? ceil_div(p.T_pad, kTokThreads) : ceil_div(T, kTokThreads), p.done, loss, stats);
         if (!back) continue;
         if (p.dense) {
             // the contractions run on what the sweep stored: every row of the piece, scaled by c_t

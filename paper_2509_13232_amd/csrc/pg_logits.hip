@@ -327,9 +327,10 @@ int logits_fwd(const spo_pg_desc *d, float *loss, float *logp, float *lse, float
         if (d->dtype == SPO_BF16) launch_row_lse<bf16_t>(d, p, s);
         else launch_row_lse<float>(d, p, s);
     }
-    token_loss_kernel<<<static_cast<unsigned>(p.nblk_tok), token_threads(p.grid.nseg, p.nblk_tok), 0, s>>>(
-        p.row_max, p.row_sum, p.grid.nseg, d->T, p.z_target, token_inputs(d, 0, d->T), logp, lse, p.partials,
-        TokenGrad{}, p.nblk_tok, p.done, loss, stats);
+    const TokenShape tok = token_shape(p.grid.nseg, p.nblk_tok);
+    token_loss_kernel<<<tok.blocks, tok.threads, 0, s>>>(
+        p.row_max, p.row_sum, p.grid.nseg, tok.ways, d->T, p.z_target, token_inputs(d, 0, d->T), logp, lse, p.partials,
+        TokenGrad{}, p.nblk_tok, p.nblk_tok, p.done, loss, stats);
     return launch_status();
 }
 

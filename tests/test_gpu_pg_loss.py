@@ -599,6 +599,43 @@ def test_token_kernels_edges(spo, oracle, T, B, offset):
     assert rel_l2(f64(dl), rb["d_logits"]) < 1e-5 and not dl[t(mask) == 0].any()
 
 
+@pytest.mark.parametrize("T,V", [
+    *[(T, V) for T in (1, 64, 65, 129, 200, 320)   # 1 to 5 blocks of 64 tokens: whole workgroups and ragged ones
+      for V in (8, 20000, 60000)],                 # rows in 1, 5 and 15 segments: 1, 2 and 4 wavefronts per block
+    (131073, 8), (140000, 8), (262145, 8)])        # 4, 8 and 16 blocks per workgroup, the last workgroup ragged
+def test_token_blocks_per_workgroup(spo, oracle, T, V):
+    say(f"token blocks T={T} V={V}")
+    rng = np.random.default_rng([T, V, 6])
+    logits = (rng.standard_normal((T, V)) * 2).astype(np.float32)
+    tg, adv = rng.integers(0, V, T).astype(np.int32), np.array([0.7, -1.3], np.float32)
+    cu, mask = np.array([0, T // 3, T], np.int32), (np.arange(T) % 5 != 1).astype(np.uint8)
+    args = lambda old: (None, None, tg, old, mask, adv.astype(np.float64), cu, 0.2, 0.28)
+    logp = oracle.pg_loss_fwd(*args(np.zeros(T)), logits=logits.astype(np.float64))["logp"]
+    old = (logp + rng.choice([-0.1, 0.1, 0.5], T)).astype(np.float32)
+    ref = oracle.pg_loss_fwd(*args(old.astype(np.float64)), logits=logits.astype(np.float64))
+    t = lambda x: torch.as_tensor(x).cuda()
+    desc = spo.make_desc(None, None, t(tg), t(old), t(mask), t(adv), t(cu), 0.2, 0.28, logits=t(logits))
+    for _ in range(2):
+        loss, lp, lse, stats = spo.spo_pg_loss_fwd(desc)
+        torch.cuda.synchronize()
+        np.testing.assert_allclose(f64(lp), ref["logp"], atol=1e-5, rtol=0)
+        np.testing.assert_allclose(f64(lse), ref["lse"], atol=1e-5, rtol=0)
+        m = mask.astype(bool)
+        st = f64(stats)
+        assert st[0] == ref["M"] and abs(st[1] - (1 - ref["active"][m].mean())) < 1e-6
+        assert abs(st[2] - ref["ratio"][m].mean()) < 1e-4 and abs(loss.item() - ref["loss"]) <= 1e-5
+
+
+def test_many_tokens_of_few_splits(spo, oracle):
+    # 6 splits, and enough blocks of tokens that one wavefront merges all of them, eight blocks per workgroup
+    say("fused bf16 T=140001 H=64 V=1500, forward")
+    case = Case(wl.scaled(MID, name="long", H=64, V=1500), [40000, 1, 100000])
+    case.set_old_from_oracle(oracle)
+    fwd = spo.spo_pg_loss_fwd(case.to_gpu(spo, 0))
+    torch.cuda.synchronize()
+    check_forward(case, oracle, fwd)
+
+
 def test_target_id_out_of_range_gives_nan_not_garbage(spo, oracle):
     # sampled-token ids are not validated on the host; an id outside [0, V) must neither read out of
     # bounds nor leave a stale number behind: the token's log-prob is NaN, all other tokens are untouched
