@@ -123,7 +123,8 @@ struct PrepJobs {
     float *z_target, *ref2;
     int64_t T_ref;                // entries of ref2
     uint32_t *done;
-    int64_t target_blocks;        // four tokens each
+    int64_t target_blocks;        // four wavefronts of target_run (1 or kTargetRun) tokens each
+    int target_run;
     const uint8_t *mask;
     double *count;                // NULL: not counted
     float *g;                     // NULL: no gradient factors
@@ -137,6 +138,12 @@ struct PrepJobs {
 // One workgroup takes 1024 tokens per round; four rounds save two launches and pass beside the head's tiles (512
 // tokens: the whole launch 6 us).
 constexpr int64_t kPrepGradTokens = 4096;
+
+// Tokens whose target logits one wavefront forms at a time.  Four, their loads together, where there are more tokens
+// than the chip has wavefronts and a row is so short that a wavefront waits for it more than it reads (bf16, 200000
+// tokens of 64 values 55 -> 26 us, 180000 of 1024 93 -> 68; 170000 of 2048 130 -> 162).
+constexpr int kTargetRun = 4;
+constexpr int64_t kTargetRunTokens = 16384, kTargetRunBytes = 2048;
 
 constexpr int kPrepTile = 64;
 template <typename T_> constexpr int kPrepPitch = sizeof(T_) == 2 ? 66 : 65;
@@ -341,8 +348,8 @@ gather_chunk_kernel(const T_ *__restrict__ X, int64_t H, const int32_t *__restri
 // ----------------------------------------------------------------------------
 // forward: logit of the sampled token
 // ----------------------------------------------------------------------------
-// z_target[t] = h_t . W[target[t]] (W with one row per vocabulary entry), one wavefront per
-// token, products and sum in fp32.  The sweep below does not have to watch for this one
+// z_target[t] = h_t . W[target[t]] (W with one row per vocabulary entry), by one wavefront,
+// products and sum in fp32.  The sweep below does not have to watch for this one
 // entry of every row.  An id outside [0, V) gives NaN (the token's log-prob, and with it the
 // loss, then say so instead of carrying an arbitrary number).
 __device__ __forceinline__ float dot8(const uint4 a, const uint4 b) {
@@ -356,22 +363,46 @@ __device__ __forceinline__ float dot8(const uint4 a, const uint4 b) {
     return s;
 }
 
-template <typename T_>
-__device__ __forceinline__ float target_logit(const T_ *__restrict__ X, const T_ *__restrict__ Wvh, int64_t H, int64_t V,
-                                              int64_t y, int64_t t, int lane) {
-    if (y < 0 || y >= V) return __builtin_nanf("");
-    float s = 0.0f;
-    if constexpr (sizeof(T_) == 2) {
-        const uint4 *x = reinterpret_cast<const uint4 *>(X + t * H), *w = reinterpret_cast<const uint4 *>(Wvh + y * H);
-        for (int i = lane; i < H / 8; i += kWave) s += dot8(x[i], w[i]);  // H is a multiple of 64
-    } else {
-        const float4 *x = reinterpret_cast<const float4 *>(X + t * H), *w = reinterpret_cast<const float4 *>(Wvh + y * H);
-        for (int i = lane; i < H / 4; i += kWave) {
-            const float4 a = x[i], b = w[i];
-            s = fmaf(a.x, b.x, s); s = fmaf(a.y, b.y, s); s = fmaf(a.z, b.z, s); s = fmaf(a.w, b.w, s);
+// The target logits of K consecutive tokens from t on (NaN past T) by one wavefront, the loads of all in flight together.
+template <int K, typename T_>
+__device__ __forceinline__ void target_logits(const T_ *__restrict__ X, const T_ *__restrict__ Wvh, int64_t H, int64_t V, int64_t T,
+                                              const int32_t *__restrict__ target, int64_t t, int lane, float (&z)[K]) {
+    constexpr int N = 16 / sizeof(T_);  // values per 16-byte load
+    const uint4 *x[K], *w[K];
+    bool ok[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int64_t y = t + k < T ? target[t + k] : -1;
+        ok[k] = y >= 0 && y < V;
+        x[k] = reinterpret_cast<const uint4 *>(X + (ok[k] ? t + k : 0) * H);  // (of the others: the first row, not used)
+        w[k] = reinterpret_cast<const uint4 *>(Wvh + (ok[k] ? y : 0) * H);
+        z[k] = 0.0f;
+    }
+#pragma unroll 4 / K
+    for (int i = lane; i < H / N; i += kWave) {  // H is a multiple of 64
+        uint4 a[K], b[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            a[k] = x[k][i];
+            b[k] = w[k][i];
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            if constexpr (sizeof(T_) == 2) {
+                z[k] += dot8(a[k], b[k]);
+            } else {
+                z[k] = fmaf(__uint_as_float(a[k].x), __uint_as_float(b[k].x), z[k]);
+                z[k] = fmaf(__uint_as_float(a[k].y), __uint_as_float(b[k].y), z[k]);
+                z[k] = fmaf(__uint_as_float(a[k].z), __uint_as_float(b[k].z), z[k]);
+                z[k] = fmaf(__uint_as_float(a[k].w), __uint_as_float(b[k].w), z[k]);
+            }
         }
     }
-    return wave_sum(s);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const float s = wave_sum(z[k]);
+        z[k] = ok[k] ? s : __builtin_nanf("");
+    }
 }
 
 // The reference of a token whose logits are stored as scaled probabilities (see below, one-call form without
@@ -380,6 +411,21 @@ __device__ __forceinline__ float target_logit(const T_ *__restrict__ X, const T_
 __device__ __forceinline__ float probs_reference(float z_target, float old_logp) {
     const float r = (z_target - old_logp) * kLog2e;
     return fabsf(r) < 3.0e38f ? r : 0.0f;  // not NaN, not infinite
+}
+
+// Target logits and references of 4 * K tokens by one workgroup.
+template <int K, typename T_>
+__device__ __forceinline__ void prep_targets(const PrepJobs &j, int64_t block) {
+    const int64_t t = (block * 4 + (threadIdx.x >> 6)) * K;
+    const int lane = threadIdx.x & 63;
+    float z[K];
+    target_logits<K>(static_cast<const T_ *>(j.X), static_cast<const T_ *>(j.Wrows), j.H, j.V, j.T, j.target, t, lane, z);
+    float mine = z[0];  // lane k: token t + k
+#pragma unroll
+    for (int k = 1; k < K; ++k) mine = lane == k ? z[k] : mine;
+    if (lane >= K) return;
+    if (t + lane < j.T) j.z_target[t + lane] = mine;
+    if (j.ref2 && t + lane < j.T_ref) j.ref2[t + lane] = t + lane < j.T ? probs_reference(mine, j.old_logp[t + lane]) : 0.0f;
 }
 
 template <typename T_, bool HV>
@@ -402,16 +448,8 @@ __global__ void __launch_bounds__(256) prep_kernel(PrepJobs j) {
     }
     b -= j.row_blocks;
     if (b < j.target_blocks) {
-        const int64_t t = b * 4 + (threadIdx.x >> 6);
-        const int lane = threadIdx.x & 63;
-        float ref = 0.0f;
-        if (t < j.T) {
-            const float z = target_logit(static_cast<const T_ *>(j.X), static_cast<const T_ *>(j.Wrows), j.H, j.V,
-                                         j.target[t], t, lane);
-            if (lane == 0) j.z_target[t] = z;
-            if (j.ref2) ref = probs_reference(z, j.old_logp[t]);
-        }
-        if (j.ref2 && t < j.T_ref && lane == 0) j.ref2[t] = ref;
+        if (j.target_run > 1) prep_targets<kTargetRun, T_>(j, b);
+        else prep_targets<1, T_>(j, b);
         return;
     }
     b -= j.target_blocks;
@@ -475,7 +513,9 @@ static void launch_prep_with_targets(const spo_pg_desc *d, PrepJobs j, float *z_
     j.ref2 = ref2;
     j.T_ref = T_ref;
     j.done = done;
-    j.target_blocks = ceil_div(ref2 ? T_ref : d->T, 4);
+    const int64_t tokens = ref2 ? T_ref : d->T;
+    j.target_run = tokens > kTargetRunTokens && d->H * (d->dtype == SPO_FP32 ? 4 : 2) <= kTargetRunBytes ? kTargetRun : 1;
+    j.target_blocks = ceil_div(tokens, 4 * j.target_run);
     launch_prep(d, j, s);
 }
 

@@ -636,6 +636,20 @@ def test_many_tokens_of_few_splits(spo, oracle):
     check_forward(case, oracle, fwd)
 
 
+@pytest.mark.parametrize("dtype,H", [("bf16", 64), ("bf16", 1024), ("bf16", 1088), ("fp32", 192), ("fp32", 576)])
+@pytest.mark.parametrize("T", [16384, 16385, 16387])   # four target logits per wavefront from the second on, where rows are short
+def test_target_logits_of_long_batches(spo, oracle, dtype, H, T):
+    say(f"target logits {dtype} T={T} H={H}")
+    case = Case(wl.scaled(MID, name="targets", H=H, V=40, dtype=dtype), [T - 5, 5])
+    case.set_old_from_oracle(oracle)
+    desc = case.to_gpu(spo, 0)
+    *fwd, dx, dw = spo.spo_pg_loss_fwd_bwd(desc, 1.0, d_hidden_dtype=torch.float32)   # its references are made there too
+    torch.cuda.synchronize()
+    check_forward(case, oracle, fwd)
+    rb = oracle.pg_loss_bwd(*case.oracle_inputs(), *case.eps)
+    assert rel_l2(f64(dx), rb["d_hidden"]) < GRAD_TOL and rel_l2(f64(dw), rb["d_W"]) < GRAD_TOL
+
+
 def test_target_id_out_of_range_gives_nan_not_garbage(spo, oracle):
     # sampled-token ids are not validated on the host; an id outside [0, V) must neither read out of
     # bounds nor leave a stale number behind: the token's log-prob is NaN, all other tokens are untouched
