@@ -18,6 +18,10 @@ namespace spo {
 // 806 us, two rounds of four 842 us).
 // Arrays that no cache can hold are read and written with the non-temporal hint: the forward of the
 // next pass then finds no modified lines of the gradients to drain first (forward 437 -> 350 us).
+// Rows of a few thousand entries are bound by instructions as well: a thread works on two or three vectors per
+// row.  There vectors that a segment does not have are not worked on, a segment of one round has no second one to
+// request, and a wavefront's pairs are merged with one exponential (60000 rows of 4104 in bf16: 138 -> 81 us;
+// a workgroup per row without segments took 96).
 constexpr int kRowThreads = 256;
 constexpr int kLseGroup = 4, kLseRounds = 2, kGradGroup = 2;
 constexpr int64_t kStreamBytes = int64_t(256) << 20;  // the Infinity Cache
@@ -26,7 +30,6 @@ constexpr int64_t kStreamBytes = int64_t(256) << 20;  // the Infinity Cache
 template <typename T> struct Vec;
 template <> struct Vec<bf16_t> {
     static constexpr int N = 8;
-    static constexpr uint32_t kNegInf = 0xff80ff80u;  // a pair of -inf
     __device__ static __forceinline__ void unpack(const uint4 &u, float (&x)[8]) {
         const uint32_t w[4] = {u.x, u.y, u.z, u.w};
 #pragma unroll
@@ -44,7 +47,6 @@ template <> struct Vec<bf16_t> {
 };
 template <> struct Vec<float> {
     static constexpr int N = 4;
-    static constexpr uint32_t kNegInf = 0xff800000u;
     __device__ static __forceinline__ void unpack(const uint4 &u, float (&x)[4]) {
         x[0] = __uint_as_float(u.x); x[1] = __uint_as_float(u.y); x[2] = __uint_as_float(u.z); x[3] = __uint_as_float(u.w);
     }
@@ -97,6 +99,14 @@ struct RowGrid {
     __host__ dim3 blocks() const { return fold_grid(ceil_div(rows * nseg, per_wg)); }
 };
 
+// The unit of a group of TR threads, a value the compiler knows to be the same in a whole wavefront: its place and
+// extent are then scalar arithmetic (30000 rows of 4104 in bf16: 66 -> 62 us).
+template <int TR>
+__device__ __forceinline__ int64_t group_unit() {
+    if constexpr (TR == kRowThreads) return flat_block();
+    else return flat_block() * (kRowThreads / TR) + __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / TR);
+}
+
 // running (max, sum of exp(x - max)) merged with another pair
 __device__ __forceinline__ void lse_merge(float &m, float &s, float om, float os) {
     const float nm = fmaxf(m, om);
@@ -106,13 +116,13 @@ __device__ __forceinline__ void lse_merge(float &m, float &s, float om, float os
 
 // (max, sum-exp) of one segment of a row, by TR threads (a workgroup or one wavefront of it), and the
 // target's logit.  part_max / part_sum [segment][row].  Also clears *done.
-template <typename T, int TR, bool Stream>
+template <typename T, int TR, int Rounds, bool Stream>
 __global__ void __launch_bounds__(kRowThreads)
 logits_row_lse_kernel(const T *__restrict__ logits, int64_t V, RowGrid grid, const int32_t *__restrict__ target,
                       float *__restrict__ part_max, float *__restrict__ part_sum, float *__restrict__ z_target,
                       uint32_t *__restrict__ done) {
     constexpr int N = Vec<T>::N, U = kLseGroup;
-    const int64_t unit = flat_block() * (kRowThreads / TR) + threadIdx.x / TR;
+    const int64_t unit = group_unit<TR>();
     const int tid = threadIdx.x % TR;
     if (unit == 0 && threadIdx.x == 0) *done = 0u;  // for the kernel that follows
     if (unit >= grid.units()) return;  // TR < kRowThreads only: no barrier below in that case
@@ -135,37 +145,50 @@ logits_row_lse_kernel(const T *__restrict__ logits, int64_t V, RowGrid grid, con
     const T *body = p + sp.head;
     auto request = [&](uint4 (&v)[U], int i0) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int i = i0 + u * TR;
-            v[u] = make_uint4(Vec<T>::kNegInf, Vec<T>::kNegInf, Vec<T>::kNegInf, Vec<T>::kNegInf);  // counts as nothing
-            if (i < sp.nvec) v[u] = load16<Stream>(body + i * N);
-        }
+        for (int u = 0; u < U; ++u)
+            if (i0 + u * TR < sp.nvec) v[u] = load16<Stream>(body + (i0 + u * TR) * N);
     };
-    uint4 cur[U], nxt[U];
-    request(cur, tid);
-    for (int i0 = tid; i0 < sp.nvec; i0 += U * TR) {
-        request(nxt, i0 + U * TR);
-        // one new maximum and one rescaling of the running sum for the whole group
+    auto take = [&](const uint4 (&v)[U], int i0) {
+        // one new maximum and one rescaling of the running sum for the whole group; vectors past the end are left out
+        // (rows of 4104: one in two of the group's)
         float x[U][N], mx = m;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            Vec<T>::unpack(cur[u], x[u]);
+            if (i0 + u * TR >= sp.nvec) break;
+            Vec<T>::unpack(v[u], x[u]);
 #pragma unroll
             for (int i = 0; i < N; ++i) mx = fmaxf(mx, x[u][i]);
         }
         const float nm2 = -mx * kLog2e;
         float a[U] = {};
 #pragma unroll
-        for (int u = 0; u < U; ++u)
+        for (int u = 0; u < U; ++u) {
+            if (i0 + u * TR >= sp.nvec) break;
 #pragma unroll
             for (int i = 0; i < N; ++i) a[u] += __builtin_amdgcn_exp2f(fmaf(x[u][i], kLog2e, nm2));
+        }
         s = s * __builtin_amdgcn_exp2f((m - mx) * kLog2e) + ((a[0] + a[1]) + (a[2] + a[3]));
         m = mx;
+    };
+    uint4 cur[U];
+    request(cur, tid);
+    if constexpr (Rounds > 1) {
+        uint4 nxt[U];
+        for (int i0 = tid; i0 < sp.nvec; i0 += U * TR) {
+            request(nxt, i0 + U * TR);
+            take(cur, i0);
 #pragma unroll
-        for (int u = 0; u < U; ++u) cur[u] = nxt[u];
+            for (int u = 0; u < U; ++u) cur[u] = nxt[u];
+        }
+    } else {
+        take(cur, tid);
     }
+    // one maximum for the wavefront, then one rescaling and the sum (merging pairs takes two exponentials per step)
+    float top = m;
 #pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) lse_merge(m, s, __shfl_xor(m, o, kWave), __shfl_xor(s, o, kWave));
+    for (int o = kWave / 2; o > 0; o >>= 1) top = fmaxf(top, __shfl_xor(top, o, kWave));
+    s = wave_sum(s * __builtin_amdgcn_exp2f((m - top) * kLog2e));
+    m = top;
     if constexpr (TR > kWave) {
         __shared__ float sm[TR / kWave], ss[TR / kWave];
         const int wave = threadIdx.x >> 6;
@@ -191,7 +214,7 @@ __global__ void __launch_bounds__(kRowThreads)
 logits_row_grad_kernel(const T *__restrict__ logits, int64_t V, RowGrid grid, const int32_t *__restrict__ target,
                        const float *__restrict__ lse, const float *__restrict__ g, T *__restrict__ d_logits) {
     constexpr int N = Vec<T>::N, U = kGradGroup;
-    const int64_t unit = flat_block() * (kRowThreads / TR) + threadIdx.x / TR;
+    const int64_t unit = group_unit<TR>();
     const int tid = threadIdx.x % TR;
     if (unit >= grid.units()) return;
     const uint32_t nseg = static_cast<uint32_t>(grid.nseg);
@@ -235,24 +258,29 @@ logits_row_grad_kernel(const T *__restrict__ logits, int64_t V, RowGrid grid, co
     }
 }
 
-// How the rows are cut: segments of `rounds` rounds of `group` vectors per thread.  Rows that give a
-// workgroup less than half a round go to single wavefronts, four to a workgroup.
-static RowGrid row_grid(const spo_pg_desc *d, int group, int rounds) {
+// How the rows are cut: into as few equal segments as keep within `rounds` rounds of `group` vectors per thread
+// (8000 rows of 16392 in bf16 in segments of 16384 and 8: 68 us, in halves 50).  Rows that give a workgroup little work go
+// to single wavefronts, four to a workgroup: up to narrow_eighths eighths of a round (60000 rows of 4104 in bf16:
+// a workgroup each 116 us, two wavefronts each 96; of 8192, a whole round, 84 against 97).
+constexpr int kLseNarrow = 5, kGradNarrow = 4;
+static RowGrid row_grid(const spo_pg_desc *d, int group, int rounds, int narrow_eighths) {
     const int64_t n = d->dtype == SPO_FP32 ? 4 : 8;  // elements per vector
     RowGrid g;
     g.rows = d->T;
-    const bool narrow = d->V * 2 <= kRowThreads * group * n;
+    const bool narrow = d->V * 8 <= kRowThreads * group * n * narrow_eighths;
     g.per_wg = narrow ? kRowThreads / kWave : 1;
     g.seg_len = (narrow ? kWave : kRowThreads) * group * n * rounds;
     g.nseg = static_cast<int>(ceil_div(d->V, g.seg_len));
+    constexpr int64_t kLine = 64;  // elements: segments of a row start on cache lines when the row does
+    g.seg_len = ceil_div(ceil_div(d->V, g.nseg), kLine) * kLine;  // at most what it was: as many segments, none empty
     return g;
 }
 
 // the forward goes down to one round per segment where two would leave compute units without their
 // eight workgroups (256 x 151936 bf16: 17.4 against 18.0 us)
 static RowGrid lse_grid(const spo_pg_desc *d) {
-    const RowGrid g = row_grid(d, kLseGroup, kLseRounds);
-    return g.units() >= 2048 ? g : row_grid(d, kLseGroup, 1);
+    const RowGrid g = row_grid(d, kLseGroup, kLseRounds, kLseNarrow);
+    return g.units() >= 2048 ? g : row_grid(d, kLseGroup, 1, kLseNarrow);
 }
 
 static bool streams(const spo_pg_desc *d) {
@@ -288,13 +316,15 @@ static LogitsFwdPlan plan_logits_fwd(const spo_pg_desc *d, void *ws) {
 
 template <typename T, int TR, bool Stream>
 static void launch_row_lse(const spo_pg_desc *d, const LogitsFwdPlan &p, hipStream_t s) {
-    logits_row_lse_kernel<T, TR, Stream><<<p.grid.blocks(), kRowThreads, 0, s>>>(
+    auto *kernel = p.grid.seg_len <= TR * kLseGroup * Vec<T>::N ? logits_row_lse_kernel<T, TR, 1, Stream>
+                                                               : logits_row_lse_kernel<T, TR, kLseRounds, Stream>;
+    kernel<<<p.grid.blocks(), kRowThreads, 0, s>>>(
         static_cast<const T *>(d->logits), d->V, p.grid, d->target, p.row_max, p.row_sum, p.z_target,
         p.done);
 }
 template <typename T>
 static void launch_row_lse(const spo_pg_desc *d, const LogitsFwdPlan &p, hipStream_t s) {
-    if (p.grid.per_wg > 1) launch_row_lse<T, kWave, false>(d, p, s);
+    if (p.grid.per_wg > 1) streams(d) ? launch_row_lse<T, kWave, true>(d, p, s) : launch_row_lse<T, kWave, false>(d, p, s);
     else if (streams(d)) launch_row_lse<T, kRowThreads, true>(d, p, s);
     else launch_row_lse<T, kRowThreads, false>(d, p, s);
 }
@@ -307,7 +337,7 @@ static void launch_row_grad(const spo_pg_desc *d, const RowGrid &grid, const flo
 }
 template <typename T>
 static void launch_row_grad(const spo_pg_desc *d, const float *lse, const float *g, void *d_logits, hipStream_t s) {
-    const RowGrid grid = row_grid(d, kGradGroup, 1);
+    const RowGrid grid = row_grid(d, kGradGroup, 1, kGradNarrow);
     if (grid.per_wg > 1) launch_row_grad<T, kWave, false>(d, grid, lse, g, d_logits, s);
     else if (streams(d)) launch_row_grad<T, kRowThreads, true>(d, grid, lse, g, d_logits, s);
     else launch_row_grad<T, kRowThreads, false>(d, grid, lse, g, d_logits, s);

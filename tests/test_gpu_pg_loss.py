@@ -566,6 +566,16 @@ def test_logits_in_row_edges(spo, oracle, dtype, T, V, offset):
         assert (np.abs(f64(dl) - rb["d_logits"]) <= (2e-4 if dtype == "fp32" else 5e-3) * scale).all()
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("T,V,offset", [
+    (2100, 2560, 0), (2100, 2561, 1), (2100, 5120, 3), (2100, 5121, 0),   # longest rows of single wavefronts, and the next
+    (2100, 8192, 0), (2100, 8193, 1),             # a workgroup's row in one round, and in two
+    (1100, 16392, 1),                             # halves of a row
+    (59000, 2300, 0)])                            # wavefronts' rows that no cache holds
+def test_logits_in_segments(spo, oracle, dtype, T, V, offset):
+    test_logits_in_row_edges(spo, oracle, dtype, T, V, offset)
+
+
 @pytest.mark.parametrize("T,B,offset", [
     (63, 3, 0), (64, 3, 1), (65, 1, 15),            # one workgroup of tokens, whole and one more; masks off 16-byte boundaries
     (5000, 1023, 3), (5000, 1024, 0),               # response offsets kept in LDS, and too many for it
