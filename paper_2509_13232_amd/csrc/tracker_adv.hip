@@ -399,7 +399,8 @@ advantages_wide_kernel(const float *__restrict__ alpha, const float *__restrict_
 }
 
 // Diagnostics of the unnormalised advantages (one workgroup, fp64, fixed order).  Bound by the latency
-// of a thread's loads, so kDiagAhead responses are requested at a time.
+// of a thread's loads, so kDiagAhead responses are requested at a time, and in long batches by their instructions:
+// only a thread's last group asks which of its responses exist (10^6 responses: 275 us if every group does, 194).
 constexpr int kDiagAhead = 8;
 
 __global__ void __launch_bounds__(kAdvThreads)
@@ -407,7 +408,18 @@ advantage_diagnostics_kernel(const float *__restrict__ adv_raw, const float *__r
                              float tau_tight, float tau_loose, float *__restrict__ diag) {
     __shared__ double scratch[4 * kAdvThreads / kWave];
     auto each = [&](auto f) {  // f(advantage, reward) for this thread's responses, in order
-        for (int64_t k0 = threadIdx.x; k0 < B; k0 += kDiagAhead * kAdvThreads) {
+        int64_t k0 = threadIdx.x;
+        for (; k0 + (kDiagAhead - 1) * kAdvThreads < B; k0 += kDiagAhead * kAdvThreads) {
+            float a[kDiagAhead], r[kDiagAhead];
+#pragma unroll
+            for (int i = 0; i < kDiagAhead; ++i) {
+                a[i] = adv_raw[k0 + i * kAdvThreads];
+                r[i] = reward[k0 + i * kAdvThreads];
+            }
+#pragma unroll
+            for (int i = 0; i < kDiagAhead; ++i) f(a[i], r[i]);
+        }
+        if (k0 < B) {  // this thread's last ones
             float a[kDiagAhead], r[kDiagAhead];
 #pragma unroll
             for (int i = 0; i < kDiagAhead; ++i) {

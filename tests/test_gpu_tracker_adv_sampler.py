@@ -491,3 +491,16 @@ def test_advantages_from_the_estimate_itself(spo, oracle):
     np.testing.assert_allclose(raw.cpu().numpy(), eraw, rtol=RTOL, atol=1e-6)
     np.testing.assert_allclose(nrm.cpu().numpy(), enrm, rtol=RTOL, atol=1e-6)
     np.testing.assert_allclose(st.cpu().numpy(), est, rtol=RTOL)
+
+
+@pytest.mark.parametrize("B", [7168, 7169, 8191, 8192, 8193, 15361, 100003])   # a thread's whole groups of eight, and what is left
+def test_diagnostics_of_long_batches(spo, B):
+    say(f"advantage diagnostics B={B}")
+    rng = np.random.default_rng(B)
+    a = (rng.standard_normal(B) * 0.05 + 3.0 * (rng.random(B) < 0.1)).astype(np.float32)
+    r = rng.random(B).astype(np.float32)
+    diag = spo.spo_advantage_diagnostics(dev(a), dev(r), 1e-3, 0.02)
+    torch.cuda.synchronize()
+    a64, r64 = a.astype(np.float64), r.astype(np.float64)
+    want = [(np.abs(a) <= np.float32(1e-3)).mean(), (np.abs(a) <= np.float32(0.02)).mean(), a64.var(), r64.var()]
+    np.testing.assert_allclose(diag.cpu().numpy(), want, rtol=2e-7, atol=0)   # fp64 sums, one rounding to fp32
