@@ -285,10 +285,12 @@ __device__ __forceinline__ void raw_advantages(const float *__restrict__ alpha, 
 // avoids the cancellation of the sum-of-squares shortcut.
 //
 // Bound by the latency of id -> (alpha, beta): each of the three passes waited for both loads, one
-// response per thread after the other.  Up to PER responses per thread are now requested
-// together and stay in registers for all passes (a step of 4096 responses to 2^20 prompts: 57 -> 48 us);
+// response per thread after the other.  Up to PER responses per thread stay in registers for all passes, their
+// loads requested kAdvBatch at a time (a step of 4096 responses to 2^20 prompts: 57 -> 48 us; 8192 of them
+// 31 -> 15 us, 16383 120 -> 47; all sixteen at once do not fit the registers of 1024 threads: 21 and 51).
 // PER = 0 is the form without a limit.
 constexpr int kAdvThreads = 1024;
+constexpr int kAdvBatch = 8;
 
 template <int PER>
 __global__ void __launch_bounds__(kAdvThreads)
@@ -297,14 +299,24 @@ advantages_kernel(const float *__restrict__ alpha, const float *__restrict__ bet
                   double eps_norm, int use_baseline, float *__restrict__ adv_raw,
                   float *__restrict__ adv_norm, float *__restrict__ stats, int64_t N, int32_t *__restrict__ info) {
     __shared__ double scratch[kAdvThreads / kWave];
-    const int tid = threadIdx.x, NT = blockDim.x;
+    const int tid = threadIdx.x, NT = PER ? blockDim.x : kAdvThreads;
     auto raw = [&](int k) { return raw_advantage(alpha, beta, idx, reward, use_baseline, N, info, k); };
     if (info) {
         if (tid == 0) info[0] = 0;
         __syncthreads();
     }
     double kept[PER ? PER : 1];
-    if constexpr (PER > 0) raw_advantages<PER>(alpha, beta, idx, reward, use_baseline, N, info, tid, NT, B, kept);
+    if constexpr (PER > kAdvBatch) {
+#pragma unroll
+        for (int h = 0; h < PER; h += kAdvBatch) {
+            double part[kAdvBatch] = {};
+            if (h * NT < B) raw_advantages<kAdvBatch>(alpha, beta, idx, reward, use_baseline, N, info, tid + h * NT, NT, B, part);
+#pragma unroll
+            for (int i = 0; i < kAdvBatch; ++i) kept[h + i] = part[i];
+        }
+    } else if constexpr (PER > 0) {
+        raw_advantages<PER>(alpha, beta, idx, reward, use_baseline, N, info, tid, NT, B, kept);
+    }
     auto each = [&](auto f) {  // f(k, raw advantage) for this thread's responses, in order
         if constexpr (PER > 0) {
 #pragma unroll

@@ -504,3 +504,9 @@ def test_diagnostics_of_long_batches(spo, B):
     a64, r64 = a.astype(np.float64), r.astype(np.float64)
     want = [(np.abs(a) <= np.float32(1e-3)).mean(), (np.abs(a) <= np.float32(0.02)).mean(), a64.var(), r64.var()]
     np.testing.assert_allclose(diag.cpu().numpy(), want, rtol=2e-7, atol=0)   # fp64 sums, one rounding to fp32
+
+
+@pytest.mark.parametrize("B", [8191, 8192, 8193, 15360, 15361])   # eight responses per thread, and up to sixteen
+@pytest.mark.parametrize("beta", [True, False])
+def test_advantages_in_two_batches_of_loads(spo, oracle, B, beta):
+    test_advantages_kept_in_registers(spo, oracle, B, beta)
