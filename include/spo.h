@@ -80,11 +80,11 @@ const char *spo_status_string(int status);
  *               and every v_i is 0 or 1) nothing can be drawn: all entries are
  *               -1 and info[0] = 1.
  * max_attempts  bound on attempts per slot (0 selects 65536).  Without replacement the
- *               slots draw side by side, a thread each, a few us per attempt (less for
- *               N <= 4096): a batch that takes most of the prompts with non-zero weight
- *               needs many attempts for its last slots (about N ln N draws to collect
- *               the last of N equal weights), so such a call can take max_attempts of
- *               them in a row before it gives up; info[0] and info[1] tell.
+ *               slots draw side by side, 4 to 8 us per attempt (up to 190 where 16384 of
+ *               them want the same prompt): a batch that takes most of the prompts with
+ *               non-zero weight needs many attempts for its last slots (about N ln N
+ *               draws to collect the last of N equal weights), so such a call can take
+ *               max_attempts of them in a row before it gives up; info[0] and info[1] tell.
  * ws            spo_sample_prompts_workspace_bytes(N, B) bytes, 256-byte aligned.
  * Limits: 1 <= N < 2^31, 1 <= B <= 16384 (replace = 0) or B < 2^31 (replace = 1).
  * ------------------------------------------------------------------------- */

@@ -230,7 +230,8 @@ def philox4x32_10(ctr, key):
 
 
 def sample_prompts(alpha, beta, B, eps=0.05, seed=0, iteration=0, replace=False,
-                   max_attempts=1 << 20, return_attempts=False):
+                   max_attempts=1 << 20, return_attempts=False, allow_exhausted=False):
+    """Indices of the draw.  A slot that runs out of attempts is an error, or -1 with allow_exhausted."""
     a = _arr(alpha, np.float32)
     b = _arr(beta, np.float32)
     N = a.shape[0]
@@ -241,7 +242,7 @@ def sample_prompts(alpha, beta, B, eps=0.05, seed=0, iteration=0, replace=False,
     rc = _load().spo_oracle_sample(_p(a, _f), _p(b, _f), N, B, float(eps), int(seed),
                                    int(iteration), int(bool(replace)), int(max_attempts),
                                    _p(idx, _i32), _p(att, _u32))
-    if rc != 0:
+    if rc != 0 and not allow_exhausted:
         raise RuntimeError("sampler exceeded max_attempts")
     return (idx, att) if return_attempts else idx
 

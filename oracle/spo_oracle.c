@@ -241,8 +241,11 @@ static int64_t first_above(const uint64_t *cdf, int64_t N, uint64_t t)
 /* Draw B prompt indices with probability proportional to the weights.
  * replace = 0: successive weighted draws, a draw that returns an index already
  * taken by an earlier slot is repeated with the next attempt number.
- * Returns 0, or -1 if a slot needed more than max_attempts attempts.
- * attempts[k] (optional) receives the attempt number slot k settled on. */
+ * A slot that finds no free index in max_attempts attempts gets -1 and holds
+ * nothing; the slots after it go on.
+ * Returns 0, or -1 if a slot ran out of attempts (or nothing can be drawn).
+ * attempts[k] (optional) receives the attempt number slot k settled on
+ * (max_attempts if it ran out). */
 int spo_oracle_sample(const float *alpha, const float *beta, int64_t N, int32_t B,
                       double eps, uint64_t seed, uint64_t iteration, int replace,
                       uint32_t max_attempts, int32_t *idx_out, uint32_t *attempts)
@@ -260,7 +263,7 @@ int spo_oracle_sample(const float *alpha, const float *beta, int64_t N, int32_t 
         for (int32_t k = 0; k < B; ++k) idx_out[k] = -1;
         rc = -1;
     }
-    for (int32_t k = 0; k < B && rc == 0; ++k) {
+    for (int32_t k = 0; k < B && total != 0; ++k) {
         uint32_t a = 0;
         for (;;) {
             uint64_t r = draw_bits(seed, iteration, (uint32_t)k, a);
@@ -272,7 +275,12 @@ int spo_oracle_sample(const float *alpha, const float *beta, int64_t N, int32_t 
                 if (attempts) attempts[k] = a;
                 break;
             }
-            if (++a >= max_attempts) { rc = -1; break; }
+            if (++a >= max_attempts) {
+                idx_out[k] = -1;
+                if (attempts) attempts[k] = a;
+                rc = -1;
+                break;
+            }
         }
     }
     free(cdf);

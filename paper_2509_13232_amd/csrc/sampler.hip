@@ -13,6 +13,7 @@
 #include <mutex>
 
 #include "common.hpp"
+#include "sampler_claims.hpp"
 
 namespace spo {
 
@@ -120,8 +121,6 @@ scan_block_sums_kernel(uint64_t *__restrict__ block_sums, int64_t nblocks) {
     }
 }
 
-constexpr int32_t kNoOwner = 0x7fffffff;  // no slot has claimed the prompt
-
 // Phase 3: inclusive CDF of the codes, its last value as *total, and (owner != NULL) the claims
 // cleared, with info.  summed: block_sums holds what scan_block_sums_kernel made of it; otherwise
 // (at most kInlineBlocks blocks) every block adds up the sums before its own.
@@ -210,42 +209,8 @@ draw_with_replacement_kernel(const uint64_t *__restrict__ cdf, int64_t N, const 
 // end, whatever the order of the claims: the result is the sequential one on every run, no slot waits
 // for another, and no barrier is needed.  (One workgroup in sweeps over all slots: 121 us for 4096 of
 // 2^20 prompts, this: 12 us, and 4 us for the indices.)  Attempts only grow and stop at max_attempts.
-//
-// A claim is slot << kAttemptBits | attempt, so the one word that decides who holds a candidate also
-// says where a displaced slot goes on.  Attempts beyond its bits are filed as the largest; such a slot
-// finds its attempt again by repeating its draws from there (it stands on the first of them that gives
-// this candidate: it was never turned away here before, or a lower slot would hold it).
-constexpr int kAttemptBits = 17;
-constexpr uint32_t kAttemptMost = (1u << kAttemptBits) - 2;  // every claim is below kNoOwner
-static_assert((static_cast<uint32_t>(kMaxSlotsNoReplace - 1) << kAttemptBits | kAttemptMost) < static_cast<uint32_t>(kNoOwner),
-              "claims fit 31 bits");
-
-// Settles slot k and the slots displaced on the way; returns the highest attempt reached.
-//   draw(k, n)    candidate of attempt n of slot k
-//   claim(c, v)   atomic minimum of owner[c] and v, returning what was there
-//   fail(k)       slot k has run out of attempts
-template <typename Draw, typename Claim, typename Fail>
-__device__ __forceinline__ uint32_t settle_slot(uint32_t k, uint32_t max_attempts, Draw draw, Claim claim, Fail fail) {
-    uint32_t attempt = 0, most = 0;
-    for (;;) {
-        most = attempt > most ? attempt : most;
-        if (attempt >= max_attempts) {
-            fail(k);
-            return most;
-        }
-        const int32_t c = draw(k, attempt);
-        const int32_t filed = static_cast<int32_t>(k << kAttemptBits | (attempt < kAttemptMost ? attempt : kAttemptMost));
-        const int32_t was = claim(c, filed);
-        if (was == kNoOwner) return most;
-        if (was > filed) {  // displaced (a slot never meets a claim of its own)
-            k = static_cast<uint32_t>(was) >> kAttemptBits;
-            attempt = static_cast<uint32_t>(was) & ((1u << kAttemptBits) - 1);
-            if (attempt == kAttemptMost)
-                while (draw(k, attempt) != c) ++attempt;
-        }
-        ++attempt;
-    }
-}
+typedef Claims<17> SlotClaims;
+static_assert(SlotClaims::kMaxSlots >= kMaxSlotsNoReplace, "claims fit 31 bits");
 
 // The claims over many workgroups; the one place they meet is the atomics on owner[].
 __global__ void __launch_bounds__(kWave)
@@ -260,7 +225,7 @@ draw_claim_kernel(const uint64_t *__restrict__ cdf, int64_t N, const uint64_t *_
         if (info && k == 0) info[0] = 1;
         return;
     }
-    const uint32_t most = settle_slot(
+    const uint32_t most = SlotClaims::settle(
         k, max_attempts, [&](uint32_t s, uint32_t n) { return draw_index(cdf, N, total, seed, iteration, s, n); },
         [&](int32_t c, int32_t v) { return atomicMin(&owner[c], v); },
         [&](uint32_t s) {
@@ -283,7 +248,7 @@ place_slots_kernel(const int32_t *__restrict__ owner, int64_t N, int32_t *__rest
 #pragma unroll
     for (int j = 0; j < PER; ++j)
         if (o[j] != kNoOwner)
-            idx_out[o[j] >> kAttemptBits] = static_cast<int32_t>(static_cast<int64_t>(blockIdx.x) * (256 * PER) + j * 256 + threadIdx.x);
+            idx_out[SlotClaims::slot(o[j])] = static_cast<int32_t>(static_cast<int64_t>(blockIdx.x) * (256 * PER) + j * 256 + threadIdx.x);
 }
 
 // Everything in one workgroup, for tables of at most kScanItems prompts: the CDF and the
@@ -331,7 +296,7 @@ sample_small_kernel(const float *__restrict__ alpha, const float *__restrict__ b
     }
     uint32_t most = 0;
     for (int k = tid; k < B; k += NT) {
-        const uint32_t m = settle_slot(k, max_attempts, draw, [&](int32_t c, int32_t v) { return atomicMin(&owner[c], v); },
+        const uint32_t m = SlotClaims::settle(k, max_attempts, draw, [&](int32_t c, int32_t v) { return atomicMin(&owner[c], v); },
                                        [&](uint32_t s) {
                                            idx_out[s] = -1;
                                            failed = 1;
@@ -341,7 +306,7 @@ sample_small_kernel(const float *__restrict__ alpha, const float *__restrict__ b
     if (most) atomicMax(&most_sh, static_cast<int>(most));
     __syncthreads();
     for (int c = tid; c < N; c += NT)
-        if (owner[c] != kNoOwner) idx_out[owner[c] >> kAttemptBits] = c;
+        if (owner[c] != kNoOwner) idx_out[SlotClaims::slot(owner[c])] = c;
     if (info && tid == 0) {
         info[0] = failed;
         info[1] = most_sh;
@@ -380,7 +345,9 @@ static int sample_launch(const float *alpha, const float *beta, int64_t N, int32
                          uint64_t seed, uint64_t iteration, int replace, uint32_t max_attempts,
                          int32_t *idx_out, int32_t *info, void *ws, hipStream_t s) {
     const SamplerWorkspace w = sampler_layout(ws, N);
-    if (max_attempts == 0) max_attempts = 1u << 16;  // bounds a hopeless draw to a fraction of a second
+    // The bound on a hopeless draw: 0.3 s for 4096 slots on 100 prompts of a large table (4 to 8 us per attempt), up to
+    // 12 s where 16384 slots want the same prompt (190 us: their claims meet at one address).
+    if (max_attempts == 0) max_attempts = 1u << 16;
     if (N <= kScanItems && B <= kScanItems) {
         unsigned threads = kWave;
         while (threads < kScanThreads && static_cast<int64_t>(threads) * kScanRows < std::max<int64_t>(N, B)) threads *= 2;

@@ -352,19 +352,26 @@ def test_sampler_table_sizes(spo, oracle, N, B, replace):
         assert np.array_equal(gidx.cpu().numpy(), eidx) and info.cpu().tolist() == [0, int(eatt.max())]
 
 
-def test_sampler_exhausted_attempts_over_many_workgroups(spo, oracle):
-    # 5000 prompts, all weight on a few: a slot that finds none of them free within 3 attempts gets -1, the
-    # others keep what the sequential draw gives them (slots that fail hold nothing)
-    say("sample_prompts exhausted attempts N=5000 B=200")
-    rng = np.random.default_rng(8)
-    a, b = np.zeros(5000, np.float32), np.ones(5000, np.float32)
-    a[rng.choice(5000, 150, replace=False)] = 1.0
-    gidx, info = spo.spo_sample_prompts(dev(a), dev(b), 200, 0.0, 4, 2, False, max_attempts=3, return_info=True)
-    first = spo.spo_sample_prompts(dev(a), dev(b), 1, 0.0, 4, 2, True)
-    torch.cuda.synchronize()
-    out = gidx.cpu().numpy()
-    assert out[0] == first.item() and (a[out[out >= 0]] > 0).all() and len(set(out[out >= 0].tolist())) == (out >= 0).sum()
-    assert info.cpu().tolist() == [1, 3] and (out == -1).sum() >= 50
+@pytest.mark.parametrize("N,B,nonzero,max_attempts", [
+    (5000, 200, 150, 3), (5000, 4000, 3000, 5),          # claims over many workgroups
+    (5000, 5000, 4999, 400),                             # long chains, then a few that run out
+    (4096, 200, 150, 3), (4096, 4096, 3000, 4),          # a table in LDS
+    (300, 300, 299, 20), (64, 64, 1, 7)])
+def test_sampler_exhausted_attempts_over_many_workgroups(spo, oracle, N, B, nonzero, max_attempts):
+    # all weight on some of the prompts: a slot that finds none of them free within its attempts gets -1 and
+    # holds nothing; the others keep what the sequential draw gives them
+    say(f"sample_prompts exhausted attempts N={N} B={B} nonzero={nonzero} max_attempts={max_attempts}")
+    rng = np.random.default_rng([N, B, nonzero])
+    a, b = np.zeros(N, np.float32), np.ones(N, np.float32)
+    a[rng.choice(N, nonzero, replace=False)] = rng.uniform(0.1, 3.0, nonzero)
+    eidx, eatt = oracle.sample_prompts(a, b, B, 0.0, 4, 2, False, max_attempts=max_attempts, return_attempts=True,
+                                       allow_exhausted=True)
+    assert (eidx == -1).any() and (eidx >= 0).sum() > nonzero // 3
+    for _ in range(2):
+        gidx, info = spo.spo_sample_prompts(dev(a), dev(b), B, 0.0, 4, 2, False, max_attempts=max_attempts, return_info=True)
+        torch.cuda.synchronize()
+        assert np.array_equal(gidx.cpu().numpy(), eidx)
+        assert info.cpu().tolist() == [1, int(eatt.max())] and eatt.max() == max_attempts
 
 
 def test_sampler_reports_exhausted_attempts(spo, oracle):

@@ -1,5 +1,5 @@
-"""Host-side sanitizer runs (no GPU): the fp64 oracle and the argument-check layer of the C ABI,
-each built with AddressSanitizer and UndefinedBehaviorSanitizer and driven by a small program
+"""Host-side sanitizer runs (no GPU): the fp64 oracle, the argument-check layer of the C ABI and the claims
+of the sampler, each built with AddressSanitizer and UndefinedBehaviorSanitizer and driven by a small program
 under tests/san/.  The sanitizer runtimes are linked into those programs, nothing is preloaded."""
 import os
 import re
@@ -50,3 +50,14 @@ def test_abi_argument_checks_run_clean_under_asan_and_ubsan(tmp_path):
     r = subprocess.run([exe], capture_output=True, text=True, env=dict(ENV, ASAN_OPTIONS="detect_leaks=0"), timeout=300)
     assert r.returncode == 0, (r.stdout + r.stderr)[-3000:]
     assert "ABI host-side sanitizer run ok" in r.stdout
+
+
+def test_claims_of_a_draw_without_replacement_follow_the_sequential_rule(tmp_path):
+    # whatever the order of the claims, and also where a displaced slot has to find its attempt again
+    exe = str(tmp_path / "claims")
+    csrc = os.path.join(ROOT, "paper_2509_13232_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all", "-pthread",
+                    "-Wall", "-Wextra", "-I" + csrc, os.path.join(SAN, "claims_driver.cpp"), "-o", exe], check=True)
+    r = subprocess.run([exe], capture_output=True, text=True, env=ENV, timeout=300)
+    assert r.returncode == 0, (r.stdout + r.stderr)[-3000:]
+    assert "claims follow the sequential rule" in r.stdout
