@@ -258,11 +258,13 @@ logits_row_grad_kernel(const T *__restrict__ logits, int64_t V, RowGrid grid, co
     }
 }
 
-// How the rows are cut: into as few equal segments as keep within `rounds` rounds of `group` vectors per thread
-// (8000 rows of 16392 in bf16 in segments of 16384 and 8: 68 us, in halves 50).  Rows that give a workgroup little work go
+// How the rows are cut: into segments of `rounds` rounds of `group` vectors per thread, of which a short rest is one
+// more.  Where that would be one of few, all are made equal (8000 rows of 16392 in bf16 in segments of 16384 and 8:
+// 68 us, in halves 50); where it is one of many, whole rounds are the better cut (8192 rows of 151936, loss and
+// gradient in turn: 1200 us, in equal segments 1216).  Rows that give a workgroup little work go
 // to single wavefronts, four to a workgroup: up to narrow_eighths eighths of a round (60000 rows of 4104 in bf16:
 // a workgroup each 116 us, two wavefronts each 96; of 8192, a whole round, 84 against 97).
-constexpr int kLseNarrow = 5, kGradNarrow = 4;
+constexpr int kLseNarrow = 5, kGradNarrow = 4, kFewSegments = 8;
 static RowGrid row_grid(const spo_pg_desc *d, int group, int rounds, int narrow_eighths) {
     const int64_t n = d->dtype == SPO_FP32 ? 4 : 8;  // elements per vector
     RowGrid g;
@@ -271,8 +273,9 @@ static RowGrid row_grid(const spo_pg_desc *d, int group, int rounds, int narrow_
     g.per_wg = narrow ? kRowThreads / kWave : 1;
     g.seg_len = (narrow ? kWave : kRowThreads) * group * n * rounds;
     g.nseg = static_cast<int>(ceil_div(d->V, g.seg_len));
-    constexpr int64_t kLine = 64;  // elements: segments of a row start on cache lines when the row does
-    g.seg_len = ceil_div(ceil_div(d->V, g.nseg), kLine) * kLine;  // at most what it was: as many segments, none empty
+    // of few segments, equal ones: at most as long as they were, so as many of them, none empty
+    constexpr int64_t kLine = 64;  // elements: they start on cache lines when the row does
+    if (g.nseg <= kFewSegments) g.seg_len = ceil_div(ceil_div(d->V, g.nseg), kLine) * kLine;
     return g;
 }
 
