@@ -118,7 +118,8 @@ def _check(status: int, where: str):
 
 # The smallest calls (a step of 16 prompts, a few rows of logits) are bound by this file: 35 us for the three
 # calls of a prompt step, 12 us of kernels; 27 us since.  Pointers and the stream therefore go to ctypes as plain
-# integers, which the argument types turn into pointers, and no output is a slice of a larger tensor.
+# integers, which the argument types turn into pointers, and no output is a slice of a larger tensor.  The raw
+# stream comes from the accessor behind torch.cuda.current_stream, without the Stream object that this builds.
 def _ptr(t):
     return None if t is None else t.data_ptr()
 

@@ -27,7 +27,7 @@ __device__ __forceinline__ Surrogate surrogate(float logp, float old_logp, float
     return r;
 }
 
-// Per-block partial sums of the forward, added in block order by the last block to finish.
+// Per-block partial sums of the forward, added in block order by the last workgroup to finish.
 struct FwdPartial {
     double sum_obj, count, clipped, sum_ratio;
 };
@@ -88,10 +88,10 @@ constexpr int kTokThreads = kWave;  // tokens per block
 constexpr int kTokWaves = 16;       // most wavefronts per workgroup
 
 // How a launch over n_blocks blocks is cut: four splits for each of `ways` wavefronts while the blocks alone do not
-// fill the chip (kTokChipWaves), and several blocks per workgroup, more where there would be more than kTokChipGroups
-// workgroups: their counts meet at one address, 11 ns apart.  (200000 tokens of two splits: 19 us, 27 with four blocks
-// per workgroup and 71 with one, of 16 wavefronts.)
-constexpr int kTokChipWaves = 2048, kTokChipGroups = 512;
+// fill the chip (kTokChipWaves), and from kTokFewBlocks on several blocks per workgroup, more where there would be
+// more than kTokChipGroups workgroups: their counts meet at one address, 11 ns apart.  (200000 tokens of two splits:
+// 19 us, 27 with four blocks per workgroup and 71 with one, of 16 wavefronts.)
+constexpr int kTokChipWaves = 2048, kTokChipGroups = 512, kTokFewBlocks = 64;
 struct TokenShape {
     unsigned blocks, threads;
     int ways;
@@ -100,7 +100,7 @@ static inline TokenShape token_shape(int nsplit, int64_t n_blocks) {
     int ways = 1;
     while (ways < kTokWaves && ways * 4 < nsplit && ways * n_blocks < kTokChipWaves) ways *= 2;
     int waves = ways;
-    while (waves < 4 ? waves / ways < n_blocks : waves < kTokWaves && n_blocks * ways / waves > kTokChipGroups) waves *= 2;
+    while (waves < 4 ? n_blocks >= kTokFewBlocks : waves < kTokWaves && n_blocks * ways / waves > kTokChipGroups) waves *= 2;
     return TokenShape{static_cast<unsigned>(ceil_div(n_blocks, waves / ways)), static_cast<unsigned>(waves * kWave), ways};
 }
 

@@ -433,7 +433,7 @@ __global__ void __launch_bounds__(256) prep_kernel(PrepJobs j) {
     __shared__ __attribute__((aligned(16))) T_ tile[kPrepTile * kPrepPitch<T_>];
     __shared__ int scratch[256 / kWave];
     int64_t b = flat_block();
-    if (b == 0 && threadIdx.x == 0 && j.done) *j.done = 0u;  // counts the workgroups of the token kernel
+    if (b == 0 && threadIdx.x == 0 && j.done) *j.done = 0u;  // counts the token kernel's finished blocks
     if (b < j.head_blocks) return prep_head_tile<T_, HV>(j, b, tile);
     b -= j.head_blocks;
     if (b < j.row_blocks) {

@@ -86,8 +86,8 @@ def kernel_trace(args, b):
         o.append(f"    {_short(r['Name'])[:58]:58s} {int(r['Calls']):6d} {int(r['TotalDurationNs']) / 1e6:11.3f} "
                  f"{float(r['AverageNs']) / 1e6:10.4f} {float(r['Percentage']):7.3f}")
     o.append("\ngemm_store_kernel<false> is the dHidden contraction, gemm_store_kernel<true> the dW contraction;")
-    o.append("fwd_sweep_kernel<true> is the sweep that also stores a piece's logits, dz_from_logits_kernel the pass that turns")
-    o.append("them into logit gradients. The batch is walked in pieces (one call) or the backward in chunks of tokens that")
+    o.append("fwd_sweep_kernel<0> forms log-sum-exps only, <1> also stores a piece's logits (batches with a loss mask), which")
+    o.append("dz_from_logits_kernel turns into logit gradients, <2> its scaled probabilities (without). The batch is walked in pieces (one call) or the backward in chunks of tokens that")
     o.append("carry a gradient (two calls); per-launch averages are over all launches of a step, the last of which is")
     o.append("shorter. Kernels outside the spo namespace are torch's input generation.\n")
     return "\n".join(o)

@@ -610,9 +610,10 @@ def test_token_kernels_edges(spo, oracle, T, B, offset):
 
 
 @pytest.mark.parametrize("T,V", [
-    *[(T, V) for T in (1, 64, 65, 129, 200, 320)   # 1 to 5 blocks of 64 tokens: whole workgroups and ragged ones
+    *[(T, V) for T in (1, 64, 65, 129, 200, 320)   # 1 to 5 blocks of 64 tokens, a workgroup each
       for V in (8, 20000, 60000)],                 # rows in 1, 5 and 15 segments: 1, 2 and 4 wavefronts per block
-    (131073, 8), (140000, 8), (262145, 8)])        # 4, 8 and 16 blocks per workgroup, the last workgroup ragged
+    (4033, 8), (4225, 20000), (4097, 60000),       # from 64 blocks on 4, 2 and 1 per workgroup, the last one ragged
+    (131073, 8), (140000, 8), (262145, 8)])        # 4, 8 and 16 blocks per workgroup
 def test_token_blocks_per_workgroup(spo, oracle, T, V):
     say(f"token blocks T={T} V={V}")
     rng = np.random.default_rng([T, V, 6])
