@@ -87,9 +87,10 @@ def kernel_trace(args, b):
                  f"{float(r['AverageNs']) / 1e6:10.4f} {float(r['Percentage']):7.3f}")
     o.append("\ngemm_store_kernel<false> is the dHidden contraction, gemm_store_kernel<true> the dW contraction;")
     o.append("fwd_sweep_kernel<0> forms log-sum-exps only, <1> also stores a piece's logits (batches with a loss mask), which")
-    o.append("dz_from_logits_kernel turns into logit gradients, <2> its scaled probabilities (without). The batch is walked in pieces (one call) or the backward in chunks of tokens that")
-    o.append("carry a gradient (two calls); per-launch averages are over all launches of a step, the last of which is")
-    o.append("shorter. Kernels outside the spo namespace are torch's input generation.\n")
+    o.append("dz_from_logits_kernel turns into logit gradients, <2> its scaled probabilities (without). The batch is walked in")
+    o.append("pieces (one call) or the backward in chunks of tokens that carry a gradient (two calls); per-launch averages are")
+    o.append("over all launches of a step, the last of which is shorter. Kernels outside the spo namespace are torch's input")
+    o.append("generation.\n")
     return "\n".join(o)
 
 
