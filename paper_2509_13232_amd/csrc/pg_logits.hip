@@ -23,6 +23,10 @@ namespace spo {
 // request, and a wavefront's pairs are merged with one exponential (60000 rows of 4104 in bf16: 138 -> 81 us;
 // a workgroup per row without segments took 96).
 constexpr int kRowThreads = 256;
+// Largest magnitude of a maximum at which the exponents are formed in one multiply-add.  What is lost with the
+// maximum's product is half of its last place: a factor common to all, as small as the log-sum-exp's own rounding up to
+// here, but past the range of exponents in rows that are masked with -1e30 throughout.
+constexpr float kFarLogit = 65536.0f;
 constexpr int kLseGroup = 4, kLseRounds = 2, kGradGroup = 2;
 constexpr int64_t kStreamBytes = int64_t(256) << 20;  // the Infinity Cache
 
@@ -161,12 +165,16 @@ logits_row_lse_kernel(const T *__restrict__ logits, int64_t V, RowGrid grid, con
         }
         const float nm2 = -mx * kLog2e;
         float a[U] = {};
+        auto add = [&](auto exponent) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (i0 + u * TR >= sp.nvec) break;
+            for (int u = 0; u < U; ++u) {
+                if (i0 + u * TR >= sp.nvec) break;
 #pragma unroll
-            for (int i = 0; i < N; ++i) a[u] += __builtin_amdgcn_exp2f(fmaf(x[u][i], kLog2e, nm2));
-        }
+                for (int i = 0; i < N; ++i) a[u] += __builtin_amdgcn_exp2f(exponent(x[u][i]));
+            }
+        };
+        if (__any(i0 < sp.nvec && fabsf(mx) > kFarLogit)) add([&](float v) { return (v - mx) * kLog2e; });
+        else add([&](float v) { return fmaf(v, kLog2e, nm2); });
         s = s * __builtin_amdgcn_exp2f((m - mx) * kLog2e) + ((a[0] + a[1]) + (a[2] + a[3]));
         m = mx;
     };

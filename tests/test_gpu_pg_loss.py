@@ -576,6 +576,37 @@ def test_logits_in_segments(spo, oracle, dtype, T, V, offset):
     test_logits_in_row_edges(spo, oracle, dtype, T, V, offset)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("T,V", [(9, 7), (9, 1000), (9, 1001), (9, 6001), (2100, 8193), (9, 33001)])
+def test_logits_far_from_zero(spo, dtype, T, V):
+    # rows masked throughout with a large finite value, alone or but for one entry, and rows far off zero: the
+    # log-sum-exp is that of the differences, to the rounding of the row's largest logit
+    say(f"logits far from zero {dtype} T={T} V={V}")
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    rng = np.random.default_rng([T, V])
+    z = rng.standard_normal((T, V)) * 3
+    z[0], z[1], z[2], z[3] = -9.9e29, -9.9e29, -1e9, -1e9   # (what lies below -1e30 counts as -inf)
+    z[1, V // 2] = 2.0
+    z[3, V - 1] = 1e9
+    z[4] += 3e4
+    z[5] -= 1e5
+    z[6, ::2] = -9.9e29
+    logits = torch.as_tensor(z, dtype=torch.float32).to(tdt)
+    z64 = f64(logits)
+    top = z64.max(axis=1)
+    want = top + np.log(np.exp(z64 - top[:, None]).sum(axis=1))
+    t = lambda x: torch.as_tensor(x).cuda()
+    tg = z64.argmax(axis=1).astype(np.int32)
+    desc = spo.make_desc(None, None, t(tg), torch.zeros(T, device="cuda"), None, t(np.ones(1, np.float32)),
+                         t(np.array([0, T], np.int32)), 0.2, 0.28, logits=logits.cuda())
+    _, lp, lse, _ = spo.spo_pg_loss_fwd(desc)
+    torch.cuda.synchronize()
+    # one rounding of max + log(sum) to fp32, and a few 1e-7 of the sum
+    np.testing.assert_allclose(f64(lse), want, rtol=2.0 ** -23, atol=1e-5)
+    err = np.abs(f64(lp) - (z64[np.arange(T), tg] - want))
+    assert (err <= 2.0 ** -23 * np.abs(want) + 1e-5).all()
+
+
 @pytest.mark.parametrize("T,B,offset", [
     (63, 3, 0), (64, 3, 1), (65, 1, 15),            # one workgroup of tokens, whole and one more; masks off 16-byte boundaries
     (5000, 1023, 3), (5000, 1024, 0),               # response offsets kept in LDS, and too many for it
