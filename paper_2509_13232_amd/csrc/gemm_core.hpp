@@ -475,7 +475,7 @@ struct TileOrder {
         return total / (kRun * kXcds) * (kRun * kXcds) + (total % (kRun * kXcds) + kXcds - 1) / kXcds * kXcds;
     }
     // item of workgroup bid: runs of 32 to each XCD in turn, the rest in eight equal runs; false past the last
-    __device__ static bool item(uint32_t bid, uint32_t total, uint32_t &i) {
+    __device__ static __forceinline__ bool item(uint32_t bid, uint32_t total, uint32_t &i) {
         constexpr uint32_t round = kRun * kXcds;
         const uint32_t whole = total / round * round;
         uint32_t j = bid, run = kRun, base = bid / round * round;
@@ -489,7 +489,7 @@ struct TileOrder {
         return i < total;
     }
     // the i-th tile: bands of four tile rows, patch after patch along N
-    __device__ void at(uint32_t i, int64_t &tm, int64_t &tn) const {
+    __device__ __forceinline__ void at(uint32_t i, int64_t &tm, int64_t &tn) const {
         const uint32_t m = static_cast<uint32_t>(nM), n = static_cast<uint32_t>(nN);
         const uint32_t band = i / (kPatchM * n), j = i - band * kPatchM * n;
         const uint32_t h = m - kPatchM * band < kPatchM ? m - kPatchM * band : kPatchM;

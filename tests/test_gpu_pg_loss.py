@@ -245,6 +245,20 @@ def test_last_round_of_dHidden_tiles_cut_along_the_vocabulary(spo, oracle, mask_
     assert not got[scale == 0].any()
 
 
+@pytest.mark.parametrize("T,H,V", [
+    (600, 1344, 11200),    # 44 x 6 tiles of d_W in bands of 24: the 8 cut tiles are the end of the last, half a band
+    (11300, 1344, 520)])   # 45 x 6 of d_hidden: 14 cut tiles, two thirds of a patch of 4 x 6 and a row of 6
+def test_cut_tiles_where_bands_divide_no_round(spo, oracle, T, H, V, one_call):
+    say(f"fused bf16 T={T} H={H} V={V} one_call={one_call}: cut tiles in the order of the launch")
+    case = Case(wl.scaled(MID, name="bands", H=H, V=V), [T // 3, T - T // 3])
+    case.set_old_from_oracle(oracle)
+    fwd, dx, dw = run_fwd_bwd(spo, case, one_call=one_call)
+    rb = oracle.pg_loss_bwd(*case.oracle_inputs(), *case.eps)
+    for got, ref in ((f64(dx), rb["d_hidden"]), (f64(dw), rb["d_W"])):
+        assert rel_l2(got, ref) < GRAD_TOL
+        np.testing.assert_allclose(got, ref, atol=2e-2 * np.abs(ref).max(), rtol=0)
+
+
 DEEP = wl.scaled(wl.CONFIGS["C2"], name="deep", H=320, V=1100)
 DEEP_LENGTHS = [9000, 7000, 12001, 5000, 6999]  # T = 40000: 157 token tiles, three chunks of 16384
 
