@@ -22,6 +22,8 @@
 // holds column n = l % 16 and, in register r, row m = 4*(l/16) + r.
 // Callers put the index they reduce over or scale by per row of the tile
 // (vocabulary entries) on m and the index with per-lane constants (tokens) on n.
+// With Across the instruction gets its operands exchanged: lane l holds row m = l % 16
+// and, in register r, column n = 4*(l/16) + r, four consecutive values of an output row.
 #pragma once
 
 #include <type_traits>
@@ -191,6 +193,11 @@ struct Tile {
         __builtin_amdgcn_sched_barrier(0);
     }
 
+    template <bool Across>
+    __device__ static __forceinline__ AccBlock mfma(const bf16x8_t &a, const bf16x8_t &b, const AccBlock &c) {
+        return Across ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, a, c, 0, 0, 0) : __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+    }
+
     // acc += A[m0.., :K] * B[n0.., :K]^T for ONE tile, K = kBK * KT.  lds: LDS_BYTES bytes,
     // 16-byte aligned.  All threads of the block must call this together.
     //
@@ -201,6 +208,7 @@ struct Tile {
     // k-slices: before it a wavefront has all its reads of stage s in registers and its share of
     // stage s+1 landed; after it stage s+1 may be read and the buffer of stage s is refilled with
     // stage s+2 (one DMA instruction per four MFMAs).
+    template <bool Across = false>
     __device__ static __forceinline__ void mainloop(const Operands &t, int KT, char *lds, Acc &acc) {
         static_assert(KK == 2 && kStages == 2, "two k-slices per stage, two stages");
         static_assert((FM + FN) * 2 <= FM * FN && STAGE_LOADS * 4 <= FM * FN, "reads and DMA fit between the MFMAs of a slice");
@@ -243,7 +251,7 @@ struct Tile {
                     read_frag(kt, 1, 1, j / 2);
                     __builtin_amdgcn_sched_barrier(0);
                 }
-                acc[fm][fn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[0][fm], bf[0][fn], acc[fm][fn], 0, 0, 0);
+                acc[fm][fn] = mfma<Across>(af[0][fm], bf[0][fn], acc[fm][fn]);
                 __builtin_amdgcn_sched_barrier(0);
             }
             asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
@@ -260,7 +268,7 @@ struct Tile {
                     if (FEED) d.one(kt + 2, kt % kStages, j / 4);
                     __builtin_amdgcn_sched_barrier(0);
                 }
-                acc[fm][fn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[1][fm], bf[1][fn], acc[fm][fn], 0, 0, 0);
+                acc[fm][fn] = mfma<Across>(af[1][fm], bf[1][fn], acc[fm][fn]);
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
@@ -341,6 +349,7 @@ struct Tile {
     // 4*(s%4).. of a 16-column block, so lane i ends up with rows k0..k0+3 of column i; the
     // group index selects k0 = 8*(l/16) and a second read 4 rows down completes the 8 values
     // per lane that the MFMA wants (two reads per fragment, one read per MFMA while they last).
+    template <bool Across = false>
     __device__ static __forceinline__ void mainloop_kmajor(const char *__restrict__ A, int64_t lda_bytes, int64_t m0, int64_t Mr,
                                                            const char *__restrict__ B, int64_t ldb_bytes, int64_t n0, int64_t Nr,
                                                            int KT, char *lds, Acc &acc, int64_t a_sub = 0, int64_t b_sub = 0) {
@@ -416,7 +425,7 @@ struct Tile {
                     read_half(1, 1, j);
                     __builtin_amdgcn_sched_barrier(0);
                 }
-                acc[fm][fn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag(ah[0][fm]), frag(bh[0][fn]), acc[fm][fn], 0, 0, 0);
+                acc[fm][fn] = mfma<Across>(frag(ah[0][fm]), frag(bh[0][fn]), acc[fm][fn]);
                 __builtin_amdgcn_sched_barrier(0);
             }
             asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
@@ -434,7 +443,7 @@ struct Tile {
                     if (FEED) d.one(kt + 2, j / 4);
                     __builtin_amdgcn_sched_barrier(0);
                 }
-                acc[fm][fn] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag(ah[1][fm]), frag(bh[1][fn]), acc[fm][fn], 0, 0, 0);
+                acc[fm][fn] = mfma<Across>(frag(ah[1][fm]), frag(bh[1][fn]), acc[fm][fn]);
                 __builtin_amdgcn_sched_barrier(0);
             }
         };

@@ -1002,12 +1002,152 @@ constexpr int kLimitRows = 1, kLimitK = 2;
 // dimension N) and reduce_split_kernel adds the parts in a fixed order: shapes with fewer
 // tiles than the chip has compute units still fill it, and the result does not depend on timing.
 //
-// Epilogue: the accumulators go out through LDS (the operand stages are free by then), half a
-// tile at a time: a lane holds four consecutive ROWS of one column, so stored directly a
-// wavefront would scatter 64-byte pieces over many rows per instruction; from LDS every
-// wavefront writes (or reads, adds and rewrites) whole rows of 256 values, 16 bytes per lane.
-// LDS layout of a half tile: 128 rows x 1024 bytes, the 64-byte piece c of row r at position
-// c ^ ((r / 4) % 4): the four lane groups, whose rows lie 4 apart, hit different banks.
+// The instruction gets its operands exchanged (Across), so that a lane holds runs of four consecutive columns of one
+// output row.
+//
+// Epilogue: straight from the accumulators, 16 bytes per lane, 64 contiguous bytes of 16 rows per instruction, and
+// nothing that waits between the stores.  (Through LDS, a half tile at a time with a look at the row's place and scale
+// per row, every store waited for the one before: 12.6 us per tile in a launch of 16 workgroups, where a compute unit
+// stores 256 KB in 2.)  Added to fp32 rows: the old values of the next 16 rows are requested before those of this 16
+// are rewritten.
+struct GemmOut {
+    void *out;
+    int64_t ldo, m0, m_end;          // rows m0.. below m_end
+    int n0, N;                       // columns n0.. below N
+    int dtype, accumulate;
+    const int32_t *row_map;          // NULL: rows in place
+    const float *row_scale;          // NULL: unscaled
+};
+
+// values that may only be aligned to their elements (the hardware takes it)
+typedef float f32x4u_t __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x4u_t __attribute__((ext_vector_type(4), aligned(2)));
+
+// Adds: sums are added to and rows are in place (dW); otherwise neither is added to.
+template <bool Adds>
+__device__ __forceinline__ void store_tile(const TL::Acc &acc, const GemmOut &o) {
+    constexpr int R = TL::FM, C = TL::FN;  // 16 x 16 blocks down and across
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));  // not to be traced: nothing derived from it is to live through the main loop
+    const int grp = lane >> 4, col = lane & 15;
+    const int n_first = o.n0 + TL::wave_n0();
+    const int rows = static_cast<int>(o.m_end), m_wave = static_cast<int>(o.m0) + TL::wave_m0();
+    int at[R], place[R];
+    float scale[R];
+    bool live[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        const int m = m_wave + i * TL::MI + col;
+        live[i] = m < rows;
+        place[i] = at[i] = live[i] ? m : rows - 1;  // always a load, none of them behind a branch
+        scale[i] = 1.0f;
+    }
+    if (!Adds && o.row_map)
+#pragma unroll
+        for (int i = 0; i < R; ++i) place[i] = o.row_map[at[i]];
+    if (!Adds && o.row_scale)
+#pragma unroll
+        for (int i = 0; i < R; ++i) scale[i] = o.row_scale[at[i]];
+    auto row = [&](int i) { return place[i] * o.ldo; };  // where this lane's rows begin, in elements
+    if (o.dtype == SPO_FP32) {
+        float *out = static_cast<float *>(o.out) + n_first + 4 * grp;
+        const int n = n_first + 4 * grp;
+        if (Adds && o.accumulate) {
+            constexpr int G = 2;  // blocks down that are requested at a time
+            const bool whole = m_wave + TL::WM <= rows && n_first + TL::WN <= o.N;
+            f32x4u_t old[2][G][C];
+            if (whole) {  // (a condition on every store would have the next values wait for the stores)
+                auto request = [&](int i) {
+#pragma unroll
+                    for (int j = 0; j < G * C; ++j)
+                        old[i / G & 1][j / C][j % C] = *reinterpret_cast<const f32x4u_t *>(out + row(i + j / C) + j % C * TL::MI);
+                };
+                request(0);
+#pragma unroll
+                for (int i = 0; i < R; i += G) {
+                    if (i + G < R) request(i + G);
+#pragma unroll
+                    for (int j = 0; j < G * C; ++j)
+                        *reinterpret_cast<f32x4u_t *>(out + row(i + j / C) + j % C * TL::MI) =
+                            old[i / G & 1][j / C][j % C] + acc[i + j / C][j % C];
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < R; i += G) {
+#pragma unroll
+                    for (int j = 0; j < G * C; ++j)
+                        if (live[i + j / C] && n + j % C * TL::MI + 3 < o.N)
+                            old[0][j / C][j % C] = *reinterpret_cast<const f32x4u_t *>(out + row(i + j / C) + j % C * TL::MI);
+                    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): here, or every store below waits for the one before
+#pragma unroll
+                    for (int j = 0; j < G * C; ++j)
+                        if (live[i + j / C] && n + j % C * TL::MI + 3 < o.N)
+                            *reinterpret_cast<f32x4u_t *>(out + row(i + j / C) + j % C * TL::MI) =
+                                old[0][j / C][j % C] + acc[i + j / C][j % C];
+                }
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < R; ++i)
+#pragma unroll
+                for (int j = 0; j < C; ++j)
+                    if (live[i] && n + j * TL::MI + 3 < o.N)
+                        *reinterpret_cast<f32x4u_t *>(out + row(i) + j * TL::MI) = acc[i][j] * scale[i];
+        }
+        if (n_first + TL::WN > o.N && o.N % 4 != 0) {  // the last columns, where they are no whole run
+#pragma unroll
+            for (int i = 0; i < R; ++i)
+#pragma unroll
+                for (int j = 0; j < C; ++j) {
+                    const int c = n + j * TL::MI;
+                    if (!live[i] || c + 3 < o.N) continue;
+#pragma unroll
+                    for (int r = 0; r < 3; ++r)  // (c + 3 is past them)
+                        if (c + r < o.N) {
+                            float *p = out + row(i) + j * TL::MI + r;
+                            *p = Adds && o.accumulate ? *p + acc[i][j][r] : acc[i][j][r] * scale[i];
+                        }
+                }
+        }
+        return;
+    }
+    // bf16, never added to: after an exchange between neighbouring lane groups a lane holds eight consecutive columns
+    uint16_t *out = static_cast<uint16_t *>(o.out);
+    const int n = n_first + (grp & 1) * TL::MI + (grp & 2) * 4;
+    auto eight = [&](int i, int j) {
+        uint32_t lo[2], hi[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const auto v = acc[i][j + q] * scale[i];
+            lo[q] = pack_bf16x2_rn(v[0], v[1]);
+            hi[q] = pack_bf16x2_rn(v[2], v[3]);
+        }
+        swap_lane_groups(lo[0], lo[1]);
+        swap_lane_groups(hi[0], hi[1]);
+        return u32x4u_t{lo[0], hi[0], lo[1], hi[1]};
+    };
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int j = 0; j < C; j += 2) {
+            const u32x4u_t w = eight(i, j);
+            if (live[i] && n + j * TL::MI + 7 < o.N) *reinterpret_cast<u32x4u_t *>(out + row(i) + n + j * TL::MI) = w;
+        }
+    if (n_first + TL::WN > o.N && o.N % 8 != 0) {
+#pragma unroll
+        for (int i = 0; i < R; ++i)
+#pragma unroll
+            for (int j = 0; j < C; j += 2) {
+                const u32x4u_t w = eight(i, j);
+                const int c = n + j * TL::MI;
+                if (!live[i] || c + 7 < o.N) continue;
+#pragma unroll
+                for (int r = 0; r < 7; ++r)
+                    if (c + r < o.N) out[row(i) + c + r] = static_cast<uint16_t>(w[r / 2] >> (16 * (r & 1)));
+            }
+    }
+}
+
 template <bool KMajor>
 __global__ void __launch_bounds__(TL::NT)
 gemm_store_kernel(const char *__restrict__ A, int64_t lda_bytes, int64_t M, const char *__restrict__ B,
@@ -1018,7 +1158,6 @@ gemm_store_kernel(const char *__restrict__ A, int64_t lda_bytes, int64_t M, cons
     extern __shared__ __attribute__((aligned(16))) char lds[];
     constexpr int bpt = TL::BM / kBlockK;  // blocks per tile edge
     static_assert(TL::BM % kBlockK == 0 && TL::BN == TL::BM, "a tile of a blocked operand is a whole number of blocks");
-    static_assert(TL::WGM == 2 && TL::BN * 4 * (TL::BM / 2) <= TL::LDS_BYTES, "half a tile of fp32 fits the operand stages");
     int64_t m_end = M;
     if (n_act && limit == kLimitRows) m_end = active_rows(n_act, row_base, M);
     // (rows that are not there, known on the device only, leave the ids at the end without a tile)
@@ -1059,121 +1198,24 @@ gemm_store_kernel(const char *__restrict__ A, int64_t lda_bytes, int64_t M, cons
         if (KMajor) {
             const int64_t Mr = (M + 7) & ~int64_t(7), Nr = (N + 7) & ~int64_t(7);
             const char *Ak = A + kt0 * (kBK * lda_bytes), *Bk = B + kt0 * (kBK * ldb_bytes);  // rows are the contraction index
-            TL::mainloop_kmajor(a_blk ? Ak + tm * bpt * a_blk : Ak, lda_bytes, a_blk ? 0 : m0, a_blk ? TL::BM : Mr,
-                                b_blk ? Bk + tn * bpt * b_blk : Bk, ldb_bytes, b_blk ? 0 : n0, b_blk ? TL::BN : Nr, KT, lds,
-                                acc, a_blk, b_blk);
+            TL::mainloop_kmajor<true>(a_blk ? Ak + tm * bpt * a_blk : Ak, lda_bytes, a_blk ? 0 : m0, a_blk ? TL::BM : Mr,
+                                      b_blk ? Bk + tn * bpt * b_blk : Bk, ldb_bytes, b_blk ? 0 : n0, b_blk ? TL::BN : Nr, KT, lds,
+                                      acc, a_blk, b_blk);
         } else {
             // k-step kt of an operand starts blk bytes (blocked) or one stage of 128 bytes (row-major) further on
             const int64_t sa = a_blk ? a_blk : kBK * 2, sb = b_blk ? b_blk : kBK * 2;
-            TL::mainloop(typename TL::Operands{A + kt0 * sa, lda_bytes, m0, M, B + kt0 * sb, ldb_bytes, n0, N, a_blk, b_blk},
-                         KT, lds, acc);
+            TL::mainloop<true>(typename TL::Operands{A + kt0 * sa, lda_bytes, m0, M, B + kt0 * sb, ldb_bytes, n0, N, a_blk, b_blk},
+                               KT, lds, acc);
         }
     }
-    // where the tile goes: its place in the output, or (parts of a contraction) a plain fp32 tile
-    int64_t om0 = m0, on0 = n0, oN = N;
-    if (nsplit > 1) {  // partial results [part][M][N], no row map
-        out = partials + static_cast<int64_t>(part) * M * N;
-        ldo = N;
-        out_dtype = SPO_FP32;
-        accumulate = 0;
-        row_map = nullptr;
+    GemmOut o{out, ldo, m0, m_end, static_cast<int>(n0), static_cast<int>(N), out_dtype, accumulate, row_map, row_scale};
+    if (nsplit > 1 || tail == kTailCut) {  // a part: fp32, in place, unscaled (parts are scaled when they are added)
+        const bool tile = tail == kTailCut;  // [part][tile - whole][BM][BN], otherwise [part][M][N]
+        const int64_t at = tile ? (static_cast<int64_t>(part) * cut.rem + (i - cut.whole)) * (TL::BM * TL::BN) : static_cast<int64_t>(part) * M * N;
+        o = GemmOut{partials + at, tile ? TL::BN : N, tile ? 0 : m0, tile ? TL::BM : m_end, tile ? 0 : static_cast<int>(n0),
+                    tile ? TL::BN : static_cast<int>(N), SPO_FP32, 0, nullptr, nullptr};
     }
-    if (tail == kTailCut) {  // partial results [part][tile - whole][BM][BN]
-        out = partials + (static_cast<int64_t>(part) * cut.rem + (i - cut.whole)) * (TL::BM * TL::BN);
-        ldo = TL::BN;
-        out_dtype = SPO_FP32;
-        accumulate = 0;
-        row_map = nullptr;
-        om0 = on0 = 0;
-        oN = TL::BN;
-        m_end = TL::BM;
-    }
-    int lane = threadIdx.x & 63;
-    asm volatile("" : "+v"(lane));  // not to be traced: nothing derived from it is to live through the main loop
-    const int grp = lane >> 4, col = lane & 15;
-    // whole groups of four columns can move as 16 (fp32) or 8 (bf16) bytes when the rows allow it
-    const bool vec = ldo % 4 == 0 && oN % 4 == 0 && reinterpret_cast<uintptr_t>(out) % 16 == 0;
-    constexpr int HALF = TL::BM / 2, ROWS = HALF / TL::NWAVE;
-    // adding to fp32 rows: the old values of a wavefront's rows are all requested before the half
-    // tile is staged, so that their latency passes once per half tile and behind the staging
-    const bool rmw = accumulate && out_dtype == SPO_FP32 && vec;
-    const int64_t n = on0 + 4 * lane;  // this lane's four columns
-    __syncthreads();  // the operand stages are no longer read
-#pragma unroll 1
-    for (int half = 0; half < 2; ++half) {
-        const int64_t m_first = om0 + half * HALF + TL::wave_id() * ROWS;  // this wavefront's rows of the half tile
-        float4 old[ROWS];
-        if (rmw) {
-#pragma unroll
-            for (int i = 0; i < ROWS; ++i) {
-                old[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                if (m_first + i < m_end && n < oN) {
-                    const int64_t m = row_map ? row_map[m_first + i] : m_first + i;
-                    old[i] = *reinterpret_cast<const float4 *>(static_cast<const float *>(out) + m * ldo + n);
-                }
-            }
-        }
-        if (TL::wave_m0() == half * HALF) {
-#pragma unroll
-            for (int fm = 0; fm < TL::FM; ++fm)
-#pragma unroll
-                for (int fn = 0; fn < TL::FN; ++fn)
-#pragma unroll
-                    for (int r = 0; r < TL::ACC_R; ++r) {
-                        const int row = fm * TL::MI + 4 * grp + r;                  // (row / 4) % 4 == grp
-                        const int piece = (TL::wave_n0() / TL::MI + fn) ^ grp;     // 64-byte piece of the row
-                        *reinterpret_cast<float *>(lds + row * (TL::BN * 4) + piece * 64 + col * 4) = acc[fm][fn][r];
-                    }
-        }
-        __syncthreads();
-        if (rmw) {
-#pragma unroll
-            for (int i = 0; i < ROWS; ++i) {
-                const int row = TL::wave_id() * ROWS + i;
-                if (m_first + i >= m_end || n >= oN) continue;
-                const int64_t m = row_map ? row_map[m_first + i] : m_first + i;
-                const float4 v = *reinterpret_cast<const float4 *>(lds + row * (TL::BN * 4) +
-                                                                   (((lane >> 2) ^ ((row >> 2) & 3)) << 6) + (lane & 3) * 16);
-                *reinterpret_cast<float4 *>(static_cast<float *>(out) + m * ldo + n) =
-                    make_float4(old[i].x + v.x, old[i].y + v.y, old[i].z + v.z, old[i].w + v.w);
-            }
-        } else {
-#pragma unroll 4
-            for (int i = 0; i < ROWS; ++i) {
-                const int row = TL::wave_id() * ROWS + i;
-                int64_t m = m_first + i;
-                if (m >= m_end) break;  // rows are in order: nothing further down either
-                const float sc = row_scale && nsplit == 1 ? row_scale[m] : 1.0f;  // (parts are scaled when they are added)
-                if (row_map) m = row_map[m];
-                float4 v = *reinterpret_cast<const float4 *>(lds + row * (TL::BN * 4) +
-                                                             (((lane >> 2) ^ ((row >> 2) & 3)) << 6) + (lane & 3) * 16);
-                v = make_float4(v.x * sc, v.y * sc, v.z * sc, v.w * sc);
-                if (n >= oN) continue;
-                if (out_dtype == SPO_FP32) {
-                    float *o = static_cast<float *>(out) + m * ldo + n;
-                    if (vec) {
-                        *reinterpret_cast<float4 *>(o) = v;
-                    } else {
-                        const float e[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            if (n + j < oN) o[j] = accumulate ? o[j] + e[j] : e[j];
-                    }
-                } else {
-                    bf16_t *o = static_cast<bf16_t *>(out) + m * ldo + n;
-                    if (vec) {
-                        *reinterpret_cast<uint2 *>(o) = make_uint2(pack_bf16x2_rn(v.x, v.y), pack_bf16x2_rn(v.z, v.w));
-                    } else {
-                        const float e[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            if (n + j < oN) o[j] = f32_to_bf16(e[j]);
-                    }
-                }
-            }
-        }
-        __syncthreads();  // the half tile has been read: its space may be written again
-    }
+    store_tile<KMajor>(acc, o);
 }
 
 // out[row_map[m]][n] = row_scale[m] * sum over the parts (in order) of partials[part][m][n] for m

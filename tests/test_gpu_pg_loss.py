@@ -419,6 +419,32 @@ def test_bf16_dW_is_the_fp32_one_rounded(spo, oracle, T, H, V, chunk, w_layout, 
     assert rel_l2(f64(dw16), rb["d_W"]) < GRAD_TOL
 
 
+@pytest.mark.parametrize("V", [1, 3, 6, 257, 510, 1003])   # rows of d_W [H,V] that end inside a run of 4 or 8 columns
+@pytest.mark.parametrize("H", [64, 320])                    # a tile with a quarter of its rows; one and a quarter
+def test_dW_rows_that_end_anywhere(spo, oracle, V, H):
+    # the same sums in either layout of the head (rows of H values are whole runs): stored as fp32, as bf16, and added
+    # to.  Sums in fp32 in the same order: equal up to the last place of the largest (2^-23 of it, and of a product).
+    T = 90
+    say(f"fused bf16 T={T} H={H} V={V}: ends of d_W's rows")
+    case = Case(wl.scaled(MID, name="ends", H=H, V=V), [T // 3, T - T // 3])
+    case.set_old_from_oracle(oracle)
+    _, _, ref = run_fwd_bwd(spo, case, 0)
+    tol = 4 * 2.0 ** -23 * float(ref.abs().max()) + 1e-30
+    _, _, got = run_fwd_bwd(spo, case, 1)
+    assert (got - ref).abs().max() <= tol
+    _, _, got16 = run_fwd_bwd(spo, case, 1, dw_dtype=torch.bfloat16)
+    assert torch.equal(got16, got.to(torch.bfloat16))
+    # guards before and behind the array
+    buf = torch.full((H * V + 9,), 7.0, dtype=torch.float32, device="cuda")
+    dw = buf[4:4 + H * V].view(H, V)
+    desc = case.to_gpu(spo, 1)
+    _, logp, lse, _ = spo.spo_pg_loss_fwd(desc)
+    spo.spo_pg_loss_bwd(desc, logp, lse, 1.0, d_W=dw, accumulate_dW=True)
+    torch.cuda.synchronize()
+    assert bool((buf[:4] == 7.0).all()) and bool((buf[4 + H * V:] == 7.0).all())
+    assert (dw - (got.t() + 7.0)).abs().max() <= 8 * 2.0 ** -23 * 7.0 + tol
+
+
 def test_cu_seqlens_may_start_anywhere(spo, oracle):
     # a mini-batch cut out of a packed batch keeps the batch's offsets: only differences count
     say("fused bf16 mid, cu_seqlens shifted by a constant")
