@@ -29,7 +29,10 @@ namespace spo {
 
 // 8 wavefronts, each a 128 x 64 part of the tile, on 16x16x32 MFMAs (measured 4-6 % faster
 // than the same tile on 32x32x16 on the same chip: the instruction draws less power).
-typedef Tile<256, 256, 2, 4, 16> TL;
+typedef Tile<256, 256, 2, 4> TL;
+// 4 wavefronts, each a 64 x 64 part, two workgroups per compute unit: for shapes whose large tiles leave compute units
+// idle or are mostly padding (see small_tiles).
+typedef Tile<128, 128, 2, 2> TS;
 constexpr int kSplitTerms = 6;    // cross products kept by the fp32 split
 constexpr int kSweepSplits = 16;  // vocabulary splits of the forward sweep on large problems (a multiple of 8)
 // Default size of a backward chunk: as many tokens as keep the chunk's bf16 logit gradients
@@ -39,6 +42,7 @@ constexpr int kSweepSplits = 16;  // vocabulary splits of the forward sweep on l
 // at H = 4096, V = 151936 the step takes about 1 % longer with 8 GiB than with 40 GB.
 constexpr int64_t kDzBudgetBytes = int64_t(8) << 30;
 constexpr int kChipCUs = 256;
+template <typename T> constexpr int kSlots = kChipCUs * 512 / T::NT;  // workgroups that the chip holds at a time
 constexpr int kTailTiles = kChipCUs;  // fp32 tiles of room for the parts of cut contractions (see launch_gemm)
 
 static int64_t gcd64(int64_t a, int64_t b) { return b ? gcd64(b, a % b) : a; }
@@ -124,7 +128,7 @@ struct PrepJobs {
     int64_t T_ref;                // entries of ref2
     uint32_t *done;
     int64_t target_blocks;        // four wavefronts of target_run (1 or kTargetRun) tokens each
-    int target_run;
+    int target_run, target_cols;  // target_cols: Wrows is the head as [H,V], one token per wavefront
     const uint8_t *mask;
     double *count;                // NULL: not counted
     float *g;                     // NULL: no gradient factors
@@ -405,6 +409,26 @@ __device__ __forceinline__ void target_logits(const T_ *__restrict__ X, const T_
     }
 }
 
+// The same of one token where the head is [H,V]: the entries of a column lie 2 V bytes apart, eight of them in flight
+// per lane (the sum in the order of target_logits).
+__device__ __forceinline__ float target_logit_cols(const bf16_t *__restrict__ X, const bf16_t *__restrict__ W, int64_t H, int64_t V,
+                                                   int64_t T, const int32_t *__restrict__ target, int64_t t, int lane) {
+    const int64_t y = t < T ? target[t] : -1;
+    const bool ok = y >= 0 && y < V;
+    const uint4 *x = reinterpret_cast<const uint4 *>(X + (ok ? t : 0) * H);
+    const bf16_t *w = W + (ok ? y : 0);
+    float z = 0.0f;
+    for (int i = lane; i < H / 8; i += kWave) {
+        const uint4 a = x[i];
+        uint32_t b[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) b[k] = w[(i * 8 + k) * V];
+        z += dot8(a, make_uint4(b[0] | b[1] << 16, b[2] | b[3] << 16, b[4] | b[5] << 16, b[6] | b[7] << 16));
+    }
+    z = wave_sum(z);
+    return ok ? z : __builtin_nanf("");
+}
+
 // The reference of a token whose logits are stored as scaled probabilities (see below, one-call form without
 // a loss mask), times log2(e); 0 where the token has no valid target logit or old_logp is not finite (its
 // stored row stays finite and is multiplied by 0).
@@ -419,7 +443,13 @@ __device__ __forceinline__ void prep_targets(const PrepJobs &j, int64_t block) {
     const int64_t t = (block * 4 + (threadIdx.x >> 6)) * K;
     const int lane = threadIdx.x & 63;
     float z[K];
-    target_logits<K>(static_cast<const T_ *>(j.X), static_cast<const T_ *>(j.Wrows), j.H, j.V, j.T, j.target, t, lane, z);
+    bool done = false;
+    if constexpr (K == 1 && sizeof(T_) == 2)
+        if (j.target_cols) {
+            z[0] = target_logit_cols(static_cast<const bf16_t *>(j.X), static_cast<const bf16_t *>(j.Wrows), j.H, j.V, j.T, j.target, t, lane);
+            done = true;
+        }
+    if (!done) target_logits<K>(static_cast<const T_ *>(j.X), static_cast<const T_ *>(j.Wrows), j.H, j.V, j.T, j.target, t, lane, z);
     float mine = z[0];  // lane k: token t + k
 #pragma unroll
     for (int k = 1; k < K; ++k) mine = lane == k ? z[k] : mine;
@@ -514,7 +544,8 @@ static void launch_prep_with_targets(const spo_pg_desc *d, PrepJobs j, float *z_
     j.T_ref = T_ref;
     j.done = done;
     const int64_t tokens = ref2 ? T_ref : d->T;
-    j.target_run = tokens > kTargetRunTokens && d->H * (d->dtype == SPO_FP32 ? 4 : 2) <= kTargetRunBytes ? kTargetRun : 1;
+    j.target_cols = d->w_layout == SPO_W_HV && j.Wrows == d->W;
+    j.target_run = !j.target_cols && tokens > kTargetRunTokens && d->H * (d->dtype == SPO_FP32 ? 4 : 2) <= kTargetRunBytes ? kTargetRun : 1;
     j.target_blocks = ceil_div(tokens, 4 * j.target_run);
     launch_prep(d, j, s);
 }
@@ -531,9 +562,10 @@ static void launch_prep_with_targets(const spo_pg_desc *d, PrepJobs j, float *z_
 // smallest such count: longer workgroups).  67 token tiles x 594 vocabulary tiles in 16 splits are
 // 5 rounds x 38 tiles = 190, in 40 splits 11 x 15 = 165, of 155.5 that the work divided by 256 units
 // comes to.  Fewer tiles than units: a workgroup each.
+// slots: workgroups that the chip holds at a time.
 template <typename U>
-__host__ __device__ static inline U sweep_cost(U nTt, U nVt, U ns) {
-    return (nTt * ns + kChipCUs - 1) / kChipCUs * ((nVt + ns - 1) / ns);
+__host__ __device__ static inline U sweep_cost(U nTt, U nVt, U ns, U slots) {
+    return (nTt * ns + slots - 1) / slots * ((nVt + ns - 1) / ns);
 }
 // Candidates: the multiples of 8 in [sweep_splits_lo, sweep_splits_hi].  From 16 token tiles on at least
 // 16 splits (workgroups that share lines drift apart on longer runs), at most about 4096 workgroups
@@ -547,21 +579,22 @@ __host__ __device__ static inline uint32_t sweep_splits_hi(uint32_t nTt, uint32_
 }
 constexpr uint32_t kNoSplitCap = 512;
 // cap: the most splits the caller has room for (at least kSweepSplits)
-static int sweep_splits(int64_t token_tiles, int64_t vocab_tiles, uint32_t cap = kNoSplitCap) {
+static int sweep_splits(int64_t token_tiles, int64_t vocab_tiles, int slots, uint32_t cap = kNoSplitCap) {
     const uint64_t nTt = token_tiles > 0 ? token_tiles : 1, nVt = vocab_tiles;
-    if (nTt * nVt <= kChipCUs && nVt <= cap) return static_cast<int>(nVt);
+    const uint64_t chip = slots;
+    if (nTt * nVt <= chip && nVt <= cap) return static_cast<int>(nVt);
     const uint64_t hi = sweep_splits_hi(static_cast<uint32_t>(nTt), static_cast<uint32_t>(nVt), cap);
     uint64_t best = 0;
     for (uint64_t ns = sweep_splits_lo(static_cast<uint32_t>(nTt)); ns <= hi; ns += 8)
-        if (!best || sweep_cost(nTt, nVt, ns) < sweep_cost(nTt, nVt, best)) best = ns;
+        if (!best || sweep_cost(nTt, nVt, ns, chip) < sweep_cost(nTt, nVt, best, chip)) best = ns;
     return static_cast<int>(best ? best : hi);
 }
 // The same choice by a wavefront, one candidate per lane, where the number of token tiles is known on the
 // device only (the tiles of a chunk's gradients fit the memory: costs stay far below 2^22).
-__device__ __forceinline__ int sweep_splits_wave(uint32_t nTt, uint32_t nVt) {
-    if (nTt * nVt <= kChipCUs) return static_cast<int>(nVt);
+__device__ __forceinline__ int sweep_splits_wave(uint32_t nTt, uint32_t nVt, uint32_t slots) {
+    if (nTt * nVt <= slots) return static_cast<int>(nVt);
     const uint32_t hi = sweep_splits_hi(nTt, nVt, kNoSplitCap), ns = sweep_splits_lo(nTt) + 8 * (threadIdx.x & 63);
-    uint32_t key = ns <= hi ? sweep_cost(nTt, nVt, ns) << 10 | ns : 0xffffffffu;
+    uint32_t key = ns <= hi ? sweep_cost(nTt, nVt, ns, slots) << 10 | ns : 0xffffffffu;
 #pragma unroll
     for (int o = 1; o < kWave; o <<= 1) {
         const uint32_t k = __shfl_xor(key, o, kWave);
@@ -574,6 +607,11 @@ __device__ __forceinline__ int sweep_splits_wave(uint32_t nTt, uint32_t nVt) {
 // every shorter one.
 static int64_t sweep_pairs_max(int64_t nTt, int64_t nVt) {
     return std::min(nTt * std::min<int64_t>(nVt, kNoSplitCap), std::max<int64_t>(4096, nTt * kSweepSplits));
+}
+// Entries of room for the partial results of every token and split; roomy: also those of small tiles.
+static int64_t sweep_room(int64_t T, int64_t V, bool roomy) {
+    const int64_t large = sweep_pairs_max(ceil_div(T, TL::BN), ceil_div(V, TL::BM)) * TL::BN;
+    return roomy ? std::max(large, sweep_pairs_max(ceil_div(T, TS::BN), ceil_div(V, TS::BM)) * TS::BN) : large;
 }
 // The most workgroups (ids of SweepMap) for them: what is left over by eight XCDs is rounded up.
 static int64_t sweep_blocks_max(int64_t nTt, int64_t nVt) { return sweep_pairs_max(nTt, nVt) + 8; }
@@ -626,8 +664,9 @@ struct SweepMap {
     __host__ __device__ int64_t first_tile(int split) const { return split * nVt / ns; }
 };
 
-constexpr int kSweepLds = TL::LDS_BYTES + TL::NT * 32;       // operand stages + the per-thread running state
-constexpr int kSweepLdsProbs = TL::LDS_BYTES + TL::NT * 48;  // ... + the per-token references
+constexpr int kEmitNone = 0, kEmitLogits = 1, kEmitProbs = 2;  // see fwd_sweep_kernel
+// operand stages + the per-thread running state (+ the per-token references)
+template <typename T> constexpr int kSweepLds(int emit) { return T::LDS_BYTES + T::NT * (emit == kEmitProbs ? 48 : 32); }
 
 // Exchange between neighbouring groups of 16 lanes: v_permlane16_swap(a, b) swaps the odd groups
 // of a with the even groups of b.  With a, b the values a lane holds for two consecutive MFMA
@@ -662,10 +701,9 @@ __device__ __forceinline__ uint32_t pack_f16x2_rn(float lo, float hi) {
 // the softmax probabilities divided by the token's importance ratio).  The exponentials are the
 // ones the running sum needs anyway, times one factor per token and lane; exponents are capped
 // at 126 so that nothing stored is infinite.  Rows past the vocabulary are stored as zeros.
-constexpr int kEmitNone = 0, kEmitLogits = 1, kEmitProbs = 2;
-
-template <int Emit>
-__global__ void __launch_bounds__(TL::NT)
+// WCols: W is the head as [H,V], read as it is.
+template <int Emit, typename TT, bool WCols>
+__global__ void __launch_bounds__(TT::NT, 2)
 fwd_sweep_kernel(const char *__restrict__ W, int64_t ldw_bytes, int64_t V, const char *__restrict__ X,
                  int64_t ldx_bytes, int64_t T, int KT, int nsplit, int64_t nTt, int64_t nVt, int64_t T_pad,
                  float *__restrict__ part_max, float *__restrict__ part_sum, uint16_t *__restrict__ Z, int64_t z_blk,
@@ -675,23 +713,23 @@ fwd_sweep_kernel(const char *__restrict__ W, int64_t ldw_bytes, int64_t V, const
     int split;
     int64_t jt;
     if (!map.tile(blockIdx.x, split, jt)) return;
-    const int64_t n0 = jt * TL::BN;
+    const int64_t n0 = jt * TT::BN;
     const int64_t vt0 = map.first_tile(split), vt1 = map.first_tile(split + 1);
     const int lane = threadIdx.x & 63;
 
     // Running (maximum, sum of exponentials) of this lane's FN tokens.  Between tiles they wait in
     // the LDS the operand stages leave free (a slot per thread): the main loop needs every register.
-    static_assert(TL::FN == 4, "one 16-byte slot each for the maxima and the sums");
+    static_assert(TT::FN == 4, "one 16-byte slot each for the maxima and the sums");
     auto state = [&] {
         int tid = threadIdx.x;
         asm volatile("" : "+v"(tid));  // not to be traced: the address is formed anew at every use
-        return reinterpret_cast<float4 *>(lds + TL::LDS_BYTES) + (Emit == kEmitProbs ? 3 : 2) * tid;
+        return reinterpret_cast<float4 *>(lds + TT::LDS_BYTES) + (Emit == kEmitProbs ? 3 : 2) * tid;
     };
     state()[0] = make_float4(kNegBig, kNegBig, kNegBig, kNegBig);
     state()[1] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     if (Emit == kEmitProbs) {  // the references of this lane's four tokens: the workgroup keeps its token tile
-        const float *r = offs + n0 + TL::wave_n0() + (lane & 15);
-        state()[2] = make_float4(r[0], r[TL::MI], r[2 * TL::MI], r[3 * TL::MI]);
+        const float *r = offs + n0 + TT::wave_n0() + (lane & 15);
+        state()[2] = make_float4(r[0], r[TT::MI], r[2 * TT::MI], r[3 * TT::MI]);
     }
     // One finished tile.  Online log-sum-exp over its rows: three operations per logit (multiply-add
     // into the exponent, exponential, add) plus its share of the maximum.  With Emit, the tile's
@@ -700,37 +738,37 @@ fwd_sweep_kernel(const char *__restrict__ W, int64_t ldw_bytes, int64_t V, const
     // consecutive vocabulary entries of one token; after an exchange between neighbouring lane
     // groups it holds 16 contiguous bytes of two 64-entry blocks out of four (the scheme of the
     // recompute's epilogue below).
-    auto finish_tile = [&](TL::Acc &acc, int64_t vt) {
-        const int64_t m0 = vt * TL::BM;
-        if (m0 + TL::BM > V) {  // ragged last tile: rows past the vocabulary do not count
+    auto finish_tile = [&](typename TT::Acc &acc, int64_t vt) {
+        const int64_t m0 = vt * TT::BM;
+        if (m0 + TT::BM > V) {  // ragged last tile: rows past the vocabulary do not count
 #pragma unroll
-            for (int fm = 0; fm < TL::FM; ++fm)
+            for (int fm = 0; fm < TT::FM; ++fm)
 #pragma unroll
-                for (int r = 0; r < TL::ACC_R; ++r)
-                    if (m0 + TL::acc_row(fm, r) >= V)
+                for (int r = 0; r < TT::ACC_R; ++r)
+                    if (m0 + TT::acc_row(fm, r) >= V)
 #pragma unroll
-                        for (int fn = 0; fn < TL::FN; ++fn) acc[fm][fn][r] = -INFINITY;
+                        for (int fn = 0; fn < TT::FN; ++fn) acc[fm][fn][r] = -INFINITY;
         }
         int l = threadIdx.x & 63;
         asm volatile("" : "+v"(l));  // not to be traced: nothing derived from it lives through the main loop
         const int grp = l >> 4, col = l & 15;
-        const int64_t wave_blk = vt * (TL::BM / kBlockK) + TL::wave_m0() / kBlockK;
+        const int64_t wave_blk = vt * (TT::BM / kBlockK) + TT::wave_m0() / kBlockK;
         const int piece = (grp & 1) * 16 + (grp & 2) * 4;  // elements: byte offset 32 * (g & 1) + 8 * (g & 2)
         float4 *st = state();
         const float4 m4 = st[0], s4 = st[1];
-        float m_run[TL::FN] = {m4.x, m4.y, m4.z, m4.w}, s_run[TL::FN] = {s4.x, s4.y, s4.z, s4.w};
-        float ref[TL::FN] = {0.0f, 0.0f, 0.0f, 0.0f};
+        float m_run[TT::FN] = {m4.x, m4.y, m4.z, m4.w}, s_run[TT::FN] = {s4.x, s4.y, s4.z, s4.w};
+        float ref[TT::FN] = {0.0f, 0.0f, 0.0f, 0.0f};
         if (Emit == kEmitProbs) {
             const float4 r4 = st[2];
             ref[0] = r4.x; ref[1] = r4.y; ref[2] = r4.z; ref[3] = r4.w;
         }
 #pragma unroll
-        for (int fn = 0; fn < TL::FN; ++fn) {
+        for (int fn = 0; fn < TT::FN; ++fn) {
             float mx = -INFINITY;
 #pragma unroll
-            for (int fm = 0; fm < TL::FM; ++fm)
+            for (int fm = 0; fm < TT::FM; ++fm)
 #pragma unroll
-                for (int r = 0; r < TL::ACC_R; ++r) mx = fmaxf(mx, acc[fm][fn][r]);
+                for (int r = 0; r < TT::ACC_R; ++r) mx = fmaxf(mx, acc[fm][fn][r]);
             // the running maximum starts at a finite sentinel, so nm is finite even when every
             // row of the tile is masked (their logits are -inf and add exact zeros)
             const float nm = fmaxf(m_run[fn], mx);
@@ -744,12 +782,12 @@ fwd_sweep_kernel(const char *__restrict__ W, int64_t ldw_bytes, int64_t V, const
                 off = fmaxf(nm, __shfl_xor(nm, 16, kWave));
                 off = fmaxf(off, __shfl_xor(off, 32, kWave));
                 if (grp == 0)
-                    offs[(vt * TL::WGM + TL::wave_m0() / TL::WM) * T_pad + n0 + TL::wave_n0() + fn * TL::MI + col] = off;
+                    offs[(vt * TT::WGM + TT::wave_m0() / TT::WM) * T_pad + n0 + TT::wave_n0() + fn * TT::MI + col] = off;
             }
             float s = 0.0f;
-            uint16_t *row = Emit ? Z + (n0 + TL::wave_n0() + fn * TL::MI + col) * kBlockK + piece : nullptr;
+            uint16_t *row = Emit ? Z + (n0 + TT::wave_n0() + fn * TT::MI + col) * kBlockK + piece : nullptr;
 #pragma unroll
-            for (int b = 0; b < TL::FM / 4; ++b) {
+            for (int b = 0; b < TT::FM / 4; ++b) {
                 uint32_t lo[4], hi[4];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
@@ -785,45 +823,44 @@ fwd_sweep_kernel(const char *__restrict__ W, int64_t ldw_bytes, int64_t V, const
         st[0] = make_float4(m_run[0], m_run[1], m_run[2], m_run[3]);
         st[1] = make_float4(s_run[0], s_run[1], s_run[2], s_run[3]);
     };
-    auto tile_ops = [&](int64_t vt) { return typename TL::Operands{W, ldw_bytes, vt * TL::BM, V, X, ldx_bytes, n0, T, 0, 0}; };
-    for (int64_t vt = vt0; vt < vt1; ++vt) {
-        TL::Acc acc;
-        TL::zero(acc);
-        TL::mainloop(tile_ops(vt), KT, lds, acc);
+        for (int64_t vt = vt0; vt < vt1; ++vt) {
+        typename TT::Acc acc;
+        TT::zero(acc);
+        TT::template mainloop<WCols, false>({W, ldw_bytes, vt * TT::BM, V, 0, 0}, {X, ldx_bytes, n0, T, 0, 0}, KT, lds, acc);
         finish_tile(acc, vt);
     }
     // merge the lane groups that hold different rows of the same token, then the WGM
     // wavefronts that share a token column
     float *red_m = reinterpret_cast<float *>(lds);
-    float *red_s = red_m + TL::WGM * TL::BN;
+    float *red_s = red_m + TT::WGM * TT::BN;
     const float4 m4 = state()[0], s4 = state()[1];
-    const float m_run[TL::FN] = {m4.x, m4.y, m4.z, m4.w}, s_run[TL::FN] = {s4.x, s4.y, s4.z, s4.w};
+    const float m_run[TT::FN] = {m4.x, m4.y, m4.z, m4.w}, s_run[TT::FN] = {s4.x, s4.y, s4.z, s4.w};
     __syncthreads();  // operand stages are no longer read
 #pragma unroll
-    for (int fn = 0; fn < TL::FN; ++fn) {
+    for (int fn = 0; fn < TT::FN; ++fn) {
         float m = m_run[fn], sum = s_run[fn];
 #pragma unroll
-        for (int o = TL::MI; o < kWave; o <<= 1) {
+        for (int o = TT::MI; o < kWave; o <<= 1) {
             const float om = __shfl_xor(m, o, kWave), os = __shfl_xor(sum, o, kWave);
             const float nm = fmaxf(m, om);
             sum = sum * __builtin_amdgcn_exp2f((m - nm) * kLog2e) + os * __builtin_amdgcn_exp2f((om - nm) * kLog2e);
             m = nm;
         }
-        if (lane < TL::MI) {
-            const int slot = (TL::wave_id() % TL::WGM) * TL::BN + TL::acc_col(fn);
+        if (lane < TT::MI) {
+            const int slot = (TT::wave_id() % TT::WGM) * TT::BN + TT::acc_col(fn);
             red_m[slot] = m;
             red_s[slot] = sum;
         }
     }
     __syncthreads();
-    for (int c = threadIdx.x; c < TL::BN; c += TL::NT) {
+    for (int c = threadIdx.x; c < TT::BN; c += TT::NT) {
         float nm = kNegBig;
 #pragma unroll
-        for (int w = 0; w < TL::WGM; ++w) nm = fmaxf(nm, red_m[w * TL::BN + c]);
+        for (int w = 0; w < TT::WGM; ++w) nm = fmaxf(nm, red_m[w * TT::BN + c]);
         float s = 0.0f;
 #pragma unroll
-        for (int w = 0; w < TL::WGM; ++w)
-            s += red_s[w * TL::BN + c] * __builtin_amdgcn_exp2f((red_m[w * TL::BN + c] - nm) * kLog2e);
+        for (int w = 0; w < TT::WGM; ++w)
+            s += red_s[w * TT::BN + c] * __builtin_amdgcn_exp2f((red_m[w * TT::BN + c] - nm) * kLog2e);
         part_max[split * T_pad + n0 + c] = nm;
         part_sum[split * T_pad + n0 + c] = s;
     }
@@ -844,38 +881,35 @@ fwd_sweep_kernel(const char *__restrict__ W, int64_t ldw_bytes, int64_t V, const
 // Workgroups map to (token tile, vocabulary split) as in the forward sweep (SweepMap).  The
 // gradients go from the accumulators to memory without a detour through LDS.
 
-__global__ void __launch_bounds__(TL::NT)
+template <typename TT, bool WCols>
+__global__ void __launch_bounds__(TT::NT, 2)
 recompute_dz_kernel(const char *__restrict__ W, int64_t ldw_bytes, int64_t V,
                     const char *__restrict__ X, int64_t ldx_bytes, int64_t T_valid, int KT,
                     const float4 *__restrict__ tok, int64_t nVt, bf16_t *__restrict__ dZ,
                     int64_t dz_blk, const int32_t *__restrict__ n_act, int64_t row_base) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    static_assert(TL::BM % kBlockK == 0 && kBlockK == 4 * TL::MI && TL::FM % 4 == 0,
+    static_assert(TT::BM % kBlockK == 0 && kBlockK == 4 * TT::MI && TT::FM % 4 == 0,
                   "a block of dZ is four MFMA blocks of vocabulary rows");
     const int act = static_cast<int>(active_rows(n_act, row_base, T_valid));
     if (act == 0) return;
-    const uint32_t act_tt = static_cast<uint32_t>((act + TL::BN - 1) / TL::BN);
-    const SweepMap map(act_tt, nVt, sweep_splits_wave(act_tt, static_cast<uint32_t>(nVt)));
+    const uint32_t act_tt = static_cast<uint32_t>((act + TT::BN - 1) / TT::BN);
+    const SweepMap map(act_tt, nVt, sweep_splits_wave(act_tt, static_cast<uint32_t>(nVt), kSlots<TT>));
     int split;
     int64_t jt;
     if (!map.tile(blockIdx.x, split, jt)) return;
     const int tn = static_cast<int>(jt);
     const int vt0 = static_cast<int>(map.first_tile(split)), vt1 = static_cast<int>(map.first_tile(split + 1));
-    auto tile_ops = [&](int tile_m, int tile_n) {
-        return typename TL::Operands{W, ldw_bytes, static_cast<int64_t>(tile_m) * TL::BM, V, X, ldx_bytes,
-                                     static_cast<int64_t>(tile_n) * TL::BN, T_valid, 0, 0};
-    };
     // gradients of one finished tile
-    auto emit = [&](TL::Acc &acc, int tile_m, int tile_n) {
-        const int m0 = tile_m * TL::BM, n0 = tile_n * TL::BN;
-        if (m0 + TL::BM > V) {  // ragged last tile: rows past the vocabulary get probability zero
+    auto emit = [&](typename TT::Acc &acc, int tile_m, int tile_n) {
+        const int m0 = tile_m * TT::BM, n0 = tile_n * TT::BN;
+        if (m0 + TT::BM > V) {  // ragged last tile: rows past the vocabulary get probability zero
 #pragma unroll
-            for (int fm = 0; fm < TL::FM; ++fm)
+            for (int fm = 0; fm < TT::FM; ++fm)
 #pragma unroll
-                for (int r = 0; r < TL::ACC_R; ++r)
-                    if (m0 + TL::acc_row(fm, r) >= V)
+                for (int r = 0; r < TT::ACC_R; ++r)
+                    if (m0 + TT::acc_row(fm, r) >= V)
 #pragma unroll
-                        for (int fn = 0; fn < TL::FN; ++fn) acc[fm][fn][r] = -INFINITY;
+                        for (int fn = 0; fn < TT::FN; ++fn) acc[fm][fn][r] = -INFINITY;
         }
         // A lane holds runs of four consecutive vocabulary entries (8 bytes of bf16) of ONE token,
         // at offset 32 * (fm % 4) + 8 * group inside that token's 128-byte row of a block of dZ.
@@ -886,26 +920,26 @@ recompute_dz_kernel(const char *__restrict__ W, int64_t ldw_bytes, int64_t V,
         int lane = threadIdx.x & 63;
         asm volatile("" : "+v"(lane));
         const int grp = lane >> 4, col = lane & 15;
-        const int wave_blk = tile_m * (TL::BM / kBlockK) + TL::wave_m0() / kBlockK;
+        const int wave_blk = tile_m * (TT::BM / kBlockK) + TT::wave_m0() / kBlockK;
         const int piece = (grp & 1) * 16 + (grp & 2) * 4;  // elements: byte offset 32 * (g & 1) + 8 * (g & 2)
         // the records of this wavefront's 64 tokens, one per lane (handed round with lane shuffles below)
-        const float4 rec = tok[static_cast<int64_t>(n0) + TL::wave_n0() + lane];
+        const float4 rec = tok[static_cast<int64_t>(n0) + TT::wave_n0() + lane];
 #pragma unroll
-        for (int fn = 0; fn < TL::FN; ++fn) {
-            const int src = fn * TL::MI + col;
+        for (int fn = 0; fn < TT::FN; ++fn) {
+            const int src = fn * TT::MI + col;
             const float ag = __shfl(rec.x, src, kWave), nl = __shfl(rec.y, src, kWave);
             const uint32_t ts = __float_as_uint(__shfl(rec.z, src, kWave));
             // the values are formed as |g| * p >= 0; the sign of -g is put on afterwards, two at a time
             const uint32_t sgn = (ts & 0x80000000u) ? 0x80008000u : 0u;
             // where the target's vocabulary row sits among this wave's rows, if it does
-            const int dy = static_cast<int>(ts & 0x7fffffffu) - (m0 + TL::wave_m0());
+            const int dy = static_cast<int>(ts & 0x7fffffffu) - (m0 + TT::wave_m0());
             int fq = 0, rq = 0, gq = 0;
-            const bool in_wave = static_cast<unsigned>(dy) < static_cast<unsigned>(TL::WM);
-            if (in_wave) TL::locate(dy, fq, rq, gq);
+            const bool in_wave = static_cast<unsigned>(dy) < static_cast<unsigned>(TT::WM);
+            if (in_wave) TT::locate(dy, fq, rq, gq);
             const bool mine = in_wave && gq == grp;
-            bf16_t *row = dZ + static_cast<int64_t>(n0 + TL::wave_n0() + fn * TL::MI + col) * kBlockK + piece;
+            bf16_t *row = dZ + static_cast<int64_t>(n0 + TT::wave_n0() + fn * TT::MI + col) * kBlockK + piece;
 #pragma unroll
-            for (int b = 0; b < TL::FM / 4; ++b) {
+            for (int b = 0; b < TT::FM / 4; ++b) {
                 uint32_t lo[4], hi[4];  // bf16 pairs: lo = rows +0,+1, hi = rows +2,+3 of the run of block 4b+q
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
@@ -947,9 +981,10 @@ recompute_dz_kernel(const char *__restrict__ W, int64_t ldw_bytes, int64_t V,
         }
     };
     for (int tm = vt0; tm < vt1; ++tm) {
-        TL::Acc acc;
-        TL::zero(acc);
-        TL::mainloop(tile_ops(tm, tn), KT, lds, acc);
+        typename TT::Acc acc;
+        TT::zero(acc);
+        TT::template mainloop<WCols, false>({W, ldw_bytes, static_cast<int64_t>(tm) * TT::BM, V, 0, 0},
+                                   {X, ldx_bytes, static_cast<int64_t>(tn) * TT::BN, T_valid, 0, 0}, KT, lds, acc);
         emit(acc, tm, tn);
     }
 }
@@ -962,18 +997,19 @@ recompute_dz_kernel(const char *__restrict__ W, int64_t ldw_bytes, int64_t V,
 // Tiles count in the order in which they are launched (TileOrder): the tiles that run are then whole rounds.  (Counted
 // row by row, the tiles left out were spread over the last patches, and where a band of patches is no divisor of a
 // round the rest took a round more: dHidden of 5000 x 3648 x 151936, 256 + 44 tiles, 6667 us, half of that now.)
-// k_steps: the contraction's length before it is limited on the device.  Where the short round is all there
-// is, the extra launch has to be worth it (kCutSteps).
-constexpr int kCutSteps = 8;
+// k_steps: the contraction's length before it is limited on the device.  The steps that a cut saves have to be worth its
+// two launches and the parts' way through memory, 19 us together (a step of small tiles takes about half as long).
+constexpr int kCutSteps = 12;
 struct TailCut {
     int64_t whole;  // tiles that run in whole rounds (all of them when nothing is cut)
     int rem, parts;
-    __host__ __device__ __forceinline__ TailCut(int64_t tiles, int64_t k_steps) : whole(tiles), rem(0), parts(1) {
-        const int r = static_cast<int>(tiles % kChipCUs);
-        if (r > 0 && r <= kChipCUs / 2 && (tiles > kChipCUs || k_steps >= kCutSteps)) {
+    __host__ __device__ __forceinline__ TailCut(int64_t tiles, int64_t k_steps, int slots) : whole(tiles), rem(0), parts(1) {
+        const int r = static_cast<int>(tiles % slots);
+        const int most = r > 0 ? (slots / r < 8 ? slots / r : 8) : 1;
+        if (most > 1 && (k_steps - k_steps / most) * kChipCUs >= kCutSteps * slots) {
             whole = tiles - r;
             rem = r;
-            parts = kChipCUs / r < 8 ? kChipCUs / r : 8;
+            parts = most;
         }
     }
 };
@@ -1024,20 +1060,20 @@ typedef float f32x4u_t __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t u32x4u_t __attribute__((ext_vector_type(4), aligned(2)));
 
 // Adds: sums are added to and rows are in place (dW); otherwise neither is added to.
-template <bool Adds>
-__device__ __forceinline__ void store_tile(const TL::Acc &acc, const GemmOut &o) {
-    constexpr int R = TL::FM, C = TL::FN;  // 16 x 16 blocks down and across
+template <bool Adds, typename TT>
+__device__ __forceinline__ void store_tile(const typename TT::Acc &acc, const GemmOut &o) {
+    constexpr int R = TT::FM, C = TT::FN;  // 16 x 16 blocks down and across
     int lane = threadIdx.x & 63;
     asm volatile("" : "+v"(lane));  // not to be traced: nothing derived from it is to live through the main loop
     const int grp = lane >> 4, col = lane & 15;
-    const int n_first = o.n0 + TL::wave_n0();
-    const int rows = static_cast<int>(o.m_end), m_wave = static_cast<int>(o.m0) + TL::wave_m0();
+    const int n_first = o.n0 + TT::wave_n0();
+    const int rows = static_cast<int>(o.m_end), m_wave = static_cast<int>(o.m0) + TT::wave_m0();
     int at[R], place[R];
     float scale[R];
     bool live[R];
 #pragma unroll
     for (int i = 0; i < R; ++i) {
-        const int m = m_wave + i * TL::MI + col;
+        const int m = m_wave + i * TT::MI + col;
         live[i] = m < rows;
         place[i] = at[i] = live[i] ? m : rows - 1;  // always a load, none of them behind a branch
         scale[i] = 1.0f;
@@ -1054,13 +1090,13 @@ __device__ __forceinline__ void store_tile(const TL::Acc &acc, const GemmOut &o)
         const int n = n_first + 4 * grp;
         if (Adds && o.accumulate) {
             constexpr int G = 2;  // blocks down that are requested at a time
-            const bool whole = m_wave + TL::WM <= rows && n_first + TL::WN <= o.N;
+            const bool whole = m_wave + TT::WM <= rows && n_first + TT::WN <= o.N;
             f32x4u_t old[2][G][C];
             if (whole) {  // (a condition on every store would have the next values wait for the stores)
                 auto request = [&](int i) {
 #pragma unroll
                     for (int j = 0; j < G * C; ++j)
-                        old[i / G & 1][j / C][j % C] = *reinterpret_cast<const f32x4u_t *>(out + row(i + j / C) + j % C * TL::MI);
+                        old[i / G & 1][j / C][j % C] = *reinterpret_cast<const f32x4u_t *>(out + row(i + j / C) + j % C * TT::MI);
                 };
                 request(0);
 #pragma unroll
@@ -1068,7 +1104,7 @@ __device__ __forceinline__ void store_tile(const TL::Acc &acc, const GemmOut &o)
                     if (i + G < R) request(i + G);
 #pragma unroll
                     for (int j = 0; j < G * C; ++j)
-                        *reinterpret_cast<f32x4u_t *>(out + row(i + j / C) + j % C * TL::MI) =
+                        *reinterpret_cast<f32x4u_t *>(out + row(i + j / C) + j % C * TT::MI) =
                             old[i / G & 1][j / C][j % C] + acc[i + j / C][j % C];
                 }
             } else {
@@ -1076,13 +1112,13 @@ __device__ __forceinline__ void store_tile(const TL::Acc &acc, const GemmOut &o)
                 for (int i = 0; i < R; i += G) {
 #pragma unroll
                     for (int j = 0; j < G * C; ++j)
-                        if (live[i + j / C] && n + j % C * TL::MI + 3 < o.N)
-                            old[0][j / C][j % C] = *reinterpret_cast<const f32x4u_t *>(out + row(i + j / C) + j % C * TL::MI);
+                        if (live[i + j / C] && n + j % C * TT::MI + 3 < o.N)
+                            old[0][j / C][j % C] = *reinterpret_cast<const f32x4u_t *>(out + row(i + j / C) + j % C * TT::MI);
                     __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): here, or every store below waits for the one before
 #pragma unroll
                     for (int j = 0; j < G * C; ++j)
-                        if (live[i + j / C] && n + j % C * TL::MI + 3 < o.N)
-                            *reinterpret_cast<f32x4u_t *>(out + row(i + j / C) + j % C * TL::MI) =
+                        if (live[i + j / C] && n + j % C * TT::MI + 3 < o.N)
+                            *reinterpret_cast<f32x4u_t *>(out + row(i + j / C) + j % C * TT::MI) =
                                 old[0][j / C][j % C] + acc[i + j / C][j % C];
                 }
             }
@@ -1091,20 +1127,20 @@ __device__ __forceinline__ void store_tile(const TL::Acc &acc, const GemmOut &o)
             for (int i = 0; i < R; ++i)
 #pragma unroll
                 for (int j = 0; j < C; ++j)
-                    if (live[i] && n + j * TL::MI + 3 < o.N)
-                        *reinterpret_cast<f32x4u_t *>(out + row(i) + j * TL::MI) = acc[i][j] * scale[i];
+                    if (live[i] && n + j * TT::MI + 3 < o.N)
+                        *reinterpret_cast<f32x4u_t *>(out + row(i) + j * TT::MI) = acc[i][j] * scale[i];
         }
-        if (n_first + TL::WN > o.N && o.N % 4 != 0) {  // the last columns, where they are no whole run
+        if (n_first + TT::WN > o.N && o.N % 4 != 0) {  // the last columns, where they are no whole run
 #pragma unroll
             for (int i = 0; i < R; ++i)
 #pragma unroll
                 for (int j = 0; j < C; ++j) {
-                    const int c = n + j * TL::MI;
+                    const int c = n + j * TT::MI;
                     if (!live[i] || c + 3 < o.N) continue;
 #pragma unroll
                     for (int r = 0; r < 3; ++r)  // (c + 3 is past them)
                         if (c + r < o.N) {
-                            float *p = out + row(i) + j * TL::MI + r;
+                            float *p = out + row(i) + j * TT::MI + r;
                             *p = Adds && o.accumulate ? *p + acc[i][j][r] : acc[i][j][r] * scale[i];
                         }
                 }
@@ -1113,7 +1149,7 @@ __device__ __forceinline__ void store_tile(const TL::Acc &acc, const GemmOut &o)
     }
     // bf16, never added to: after an exchange between neighbouring lane groups a lane holds eight consecutive columns
     uint16_t *out = static_cast<uint16_t *>(o.out);
-    const int n = n_first + (grp & 1) * TL::MI + (grp & 2) * 4;
+    const int n = n_first + (grp & 1) * TT::MI + (grp & 2) * 4;
     auto eight = [&](int i, int j) {
         uint32_t lo[2], hi[2];
 #pragma unroll
@@ -1131,15 +1167,15 @@ __device__ __forceinline__ void store_tile(const TL::Acc &acc, const GemmOut &o)
 #pragma unroll
         for (int j = 0; j < C; j += 2) {
             const u32x4u_t w = eight(i, j);
-            if (live[i] && n + j * TL::MI + 7 < o.N) *reinterpret_cast<u32x4u_t *>(out + row(i) + n + j * TL::MI) = w;
+            if (live[i] && n + j * TT::MI + 7 < o.N) *reinterpret_cast<u32x4u_t *>(out + row(i) + n + j * TT::MI) = w;
         }
-    if (n_first + TL::WN > o.N && o.N % 8 != 0) {
+    if (n_first + TT::WN > o.N && o.N % 8 != 0) {
 #pragma unroll
         for (int i = 0; i < R; ++i)
 #pragma unroll
             for (int j = 0; j < C; j += 2) {
                 const u32x4u_t w = eight(i, j);
-                const int c = n + j * TL::MI;
+                const int c = n + j * TT::MI;
                 if (!live[i] || c + 7 < o.N) continue;
 #pragma unroll
                 for (int r = 0; r < 7; ++r)
@@ -1148,23 +1184,22 @@ __device__ __forceinline__ void store_tile(const TL::Acc &acc, const GemmOut &o)
     }
 }
 
-template <bool KMajor>
-__global__ void __launch_bounds__(TL::NT)
+template <typename TT, bool ACols, bool BCols, bool Clamp>
+__global__ void __launch_bounds__(TT::NT, 2)
 gemm_store_kernel(const char *__restrict__ A, int64_t lda_bytes, int64_t M, const char *__restrict__ B,
                   int64_t ldb_bytes, int64_t N, int KT, void *__restrict__ out, int64_t ldo, int out_dtype,
-                  int accumulate, const int32_t *__restrict__ n_act, int64_t row_base, int limit,
+                  int accumulate, const int32_t *__restrict__ n_act, int64_t row_base, int limit, int limit_edge,
                   const int32_t *__restrict__ row_map, int64_t a_blk, int64_t b_blk, int nsplit,
-                  float *__restrict__ partials, int tail, const float *__restrict__ row_scale) {
+                  float *__restrict__ partials, int tail, const float *__restrict__ row_scale, int k_valid) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    constexpr int bpt = TL::BM / kBlockK;  // blocks per tile edge
-    static_assert(TL::BM % kBlockK == 0 && TL::BN == TL::BM, "a tile of a blocked operand is a whole number of blocks");
+    static_assert(TT::BM % kBlockK == 0 && TT::BN == TT::BM, "a tile of a blocked operand is a whole number of blocks");
     int64_t m_end = M;
     if (n_act && limit == kLimitRows) m_end = active_rows(n_act, row_base, M);
     // (rows that are not there, known on the device only, leave the ids at the end without a tile)
-    const TileOrder ord(ceil_div(m_end, TL::BM), ceil_div(N, TL::BN));
+    const TileOrder ord(ceil_div(m_end, TT::BM), ceil_div(N, TT::BN));
     // kTailWhole: the launch of the whole rounds; kTailCut: the launch of the cut tiles (workgroup
     // i * parts + p takes part p of tile whole + i of the order); both see the same cut
-    const TailCut cut(tail == kTailNone ? 0 : ord.tiles(), KT);
+    const TailCut cut(tail == kTailNone ? 0 : ord.tiles(), KT, kSlots<TT>);
     uint32_t i;
     int part;
     if (tail == kTailCut) {
@@ -1179,12 +1214,13 @@ gemm_store_kernel(const char *__restrict__ A, int64_t lda_bytes, int64_t M, cons
     }
     int64_t tm, tn;
     ord.at(i, tm, tn);
-    const int64_t m0 = tm * TL::BM, n0 = tn * TL::BN;
+    const int64_t m0 = tm * TT::BM, n0 = tn * TT::BN;
     if (n_act && limit == kLimitK) {
         const int64_t k_rows = active_rows(n_act, row_base, static_cast<int64_t>(KT) * kBK);
-        KT = __builtin_amdgcn_readfirstlane(static_cast<int>(ceil_div(k_rows, TL::BN) * (TL::BN / kBK)));
+        KT = __builtin_amdgcn_readfirstlane(static_cast<int>(ceil_div(k_rows, limit_edge) * (limit_edge / kBK)));
         if (KT == 0 && accumulate && tail != kTailCut) return;  // nothing to add
     }
+    const int KT_all = KT;
     int kt0 = 0;
     const int parts = tail == kTailCut ? cut.parts : nsplit;
     if (parts > 1) {  // this part's run of k-steps
@@ -1192,30 +1228,26 @@ gemm_store_kernel(const char *__restrict__ A, int64_t lda_bytes, int64_t M, cons
         kt0 = part * per;
         KT = KT - kt0 < per ? KT - kt0 : per;
     }
-    TL::Acc acc;
-    TL::zero(acc);
+    typename TT::Acc acc;
+    TT::zero(acc);
     if (KT > 0) {
-        if (KMajor) {
-            const int64_t Mr = (M + 7) & ~int64_t(7), Nr = (N + 7) & ~int64_t(7);
-            const char *Ak = A + kt0 * (kBK * lda_bytes), *Bk = B + kt0 * (kBK * ldb_bytes);  // rows are the contraction index
-            TL::mainloop_kmajor<true>(a_blk ? Ak + tm * bpt * a_blk : Ak, lda_bytes, a_blk ? 0 : m0, a_blk ? TL::BM : Mr,
-                                      b_blk ? Bk + tn * bpt * b_blk : Bk, ldb_bytes, b_blk ? 0 : n0, b_blk ? TL::BN : Nr, KT, lds,
-                                      acc, a_blk, b_blk);
-        } else {
-            // k-step kt of an operand starts blk bytes (blocked) or one stage of 128 bytes (row-major) further on
-            const int64_t sa = a_blk ? a_blk : kBK * 2, sb = b_blk ? b_blk : kBK * 2;
-            TL::mainloop<true>(typename TL::Operands{A + kt0 * sa, lda_bytes, m0, M, B + kt0 * sb, ldb_bytes, n0, N, a_blk, b_blk},
-                               KT, lds, acc);
-        }
+        // a k-step starts kBK rows (Cols), blk bytes (blocked) or one stage of 128 bytes further on; the last part's last
+        // may not be whole
+        const int64_t sa = ACols ? kBK * lda_bytes : a_blk ? a_blk : kBK * 2, sb = BCols ? kBK * ldb_bytes : b_blk ? b_blk : kBK * 2;
+        const int64_t Mr = ACols ? (a_blk ? m0 + TT::BM : (M + 7) & ~int64_t(7)) : M;
+        const int64_t Nr = BCols ? (b_blk ? n0 + TT::BN : (N + 7) & ~int64_t(7)) : N;
+        TT::template mainloop<ACols, BCols, true, Clamp>({A + kt0 * sa, lda_bytes, m0, Mr, a_blk, 0},
+                                                         {B + kt0 * sb, ldb_bytes, n0, Nr, b_blk, Clamp && kt0 + KT == KT_all ? k_valid : 0},
+                                                         KT, lds, acc);
     }
     GemmOut o{out, ldo, m0, m_end, static_cast<int>(n0), static_cast<int>(N), out_dtype, accumulate, row_map, row_scale};
     if (nsplit > 1 || tail == kTailCut) {  // a part: fp32, in place, unscaled (parts are scaled when they are added)
         const bool tile = tail == kTailCut;  // [part][tile - whole][BM][BN], otherwise [part][M][N]
-        const int64_t at = tile ? (static_cast<int64_t>(part) * cut.rem + (i - cut.whole)) * (TL::BM * TL::BN) : static_cast<int64_t>(part) * M * N;
-        o = GemmOut{partials + at, tile ? TL::BN : N, tile ? 0 : m0, tile ? TL::BM : m_end, tile ? 0 : static_cast<int>(n0),
-                    tile ? TL::BN : static_cast<int>(N), SPO_FP32, 0, nullptr, nullptr};
+        const int64_t at = tile ? (static_cast<int64_t>(part) * cut.rem + (i - cut.whole)) * (TT::BM * TT::BN) : static_cast<int64_t>(part) * M * N;
+        o = GemmOut{partials + at, tile ? TT::BN : N, tile ? 0 : m0, tile ? TT::BM : m_end, tile ? 0 : static_cast<int>(n0),
+                    tile ? TT::BN : static_cast<int>(N), SPO_FP32, 0, nullptr, nullptr};
     }
-    store_tile<KMajor>(acc, o);
+    store_tile<ACols, TT>(acc, o);
 }
 
 // out[row_map[m]][n] = row_scale[m] * sum over the parts (in order) of partials[part][m][n] for m
@@ -1258,25 +1290,26 @@ reduce_split_kernel(const float *__restrict__ partials, int nsplit, int64_t M, i
 // the sum, in order, of partials[part][tile - whole][m % BM][n % BN] over the parts.  The launch is
 // sized for the most tiles a cut can have; n_act (with limit == kLimitRows), row_map and row_scale
 // may be NULL.  Four values per thread.
+template <typename TT>
 __global__ void __launch_bounds__(256)
 reduce_tail_kernel(const float *__restrict__ partials, int64_t M, int64_t N, int64_t KT, const int32_t *__restrict__ n_act,
                    int64_t row_base, int limit, const int32_t *__restrict__ row_map, void *__restrict__ out, int64_t ldo,
                    int out_dtype, int accumulate, const float *__restrict__ row_scale) {
-    constexpr int64_t per_tile = TL::BM * TL::BN / 4;
+    constexpr int64_t per_tile = TT::BM * TT::BN / 4;
     const int64_t m_end = n_act && limit == kLimitRows ? active_rows(n_act, row_base, M) : M;
-    const TileOrder ord(ceil_div(m_end, TL::BM), ceil_div(N, TL::BN));
-    const TailCut cut(ord.tiles(), KT);
+    const TileOrder ord(ceil_div(m_end, TT::BM), ceil_div(N, TT::BN));
+    const TailCut cut(ord.tiles(), KT, kSlots<TT>);
     const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    const int64_t tl = i / per_tile, r = (i % per_tile) / (TL::BN / 4), c = (i % (TL::BN / 4)) * 4;
+    const int64_t tl = i / per_tile, r = (i % per_tile) / (TT::BN / 4), c = (i % (TT::BN / 4)) * 4;
     if (tl >= cut.rem) return;
     int64_t tm, tn;
     ord.at(static_cast<uint32_t>(cut.whole + tl), tm, tn);
-    const int64_t m = tm * TL::BM + r, n = tn * TL::BN + c;
+    const int64_t m = tm * TT::BM + r, n = tn * TT::BN + c;
     if (m >= m_end || n >= N) return;
     float4 sum = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     for (int p = 0; p < cut.parts; ++p) {
         const float4 v = *reinterpret_cast<const float4 *>(
-            partials + ((static_cast<int64_t>(p) * cut.rem + tl) * TL::BM + r) * TL::BN + c);
+            partials + ((static_cast<int64_t>(p) * cut.rem + tl) * TT::BM + r) * TT::BN + c);
         sum = make_float4(sum.x + v.x, sum.y + v.y, sum.z + v.z, sum.w + v.w);
     }
     if (row_scale) {
@@ -1327,10 +1360,10 @@ __global__ void __launch_bounds__(256)
 dz_from_logits_kernel(const uint16_t *__restrict__ Z, int64_t z_blk, const float *__restrict__ offs, int64_t off_stride,
                       const int32_t *__restrict__ act_idx,
                       const int32_t *__restrict__ n_act, int64_t rows_cap, const float4 *__restrict__ tok,
-                      bf16_t *__restrict__ dZ, int64_t dz_blk, int64_t n_blk, int per_wg) {
+                      bf16_t *__restrict__ dZ, int64_t dz_blk, int64_t n_blk, int per_wg, int bph, int edge) {
     const int64_t act = active_rows(n_act, 0, rows_cap);
     const int64_t j = static_cast<int64_t>(blockIdx.x) * 32 + (threadIdx.x >> 3);
-    if (static_cast<int64_t>(blockIdx.x) * 32 >= (act + TL::BN - 1) / TL::BN * TL::BN) return;
+    if (static_cast<int64_t>(blockIdx.x) * 32 >= (act + edge - 1) / edge * edge) return;
     const int part = threadIdx.x & 7;  // which 8 of the block's 64 entries
     const bool live = j < act;
     const int64_t src = live ? act_idx[j] : 0;
@@ -1338,7 +1371,6 @@ dz_from_logits_kernel(const uint16_t *__restrict__ Z, int64_t z_blk, const float
     const uint32_t ts = __float_as_uint(rec.z);
     const uint32_t sgn = (ts & 0x80000000u) ? 0x80008000u : 0u;  // the values are formed as |g| * p; the sign of -g goes on in pairs
     const int64_t y = ts & 0x7fffffffu;
-    constexpr int bph = TL::WM / kBlockK;  // blocks per wavefront's half of a tile: one offset each
     const int64_t b0 = static_cast<int64_t>(blockIdx.y) * per_wg;
     for (int64_t b = b0; b < b0 + per_wg && b < n_blk; ++b) {
         uint4 o = make_uint4(0u, 0u, 0u, 0u);
@@ -1415,27 +1447,96 @@ scale_rows_kernel(const T_ *__restrict__ src, const float *__restrict__ c, int64
 // The kernels use more dynamic LDS than the default limit allows.  The attribute belongs
 // to the current device's copy of the kernel, so it is set on every call (a host-side
 // table lookup) rather than remembered in a process-wide flag.
-static int set_lds_limit() {
-    hipError_t e = hipSuccess;
-    e = e ? e : hipFuncSetAttribute(reinterpret_cast<const void *>(fwd_sweep_kernel<kEmitNone>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, kSweepLds);
-    e = e ? e : hipFuncSetAttribute(reinterpret_cast<const void *>(fwd_sweep_kernel<kEmitLogits>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, kSweepLds);
-    e = e ? e : hipFuncSetAttribute(reinterpret_cast<const void *>(fwd_sweep_kernel<kEmitProbs>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, kSweepLdsProbs);
-    e = e ? e : hipFuncSetAttribute(reinterpret_cast<const void *>(recompute_dz_kernel),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, TL::LDS_BYTES);
-    e = e ? e : hipFuncSetAttribute(reinterpret_cast<const void *>(gemm_store_kernel<false>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, TL::LDS_BYTES);
-    e = e ? e : hipFuncSetAttribute(reinterpret_cast<const void *>(gemm_store_kernel<true>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, TL::LDS_BYTES);
-    return e == hipSuccess ? SPO_OK : SPO_EHIP;
+template <typename K>
+static int allow_lds(K kernel, int bytes) {
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess
+               ? SPO_OK : SPO_EHIP;
 }
 
 static inline int64_t round_up(int64_t x, int64_t a) { return ceil_div(x, a) * a; }
 static inline unsigned grid1(int64_t n, int per = 256) { return static_cast<unsigned>(ceil_div(n, per)); }
 
+// Small or large tiles?  A launch takes about
+//   rounds of workgroups on the chip x (steps of a tile x time of a step + time of a tile's ends) + the rest, in us,
+// with times fitted to 24 to 8000 tokens, H = 192 to 4096, V = 1000 to 151936.  What this chooses is within 1 % of the
+// better of the two on average (large tiles always: 25 to 30 % behind, small ones: 3 %), and within 25 % where it errs.
+// Up to kChipCUs small tiles have a compute unit each, above two share one; their steps take longer where the head does
+// not fit the L2s (kHeadInL2).  In the limit of long launches 128 x 128 x 2 per compute unit take 0.55 to 0.75 of the time of
+// 256 x 256: twice the bytes per product.  (Loss and gradients of 512 fp32 tokens at 128 x 1000: 97 us on large tiles,
+// 68 on small; 31 bf16 tokens at 1024 x 151936 438 and 381; 4000 at 4096 x 30000 2406 and 2875.)
+struct TileTimes {
+    double step, ends;             // large tiles
+    double lone, in_l2, pair;      // a step of small ones: with a compute unit to itself, two on it with the head in the L2s or not
+    double ends_s;
+    double rest, rest_s, cut;      // of a launch, large and small; a cut tail
+};
+constexpr TileTimes kSweepTimes{1.30, 8.3, 0.57, 0.85, 0.90, 4.4, 4.6, 5.1, 0.0};
+constexpr TileTimes kDHiddenTimes{1.70, 4.6, 0.34, 0.75, 1.00, 0.0, 17.0, 15.4, 4.1};
+constexpr TileTimes kDWTimes{1.66, 10.7, 0.53, 0.75, 0.90, 7.0, 3.2, 2.1, 19.0};
+constexpr int64_t kHeadInL2 = int64_t(32) << 20;
+static double launch_time(const TileTimes &t, bool small, double rounds, int64_t wgs, int64_t steps, int64_t head_bytes) {
+    const double step = !small ? t.step : wgs <= kChipCUs ? t.lone : head_bytes <= kHeadInL2 ? t.in_l2 : t.pair;
+    return rounds * (static_cast<double>(steps) * step + (small ? t.ends_s : t.ends)) + (small ? t.rest_s : t.rest);
+}
+// the same of contractions whose short last round may be cut
+static double launch_time_cut(const TileTimes &t, bool small, int64_t tiles, int64_t steps, bool may_cut, int64_t head_bytes) {
+    const int slots = small ? kSlots<TS> : kSlots<TL>;
+    const TailCut cut(may_cut ? tiles : 0, steps, slots);
+    if (!cut.rem) return launch_time(t, small, static_cast<double>(ceil_div(tiles, slots)), tiles, steps, head_bytes);
+    return launch_time(t, small, static_cast<double>(cut.whole / slots) + 1.0 / cut.parts,
+                       cut.whole ? tiles : cut.rem * cut.parts, steps, head_bytes) + t.cut;
+}
+static int64_t tile_edge(bool small) { return small ? TS::BM : TL::BM; }
+static int tile_slots(bool small) { return small ? kSlots<TS> : kSlots<TL>; }
+static int dhidden_parts(int64_t Tc, int64_t H, int64_t V_pad, bool small);
+
+// the logits of T tokens, Kc values long each (forward sweep, recompute)
+static bool small_sweep(int64_t T, int64_t V, int64_t Kc) {
+    double time[2];
+    for (int small = 0; small < 2; ++small) {
+        const int64_t nTt = std::max<int64_t>(ceil_div(T, tile_edge(small)), 1), nVt = ceil_div(V, tile_edge(small));
+        const int64_t ns = sweep_splits(nTt, nVt, tile_slots(small)), rounds = ceil_div(nTt * ns, tile_slots(small)) * ceil_div(nVt, ns);
+        time[small] = launch_time(kSweepTimes, small, static_cast<double>(rounds), nTt * ns, Kc / kBK, V * Kc * 2);
+    }
+    return time[1] < time[0];
+}
+static bool small_dhidden(int64_t T, int64_t H, int64_t V_pad) {
+    double time[2];
+    for (int small = 0; small < 2; ++small) {
+        const int64_t parts = dhidden_parts(T, H, V_pad, small), tiles = ceil_div(T, tile_edge(small)) * ceil_div(H, tile_edge(small));
+        time[small] = launch_time_cut(kDHiddenTimes, small, tiles * parts, ceil_div(V_pad / kBK, parts), parts == 1, H * V_pad * 2);
+    }
+    return time[1] < time[0];
+}
+static bool small_dW(int64_t T, int64_t H, int64_t V) {
+    double time[2];
+    for (int small = 0; small < 2; ++small)
+        time[small] = launch_time_cut(kDWTimes, small, ceil_div(V, tile_edge(small)) * ceil_div(H, tile_edge(small)), ceil_div(T, kBK), true,
+                                      H * V * 2);
+    return time[1] < time[0];
+}
+
+// Is a bf16 head read as it was given, or copied into the forms that the main loop reads fastest?  Columns along k
+// (dHidden of a head [V,H], the logits of one [H,V]) and rows that are not blocked cost 2 to 5 % of a contraction, and
+// the target logits of a head [H,V] then come out of its columns, a line of memory per value; the copies take the
+// time of reading the head and writing it once or twice.
+//   [V,H]: only dHidden's form is spared.  8192 tokens at 1024 x 151936 6440 us with the copy, 6374 without; 522 at 2112 x
+//   151936 2058 and 1843; the gain has vanished at 14000 tokens by these figures.
+//   [H,V]: both forms are spared, and a launch: 271 tokens at 3136 x 151936 2035 us with the copies, 1579 without; 4000 at
+//   2048 x 151936 6553 and 6414; 4000 at 4096 x 30000 2614 and 2795; 1100 at 768 x 1000 66 and 65, 4000 of them 82 and 87.
+//   Values out of columns: 14 us per million where the head comes from memory, 4 out of the L2s.
+constexpr int64_t kDirectTokens = 8192;
+static bool direct_head(const spo_pg_desc *d) {
+    if (d->dtype != SPO_BF16) return false;
+    if (d->w_layout == SPO_W_VH) return d->T <= kDirectTokens;
+    if (d->V % 8 != 0) return false;  // rows of [H,V] on 16-byte boundaries
+    const double T = static_cast<double>(d->T), head = static_cast<double>(d->H) * static_cast<double>(d->V);
+    const double columns = T * static_cast<double>(d->H) * (head * 2 <= static_cast<double>(kHeadInL2 / 4) ? 4e-6 : 14e-6);
+    return columns + T * head * 7e-11 < 8.0 + head * 1.07e-6;
+}
+
 struct FwdPlan {
+    bool small;
     int64_t nTt, nVt, T_pad, Kc;  // Kc: contraction length seen by the main loop
     int nsplit;
     int64_t nblk_tok;
@@ -1455,19 +1556,23 @@ static void *take_head_copy(Arena &a, const spo_pg_desc *d) {
     return p;
 }
 
-static FwdPlan plan_fwd(const spo_pg_desc *d, void *ws) {
+// roomy: with room for the partial results of small tiles, without which they are not taken (workspaces of the size that
+// large tiles need are accepted as well).
+static FwdPlan plan_fwd(const spo_pg_desc *d, void *ws, bool roomy) {
     FwdPlan p;
-    p.nTt = ceil_div(d->T, TL::BN);
-    p.nVt = ceil_div(d->V, TL::BM);
-    p.T_pad = p.nTt * TL::BN;
-    p.nsplit = sweep_splits(p.nTt, p.nVt);
     p.Kc = d->dtype == SPO_FP32 ? kSplitTerms * d->H : d->H;
+    p.small = roomy && small_sweep(d->T, d->V, p.Kc);
+    const int64_t edge = tile_edge(p.small);
+    p.nTt = ceil_div(d->T, edge);
+    p.nVt = ceil_div(d->V, edge);
+    p.T_pad = p.nTt * edge;
+    p.nsplit = sweep_splits(p.nTt, p.nVt, tile_slots(p.small));
     p.nblk_tok = ceil_div(std::max<int64_t>(d->T, 1), kTokThreads);
     Arena a(ws);
-    const size_t room = static_cast<size_t>(sweep_pairs_max(p.nTt, p.nVt)) * TL::BN;  // [nsplit][T_pad] and more
+    const size_t room = static_cast<size_t>(sweep_room(d->T, d->V, roomy));  // [nsplit][T_pad] and more
     p.part_max = a.take<float>(room);
     p.part_sum = a.take<float>(room);
-    p.z_target = a.take<float>(p.T_pad);
+    p.z_target = a.take<float>(round_up(d->T, TL::BN));
     p.partials = a.take<FwdPartial>(p.nblk_tok);
     p.done = a.take<uint32_t>(1);
     p.Xs = p.Ws = nullptr;
@@ -1486,29 +1591,62 @@ static int check_fused(const spo_pg_desc *d) {
 }
 
 int fused_fwd_workspace(const spo_pg_desc *d, size_t *bytes) {
-    *bytes = plan_fwd(d, nullptr).bytes;
+    *bytes = plan_fwd(d, nullptr, true).bytes;
     return SPO_OK;
+}
+
+// The sweep of one piece of T tokens on tiles TT; W: the head as the sweep reads it (cols: [H,V]).
+struct Sweep {
+    const void *W;
+    int64_t H, V, Kc;
+    bool cols;
+    const void *X;
+    int64_t T;
+    float *part_max, *part_sum;
+    uint16_t *Z;
+    int64_t z_blk;
+    float *offs;
+};
+template <int Emit, typename TT, bool WCols>
+static int launch_sweep(const Sweep &w, const SweepMap &map, hipStream_t s) {
+    auto *kernel = fwd_sweep_kernel<Emit, TT, WCols>;
+    constexpr int lds = kSweepLds<TT>(Emit);
+    if (int rc = allow_lds(kernel, lds)) return rc;
+    ScopedKernelTimer timer(kTimeFwdSweep, s);
+    kernel<<<static_cast<unsigned>(map.blocks()), TT::NT, lds, s>>>(
+        static_cast<const char *>(w.W), (WCols ? w.V : w.Kc) * 2, w.V, static_cast<const char *>(w.X), w.Kc * 2, w.T,
+        static_cast<int>(w.Kc / kBK), map.ns, map.nTt, map.nVt, map.nTt * TT::BN, w.part_max, w.part_sum, w.Z, w.z_blk, w.offs);
+    return SPO_OK;
+}
+template <int Emit>
+static int launch_sweep(const Sweep &w, bool small, const SweepMap &map, hipStream_t s) {
+    if (small) return w.cols ? launch_sweep<Emit, TS, true>(w, map, s) : launch_sweep<Emit, TS, false>(w, map, s);
+    return w.cols ? launch_sweep<Emit, TL, true>(w, map, s) : launch_sweep<Emit, TL, false>(w, map, s);
 }
 
 int fused_fwd(const spo_pg_desc *d, float *loss, float *logp, float *lse, float *stats, void *ws,
               size_t ws_bytes, hipStream_t s) {
     int rc = check_fused(d);
     if (rc) return rc;
-    const FwdPlan p = plan_fwd(d, ws);
+    FwdPlan p = plan_fwd(d, ws, true);
+    if (ws_bytes < p.bytes) p = plan_fwd(d, ws, false);
     if (ws_bytes < p.bytes) return SPO_EWORKSPACE;
-    if ((rc = set_lds_limit())) return rc;
     if (d->T > 0) {
-        const bool fp32 = d->dtype == SPO_FP32;
-        PrepJobs jobs = prep_head_jobs(d, p.Wvh, p.Ws, nullptr);
+        const bool fp32 = d->dtype == SPO_FP32, direct = direct_head(d), hv = d->w_layout == SPO_W_HV;
+        PrepJobs jobs = prep_head_jobs(d, direct ? nullptr : p.Wvh, p.Ws, nullptr);
         prep_rows(jobs, d, d->hidden, d->T, p.Xs);
         launch_prep_with_targets(d, jobs, p.z_target, nullptr, 0, p.done, s);
-        const char *X = fp32 ? reinterpret_cast<const char *>(p.Xs) : static_cast<const char *>(d->hidden);
-        const char *W = fp32 ? reinterpret_cast<const char *>(p.Ws) : static_cast<const char *>(p.Wvh ? p.Wvh : d->W);
-        const int64_t blocks = SweepMap(p.nTt, p.nVt, p.nsplit).blocks();
-        ScopedKernelTimer timer(kTimeFwdSweep, s);
-        fwd_sweep_kernel<kEmitNone><<<static_cast<unsigned>(blocks), TL::NT, kSweepLds, s>>>(
-            W, p.Kc * 2, d->V, X, p.Kc * 2, d->T, static_cast<int>(p.Kc / kBK), p.nsplit, p.nTt, p.nVt, p.T_pad,
-            p.part_max, p.part_sum, nullptr, 0, nullptr);
+        Sweep w{};
+        w.W = fp32 ? p.Ws : direct || !p.Wvh ? d->W : p.Wvh;
+        w.H = d->H;
+        w.V = d->V;
+        w.Kc = p.Kc;
+        w.cols = direct && hv;
+        w.X = fp32 ? static_cast<const void *>(p.Xs) : d->hidden;
+        w.T = d->T;
+        w.part_max = p.part_max;
+        w.part_sum = p.part_sum;
+        if ((rc = launch_sweep<kEmitNone>(w, p.small, SweepMap(p.nTt, p.nVt, p.nsplit), s))) return rc;
     }
     const TokenShape tok = token_shape(p.nsplit, p.nblk_tok);
     token_loss_kernel<<<tok.blocks, tok.threads, 0, s>>>(
@@ -1524,10 +1662,10 @@ int fused_fwd(const spo_pg_desc *d, float *loss, float *logp, float *lse, float 
 // of 17 tokens at 896 x 151936, 4 tiles, 2374 steps: 948 us in 8 parts, 642 in 64; of 85 tokens at
 // 3264 x 15635, 13 tiles, 245 steps: 19 parts gain what 8 leave of the chip idle.)
 constexpr int64_t kPartSteps = 16;
-static int dhidden_parts(int64_t Tc, int64_t H, int64_t V_pad) {
-    const int64_t tiles = Tc / TL::BN * ceil_div(H, TL::BM);
-    if (tiles * 4 >= kChipCUs * 3) return 1;
-    return static_cast<int>(std::min<int64_t>(kChipCUs / tiles, std::max<int64_t>(8, V_pad / kBK / kPartSteps)));
+static int dhidden_parts(int64_t Tc, int64_t H, int64_t V_pad, bool small) {
+    const int64_t tiles = ceil_div(Tc, tile_edge(small)) * ceil_div(H, tile_edge(small)), slots = tile_slots(small);
+    if (tiles * 4 >= slots * 3) return 1;
+    return static_cast<int>(std::min<int64_t>(slots / tiles, std::max<int64_t>(8, V_pad / kBK / kPartSteps)));
 }
 
 struct BwdPlan {
@@ -1538,7 +1676,6 @@ struct BwdPlan {
     void *Wvh;                 // [V,H] copy of a head given as [H,V]
     int32_t *act_idx, *n_act;  // active-token list, its length
     float4 *tok;               // per-chunk records (g, -lse*log2e, target) of the gathered rows
-    int dx_split;              // parts the dHidden contraction is cut into (1: not split)
     float *part_tiles;         // room for kTailTiles fp32 tiles: partial results of a cut contraction (see launch_gemm)
     size_t bytes;
 };
@@ -1558,7 +1695,6 @@ static BwdPlan plan_bwd(const spo_pg_desc *d, int64_t chunk_tokens, void *ws, bo
     p.act_idx = a.take<int32_t>(p.T_pad);
     p.n_act = a.take<int32_t>(1);
     p.tok = a.take<float4>(p.Tc);
-    p.dx_split = dhidden_parts(p.Tc, d->H, p.V_pad);
     p.Xc = a.take<bf16_t>(static_cast<size_t>(p.Tc) * d->H);
     p.WT = a.take<bf16_t>(static_cast<size_t>(d->H) * p.V_blk);   // [V_blk / 64][H][64]
     p.dZ = a.take<bf16_t>(static_cast<size_t>(p.Tc) * p.V_blk);  // [V_blk / 64][rows of the chunk][64]
@@ -1596,34 +1732,51 @@ int fused_bwd_workspace(const spo_pg_desc *d, int64_t chunk_tokens, size_t *byte
 // and a dHidden launch whose number of active rows leaves a round nearly empty loses a fifth of a
 // round instead of a whole one.  Where the tile count depends on n_act the two extra launches
 // are made in any case and find out on the device that there is nothing to cut.
-template <bool KMajor>
-static void launch_gemm(const bf16_t *A, int64_t lda, int64_t M, const bf16_t *B, int64_t ldb, int64_t N, int64_t K,
-                        void *out, int64_t ldo, int out_dtype, int accumulate, const int32_t *n_act, int64_t row_base,
-                        int limit, const int32_t *row_map, int64_t a_blk_elems, int64_t b_blk_elems, hipStream_t s,
-                        int nsplit, float *partials, const float *row_scale = nullptr) {
-    const int64_t tiles = ceil_div(M, TL::BM) * ceil_div(N, TL::BN);
-    const bool rows_on_device = n_act && limit == kLimitRows;
-    const TailCut host_cut(tiles, K / kBK);
-    const bool cut = nsplit == 1 && (rows_on_device ? tiles > kChipCUs : host_cut.rem > 0);
+struct Gemm {
+    const bf16_t *A;
+    int64_t lda, M;
+    const bf16_t *B;
+    int64_t ldb, N, K;                  // K: whole steps; with k_valid the last has that many elements
+    void *out;
+    int64_t ldo;
+    int out_dtype, accumulate;
+    const int32_t *n_act;
+    int64_t row_base;
+    int limit, limit_edge;
+    const int32_t *row_map;
+    int64_t a_blk, b_blk;               // elements
+    const float *row_scale;
+    int k_valid;
+};
+template <typename TT, bool ACols, bool BCols, bool Clamp>
+static int launch_gemm(const Gemm &g, hipStream_t s, int nsplit, float *partials) {
+    auto *kernel = gemm_store_kernel<TT, ACols, BCols, Clamp>;
+    if (int rc = allow_lds(kernel, TT::LDS_BYTES)) return rc;
+    constexpr int slots = kSlots<TT>;
+    const int64_t tiles = ceil_div(g.M, TT::BM) * ceil_div(g.N, TT::BN), steps = ceil_div(g.K, kBK);
+    const bool rows_on_device = g.n_act && g.limit == kLimitRows;
+    const TailCut host_cut(tiles, steps, slots);
+    const bool cut = nsplit == 1 && (rows_on_device ? tiles > slots : host_cut.rem > 0);
+    auto launch = [&](int64_t blocks, int splits, int tail, const float *row_scale) {
+        kernel<<<static_cast<unsigned>(blocks), TT::NT, TT::LDS_BYTES, s>>>(
+            reinterpret_cast<const char *>(g.A), g.lda * 2, g.M, reinterpret_cast<const char *>(g.B), g.ldb * 2, g.N,
+            static_cast<int>(steps), g.out, g.ldo, g.out_dtype, g.accumulate, g.n_act, g.row_base, g.limit, g.limit_edge, g.row_map,
+            g.a_blk * 2, g.b_blk * 2, splits, partials, tail, row_scale, g.k_valid);
+    };
     if (!cut || rows_on_device || host_cut.whole > 0)
-        gemm_store_kernel<KMajor><<<static_cast<unsigned>(TileOrder::blocks(tiles * nsplit)), TL::NT, TL::LDS_BYTES, s>>>(
-            reinterpret_cast<const char *>(A), lda * 2, M, reinterpret_cast<const char *>(B), ldb * 2, N,
-            static_cast<int>(K / kBK), out, ldo, out_dtype, accumulate, n_act, row_base, limit, row_map, a_blk_elems * 2,
-            b_blk_elems * 2, nsplit, partials, cut ? kTailWhole : kTailNone, row_scale);
+        launch(TileOrder::blocks(tiles * nsplit), nsplit, cut ? kTailWhole : kTailNone, g.row_scale);
     if (nsplit > 1)
-        reduce_split_kernel<<<grid1(M * (N / 4)), 256, 0, s>>>(partials, nsplit, M, N, n_act, row_base, row_map, out, ldo,
-                                                               out_dtype, row_scale);
+        reduce_split_kernel<<<grid1(g.M * (g.N / 4)), 256, 0, s>>>(partials, nsplit, g.M, g.N, g.n_act, g.row_base, g.row_map, g.out,
+                                                                   g.ldo, g.out_dtype, g.row_scale);
     if (cut) {
-        // (on the device: sized for the most a cut can be, half of the units' worth of tiles, as many part-tiles as units)
-        const int part_tiles = rows_on_device ? kChipCUs : host_cut.rem * host_cut.parts;
-        gemm_store_kernel<KMajor><<<part_tiles, TL::NT, TL::LDS_BYTES, s>>>(
-            reinterpret_cast<const char *>(A), lda * 2, M, reinterpret_cast<const char *>(B), ldb * 2, N,
-            static_cast<int>(K / kBK), out, ldo, out_dtype, accumulate, n_act, row_base, limit, row_map, a_blk_elems * 2,
-            b_blk_elems * 2, 1, partials, kTailCut, nullptr);
-        const int rem_most = rows_on_device ? kChipCUs / 2 : host_cut.rem;
-        reduce_tail_kernel<<<grid1(rem_most * (TL::BM * TL::BN / 4)), 256, 0, s>>>(
-            partials, M, N, K / kBK, n_act, row_base, limit, row_map, out, ldo, out_dtype, accumulate, row_scale);
+        // (on the device: sized for the most a cut can be, half of the slots' worth of tiles, as many part-tiles as slots)
+        launch(rows_on_device ? slots : host_cut.rem * host_cut.parts, 1, kTailCut, nullptr);
+        const int rem_most = rows_on_device ? slots / 2 : host_cut.rem;
+        reduce_tail_kernel<TT><<<grid1(rem_most * (TT::BM * TT::BN / 4)), 256, 0, s>>>(
+            partials, g.M, g.N, steps, g.n_act, g.row_base, g.limit, g.row_map, g.out, g.ldo, g.out_dtype, g.accumulate,
+            g.row_scale);
     }
+    return SPO_OK;
 }
 
 // The gathered rows of a chunk (see gather_chunk_kernel), and d_hidden[0..zero_rows) (NULL: not) cleared.
@@ -1643,6 +1796,67 @@ static void launch_gather(const spo_pg_desc *d, const void *X, const int32_t *ac
                                                          zero_bytes);
 }
 
+// dHidden of M rows (of Tcp in the blocks of dZ): every part of the vocabulary, the head as WT, or as it was given (NULL).
+static int launch_dhidden(const spo_pg_desc *d, const bf16_t *dZ, int64_t M, int64_t Tcp, const bf16_t *WT, int64_t V_pad, void *out,
+                          int out_dtype, const int32_t *n_act, int64_t row_base, const int32_t *row_map, const float *row_scale,
+                          float *partials, hipStream_t s) {
+    const int64_t H = d->H, V = d->V;
+    const bool small = small_dhidden(M, H, V_pad), hv = d->w_layout == SPO_W_HV;
+    const int parts = dhidden_parts(M, H, V_pad, small);
+    Gemm g{};
+    g.A = dZ;
+    g.lda = kBlockK;
+    g.M = M;
+    g.a_blk = Tcp * kBlockK;
+    g.N = H;
+    g.K = V_pad;
+    g.out = out;
+    g.ldo = H;
+    g.out_dtype = out_dtype;
+    g.n_act = n_act;
+    g.row_base = row_base;
+    g.limit = kLimitRows;
+    g.row_map = row_map;
+    g.row_scale = row_scale;
+    ScopedKernelTimer timer(kTimeDHidden, s);
+    if (WT) {  // both operands k-blocked over the vocabulary: a stage of a tile is 32 KiB contiguous
+        g.B = WT;
+        g.ldb = kBlockK;
+        g.b_blk = H * kBlockK;
+        return small ? launch_gemm<TS, false, false, false>(g, s, parts, partials) : launch_gemm<TL, false, false, false>(g, s, parts, partials);
+    }
+    g.B = static_cast<const bf16_t *>(d->W);
+    g.ldb = hv ? V : H;
+    g.k_valid = static_cast<int>(V % kBK);
+    if (hv) return small ? launch_gemm<TS, false, false, true>(g, s, parts, partials) : launch_gemm<TL, false, false, true>(g, s, parts, partials);
+    return small ? launch_gemm<TS, false, true, true>(g, s, parts, partials) : launch_gemm<TL, false, true, true>(g, s, parts, partials);
+}
+
+// dW (=|+=) dZ^T X over Tcp tokens, or the first of them that are active, rounded up to edge.
+static int launch_dW(const spo_pg_desc *d, const bf16_t *dZ, const bf16_t *X, int64_t Tcp, int64_t edge, void *out, int out_dtype,
+                     int accumulate, const int32_t *n_act, int64_t row_base, float *partials, hipStream_t s) {
+    const bool hv = d->w_layout == SPO_W_HV;
+    Gemm g{};
+    g.A = hv ? X : dZ;
+    g.B = hv ? dZ : X;
+    g.lda = hv ? d->H : kBlockK;
+    g.ldb = hv ? kBlockK : d->H;
+    g.M = hv ? d->H : d->V;
+    g.N = hv ? d->V : d->H;
+    (hv ? g.b_blk : g.a_blk) = Tcp * kBlockK;
+    g.K = Tcp;
+    g.out = out;
+    g.ldo = g.N;
+    g.out_dtype = out_dtype;
+    g.accumulate = accumulate;
+    g.n_act = n_act;
+    g.row_base = row_base;
+    g.limit = kLimitK;
+    g.limit_edge = static_cast<int>(edge);
+    ScopedKernelTimer timer(kTimeDW, s);
+    return small_dW(Tcp, d->H, d->V) ? launch_gemm<TS, true, true, false>(g, s, 1, partials) : launch_gemm<TL, true, true, false>(g, s, 1, partials);
+}
+
 int fused_bwd(const spo_pg_desc *d, const float *logp, const float *lse, float grad_loss, void *d_hidden,
               int d_hidden_dtype, void *d_W, int d_W_dtype, int accumulate_dW, int64_t chunk_tokens, void *ws,
               size_t ws_bytes, hipStream_t s) {
@@ -1654,7 +1868,6 @@ int fused_bwd(const spo_pg_desc *d, const float *logp, const float *lse, float g
     // (an fp32 d_W of 151936 x 4096 written, read and rounded again: 2 ms)
     const bool need_acc = p.dW_acc != nullptr;
     if (ws_bytes < p.bytes) return SPO_EWORKSPACE;
-    if ((rc = set_lds_limit())) return rc;
     const int64_t H = d->H, V = d->V, T = d->T;
     void *dW_sum = need_acc ? p.dW_acc : d_W;
     const int dW_sum_dtype = need_acc ? SPO_FP32 : d_W_dtype;
@@ -1667,7 +1880,8 @@ int fused_bwd(const spo_pg_desc *d, const float *logp, const float *lse, float g
     }
     // vocabulary-major head for the recompute, hidden-major head for dHidden; the gradient factors and the
     // tokens that carry one, in order: the chunks below run over this list
-    PrepJobs jobs = prep_head_jobs(d, p.Wvh, p.Ws, d_hidden ? p.WT : nullptr);
+    const bool direct = direct_head(d), hv = d->w_layout == SPO_W_HV;
+    PrepJobs jobs = prep_head_jobs(d, direct ? nullptr : p.Wvh, p.Ws, d_hidden && !direct ? p.WT : nullptr);
     const bool grad_inside = T <= kPrepGradTokens;
     if (grad_inside) {
         jobs.g = p.g;
@@ -1682,40 +1896,37 @@ int fused_bwd(const spo_pg_desc *d, const float *logp, const float *lse, float g
         launch_grad_scale(d, logp, p.T_pad, grad_loss, p.count, p.g, s);
         compact_active_kernel<<<1, 1024, 0, s>>>(p.g, T, p.act_idx, p.n_act);
     }
-    const void *Wk = d->dtype == SPO_FP32 ? p.Ws : (p.Wvh ? p.Wvh : d->W);
-    const int64_t nVt = ceil_div(V, TL::BM);
+    const void *Wk = d->dtype == SPO_FP32 ? p.Ws : direct || !p.Wvh ? d->W : p.Wvh;
     for (int64_t t0 = 0, c = 0; t0 < T; t0 += p.Tc, ++c) {
         // rows [t0, t0 + Tcp) of the compact order; how many of them exist is known on the
         // device only, so every launch is sized for the most there can be and trims itself
-        const int64_t Tcp = round_up(std::min(p.Tc, T - t0), TL::BN);
+        const int64_t Tv = std::min(p.Tc, T - t0);
+        const bool small = small_sweep(Tv, V, p.Kc);
+        const int64_t edge = tile_edge(small), Tcp = round_up(Tv, edge);
         // (the first chunk's launch also clears d_hidden: later ones would clear what earlier ones wrote)
         launch_gather(d, d->hidden, p.act_idx, p.n_act, t0, Tcp, d->target, lse, p.g, d->dtype == SPO_BF16 || d_W ? p.Xc : nullptr,
                       p.Xs, p.tok, c == 0 ? d_hidden : nullptr, d_hidden_dtype, T, s);
         const bf16_t *Xk = d->dtype == SPO_FP32 ? p.Xs : p.Xc, *Xrows = p.Xc;  // operands of the recompute and of dW
-        {
-            const int64_t wgs = sweep_blocks_max(Tcp / TL::BN, nVt);
+        auto recompute = [&](auto *kernel, auto tile, bool cols) {
+            typedef decltype(tile) TT;
+            if (int rc = allow_lds(kernel, TT::LDS_BYTES)) return rc;
+            const int64_t nVt = ceil_div(V, TT::BM), wgs = sweep_blocks_max(Tcp / TT::BN, nVt);
             ScopedKernelTimer timer(kTimeRecompute, s);
-            recompute_dz_kernel<<<static_cast<unsigned>(wgs), TL::NT, TL::LDS_BYTES, s>>>(
-                reinterpret_cast<const char *>(Wk), p.Kc * 2, V, reinterpret_cast<const char *>(Xk), p.Kc * 2,
+            kernel<<<static_cast<unsigned>(wgs), TT::NT, TT::LDS_BYTES, s>>>(
+                static_cast<const char *>(Wk), (cols ? V : p.Kc) * 2, V, reinterpret_cast<const char *>(Xk), p.Kc * 2,
                 Tcp, static_cast<int>(p.Kc / kBK), p.tok, nVt, p.dZ, Tcp * kBlockK, p.n_act, t0);
-        }
-        if (d_hidden) {
-            ScopedKernelTimer timer(kTimeDHidden, s);
-            // both operands k-blocked over the vocabulary: a stage of a tile is 32 KiB contiguous
-            launch_gemm<false>(p.dZ, kBlockK, Tcp, p.WT, kBlockK, H, p.V_pad, d_hidden, H, d_hidden_dtype, 0, p.n_act, t0,
-                               kLimitRows, p.act_idx + t0, Tcp * kBlockK, H * kBlockK, s, p.dx_split, p.part_tiles);
-        }
-        if (d_W) {
-            const int acc = (c > 0 || accumulate_dW) ? 1 : 0;
-            ScopedKernelTimer timer(kTimeDW, s);
-            // contraction over the chunk's tokens, the row index of both dZ and the gathered hidden rows
-            if (d->w_layout == SPO_W_VH)
-                launch_gemm<true>(p.dZ, kBlockK, V, Xrows, H, H, Tcp, dW_sum, H, dW_sum_dtype, acc, p.n_act, t0, kLimitK, nullptr,
-                                  Tcp * kBlockK, 0, s, 1, p.part_tiles);
-            else
-                launch_gemm<true>(Xrows, H, H, p.dZ, kBlockK, V, Tcp, dW_sum, V, dW_sum_dtype, acc, p.n_act, t0, kLimitK, nullptr,
-                                  0, Tcp * kBlockK, s, 1, p.part_tiles);
-        }
+            return static_cast<int>(SPO_OK);
+        };
+        if (small) rc = direct && hv ? recompute(recompute_dz_kernel<TS, true>, TS{}, true) : recompute(recompute_dz_kernel<TS, false>, TS{}, false);
+        else rc = direct && hv ? recompute(recompute_dz_kernel<TL, true>, TL{}, true) : recompute(recompute_dz_kernel<TL, false>, TL{}, false);
+        if (rc) return rc;
+        if (d_hidden && (rc = launch_dhidden(d, p.dZ, Tcp, Tcp, direct ? nullptr : p.WT, p.V_pad, d_hidden, d_hidden_dtype, p.n_act, t0,
+                                             p.act_idx + t0, nullptr, p.part_tiles, s)))
+            return rc;
+        // contraction over the chunk's tokens, the row index of both dZ and the gathered hidden rows
+        if (d_W && (rc = launch_dW(d, p.dZ, Xrows, Tcp, edge, dW_sum, dW_sum_dtype, (c > 0 || accumulate_dW) ? 1 : 0, p.n_act, t0,
+                                   p.part_tiles, s)))
+            return rc;
     }
     if (need_acc) f32_to_bf16_kernel<<<grid1(V * H / 8), 256, 0, s>>>(p.dW_acc, static_cast<bf16_t *>(d_W), V * H);
     return launch_status();
@@ -1733,8 +1944,8 @@ int fused_bwd(const spo_pg_desc *d, const float *logp, const float *lse, float g
 // Without a loss mask the pass over the stored logits is left out as well: the sweep stores
 // bf16 scaled probabilities that the contractions read as they are (probs_reference).
 struct FbPlan {
-    int64_t Tz, T_pad, V_pad, V_blk, Kc, nVt, nblk_tok;
-    int nsplit;
+    bool small;
+    int64_t Tz, T_pad, V_pad, V_blk, Kc, nVt, nblk_tok, room;  // room: entries of part_max, part_sum
     double *count;
     float *g, *z_target, *part_max, *part_sum, *offs, *dW_acc, *part_tiles, *cscale;
     bool dense;  // no loss mask: the sweep stores what the contractions read; offs: the references of all tokens
@@ -1745,11 +1956,10 @@ struct FbPlan {
     uint16_t *Z;
     bf16_t *dZ, *WT, *Xc, *Xs, *Ws;
     void *Wvh;
-    int dx_split;
     size_t bytes;
 };
 
-static FbPlan plan_fb(const spo_pg_desc *d, int64_t chunk_tokens, void *ws, bool need_dw_acc, bool want_dx) {
+static FbPlan plan_fb(const spo_pg_desc *d, int64_t chunk_tokens, void *ws, bool need_dw_acc, bool want_dx, bool roomy) {
     FbPlan p;
     p.T_pad = round_up(std::max<int64_t>(d->T, 1), TL::BN);
     p.V_pad = round_up(d->V, kBK);
@@ -1762,7 +1972,9 @@ static FbPlan plan_fb(const spo_pg_desc *d, int64_t chunk_tokens, void *ws, bool
     int64_t tz = chunk_tokens > 0 ? round_up(chunk_tokens, TL::BN) : kDzBudgetBytes / (2 * p.V_blk) / 4096 * 4096;
     if (tz < TL::BN) tz = TL::BN;
     p.Tz = std::min(tz, p.T_pad);
-    p.nsplit = sweep_splits(p.Tz / TL::BN, p.nVt);
+    p.small = roomy && small_sweep(std::min(p.Tz, d->T), d->V, p.Kc);
+    p.room = sweep_splits(p.Tz / TL::BN, p.nVt, kSlots<TL>) * p.Tz;
+    if (roomy) p.room = std::max(p.room, sweep_room(p.Tz, d->V, true));
     p.nblk_tok = p.T_pad / kTokThreads;
     static_assert(TL::BN % kTokThreads == 0, "pieces start at a block of the per-token kernels");
     Arena a(ws);
@@ -1771,15 +1983,14 @@ static FbPlan plan_fb(const spo_pg_desc *d, int64_t chunk_tokens, void *ws, bool
     p.z_target = a.take<float>(p.T_pad);
     p.partials = a.take<FwdPartial>(p.nblk_tok);
     p.done = a.take<uint32_t>(1);
-    p.part_max = a.take<float>(static_cast<size_t>(p.nsplit) * p.Tz);
-    p.part_sum = a.take<float>(static_cast<size_t>(p.nsplit) * p.Tz);
+    p.part_max = a.take<float>(static_cast<size_t>(p.room));
+    p.part_sum = a.take<float>(static_cast<size_t>(p.room));
     p.dense = d->mask == nullptr;
-    p.offs = a.take<float>(p.dense ? p.T_pad : static_cast<size_t>(p.nVt) * TL::WGM * p.Tz);
+    p.offs = a.take<float>(p.dense ? p.T_pad : static_cast<size_t>(p.V_blk / (roomy ? TS::WM : TL::WM)) * p.Tz);
     p.cscale = p.dense ? a.take<float>(p.Tz) : nullptr;
     p.act_idx = a.take<int32_t>(p.Tz);
     p.n_act = a.take<int32_t>(1);
     p.tok = a.take<float4>(p.Tz);
-    p.dx_split = want_dx ? dhidden_parts(p.Tz, d->H, p.V_pad) : 1;
     p.Xc = a.take<bf16_t>(static_cast<size_t>(p.Tz) * d->H);
     p.WT = want_dx ? a.take<bf16_t>(static_cast<size_t>(d->H) * p.V_blk) : nullptr;
     p.Z = a.take<uint16_t>(static_cast<size_t>(p.Tz) * p.V_blk);
@@ -1798,7 +2009,7 @@ static FbPlan plan_fb(const spo_pg_desc *d, int64_t chunk_tokens, void *ws, bool
 }
 
 int fused_fwd_bwd_workspace(const spo_pg_desc *d, int64_t chunk_tokens, size_t *bytes) {
-    const FbPlan p = plan_fb(d, chunk_tokens, nullptr, true, true);  // sized for the larger case
+    const FbPlan p = plan_fb(d, chunk_tokens, nullptr, true, true, true);  // sized for the larger case
     *bytes = p.bytes + room_for_shorter_chunks(d, p.Tz);
     return SPO_OK;
 }
@@ -1809,10 +2020,10 @@ int fused_fwd_bwd(const spo_pg_desc *d, float grad_loss, float *loss, float *log
     int rc = check_fused(d);
     if (rc) return rc;
     if (accumulate_dW && d_W && d_W_dtype != SPO_FP32) return SPO_EINVAL;
-    const FbPlan p = plan_fb(d, chunk_tokens, ws, d_W && d_W_dtype == SPO_BF16, d_hidden != nullptr);
+    FbPlan p = plan_fb(d, chunk_tokens, ws, d_W && d_W_dtype == SPO_BF16, d_hidden != nullptr, true);
+    if (ws_bytes < p.bytes) p = plan_fb(d, chunk_tokens, ws, d_W && d_W_dtype == SPO_BF16, d_hidden != nullptr, false);
     const bool need_acc = p.dW_acc != nullptr;  // a bf16 d_W of several pieces (see fused_bwd)
     if (ws_bytes < p.bytes) return SPO_EWORKSPACE;
-    if ((rc = set_lds_limit())) return rc;
     const int64_t H = d->H, V = d->V, T = d->T;
     void *dW_sum = need_acc ? p.dW_acc : d_W;
     const int dW_sum_dtype = need_acc ? SPO_FP32 : d_W_dtype;
@@ -1827,15 +2038,19 @@ int fused_fwd_bwd(const spo_pg_desc *d, float grad_loss, float *loss, float *log
     }
     // the head as the kernels read it: one row per vocabulary entry for the logits, one row per
     // hidden unit (blocked over the vocabulary) for dHidden; the first piece's rows; the target logits
-    PrepJobs jobs = prep_head_jobs(d, p.Wvh, p.Ws, d_hidden ? p.WT : nullptr);
+    const bool direct = direct_head(d), hv = d->w_layout == SPO_W_HV;
+    PrepJobs jobs = prep_head_jobs(d, direct ? nullptr : p.Wvh, p.Ws, d_hidden && !direct ? p.WT : nullptr);
     prep_rows(jobs, d, d->hidden, std::min(p.Tz, T), p.Xs);
     jobs.mask = d->mask;
     jobs.count = p.count;
     launch_prep_with_targets(d, jobs, p.z_target, p.dense ? p.offs : nullptr, p.T_pad, p.done, s);
-    const char *Wk = static_cast<const char *>(d->dtype == SPO_FP32 ? p.Ws : (p.Wvh ? p.Wvh : d->W));
+    const void *Wk = d->dtype == SPO_FP32 ? p.Ws : direct || !p.Wvh ? d->W : p.Wvh;
+    const bf16_t *WT = direct ? nullptr : p.WT;
+    const int64_t edge = tile_edge(p.small);
+    const int64_t T_end = (T - 1) / p.Tz * p.Tz + round_up((T - 1) % p.Tz + 1, edge);  // rows of all pieces
     const size_t x_elt = d->dtype == SPO_FP32 ? 4 : 2, dx_elt = d_hidden_dtype == SPO_FP32 ? 4 : 2;
     for (int64_t t0 = 0, c = 0; t0 < T; t0 += p.Tz, ++c) {
-        const int64_t Tv = std::min(p.Tz, T - t0), Tzp = round_up(Tv, TL::BN);
+        const int64_t Tv = std::min(p.Tz, T - t0), Tzp = round_up(Tv, edge);
         const char *Xpiece = static_cast<const char *>(d->hidden) + t0 * H * x_elt;
         const char *Xk = Xpiece;
         if (d->dtype == SPO_FP32) {
@@ -1846,20 +2061,12 @@ int fused_fwd_bwd(const spo_pg_desc *d, float grad_loss, float *loss, float *log
             }
             Xk = reinterpret_cast<const char *>(p.Xs);
         }
-        // the last piece may be shorter: its own choice of splits, within the room for partial results
-        const SweepMap map(Tzp / TL::BN, p.nVt,
-                           Tzp == p.Tz ? p.nsplit : sweep_splits(Tzp / TL::BN, p.nVt, static_cast<uint32_t>(std::min<int64_t>(p.nsplit * p.Tz / Tzp, kNoSplitCap))));
-        {
-            ScopedKernelTimer timer(kTimeFwdSweep, s);
-            if (p.dense)
-                fwd_sweep_kernel<kEmitProbs><<<static_cast<unsigned>(map.blocks()), TL::NT, kSweepLdsProbs, s>>>(
-                    Wk, p.Kc * 2, V, Xk, p.Kc * 2, Tv, static_cast<int>(p.Kc / kBK), map.ns, map.nTt, map.nVt, Tzp,
-                    p.part_max, p.part_sum, p.Z, Tzp * kBlockK, p.offs + t0);
-            else
-                fwd_sweep_kernel<kEmitLogits><<<static_cast<unsigned>(map.blocks()), TL::NT, kSweepLds, s>>>(
-                    Wk, p.Kc * 2, V, Xk, p.Kc * 2, Tv, static_cast<int>(p.Kc / kBK), map.ns, map.nTt, map.nVt, Tzp,
-                    p.part_max, p.part_sum, p.Z, Tzp * kBlockK, p.offs);
-        }
+        // a piece's own choice of splits (the last may be shorter), within the room for partial results
+        const int64_t nTt = Tzp / edge, nVt = ceil_div(V, edge);
+        const SweepMap map(nTt, nVt, sweep_splits(nTt, nVt, tile_slots(p.small),
+                                                  static_cast<uint32_t>(std::min<int64_t>(p.room / Tzp, kNoSplitCap))));
+        const Sweep w{Wk, H, V, p.Kc, direct && hv, Xk, Tv, p.part_max, p.part_sum, p.Z, Tzp * kBlockK, p.dense ? p.offs + t0 : p.offs};
+        if ((rc = p.dense ? launch_sweep<kEmitProbs>(w, p.small, map, s) : launch_sweep<kEmitLogits>(w, p.small, map, s))) return rc;
         const bool back = d_hidden || d_W;
         TokenGrad gr{};
         if (back) gr = TokenGrad{p.g + t0, Tzp, p.count, grad_loss, nullptr, nullptr, 0, V, d->target + t0};
@@ -1872,17 +2079,14 @@ int fused_fwd_bwd(const spo_pg_desc *d, float grad_loss, float *loss, float *log
         const TokenShape tok = token_shape(static_cast<int>(map.ns), n_blocks);
         token_loss_kernel<<<tok.blocks, tok.threads, 0, s>>>(
             p.part_max, p.part_sum, map.ns, tok.ways, Tzp, p.z_target + t0, token_inputs(d, t0, Tv), logp + t0, lse + t0,
-            p.partials, gr, n_blocks, back ? ceil_div(p.T_pad, kTokThreads) : ceil_div(T, kTokThreads), p.done, loss, stats);
+            p.partials, gr, n_blocks, back ? T_end / kTokThreads : ceil_div(T, kTokThreads), p.done, loss, stats);
         if (!back) continue;
         if (p.dense) {
             // the contractions run on what the sweep stored: every row of the piece, scaled by c_t
             const bf16_t *Q = p.Z;
-            if (d_hidden) {
-                ScopedKernelTimer timer(kTimeDHidden, s);
-                launch_gemm<false>(Q, kBlockK, Tv, p.WT, kBlockK, H, p.V_pad, static_cast<char *>(d_hidden) + t0 * H * dx_elt, H,
-                                   d_hidden_dtype, 0, nullptr, 0, 0, nullptr, Tzp * kBlockK, H * kBlockK, s, p.dx_split,
-                                   p.part_tiles, p.cscale);
-            }
+            if (d_hidden && (rc = launch_dhidden(d, Q, Tv, Tzp, WT, p.V_pad, static_cast<char *>(d_hidden) + t0 * H * dx_elt,
+                                                 d_hidden_dtype, nullptr, 0, nullptr, p.cscale, p.part_tiles, s)))
+                return rc;
             if (d_W) {
                 bf16_t *Xc = p.Xc;  // c_t x_t, the rows past the piece zero
                 if (d->dtype == SPO_FP32)
@@ -1891,14 +2095,9 @@ int fused_fwd_bwd(const spo_pg_desc *d, float grad_loss, float *loss, float *log
                 else
                     scale_rows_kernel<bf16_t><<<static_cast<unsigned>(Tzp), 256, 0, s>>>(
                         reinterpret_cast<const bf16_t *>(Xpiece), p.cscale, Tv, H, Xc);
-                const int acc = (c > 0 || accumulate_dW) ? 1 : 0;
-                ScopedKernelTimer timer(kTimeDW, s);
-                if (d->w_layout == SPO_W_VH)
-                    launch_gemm<true>(Q, kBlockK, V, Xc, H, H, Tzp, dW_sum, H, dW_sum_dtype, acc, nullptr, 0, 0, nullptr,
-                                      Tzp * kBlockK, 0, s, 1, p.part_tiles);
-                else
-                    launch_gemm<true>(Xc, H, H, Q, kBlockK, V, Tzp, dW_sum, V, dW_sum_dtype, acc, nullptr, 0, 0, nullptr, 0,
-                                      Tzp * kBlockK, s, 1, p.part_tiles);
+                if ((rc = launch_dW(d, Q, Xc, Tzp, edge, dW_sum, dW_sum_dtype, (c > 0 || accumulate_dW) ? 1 : 0, nullptr, 0,
+                                    p.part_tiles, s)))
+                    return rc;
             }
             continue;
         }
@@ -1913,24 +2112,14 @@ int fused_fwd_bwd(const spo_pg_desc *d, float grad_loss, float *loss, float *log
             ScopedKernelTimer timer(kTimeLogitsToDz, s);
             dz_from_logits_kernel<<<dim3(static_cast<unsigned>(Tzp / 32), grid1(n_blk, per_wg)), 256, 0, s>>>(
                 p.Z, Tzp * kBlockK, p.offs, Tzp, p.act_idx, p.n_act, Tzp, p.tok, p.dZ,
-                Tzp * kBlockK, n_blk, per_wg);
+                Tzp * kBlockK, n_blk, per_wg, (p.small ? TS::WM : TL::WM) / kBlockK, static_cast<int>(edge));
         }
-        if (d_hidden) {
-            ScopedKernelTimer timer(kTimeDHidden, s);
-            launch_gemm<false>(p.dZ, kBlockK, Tzp, p.WT, kBlockK, H, p.V_pad, static_cast<char *>(d_hidden) + t0 * H * dx_elt, H,
-                               d_hidden_dtype, 0, p.n_act, 0, kLimitRows, p.act_idx, Tzp * kBlockK, H * kBlockK, s,
-                               p.dx_split, p.part_tiles);
-        }
-        if (d_W) {
-            const int acc = (c > 0 || accumulate_dW) ? 1 : 0;
-            ScopedKernelTimer timer(kTimeDW, s);
-            if (d->w_layout == SPO_W_VH)
-                launch_gemm<true>(p.dZ, kBlockK, V, Xrows, H, H, Tzp, dW_sum, H, dW_sum_dtype, acc, p.n_act, 0, kLimitK, nullptr,
-                                  Tzp * kBlockK, 0, s, 1, p.part_tiles);
-            else
-                launch_gemm<true>(Xrows, H, H, p.dZ, kBlockK, V, Tzp, dW_sum, V, dW_sum_dtype, acc, p.n_act, 0, kLimitK, nullptr,
-                                  0, Tzp * kBlockK, s, 1, p.part_tiles);
-        }
+        if (d_hidden && (rc = launch_dhidden(d, p.dZ, Tzp, Tzp, WT, p.V_pad, static_cast<char *>(d_hidden) + t0 * H * dx_elt,
+                                             d_hidden_dtype, p.n_act, 0, p.act_idx, nullptr, p.part_tiles, s)))
+            return rc;
+        if (d_W && (rc = launch_dW(d, p.dZ, Xrows, Tzp, edge, dW_sum, dW_sum_dtype, (c > 0 || accumulate_dW) ? 1 : 0, p.n_act, 0,
+                                   p.part_tiles, s)))
+            return rc;
     }
     if (need_acc) f32_to_bf16_kernel<<<grid1(V * H / 8), 256, 0, s>>>(p.dW_acc, static_cast<bf16_t *>(d_W), V * H);
     return launch_status();

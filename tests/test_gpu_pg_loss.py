@@ -419,6 +419,82 @@ def test_bf16_dW_is_the_fp32_one_rounded(spo, oracle, T, H, V, chunk, w_layout, 
     assert rel_l2(f64(dw16), rb["d_W"]) < GRAD_TOL
 
 
+def torch_reference(case):
+    """Loss, log-probs and gradients in fp64 by torch's autograd, on the GPU (shapes that take the oracle minutes)."""
+    d = "cuda"
+    h, w = case.hidden.to(d, torch.float64).requires_grad_(), case.W.to(d, torch.float64).requires_grad_()
+    y = torch.as_tensor(case.target).to(d).long()
+    old = torch.as_tensor(case.old).to(d, torch.float64)
+    m = torch.ones(case.T, dtype=torch.float64, device=d) if case.mask is None else torch.as_tensor(case.mask).to(d, torch.float64)
+    adv = torch.repeat_interleave(torch.as_tensor(case.adv).to(d, torch.float64), torch.as_tensor(np.diff(case.cu)).to(d))
+    logp = torch.log_softmax(h @ w.t(), dim=1).gather(1, y[:, None])[:, 0]
+    ratio = torch.exp(logp - old)
+    obj = torch.minimum(ratio * adv, ratio.clamp(1 - case.eps[0], 1 + case.eps[1]) * adv)
+    loss = -(m * obj).sum() / m.sum()
+    loss.backward()
+    return loss.item(), logp.detach(), h.grad, w.grad
+
+
+@pytest.mark.parametrize("T,H,V", [
+    (1000, 2112, 20008),   # large tiles in all contractions: 4 x 79 tiles of logits, 8.25 across d_hidden
+    (2300, 2112, 12003),   # the same, rows of a head [H,V] that start anywhere: copied
+    (900, 2048, 8200),     # large tiles for the logits and d_W, small ones for d_hidden
+    (700, 4096, 8300)])    # small, large, small
+@pytest.mark.parametrize("w_layout", [0, 1])
+@pytest.mark.parametrize("mask_frac", [None, 0.2], ids=["no_mask", "masked"])
+def test_tiles_of_both_sizes(spo, T, H, V, w_layout, mask_frac, one_call):
+    say(f"fused bf16 T={T} H={H} V={V} layout={w_layout} mask={mask_frac} one_call={one_call}: large and small tiles")
+    case = Case(wl.scaled(MID, name="both", H=H, V=V), [T // 3, T - T // 3], mask_frac=mask_frac)
+    case.old = np.zeros(T, np.float32)
+    logp = torch_reference(case)[1].cpu().numpy()
+    case.old = (logp + case.noise).astype(np.float32)
+    for _ in range(3):  # no ratio near a clip bound
+        r = np.exp(logp - case.old)
+        case.old[(np.abs(r / (1 - case.eps[0]) - 1) < 2e-3) | (np.abs(r / (1 + case.eps[1]) - 1) < 2e-3)] += np.float32(0.01)
+    loss, logp, gx, gw = torch_reference(case)
+    fwd, dx, dw = run_fwd_bwd(spo, case, w_layout, one_call=one_call)
+    assert abs(fwd[0].item() - loss) <= 2e-3 * abs(loss) + 1e-7
+    assert (fwd[1].double() - logp).abs().max() < 2e-4
+    for got, ref in ((dx, gx), (dw, gw)):
+        assert float((got.double() - ref).norm() / ref.norm()) < GRAD_TOL
+        assert float((got.double() - ref).abs().max()) <= 2e-2 * float(ref.abs().max())
+
+
+@pytest.mark.parametrize("T,H,V,mask_frac", [(512, 128, 1000, None), (713, 256, 3000, 0.25)])
+def test_workspaces_down_to_what_large_tiles_need(spo, oracle, T, H, V, mask_frac):
+    # small tiles have more partial results; a workspace without that room is served by large ones
+    say(f"fused bf16 T={T} H={H} V={V} mask={mask_frac}: smallest workspaces")
+    case = Case(wl.scaled(MID, name="room", H=H, V=V), [T // 3, T - T // 3], mask_frac=mask_frac)
+    case.set_old_from_oracle(oracle)
+    desc = case.to_gpu(spo)
+    import ctypes
+    L, d = spo.lib(), desc[0]
+    buf = torch.empty(L.spo_pg_loss_fwd_bwd_workspace_bytes(ctypes.byref(d), 0), dtype=torch.uint8, device="cuda")
+    f = lambda n: torch.empty(n, dtype=torch.float32, device="cuda")
+    out = [f(1), f(T), f(T), f(4)]
+    dx, dw = f(T * H), f(V * H)
+    def fwd(n):
+        return L.spo_pg_loss_fwd(ctypes.byref(d), *[o.data_ptr() for o in out], buf.data_ptr(), n, None)
+    def both(n):
+        return L.spo_pg_loss_fwd_bwd(ctypes.byref(d), 1.0, *[o.data_ptr() for o in out], dx.data_ptr(), 0, dw.data_ptr(), 0, 0, 0,
+                                     buf.data_ptr(), n, None)
+    for call, size in ((fwd, L.spo_pg_loss_fwd_workspace_bytes(ctypes.byref(d))), (both, buf.numel())):
+        assert call(size) == 0
+        torch.cuda.synchronize()
+        want = [t.clone() for t in (*out, dx, dw)] if call is both else [t.clone() for t in out]
+        lo, hi = 0, size    # refused, accepted
+        while hi - lo > 256:
+            mid = (lo + hi) // 512 * 256
+            if call(mid) == 0:
+                hi = mid
+            else:
+                lo = mid
+        assert hi < size and call(hi) == 0
+        torch.cuda.synchronize()
+        for a, b in zip(want, (*out, dx, dw)):
+            assert float((a - b).norm()) <= 1e-3 * float(a.norm()) + 1e-9
+
+
 @pytest.mark.parametrize("V", [1, 3, 6, 257, 510, 1003])   # rows of d_W [H,V] that end inside a run of 4 or 8 columns
 @pytest.mark.parametrize("H", [64, 320])                    # a tile with a quarter of its rows; one and a quarter
 def test_dW_rows_that_end_anywhere(spo, oracle, V, H):
