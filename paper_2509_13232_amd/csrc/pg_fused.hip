@@ -1486,6 +1486,9 @@ static double launch_time_cut(const TileTimes &t, bool small, int64_t tiles, int
     return launch_time(t, small, static_cast<double>(cut.whole / slots) + 1.0 / cut.parts,
                        cut.whole ? tiles : cut.rem * cut.parts, steps, head_bytes) + t.cut;
 }
+// Long launches run at the power cap, where the smaller tiles' extra traffic costs more than fitted: they have to be ahead
+// by an eighth there (dW of 40485 tokens at 512 x 86540: the whole call 11.38 ms on large tiles, 11.97 on small).
+static bool small_is_faster(const double (&time)[2]) { return time[1] < time[0] * (time[0] > 500.0 ? 0.875 : 1.0); }
 static int64_t tile_edge(bool small) { return small ? TS::BM : TL::BM; }
 static int tile_slots(bool small) { return small ? kSlots<TS> : kSlots<TL>; }
 static int dhidden_parts(int64_t Tc, int64_t H, int64_t V_pad, bool small);
@@ -1498,22 +1501,25 @@ static bool small_sweep(int64_t T, int64_t V, int64_t Kc) {
         const int64_t ns = sweep_splits(nTt, nVt, tile_slots(small)), rounds = ceil_div(nTt * ns, tile_slots(small)) * ceil_div(nVt, ns);
         time[small] = launch_time(kSweepTimes, small, static_cast<double>(rounds), nTt * ns, Kc / kBK, V * Kc * 2);
     }
-    return time[1] < time[0];
+    return small_is_faster(time);
 }
 static bool small_dhidden(int64_t T, int64_t H, int64_t V_pad) {
+    // large tiles that fill the chip by themselves: long steps of a vocabulary, where they are faster than fitted (16000
+    // tokens at 256 x 40000 343 and 432 us, 17497 at 640 x 35002 767 and 816, 11238 at 192 x 151936 743 and 1098)
+    if (dhidden_parts(T, H, V_pad, false) == 1) return false;
     double time[2];
     for (int small = 0; small < 2; ++small) {
         const int64_t parts = dhidden_parts(T, H, V_pad, small), tiles = ceil_div(T, tile_edge(small)) * ceil_div(H, tile_edge(small));
         time[small] = launch_time_cut(kDHiddenTimes, small, tiles * parts, ceil_div(V_pad / kBK, parts), parts == 1, H * V_pad * 2);
     }
-    return time[1] < time[0];
+    return small_is_faster(time);
 }
 static bool small_dW(int64_t T, int64_t H, int64_t V) {
     double time[2];
     for (int small = 0; small < 2; ++small)
         time[small] = launch_time_cut(kDWTimes, small, ceil_div(V, tile_edge(small)) * ceil_div(H, tile_edge(small)), ceil_div(T, kBK), true,
                                       H * V * 2);
-    return time[1] < time[0];
+    return small_is_faster(time);
 }
 
 // Is a bf16 head read as it was given, or copied into the forms that the main loop reads fastest?  Columns along k
