@@ -1,7 +1,7 @@
-// Prioritized prompt sampling: weights -> exact integer CDF -> Philox draws.
+// Prioritized prompt sampling: weights -> exact integer CDFs -> Philox draws.
 // Method, "Prioritized Prompt Sampling" (sampling-weight equation and the batch
-// draw of the training loop).  The O(N) part (weights + scan) streams the tracker
-// once per phase; the draw itself is B searches of the CDF.  Tables of one scan block are
+// draw of the training loop).  The O(N) part (weights + scans of blocks) streams the tracker
+// once; the draw itself is B searches, of the blocks' sums and of a block's CDF.  Tables of one scan block are
 // handled by a single launch that keeps the CDF in LDS (a step of 16 prompts: 7 launches -> 3,
 // 52 us -> 35 us, what is left being the host's).
 //
@@ -20,7 +20,7 @@ namespace spo {
 constexpr int kScanThreads = 1024;
 constexpr int kScanRows = 4;                                // rows of kScanThreads items per block
 constexpr int kScanItems = kScanThreads * kScanRows;        // 4096 items per block
-constexpr int kInlineBlocks = kScanThreads;                 // block sums that every block adds up by itself
+constexpr int kInlineBlocks = 1024;                         // block sums that every workgroup of a draw adds up by itself
 constexpr int kMaxSlotsNoReplace = 16384;
 
 __device__ __forceinline__ uint64_t weight_code(float alpha, float beta, double eps) {
@@ -84,69 +84,96 @@ __device__ __forceinline__ void weight_rows(const float *__restrict__ alpha, con
     }
 }
 
-// Phase 1: per-block sum of the weight codes.
+// Phase 1: the inclusive CDF of the codes inside every block of kScanItems prompts and the blocks' sums, the claims
+// cleared (owner != NULL) with info.  One pass over the tracker; what lies before a block is added up by the draws (the
+// sums first and the CDF over the whole table in a second pass took 21 us at 2^20 prompts).  A thread takes four
+// prompts in a row, so that one scan over the threads is left (rows of 1024 prompts, four scans side by side: 13.0 us, this
+// 11.4; 7.5 and 5.0 for five blocks).
+template <typename V4>
+__device__ __forceinline__ V4 load4(const void *p) {
+    typedef V4 U __attribute__((aligned(4)));
+    return *static_cast<const U *>(p);
+}
 __global__ void __launch_bounds__(kScanThreads)
-weight_block_sums_kernel(const float *__restrict__ alpha, const float *__restrict__ beta, int64_t N,
-                         double eps, uint64_t *__restrict__ block_sums) {
-    __shared__ uint64_t scratch[kScanThreads / kWave];
-    uint64_t x[kScanRows];
-    weight_rows(alpha, beta, N, eps, static_cast<int64_t>(blockIdx.x) * kScanItems, x);
-    uint64_t s = 0;
+weight_scan_kernel(const float *__restrict__ alpha, const float *__restrict__ beta, int64_t N, double eps,
+                   uint64_t *__restrict__ cdf, uint64_t *__restrict__ block_sums, int32_t *__restrict__ owner,
+                   int32_t *__restrict__ info) {
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    static_assert(kScanRows == 4, "four prompts per thread");
+    constexpr int NW = kScanThreads / kWave;
+    __shared__ uint64_t wave_sums[NW];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * kScanItems + threadIdx.x * 4;
+    f4 a = {0.0f, 0.0f, 0.0f, 0.0f}, b = a;
+    if (i + 3 < N) {
+        a = load4<f4>(alpha + i);
+        b = load4<f4>(beta + i);
+    } else {
 #pragma unroll
-    for (int r = 0; r < kScanRows; ++r) s += x[r];
-    s = block_sum(s, scratch);
-    if (threadIdx.x == 0) block_sums[blockIdx.x] = s;
+        for (int r = 0; r < 3; ++r)
+            if (i + r < N) {
+                a[r] = alpha[i + r];
+                b[r] = beta[i + r];
+            }
+    }
+    uint64_t x[4], run = 0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) x[r] = run += i + r < N ? weight_code(a[r], b[r], eps) : 0;
+    uint64_t upto = run;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const uint64_t y = __shfl_up(upto, o, kWave);
+        if (lane >= o) upto += y;
+    }
+    if (lane == kWave - 1) wave_sums[wave] = upto;
+    __syncthreads();
+    uint64_t before = upto - run, tot = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        const uint64_t v = wave_sums[w];
+        before += w < wave ? v : 0;
+        tot += v;
+    }
+    typedef uint64_t u2 __attribute__((ext_vector_type(2)));
+    typedef int32_t i4 __attribute__((ext_vector_type(4)));
+    if (i + 3 < N) {  // (the tables begin on 256-byte boundaries)
+        *reinterpret_cast<u2 *>(cdf + i) = u2{before + x[0], before + x[1]};
+        *reinterpret_cast<u2 *>(cdf + i + 2) = u2{before + x[2], before + x[3]};
+        if (owner) *reinterpret_cast<i4 *>(owner + i) = i4{kNoOwner, kNoOwner, kNoOwner, kNoOwner};
+    } else {
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+            if (i + r < N) {
+                cdf[i + r] = before + x[r];
+                if (owner) owner[i + r] = kNoOwner;
+            }
+    }
+    if (threadIdx.x == 0) {
+        block_sums[blockIdx.x] = tot;
+        if (blockIdx.x == 0 && owner && info) info[0] = info[1] = 0;
+    }
 }
 
-// Phase 2, only where there are more than kInlineBlocks blocks: exclusive scan of the block sums
+// Phase 2, only where there are more than kInlineBlocks blocks: inclusive scan of the block sums
 // (one workgroup, carried in chunks).
 __global__ void __launch_bounds__(kScanThreads)
 scan_block_sums_kernel(uint64_t *__restrict__ block_sums, int64_t nblocks) {
     __shared__ uint64_t lds[kWave + 1];
     uint64_t carry = 0;
     for (int64_t base = 0; base < nblocks; base += kScanItems) {
-        uint64_t v[kScanRows], x[kScanRows], tot;
+        uint64_t x[kScanRows], tot;
 #pragma unroll
         for (int r = 0; r < kScanRows; ++r) {
             const int64_t i = base + r * kScanThreads + threadIdx.x;
-            v[r] = x[r] = i < nblocks ? block_sums[i] : 0;
+            x[r] = i < nblocks ? block_sums[i] : 0;
         }
         block_scan_rows(x, lds, tot);
 #pragma unroll
         for (int r = 0; r < kScanRows; ++r) {
             const int64_t i = base + r * kScanThreads + threadIdx.x;
-            if (i < nblocks) block_sums[i] = carry + x[r] - v[r];
+            if (i < nblocks) block_sums[i] = carry + x[r];
         }
         carry += tot;
-    }
-}
-
-// Phase 3: inclusive CDF of the codes, its last value as *total, and (owner != NULL) the claims
-// cleared, with info.  summed: block_sums holds what scan_block_sums_kernel made of it; otherwise
-// (at most kInlineBlocks blocks) every block adds up the sums before its own.
-__global__ void __launch_bounds__(kScanThreads)
-weight_cdf_kernel(const float *__restrict__ alpha, const float *__restrict__ beta, int64_t N, double eps,
-                  const uint64_t *__restrict__ block_sums, int summed, uint64_t *__restrict__ cdf,
-                  uint64_t *__restrict__ total, int32_t *__restrict__ owner, int32_t *__restrict__ info) {
-    __shared__ uint64_t lds[kWave + 1];
-    const int64_t base = static_cast<int64_t>(blockIdx.x) * kScanItems;
-    uint64_t before;
-    if (summed) before = block_sums[blockIdx.x];
-    else before = block_sum(threadIdx.x < blockIdx.x ? block_sums[threadIdx.x] : uint64_t(0), lds);
-    uint64_t x[kScanRows], tot;
-    weight_rows(alpha, beta, N, eps, base, x);
-    block_scan_rows(x, lds, tot);
-#pragma unroll
-    for (int r = 0; r < kScanRows; ++r) {
-        const int64_t i = base + r * kScanThreads + threadIdx.x;
-        if (i < N) {
-            cdf[i] = before + x[r];
-            if (owner) owner[i] = kNoOwner;
-        }
-    }
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
-        *total = before + tot;
-        if (owner && info) info[0] = info[1] = 0;
     }
 }
 
@@ -168,37 +195,114 @@ __device__ __forceinline__ uint64_t philox_bits(uint64_t seed, uint64_t iteratio
     return static_cast<uint64_t>(c0) | (static_cast<uint64_t>(c1) << 32);
 }
 
-// index of draw (slot, attempt): first i with cdf[i] > floor(bits * total / 2^64).  Each round asks 15
-// entries at once, a sixteenth of the range apart: five dependent loads for 2^20 prompts instead of
-// twenty.
-__device__ __forceinline__ int32_t draw_index(const uint64_t *__restrict__ cdf, int64_t N, uint64_t total,
-                                              uint64_t seed, uint64_t iteration, uint32_t slot, uint32_t attempt) {
-    const uint64_t t = __umul64hi(philox_bits(seed, iteration, slot, attempt), total);
-    uint32_t lo = 0, hi = static_cast<uint32_t>(N);  // N < 2^31; cdf[i] <= t below lo, > t from hi on
+// First index in [lo, hi) whose entry of v[] is above t (hi: none; entries do not fall).  Each round asks 15 entries at
+// once, a sixteenth of the range apart: three dependent loads for a block of 4096.
+__device__ __forceinline__ uint32_t first_above(const uint64_t *__restrict__ v, uint32_t lo, uint32_t hi, uint64_t t) {
     while (lo < hi) {
         const uint32_t step = (hi - lo + 15) / 16;
         uint32_t c = 0;
 #pragma unroll
         for (uint32_t j = 1; j < 16; ++j) {
             const uint32_t p = lo + j * step - 1;
-            const uint64_t v = cdf[p < hi ? p : hi - 1];  // always a load, none of them behind a branch
-            c += static_cast<uint32_t>(v <= t) & static_cast<uint32_t>(p < hi);
+            const uint64_t x = v[p < hi ? p : hi - 1];  // always a load, none of them behind a branch
+            c += static_cast<uint32_t>(x <= t) & static_cast<uint32_t>(p < hi);
         }
         lo += c * step;
         const uint32_t end = lo + step - 1;  // the first probe above t, if one was
         hi = c < 15 && end < hi ? end : hi;
     }
-    return static_cast<int32_t>(lo);
+    return lo;
 }
 
+// The tables of a draw: the CDF inside every block, and the inclusive sums over the blocks, in LDS (`sums`, kInlineBlocks
+// entries) or, where there are more, in memory as scan_block_sums_kernel left them.
+struct DrawTables {
+    const uint64_t *cdf, *sums;
+    uint32_t N, nblocks;
+    uint64_t total;
+
+    // All threads of the workgroup (whole wavefronts) call this; `sums` holds kInlineBlocks values.
+    __device__ __forceinline__ DrawTables(const uint64_t *cdf_, const uint64_t *block_sums, int64_t N_, int64_t nb, uint64_t *lds)
+        : cdf(cdf_), sums(block_sums), N(static_cast<uint32_t>(N_)), nblocks(static_cast<uint32_t>(nb)) {
+        if (nblocks <= kInlineBlocks) {
+            if (threadIdx.x < kWave) {  // one wavefront scans them, a run of consecutive ones per lane
+                constexpr int RUN = kInlineBlocks / kWave;
+                const uint32_t per = (nblocks + kWave - 1) / kWave, first = threadIdx.x * per;
+                uint64_t x[RUN], run = 0;
+#pragma unroll
+                for (uint32_t j = 0; j < RUN; ++j) x[j] = j < per && first + j < nblocks ? block_sums[first + j] : 0;
+#pragma unroll
+                for (uint32_t j = 0; j < RUN; ++j) run += x[j];
+                uint64_t before = run;
+#pragma unroll
+                for (int o = 1; o < kWave; o <<= 1) {
+                    const uint64_t y = __shfl_up(before, o, kWave);
+                    if (static_cast<int>(threadIdx.x) >= o) before += y;
+                }
+                before -= run;
+#pragma unroll
+                for (uint32_t j = 0; j < RUN; ++j) {
+                    before += x[j];
+                    if (j < per && first + j < nblocks) lds[first + j] = before;
+                }
+            }
+            sums = lds;
+            __syncthreads();
+        }
+        total = sums[nblocks - 1];
+    }
+    // index of draw (slot, attempt): first i whose entry of the CDF over the table is above floor(bits * total / 2^64)
+    __device__ __forceinline__ int32_t index(uint64_t seed, uint64_t iteration, uint32_t slot, uint32_t attempt) const {
+        const uint64_t t = __umul64hi(philox_bits(seed, iteration, slot, attempt), total);
+        uint32_t b = 0, hi = nblocks - 1;  // t < total: the last block's sum is above t
+        if (nblocks <= kInlineBlocks) {  // LDS answers fast: a plain binary search
+            while (b < hi) {
+                const uint32_t mid = (b + hi) >> 1;
+                if (sums[mid] > t) hi = mid; else b = mid + 1;
+            }
+        } else {
+            b = first_above(sums, 0, hi, t);
+        }
+        const uint64_t rest = t - (b ? sums[b - 1] : 0);
+        const uint32_t lo = b * kScanItems, end = N - lo < kScanItems ? N : lo + kScanItems;
+        return static_cast<int32_t>(first_above(cdf, lo, end, rest));
+    }
+    // The same by a whole wavefront for one draw (slot and attempt the same in every lane): 64 entries at once, two
+    // dependent loads of a block, one each per lane.
+    __device__ __forceinline__ int32_t index_wave(uint64_t seed, uint64_t iteration, uint32_t slot, uint32_t attempt) const {
+        const uint32_t lane = threadIdx.x & (kWave - 1);
+        const uint64_t t = __umul64hi(philox_bits(seed, iteration, slot, attempt), total);
+        auto first = [&](const uint64_t *v, uint32_t lo, uint32_t hi, uint32_t step, uint64_t x) {  // the first of 64 probes above x
+            const uint32_t p = lo + (lane + 1) * step - 1;
+            return static_cast<uint32_t>(__builtin_ctzll(__ballot(v[p < hi ? p : hi - 1] > x)));  // (the last entry is)
+        };
+        uint32_t b;
+        if (nblocks <= kInlineBlocks) {
+            constexpr uint32_t RUN = kInlineBlocks / kWave;
+            b = RUN * first(sums, 0, nblocks, RUN, t);
+            b += first(sums, b, nblocks - b < RUN ? nblocks : b + RUN, 1, t);
+        } else {
+            b = first_above(sums, 0, nblocks - 1, t);
+        }
+        const uint64_t rest = t - (b ? sums[b - 1] : 0);
+        uint32_t lo = b * kScanItems;
+        const uint32_t end = N - lo < kScanItems ? N : lo + kScanItems;
+        lo += kWave * first(cdf, lo, end, kWave, rest);
+        return static_cast<int32_t>(lo + first(cdf, lo, end, 1, rest));
+    }
+};
+static_assert(kScanItems == kWave * kWave, "two rounds of 64 probes find an entry of a block");
+
 __global__ void __launch_bounds__(256)
-draw_with_replacement_kernel(const uint64_t *__restrict__ cdf, int64_t N, const uint64_t *__restrict__ total,
+draw_with_replacement_kernel(const uint64_t *__restrict__ cdf, int64_t N, const uint64_t *__restrict__ block_sums, int64_t nblocks,
                              uint64_t seed, uint64_t iteration, int B, int32_t *__restrict__ idx_out,
                              int32_t *__restrict__ info) {
+    __shared__ uint64_t lds[kInlineBlocks];
+    const DrawTables tab(cdf, block_sums, N, nblocks, lds);
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    const uint64_t tot = *total;  // zero: every weight is zero, nothing can be drawn
-    if (k < B) idx_out[k] = tot ? draw_index(cdf, N, tot, seed, iteration, k, 0) : -1;
-    if (info && k == 0) { info[0] = tot ? 0 : 1; info[1] = 0; }
+    // a total of zero: every weight is zero, nothing can be drawn
+    if (k < B) idx_out[k] = tab.total ? tab.index(seed, iteration, k, 0) : -1;
+    if (info && k == 0) { info[0] = tab.total ? 0 : 1; info[1] = 0; }
 }
 
 // Successive sampling without replacement: slot k takes its first attempt that no slot before it has
@@ -212,27 +316,39 @@ draw_with_replacement_kernel(const uint64_t *__restrict__ cdf, int64_t N, const 
 typedef Claims<17> SlotClaims;
 static_assert(SlotClaims::kMaxSlots >= kMaxSlotsNoReplace, "claims fit 31 bits");
 
-// The claims over many workgroups; the one place they meet is the atomics on owner[].
-__global__ void __launch_bounds__(kWave)
-draw_claim_kernel(const uint64_t *__restrict__ cdf, int64_t N, const uint64_t *__restrict__ total_p, uint64_t seed,
-                  uint64_t iteration, int B, uint32_t max_attempts, int32_t *__restrict__ idx_out,
+// The claims over many workgroups, a wavefront per slot; the one place they meet is the atomics on owner[].  Bound by the
+// latency of an attempt, twice that where a slot is turned away: a lane per slot asks for 15 entries of a block three times
+// in a row (4096 of 2^20 prompts: 10.7 us), a wavefront for 64 twice (7.6).
+__global__ void __launch_bounds__(256)
+draw_claim_kernel(const uint64_t *__restrict__ cdf, int64_t N, const uint64_t *__restrict__ block_sums, int64_t nblocks,
+                  uint64_t seed, uint64_t iteration, int B, uint32_t max_attempts, int32_t *__restrict__ idx_out,
                   int32_t *__restrict__ info, int32_t *__restrict__ owner) {
-    const uint32_t k = blockIdx.x * kWave + threadIdx.x;
-    const uint64_t total = *total_p;
+    __shared__ uint64_t lds[kInlineBlocks];
+    const DrawTables tab(cdf, block_sums, N, nblocks, lds);
+    const uint32_t k = __builtin_amdgcn_readfirstlane(blockIdx.x * (256 / kWave) + threadIdx.x / kWave);
+    const bool lead = (threadIdx.x & (kWave - 1)) == 0;
     if (k >= static_cast<uint32_t>(B)) return;
-    if (total == 0) {  // every weight is zero: nothing can be drawn
-        idx_out[k] = -1;
-        if (info && k == 0) info[0] = 1;
+    if (tab.total == 0) {  // every weight is zero: nothing can be drawn
+        if (lead) {
+            idx_out[k] = -1;
+            if (info && k == 0) info[0] = 1;
+        }
         return;
     }
     const uint32_t most = SlotClaims::settle(
-        k, max_attempts, [&](uint32_t s, uint32_t n) { return draw_index(cdf, N, total, seed, iteration, s, n); },
-        [&](int32_t c, int32_t v) { return atomicMin(&owner[c], v); },
+        k, max_attempts,
+        [&](uint32_t s, uint32_t n) { return static_cast<int32_t>(__builtin_amdgcn_readfirstlane(tab.index_wave(seed, iteration, s, n))); },
+        [&](int32_t c, int32_t v) {
+            int32_t was = 0;
+            if (lead) was = atomicMin(&owner[c], v);
+            return static_cast<int32_t>(__builtin_amdgcn_readfirstlane(was));
+        },
         [&](uint32_t s) {
+            if (!lead) return;
             idx_out[s] = -1;
             if (info) atomicOr(&info[0], 1);
         });
-    if (info && most) atomicMax(&info[1], static_cast<int32_t>(most));
+    if (lead && info && most) atomicMax(&info[1], static_cast<int32_t>(most));
 }
 
 // The other slots' indices, from the prompts they hold.
@@ -314,7 +430,7 @@ sample_small_kernel(const float *__restrict__ alpha, const float *__restrict__ b
 }
 
 struct SamplerWorkspace {
-    uint64_t *cdf, *block_sums, *total;
+    uint64_t *cdf, *block_sums;
     int32_t *owner;
     size_t bytes;
 };
@@ -324,7 +440,7 @@ static SamplerWorkspace sampler_layout(void *ws, int64_t N) {
     SamplerWorkspace w;
     w.cdf = a.take<uint64_t>(static_cast<size_t>(N));
     w.block_sums = a.take<uint64_t>(static_cast<size_t>(ceil_div(N, kScanItems)));
-    w.total = a.take<uint64_t>(1);
+    a.take<uint64_t>(1);  // (a size that programs may have kept)
     w.owner = a.take<int32_t>(static_cast<size_t>(N));
     w.bytes = a.used;
     return w;
@@ -356,17 +472,14 @@ static int sample_launch(const float *alpha, const float *beta, int64_t N, int32
         return launch_status();
     }
     const int64_t nblocks = ceil_div(N, kScanItems);
-    const bool summed = nblocks > kInlineBlocks;
-    if (nblocks > 1)
-        weight_block_sums_kernel<<<static_cast<unsigned>(nblocks), kScanThreads, 0, s>>>(alpha, beta, N, eps_explore, w.block_sums);
-    if (summed) scan_block_sums_kernel<<<1, kScanThreads, 0, s>>>(w.block_sums, nblocks);
-    weight_cdf_kernel<<<static_cast<unsigned>(nblocks), kScanThreads, 0, s>>>(
-        alpha, beta, N, eps_explore, w.block_sums, summed, w.cdf, w.total, replace ? nullptr : w.owner, info);
+    weight_scan_kernel<<<static_cast<unsigned>(nblocks), kScanThreads, 0, s>>>(alpha, beta, N, eps_explore, w.cdf, w.block_sums,
+                                                                               replace ? nullptr : w.owner, info);
+    if (nblocks > kInlineBlocks) scan_block_sums_kernel<<<1, kScanThreads, 0, s>>>(w.block_sums, nblocks);
     if (replace) {
-        draw_with_replacement_kernel<<<(B + 255) / 256, 256, 0, s>>>(w.cdf, N, w.total, seed, iteration, B, idx_out, info);
+        draw_with_replacement_kernel<<<(B + 255) / 256, 256, 0, s>>>(w.cdf, N, w.block_sums, nblocks, seed, iteration, B, idx_out, info);
     } else {
-        draw_claim_kernel<<<static_cast<unsigned>(ceil_div(B, kWave)), kWave, 0, s>>>(w.cdf, N, w.total, seed, iteration, B,
-                                                                                      max_attempts, idx_out, info, w.owner);
+        draw_claim_kernel<<<static_cast<unsigned>(ceil_div(B, 256 / kWave)), 256, 0, s>>>(
+            w.cdf, N, w.block_sums, nblocks, seed, iteration, B, max_attempts, idx_out, info, w.owner);
         place_slots_kernel<<<static_cast<unsigned>(ceil_div(N, 1024)), 256, 0, s>>>(w.owner, N, idx_out);
     }
     return launch_status();
