@@ -2,6 +2,8 @@
 // Method, "A KL-Adaptive Value Tracker" and "Advantage Estimation and Policy
 // Optimization".  Plain ALU work on B <= a few thousand scattered entries:
 // launch-latency bound.
+#include <algorithm>
+
 #include "common.hpp"
 
 namespace spo {
@@ -91,7 +93,12 @@ tracker_update_unique_kernel(float *__restrict__ alpha, float *__restrict__ beta
 // observation of every id per round: 952 us for a prompt step of 40000 responses to 20000 prompts,
 // 84 us now, 30 of them here before the lists were sorted by ranks.)  A list that might overflow is applied and restarted: the ids are read in
 // batch order, so what is applied earlier is earlier in the batch.
-constexpr int kOwnThreads = 512, kOwnCap = 4096, kOwnStep = 2 * kOwnThreads;
+// What is left is latency: the ids come kOwnChunk at a time, all of a thread's in flight together, and are counted before
+// they are filed, so that a list which cannot overflow takes three barriers per chunk (4096 ids requested at a time
+// and a barrier or two per 1024 of them: 26 us for that step, 18.5 now).
+constexpr int kOwnThreads = 512, kOwnCap = 4096, kOwnVecs = 8, kOwnVec = 4 * kOwnThreads, kOwnChunk = kOwnVecs * kOwnVec;
+static_assert(kOwnVec <= kOwnCap, "the ids of one vector per thread fit an empty list");
+typedef int32_t i32x4u_t __attribute__((ext_vector_type(4), aligned(4)));  // (the list may start anywhere)
 constexpr int kOwnSpan = 2048;          // sorted observations whose rewards and discounts are in LDS at a time
 constexpr int kOwnGroups = 256;         // most workgroups: one per compute unit
 constexpr int kOwnPerGroup = 128;       // observations per workgroup below that
@@ -110,7 +117,7 @@ tracker_update_owned_kernel(float *__restrict__ alpha, float *__restrict__ beta,
     __shared__ uint64_t key[kOwnCap];  // id << 32 | place in the batch
     __shared__ double rho[kOwnSpan];
     __shared__ float rew[kOwnSpan];
-    __shared__ int count;
+    __shared__ int count, coming;
     const int tid = threadIdx.x;
     // applies the n observations in key[] (n is the same in every thread)
     auto apply_list = [&](int n) {
@@ -168,49 +175,80 @@ tracker_update_owned_kernel(float *__restrict__ alpha, float *__restrict__ beta,
         }
     };
     if (tid == 0) count = 0;
-    int bound = 0;  // the list holds at most this many
-    constexpr int AHEAD = 4;
-    for (int64_t base = 0; base < B; base += AHEAD * kOwnStep) {
-        int32_t id[AHEAD][2];
+    for (int64_t base = 0; base < B; base += kOwnChunk) {
+        i32x4u_t id[kOwnVecs];
+        if (tid == 0) coming = 0;
+        auto request = [&](int64_t k, i32x4u_t &v) {
+            if (k + 3 < B) {
+                v = *reinterpret_cast<const i32x4u_t *>(idx + k);
+            } else {
 #pragma unroll
-        for (int c = 0; c < AHEAD; ++c)
-#pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                const int64_t k = base + (2 * c + e) * kOwnThreads + tid;
-                id[c][e] = k < B ? idx[k] : 0;
+                for (int e = 0; e < 4; ++e) v[e] = k + e < B ? idx[k + e] : 0;
             }
+        };
+        auto mine = [&](int32_t i) {
+            return static_cast<uint32_t>(i) < static_cast<uint32_t>(N) &&
+                   static_cast<uint64_t>(static_cast<uint32_t>(i) * 0x9E3779B1u) >> shift == blockIdx.x;
+        };
+        auto file = [&](int64_t k) { key[atomicAdd(&count, 1)] = static_cast<uint64_t>(idx[k]) << 32 | static_cast<uint32_t>(k); };
 #pragma unroll
-        for (int c = 0; c < AHEAD; ++c) {
-            if (base + c * kOwnStep >= B) break;
-            if (bound + kOwnStep > kOwnCap) {
-                __syncthreads();
-                bound = count;
-                __syncthreads();
-                if (bound + kOwnStep > kOwnCap) {
-                    apply_list(bound);
-                    if (tid == 0) count = 0;
-                    bound = 0;
-                }
+        for (int c = 0; c < kOwnVecs; ++c) request(base + c * kOwnVec + tid * 4, id[c]);
+        uint32_t own = 0;  // bit 4 c + e: id[c][e] is this workgroup's
+        bool bad = false;
+#pragma unroll
+        for (int c = 0; c < kOwnVecs; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                own |= mine(id[c][e]) ? 1u << (4 * c + e) : 0u;
+                bad |= static_cast<uint32_t>(id[c][e]) >= static_cast<uint32_t>(N);
             }
-            __syncthreads();  // the count is set
-            bound += kOwnStep;
+        if (base + kOwnChunk > B)  // ids past the end of the list are nobody's
 #pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                const int64_t k = base + (2 * c + e) * kOwnThreads + tid;
-                if (k >= B) continue;
-                const int32_t i = id[c][e];
-                if (i < 0 || i >= N) {
-                    if (blockIdx.x == 0) {
-                        if (info) atomicOr(&info[0], kInfoRange);
-                        if (v_prev) v_prev[k] = __builtin_nanf("");
+            for (int c = 0; c < kOwnVecs; ++c)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (base + c * kOwnVec + tid * 4 + e >= B) own &= ~(1u << (4 * c + e));
+        if (blockIdx.x == 0 && bad)
+#pragma unroll 1
+            for (int j = 0; j < 4 * kOwnVecs; ++j) {
+                const int64_t k = base + (j >> 2) * kOwnVec + tid * 4 + (j & 3);
+                if (k >= B || static_cast<uint32_t>(idx[k]) < static_cast<uint32_t>(N)) continue;
+                if (info) atomicOr(&info[0], kInfoRange);
+                if (v_prev) v_prev[k] = __builtin_nanf("");
+            }
+        __syncthreads();  // coming is cleared, the list of the chunk before is complete
+        if (own) atomicAdd(&coming, __popc(own));
+        __syncthreads();
+        const int seen = count, more = coming;
+        __syncthreads();  // everyone has seen them
+        if (seen + more <= kOwnCap) {
+            while (own) {
+                const int j = __ffs(own) - 1;
+                own &= own - 1;
+                file(base + (j >> 2) * kOwnVec + tid * 4 + (j & 3));
+            }
+        } else {  // a vector per thread at a time, the list applied where the next might not fit
+            int bound = seen;
+#pragma unroll 1
+            for (int c = 0; c < kOwnVecs; ++c) {
+                if (bound + kOwnVec > kOwnCap) {
+                    __syncthreads();
+                    bound = count;
+                    __syncthreads();
+                    if (bound + kOwnVec > kOwnCap) {
+                        apply_list(bound);
+                        if (tid == 0) count = 0;
+                        bound = 0;
                     }
-                    continue;
                 }
-                const uint64_t owner = static_cast<uint64_t>(static_cast<uint32_t>(i) * 0x9E3779B1u) >> shift;
-                if (owner == blockIdx.x)
-                    key[atomicAdd(&count, 1)] = static_cast<uint64_t>(i) << 32 | static_cast<uint32_t>(k);
+                __syncthreads();  // the count is set
+                bound += kOwnVec;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (own >> (4 * c + e) & 1) file(base + c * kOwnVec + tid * 4 + e);
             }
         }
+        __syncthreads();  // count and coming have been read
     }
     __syncthreads();
     apply_list(count);
@@ -346,31 +384,34 @@ advantages_kernel(const float *__restrict__ alpha, const float *__restrict__ bet
     }
 }
 
-// The same over many workgroups, for large batches: two launches, each workgroup over kAdvSpan
-// responses.  part[0..nb) are the workgroups' sums of the raw advantages, part[nb..2nb) the sums of
+// The same over many workgroups: two launches, each workgroup over `span` responses.  One compute unit fetches a line of
+// memory per response and counter, 8192 of them for 4096 responses, in 10 us; spread over 16 units that is one latency.
+// part[0..nb) are the workgroups' sums of the raw advantages, part[nb..2nb) the sums of
 // squares about each workgroup's own mean; every workgroup of the second launch joins them
 // (squares about the common mean = own squares + n (own mean - common mean)^2) in the same fixed
 // order, so all of them hold the same mean and deviation, bit for bit, in every run.  (The order
 // differs from the one-workgroup kernel's: the two agree to fp64 rounding, not bitwise.)
-constexpr int kAdvSpan = 4096, kAdvPer = kAdvSpan / kAdvThreads;
+// Threads of a workgroup: kAdvNarrow with one response each, or kAdvThreads with kAdvPer.
+constexpr int kAdvNarrow = 256, kAdvPer = 4, kAdvSpan = kAdvThreads * kAdvPer;
 
 // phase 0: raw advantages and their partial sums; phase 1: normalised values and the statistics
-template <int Phase>
-__global__ void __launch_bounds__(kAdvThreads)
+template <int Phase, int NT, int PER>
+__global__ void __launch_bounds__(NT)
 advantages_wide_kernel(const float *__restrict__ alpha, const float *__restrict__ beta,
                        const int32_t *__restrict__ idx, const float *__restrict__ reward, int B, int ddof,
                        double eps_norm, int use_baseline, float *__restrict__ adv_raw, float *__restrict__ adv_norm,
                        float *__restrict__ stats, int64_t N, int32_t *__restrict__ info, double *__restrict__ part) {
-    __shared__ double scratch[kAdvThreads / kWave];
+    __shared__ double scratch[2 * NT / kWave];
+    constexpr int span = NT * PER;
     const int nb = gridDim.x, tid = threadIdx.x;
-    const int k0 = blockIdx.x * kAdvSpan, n = B - k0 < kAdvSpan ? B - k0 : kAdvSpan;  // n >= 1
-    double kept[kAdvPer];
-    raw_advantages<kAdvPer>(alpha, beta, use_baseline ? idx + k0 : idx, reward + k0, use_baseline, N, info, tid, kAdvThreads, n, kept);
+    const int k0 = blockIdx.x * span, n = B - k0 < span ? B - k0 : span;  // n >= 1
+    double kept[PER];
+    raw_advantages<PER>(alpha, beta, use_baseline ? idx + k0 : idx, reward + k0, use_baseline, N, info, tid, NT, n, kept);
     if (Phase == 0) {
         double s = 0.0, ss = 0.0;
 #pragma unroll
-        for (int i = 0; i < kAdvPer; ++i) {
-            const int k = tid + i * kAdvThreads;
+        for (int i = 0; i < PER; ++i) {
+            const int k = tid + i * NT;
             if (k >= n) continue;
             if (adv_raw) adv_raw[k0 + k] = static_cast<float>(kept[i]);
             s += kept[i];
@@ -378,8 +419,8 @@ advantages_wide_kernel(const float *__restrict__ alpha, const float *__restrict_
         s = block_sum(s, scratch);
         const double mu = s / static_cast<double>(n);
 #pragma unroll
-        for (int i = 0; i < kAdvPer; ++i)
-            if (tid + i * kAdvThreads < n) ss += (kept[i] - mu) * (kept[i] - mu);
+        for (int i = 0; i < PER; ++i)
+            if (tid + i * NT < n) ss += (kept[i] - mu) * (kept[i] - mu);
         ss = block_sum(ss, scratch);
         if (tid == 0) {
             part[blockIdx.x] = s;
@@ -388,10 +429,10 @@ advantages_wide_kernel(const float *__restrict__ alpha, const float *__restrict_
         return;
     }
     double s = 0.0, ss = 0.0;
-    for (int i = tid; i < nb; i += kAdvThreads) s += part[i];
+    for (int i = tid; i < nb; i += NT) s += part[i];
     const double mu = block_sum(s, scratch) / static_cast<double>(B);
-    for (int i = tid; i < nb; i += kAdvThreads) {
-        const double ni = static_cast<double>(i == nb - 1 ? B - i * kAdvSpan : kAdvSpan), d = part[i] / ni - mu;
+    for (int i = tid; i < nb; i += NT) {
+        const double ni = static_cast<double>(i == nb - 1 ? B - i * span : span), d = part[i] / ni - mu;
         ss += part[nb + i] + ni * d * d;
     }
     ss = block_sum(ss, scratch);
@@ -399,8 +440,8 @@ advantages_wide_kernel(const float *__restrict__ alpha, const float *__restrict_
     const double sigma = dn > 0.0 ? sqrt(ss / dn) : 0.0;
     const double den = sigma + eps_norm;
 #pragma unroll
-    for (int i = 0; i < kAdvPer; ++i) {
-        const int k = tid + i * kAdvThreads;
+    for (int i = 0; i < PER; ++i) {
+        const int k = tid + i * NT;
         // den is >= 0, or NaN and says so
         if (k < n) adv_norm[k0 + k] = den == 0.0 ? 0.0f : static_cast<float>((kept[i] - mu) / den);
     }
@@ -411,15 +452,35 @@ advantages_wide_kernel(const float *__restrict__ alpha, const float *__restrict_
 }
 
 // Diagnostics of the unnormalised advantages (one workgroup, fp64, fixed order).  Bound by the latency
-// of a thread's loads, so kDiagAhead responses are requested at a time, and in long batches by their instructions:
-// only a thread's last group asks which of its responses exist (10^6 responses: 275 us if every group does, 194).
+// of a thread's loads and by its fp64 instructions: up to PER responses per thread stay in registers for both passes, all
+// loads in flight together, a thread adds up its own in two chains (40000 responses: 14.5 us with eight
+// requested at a time and a second pass over memory, 11.9 now).  PER = 0 is the form without a limit: kDiagAhead responses
+// requested at a time, and only a thread's last group asks which of its responses exist (10^6 responses: 275 us if every
+// group does, 194).
 constexpr int kDiagAhead = 8;
 
+template <int PER>
 __global__ void __launch_bounds__(kAdvThreads)
 advantage_diagnostics_kernel(const float *__restrict__ adv_raw, const float *__restrict__ reward, int B,
                              float tau_tight, float tau_loose, float *__restrict__ diag) {
     __shared__ double scratch[4 * kAdvThreads / kWave];
+    float a_kept[PER ? PER : 1], r_kept[PER ? PER : 1];
+    if constexpr (PER > 0) {
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const float *a_row = adv_raw + i * kAdvThreads, *r_row = reward + i * kAdvThreads;  // one place in a register for all
+            const bool in = static_cast<int>(threadIdx.x) < B - i * kAdvThreads;
+            a_kept[i] = in ? a_row[threadIdx.x] : 0.0f;
+            r_kept[i] = in ? r_row[threadIdx.x] : 0.0f;
+        }
+    }
     auto each = [&](auto f) {  // f(advantage, reward) for this thread's responses, in order
+        if constexpr (PER > 0) {
+#pragma unroll
+            for (int i = 0; i < PER; ++i)
+                if (static_cast<int>(threadIdx.x) < B - i * kAdvThreads) f(a_kept[i], r_kept[i]);
+            return;
+        }
         int64_t k0 = threadIdx.x;
         for (; k0 + (kDiagAhead - 1) * kAdvThreads < B; k0 += kDiagAhead * kAdvThreads) {
             float a[kDiagAhead], r[kDiagAhead];
@@ -444,15 +505,20 @@ advantage_diagnostics_kernel(const float *__restrict__ adv_raw, const float *__r
                 if (k0 + i * kAdvThreads < B) f(a[i], r[i]);
         }
     };
-    double s[4] = {};  // within tau_tight, within tau_loose, advantages, rewards
+    int tight = 0, loose = 0;
+    double sa = 0.0, sr = 0.0;
     each([&](float a, float r) {
-        s[0] += fabsf(a) <= tau_tight ? 1.0 : 0.0;
-        s[1] += fabsf(a) <= tau_loose ? 1.0 : 0.0;
-        s[2] += static_cast<double>(a);
-        s[3] += static_cast<double>(r);
+        tight += fabsf(a) <= tau_tight ? 1 : 0;
+        loose += fabsf(a) <= tau_loose ? 1 : 0;
+        sa += static_cast<double>(a);
+        sr += static_cast<double>(r);
     });
+    double s[4] = {static_cast<double>(tight), static_cast<double>(loose), sa, sr};  // within tau_tight, tau_loose, advantages, rewards
     block_sums(s, scratch);
     const double ma = s[2] / B, mr = s[3] / B;
+    if constexpr (PER > 0)  // not to be traced: their fp64 values, kept from the first pass, would not fit the registers
+#pragma unroll
+        for (int i = 0; i < PER; ++i) asm volatile("" : "+v"(a_kept[i]), "+v"(r_kept[i]));
     double v[2] = {};
     each([&](float a, float r) {
         const double da = static_cast<double>(a) - ma, dr = static_cast<double>(r) - mr;
@@ -476,7 +542,11 @@ extern "C" int spo_advantage_diagnostics(const float *adv_raw, const float *rewa
                                          float tau_loose, float *diag, spo_stream_t stream) {
     if (!adv_raw || !reward || !diag) return SPO_ENULL;
     if (B < 1 || !(tau_tight >= 0.0f) || !(tau_loose >= tau_tight)) return SPO_EINVAL;
-    advantage_diagnostics_kernel<<<1, kAdvThreads, 0, as_stream(stream)>>>(adv_raw, reward, B, tau_tight, tau_loose, diag);
+    auto *kernel = B <= 8 * kAdvThreads    ? advantage_diagnostics_kernel<8>
+                   : B <= 24 * kAdvThreads ? advantage_diagnostics_kernel<24>
+                   : B <= 40 * kAdvThreads ? advantage_diagnostics_kernel<40>
+                                           : advantage_diagnostics_kernel<0>;
+    kernel<<<1, kAdvThreads, 0, as_stream(stream)>>>(adv_raw, reward, B, tau_tight, tau_loose, diag);
     return launch_status();
 }
 
@@ -543,11 +613,16 @@ extern "C" int spo_tracker_init(const float *v0, int64_t N, float rho_min, float
     return launch_status();
 }
 
-constexpr int kAdvWideMin = 4 * kAdvSpan;  // below this one workgroup is as fast
+// Batches of one response per thread are as fast in one workgroup (kAdvThreads); up to kAdvNarrowMost workgroups of
+// kAdvNarrow responses follow, then ones of kAdvSpan.
+constexpr int kAdvNarrowMost = 256;
+static size_t adv_parts_bytes(int B, int span) { return static_cast<size_t>(2 * ceil_div(B, span)) * sizeof(double); }
 
+// (never smaller for a larger batch)
 extern "C" size_t spo_advantages_workspace_bytes(int32_t B) {
     if (B < 1) return 0;
-    return static_cast<size_t>(2 * ceil_div(B, kAdvSpan)) * sizeof(double);
+    const int narrow = B < kAdvNarrowMost * kAdvNarrow ? B : kAdvNarrowMost * kAdvNarrow;
+    return std::max(adv_parts_bytes(narrow, kAdvNarrow), adv_parts_bytes(B, kAdvSpan));
 }
 
 extern "C" int spo_advantages(const float *alpha, const float *beta, int64_t N, const int32_t *idx,
@@ -559,24 +634,25 @@ extern "C" int spo_advantages(const float *alpha, const float *beta, int64_t N, 
     if (B < 1 || (use_baseline && N < 1) || ddof < 0 || ddof > 1 || !(eps_norm >= 0.0f))
         return SPO_EINVAL;
     if (ws && reinterpret_cast<uintptr_t>(ws) % 256 != 0) return SPO_EINVAL;
-    if (ws && ws_bytes < spo_advantages_workspace_bytes(B)) return SPO_EWORKSPACE;
+    if (ws && ws_bytes < adv_parts_bytes(B, kAdvSpan)) return SPO_EWORKSPACE;  // (enough for workgroups of kAdvSpan responses)
     hipStream_t s = as_stream(stream);
-    if (!ws || B < kAdvWideMin) {
-        const int threads = B <= kWave ? kWave : kAdvThreads;
-        auto *kernel = B <= kAdvThreads         ? advantages_kernel<1>
-                       : B <= 4 * kAdvThreads   ? advantages_kernel<4>
-                       : B <= 16 * kAdvThreads  ? advantages_kernel<16>
-                                                : advantages_kernel<0>;
-        kernel<<<1, threads, 0, s>>>(alpha, beta, idx, reward, B, ddof, eps_norm, use_baseline, adv_raw, adv_norm, stats, N,
-                                     info);
-        return launch_status();
-    }
-    const unsigned nb = static_cast<unsigned>(ceil_div(B, kAdvSpan));
     double *part = static_cast<double *>(ws);
-    if (info) clear_info_kernel<<<1, 1, 0, s>>>(info);
-    advantages_wide_kernel<0><<<nb, kAdvThreads, 0, s>>>(alpha, beta, idx, reward, B, ddof, eps_norm, use_baseline,
-                                                        adv_raw, adv_norm, stats, N, info, part);
-    advantages_wide_kernel<1><<<nb, kAdvThreads, 0, s>>>(alpha, beta, idx, reward, B, ddof, eps_norm, use_baseline,
-                                                        adv_raw, adv_norm, stats, N, info, part);
+    auto two = [&](auto *first, auto *second, int span, int threads) {
+        const unsigned nb = static_cast<unsigned>(ceil_div(B, span));
+        if (info) clear_info_kernel<<<1, 1, 0, s>>>(info);
+        first<<<nb, threads, 0, s>>>(alpha, beta, idx, reward, B, ddof, eps_norm, use_baseline, adv_raw, adv_norm, stats, N, info, part);
+        second<<<nb, threads, 0, s>>>(alpha, beta, idx, reward, B, ddof, eps_norm, use_baseline, adv_raw, adv_norm, stats, N, info, part);
+        return launch_status();
+    };
+    if (ws && B > kAdvThreads && B <= kAdvNarrowMost * kAdvNarrow && ws_bytes >= adv_parts_bytes(B, kAdvNarrow))
+        return two(advantages_wide_kernel<0, kAdvNarrow, 1>, advantages_wide_kernel<1, kAdvNarrow, 1>, kAdvNarrow, kAdvNarrow);
+    if (ws && B >= 4 * kAdvSpan)
+        return two(advantages_wide_kernel<0, kAdvThreads, kAdvPer>, advantages_wide_kernel<1, kAdvThreads, kAdvPer>, kAdvSpan, kAdvThreads);
+    const int threads = B <= kWave ? kWave : kAdvThreads;
+    auto *kernel = B <= kAdvThreads         ? advantages_kernel<1>
+                   : B <= 4 * kAdvThreads   ? advantages_kernel<4>
+                   : B <= 16 * kAdvThreads  ? advantages_kernel<16>
+                                            : advantages_kernel<0>;
+    kernel<<<1, threads, 0, s>>>(alpha, beta, idx, reward, B, ddof, eps_norm, use_baseline, adv_raw, adv_norm, stats, N, info);
     return launch_status();
 }

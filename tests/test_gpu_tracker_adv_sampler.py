@@ -517,3 +517,94 @@ def test_diagnostics_of_long_batches(spo, B):
 @pytest.mark.parametrize("beta", [True, False])
 def test_advantages_in_two_batches_of_loads(spo, oracle, B, beta):
     test_advantages_kept_in_registers(spo, oracle, B, beta)
+
+
+@pytest.mark.parametrize("B", [1025, 1281, 4096, 65536, 65537])   # one response per thread up to 256 workgroups, then four
+def test_advantages_spread_from_small_batches_on(spo, oracle, B):
+    cfg = wl.CONFIGS["C5"]
+    say(f"advantages over many workgroups, B={B}")
+    a, b = wl.tracker_state(cfg, 7)
+    rng = np.random.default_rng([wl.MASTER_SEED, B, 2])
+    idx = rng.integers(0, cfg.N, B).astype(np.int32)
+    r = (rng.random(B) < 0.4).astype(np.float32)
+    eraw, enrm, (mu, sigma) = oracle.advantages(a, b, idx, r, 1, 0.0, True)
+    args = (dev(a), dev(b), dev(idx), dev(r), 1, 0.0, True)
+    sizes = [spo.lib().spo_advantages_workspace_bytes(n) for n in range(1, B + 1, 97)] + [spo.lib().spo_advantages_workspace_bytes(B)]
+    assert sizes == sorted(sizes)
+    full = torch.full((sizes[-1] + 256,), 255, dtype=torch.uint8, device="cuda")
+    for n in (sizes[-1], 16 * -(-B // 4096)):   # as asked for, and what workgroups of 4096 responses need
+        full.fill_(255)
+        raw, nrm, st = spo.spo_advantages(*args, workspace=full[:n])
+        torch.cuda.synchronize()
+        assert bool((full[n:] == 255).all())
+        np.testing.assert_allclose(raw.cpu().numpy(), eraw, rtol=RTOL, atol=1e-7)
+        np.testing.assert_allclose(nrm.cpu().numpy(), enrm, rtol=RTOL, atol=1e-6)
+        np.testing.assert_allclose(st.cpu().numpy(), [mu, sigma], rtol=RTOL, atol=1e-7)
+
+
+@pytest.mark.parametrize("B", [1, 8192, 8193, 24576, 24577, 40960, 40961])   # 8, 24, 40 responses per thread, any number
+def test_diagnostics_kept_in_registers(spo, B):
+    say(f"diagnostics, B={B}")
+    rng = np.random.default_rng([B, 4])
+    adv = rng.standard_normal(B).astype(np.float32)
+    r = (rng.random(B) < 0.4).astype(np.float32)
+    d = spo.spo_advantage_diagnostics(dev(adv), dev(r), 0.1, 0.3).cpu().numpy()
+    a64 = adv.astype(np.float64)
+    want = [(np.abs(adv) <= np.float32(0.1)).mean(), (np.abs(adv) <= np.float32(0.3)).mean(), a64.var(), r.astype(np.float64).var()]
+    np.testing.assert_allclose(d, want, rtol=1e-6, atol=1e-9)
+
+
+@pytest.mark.parametrize("B,N,hot,offset", [
+    (16383, 5000, 0.0, 0), (16385, 5000, 0.0, 1),   # one chunk of ids and a little more, from an odd place on
+    (40000, 300, 0.0, 0),                           # few prompts: long lists, sorted by the other sort
+    (33000, 20000, 0.9, 3)])                        # one prompt with most of them: lists applied and restarted
+def test_tracker_update_reads_ids_in_chunks(spo, oracle, B, N, hot, offset):
+    say(f"tracker update, repeated ids, B={B} N={N} hot={hot} offset={offset}")
+    rng = np.random.default_rng([B, N])
+    idx = rng.integers(0, N, B).astype(np.int32)
+    idx[rng.random(B) < hot] = 17
+    bad = rng.integers(0, B, 5)
+    idx[bad[:3]], idx[bad[3:]] = N, -1
+    r = (rng.random(B) < 0.4).astype(np.float32)
+    kl = rng.exponential(0.02, B).astype(np.float32)
+    a, b = (rng.uniform(0.5, 50, N).astype(np.float32) for _ in range(2))
+    ea, eb = a.astype(np.float32).copy(), b.astype(np.float32).copy()
+    for k in range(B):   # sequential, one rounding to fp32 per observation
+        i = idx[k]
+        if 0 <= i < N:
+            rho = min(max(2.0 ** (-float(kl[k]) / 0.25), 0.875), 0.96)
+            ea[i] = np.float32(rho * float(ea[i]) + float(r[k]))
+            eb[i] = np.float32(rho * float(eb[i]) + (1.0 - float(r[k])))
+    ga, gb = dev(a), dev(b)
+    ids = torch.zeros(B + offset, dtype=torch.int32, device="cuda")
+    ids[offset:] = dev(idx)
+    info = torch.zeros(1, dtype=torch.int32, device="cuda")
+    vp = spo.spo_tracker_update(ga, gb, ids[offset:], dev(r), dev(kl), 0.25, 0.875, 0.96, ids_unique=False, want_v_prev=True, info=info)
+    torch.cuda.synchronize()
+    assert info.item() == 1 and torch.isnan(vp[torch.as_tensor(np.unique(bad)).cuda()]).all()
+    assert int(torch.isnan(vp).sum()) == len(np.unique(bad))
+    np.testing.assert_allclose(ga.cpu().numpy(), ea, rtol=1e-5)
+    np.testing.assert_allclose(gb.cpu().numpy(), eb, rtol=1e-5)
+
+
+@pytest.mark.parametrize("N,B", [(4097, 300), (4160, 3500), (8193, 64), (100001, 3000), ((1 << 22) + 4097, 700)])
+@pytest.mark.parametrize("replace", [False, True])
+@pytest.mark.parametrize("zeros", [False, True])
+def test_sampler_searches_of_blocks(spo, oracle, N, B, replace, zeros):
+    # ends of blocks of 4096 prompts and of runs of 64 in them, more blocks than LDS holds sums of; with eps = 0 whole
+    # blocks may have no weight at all
+    say(f"sampler, N={N} B={B} replace={replace} zeros={zeros}")
+    rng = np.random.default_rng([N, B])
+    a = rng.uniform(0.5, 50, N).astype(np.float32)
+    b = rng.uniform(0.5, 50, N).astype(np.float32)
+    if zeros:   # blocks without weight at both ends and between, but enough prompts left
+        b[: 4096 if N > 2 * 4096 else 64] = 0
+        b[N // 2: N // 2 + min(N // 8, 9000)] = 0
+        b[-1:] = 0
+        B = min(B, N // 2)
+    eps = 0.0 if zeros else 0.05
+    idx, info = spo.spo_sample_prompts(dev(a), dev(b), B, eps, 11, 5, replace, return_info=True)
+    torch.cuda.synchronize()
+    want = oracle.sample_prompts(a, b, B, eps, 11, 5, replace)
+    want = want[0] if isinstance(want, tuple) else want
+    np.testing.assert_array_equal(idx.cpu().numpy(), want)
