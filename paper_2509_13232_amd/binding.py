@@ -107,6 +107,20 @@ def lib():
     return _lib
 
 
+_calls = None
+
+
+def _plain_calls():
+    """The extension that takes the plain calls (see csrc/calls.cpp); each of its functions returns None for any other."""
+    global _calls
+    if _calls is None:
+        lib()
+        from . import _spo_calls
+        _spo_calls.set_error(SpoError)
+        _calls = _spo_calls
+    return _calls
+
+
 def status_string(status: int) -> str:
     return lib().spo_status_string(int(status)).decode()
 
@@ -116,9 +130,10 @@ def _check(status: int, where: str):
         raise SpoError(status, where)
 
 
-# The smallest calls (a step of 16 prompts, a few rows of logits) are bound by this file: 35 us for the three
-# calls of a prompt step, 12 us of kernels; 27 us since.  Pointers and the stream therefore go to ctypes as plain
-# integers, which the argument types turn into pointers, and no output is a slice of a larger tensor.  The raw
+# The smallest calls (a step of 16 prompts, a few rows of logits) are bound by the host.  What a training loop calls over
+# and over therefore goes to csrc/calls.cpp first (25 us for the three calls of a prompt step through this file, 16
+# there); the general way below takes every other call and says what is wrong with one.  Pointers and the stream go to
+# ctypes as plain integers, which the argument types turn into pointers, and no output is a slice of a larger tensor.  The raw
 # stream comes from the accessor behind torch.cuda.current_stream, without the Stream object that this builds.
 def _ptr(t):
     return None if t is None else t.data_ptr()
@@ -165,6 +180,9 @@ def spo_kernel_timing_read():
 # ------------------------------------------------------------------ sampler
 def spo_sample_prompts(alpha, beta, B, eps_explore=0.05, seed=0, iteration=0, replace=False,
                        max_attempts=0, workspace=None, return_info=False):
+    out = _plain_calls().sample_prompts(alpha, beta, B, eps_explore, seed, iteration, replace, max_attempts, workspace)
+    if out is not None:
+        return out if return_info else out[0]
     N = alpha.numel()
     _want(alpha, torch.float32, "alpha")
     _want(beta, torch.float32, "beta", N)
@@ -198,6 +216,10 @@ def spo_sample_prompts_static(alpha, beta, B, eps_explore=0.05, seed=0, iteratio
 # --------------------------------------------------------------- advantages
 def spo_advantages(alpha, beta, idx, reward, ddof=0, eps_norm=0.0, use_baseline=True, info=None, workspace=None):
     """Returns (adv_raw, adv_norm, stats).  info: optional int32[1] tensor that receives the range flag."""
+    if info is None and use_baseline is True:
+        out = _plain_calls().advantages(alpha, beta, idx, reward, ddof, eps_norm, workspace)
+        if out is not None:
+            return out
     B = reward.numel()
     _want(info, torch.int32, "info", 1)
     _want(reward, torch.float32, "reward")
@@ -218,6 +240,9 @@ def spo_advantages(alpha, beta, idx, reward, ddof=0, eps_norm=0.0, use_baseline=
 
 def spo_advantage_diagnostics(adv_raw, reward, tau_tight=1e-4, tau_loose=0.02):
     """fp32[4]: share |A|<=tau_tight, share |A|<=tau_loose, var(A), var(reward)."""
+    out = _plain_calls().advantage_diagnostics(adv_raw, reward, tau_tight, tau_loose)
+    if out is not None:
+        return out
     B = adv_raw.numel()
     _want(adv_raw, torch.float32, "adv_raw")
     _want(reward, torch.float32, "reward", B)
@@ -252,6 +277,9 @@ def spo_tracker_update(alpha, beta, idx, reward, kl, d_half, rho_min, rho_max, i
                        n_obs=None, want_v_prev=False, info=None, workspace=None, check_repeats=False):
     """Updates alpha and beta IN PLACE; returns v_prev[B] when asked.  info: optional int32[1] tensor
     (bit 1: id out of range, bit 2: repeated id with ids_unique, looked for when check_repeats)."""
+    if n_obs is None and info is None and not (want_v_prev or check_repeats) and \
+            _plain_calls().tracker_update(alpha, beta, idx, reward, kl, d_half, rho_min, rho_max, ids_unique, workspace):
+        return None
     return _tracker_update(lib().spo_tracker_update, "spo_tracker_update", alpha, beta, idx, reward, kl, d_half,
                            rho_min, rho_max, ids_unique, n_obs, want_v_prev, info, workspace, check_repeats)
 
@@ -323,6 +351,10 @@ def _per_token(T, device):
 def spo_pg_loss_fwd(desc, workspace=None, want_stats=True):
     """Returns (loss[1], logp[T], lse[T], stats[4] or None)."""
     d, keep = desc
+    if want_stats is True:
+        out = _plain_calls().pg_loss_fwd(C.addressof(d), keep[3], workspace)
+        if out is not None:
+            return out
     dev = keep[3].device
     loss = torch.empty(1, dtype=torch.float32, device=dev)
     logp = _per_token(d.T, dev)
@@ -345,6 +377,10 @@ def spo_pg_loss_bwd(desc, logp, lse, grad_loss=1.0, d_hidden_dtype=None, d_W_dty
     """Fused form: returns (d_hidden[T,H] or None, d_W in W's layout or None).
     Logits-in form: returns d_logits[T,V]."""
     d, keep = desc
+    if d_hidden_dtype is None and want_d_hidden is True and want_d_W is True:
+        out = _plain_calls().pg_loss_bwd(C.addressof(d), keep[3], logp, lse, grad_loss, d_W, accumulate_dW, chunk_tokens, workspace)
+        if out is not None:
+            return out
     dev = keep[3].device
     _want(logp, torch.float32, "logp", d.T)
     _want(lse, torch.float32, "lse", d.T)
@@ -382,6 +418,10 @@ def spo_pg_loss_fwd_bwd(desc, grad_loss=1.0, d_hidden_dtype=None, d_W_dtype=torc
                         want_stats=True):
     """Fused form only.  Returns (loss[1], logp[T], lse[T], stats[4] or None, d_hidden or None, d_W or None)."""
     d, keep = desc
+    if d_hidden_dtype is None and want_d_hidden is True and want_d_W is True and want_stats is True:
+        out = _plain_calls().pg_loss_fwd_bwd(C.addressof(d), keep[3], grad_loss, d_W, accumulate_dW, chunk_tokens, workspace)
+        if out is not None:
+            return out
     dev = keep[3].device
     hidden, W = keep[0], keep[1]
     loss = torch.empty(1, dtype=torch.float32, device=dev)

@@ -1,4 +1,5 @@
-"""Builds ``libspo_hip.so`` (gfx950 only) from ``csrc/`` with hipcc, in-tree."""
+"""Builds ``libspo_hip.so`` (gfx950 only) from ``csrc/`` with hipcc, in-tree, and ``_spo_calls.so``, the binding's plain
+calls as a Python extension (host code), beside it."""
 from __future__ import annotations
 
 import os
@@ -11,6 +12,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libspo_hip.so")
+CALLS = os.path.join(HERE, "_spo_calls.so")
 SOURCES = ["tracker_adv.hip", "sampler.hip", "pg_logits.hip", "pg_fused.hip", "pg_api.hip", "timing.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I" + INCLUDE, "-I" + CSRC,
          # packed fp32 instructions are kept out of the device code
@@ -51,17 +53,48 @@ def _compile(src: str, obj_dir: str = OBJ, extra=()) -> str:
     return obj
 
 
+def _compile_calls() -> str:
+    import sysconfig
+
+    from torch.utils import cpp_extension
+    obj = os.path.join(OBJ, "calls.o")
+    include = [INCLUDE, CSRC, sysconfig.get_paths()["include"], *cpp_extension.include_paths(), os.path.join(cpp_extension.ROCM_HOME or "/opt/rocm", "include")]
+    import torch
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-w", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *("-I" + i for i in include), "-c", os.path.join(CSRC, "calls.cpp"), "-o", obj]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        sys.stderr.write((r.stdout + r.stderr)[-6000:])
+        raise RuntimeError("g++ failed on calls.cpp")
+    return obj
+
+
+def _link_calls(obj: str) -> str:
+    import torch
+    libs = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = ["g++", "-shared", "-o", CALLS, obj, "-L" + HERE, "-l:" + os.path.basename(LIB), "-Wl,-rpath,$ORIGIN", "-L" + libs,
+           "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        sys.stderr.write((r.stdout + r.stderr)[-3000:])
+        raise RuntimeError("link of the calls failed")
+    return CALLS
+
+
 def build(verbose: bool = False) -> str:
     os.makedirs(OBJ, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
+    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as ex:
+        calls = ex.submit(_compile_calls)
         objs = list(ex.map(_compile, SOURCES))
+        calls_obj = calls.result()
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         sys.stderr.write(r.stdout + r.stderr)
         raise RuntimeError("link failed")
+    _link_calls(calls_obj)
     if verbose:
-        print("built", LIB)
+        print("built", LIB, "and", os.path.basename(CALLS))
     return LIB
 
 
