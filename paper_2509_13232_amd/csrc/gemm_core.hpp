@@ -145,6 +145,29 @@ struct Tile {
                      : "memory");
     }
 
+    // The same where `go` (wave-uniform) is not zero.  The branch is inside the assembly: seen by the compiler, a way round the
+    // requests would split the step they are spread over, and its registers would spill.
+    // (`go` comes in a vector register: the compiler may hold it in one although it is the same in every lane.)
+    __device__ static __forceinline__ void dma_if(int go, const char *base, uint32_t off, uint32_t lds_addr) {
+        int t;
+        asm volatile("v_readfirstlane_b32 %0, %4\n\ts_cmp_eq_u32 %0, 0\n\ts_cbranch_scc1 1f\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
+                     "global_load_lds_dwordx4 %2, %3\n1:"
+                     : "=&s"(t)
+                     : "s"(lds_addr), "v"(off), "s"(base), "v"(go)
+                     : "memory", "scc");
+    }
+    // Waits until at most N vector memory operations are outstanding where `some` is not zero, otherwise for all, and for
+    // all LDS reads.
+    template <int N>
+    __device__ static __forceinline__ void wait_for(int some) {
+        int t;
+        asm volatile("v_readfirstlane_b32 %0, %1\n\ts_cmp_lg_u32 %0, 0\n\ts_cbranch_scc1 1f\n\ts_waitcnt vmcnt(0)\n1:\n\t"
+                     "s_waitcnt vmcnt(%2) lgkmcnt(0)"
+                     : "=&s"(t)
+                     : "v"(some), "n"(N)
+                     : "memory", "scc");
+    }
+
     // LDS stage of an operand whose columns run along k: kBK rows of EDGE elements, chunk c of row r at position
     // c ^ ksw(r).  ksw moves bits 1-2 of the position with the row inside a group of four and the bits from 3 on with
     // the group of eight rows, so the 8-byte pieces a transposing read collects (4 rows x 32 bytes per group of 16
@@ -184,6 +207,29 @@ struct Tile {
             asm volatile("" : "+v"(tid));
             const int lane = tid & 63;
             lds_wave = lds_address(lds) + region + wave_id() * (kWave * 16);
+            aim(o);
+            if constexpr (Cols) {
+                // within 16 lanes a transposing read gives lane i element i%4 of the source lanes i/4 + 4e: source lane s
+                // points at row k0 + s/4, columns 4*(s%4).. of a 16-column block, so lane i ends up with rows
+                // k0..k0+3 of column i; the lane group sets k0 = 8*(l/16) and a second read 4 rows down
+                // completes the 8 values per lane that the MFMA wants
+#pragma unroll
+                for (int b = 0; b < F; ++b) {
+                    const int row = 8 * (lane >> 4) + ((lane & 15) >> 2), col = row0 + b * MI + 4 * (lane & 3);
+                    src[b] = lds_address(lds) + region + row * ROWB + (((col >> 3) ^ ksw<EDGE>(row)) << 4) + ((col >> 2) & 1) * 8;
+                }
+                static_assert((32 + 4) * ROWB < 65536, "slice and half offsets fit the read's offset field");
+            } else {
+                // lane reads row (l%16) of a 16-row block, chunk 4*kk + l/16
+#pragma unroll
+                for (int kk = 0; kk < KK; ++kk) src[kk] = (lane & 15) * kRowBytes + (((4 * kk + (lane >> 4)) ^ swz(lane & 15)) * 16);
+                rows = lds + region + row0 * kRowBytes;
+            }
+        }
+        // where the transfers of the tile at o.first come from
+        __device__ __forceinline__ void aim(const Operand &o) {
+            int tid = threadIdx.x;
+            asm volatile("" : "+v"(tid));
             // 32-bit byte offsets from the tile's first row (a tile spans < 4 GiB)
             const uint32_t ld = static_cast<uint32_t>(o.ld);
             if constexpr (Cols) {
@@ -198,16 +244,6 @@ struct Tile {
                                    : static_cast<uint32_t>(row) * ld + static_cast<uint32_t>((c < c_last ? c : c_last) * 16);
                 }
                 last = o.k_valid ? static_cast<uint32_t>(o.k_valid - 1) * ld + c_last * 16 : 0xffffffffu;
-                // within 16 lanes a transposing read gives lane i element i%4 of the source lanes i/4 + 4e: source lane s
-                // points at row k0 + s/4, columns 4*(s%4).. of a 16-column block, so lane i ends up with rows
-                // k0..k0+3 of column i; the lane group sets k0 = 8*(l/16) and a second read 4 rows down
-                // completes the 8 values per lane that the MFMA wants
-#pragma unroll
-                for (int b = 0; b < F; ++b) {
-                    const int row = 8 * (lane >> 4) + ((lane & 15) >> 2), col = row0 + b * MI + 4 * (lane & 3);
-                    src[b] = lds_address(lds) + region + row * ROWB + (((col >> 3) ^ ksw<EDGE>(row)) << 4) + ((col >> 2) & 1) * 8;
-                }
-                static_assert((32 + 4) * ROWB < 65536, "slice and half offsets fit the read's offset field");
             } else {
                 base = uniform(o.base + o.first * o.ld);
                 step = o.blk ? o.blk : kRowBytes;
@@ -220,21 +256,19 @@ struct Tile {
                     off[i] = (r < r_last ? r : r_last) * ld + chunk16;
                 }
                 last = o.k_valid ? r_last * ld + static_cast<uint32_t>(o.k_valid / 8 - 1) * 16 : 0xffffffffu;
-                // lane reads row (l%16) of a 16-row block, chunk 4*kk + l/16
-#pragma unroll
-                for (int kk = 0; kk < KK; ++kk) src[kk] = (lane & 15) * kRowBytes + (((4 * kk + (lane >> 4)) ^ swz(lane & 15)) * 16);
-                rows = lds + region + row0 * kRowBytes;
             }
         }
         // DMA instruction i of this thread's share of stage kt, into LDS stage buf
-        template <bool Clamp>
-        __device__ __forceinline__ void one(int kt, int buf, int i, bool end) const {
-            uint32_t o = off[i];
-            if constexpr (Clamp) {
-                const uint32_t lim = end ? last : 0xffffffffu;
-                o = o < lim ? o : lim;
-            }
-            dma(base + kt * step, o, lds_wave + buf * STAGE_BYTES + i * (NT * 16));
+        __device__ __forceinline__ void one(int kt, int buf, int i) const {
+            dma(base + kt * step, off[i], lds_wave + buf * STAGE_BYTES + i * (NT * 16));
+        }
+        __device__ __forceinline__ void one_if(int go, int kt, int buf, int i) const {
+            dma_if(go, base + kt * step, off[i], lds_wave + buf * STAGE_BYTES + i * (NT * 16));
+        }
+        // from the next stage on, pieces past the last that may be read are fetched from there
+        __device__ __forceinline__ void clamp() {
+#pragma unroll
+            for (int i = 0; i < LOADS; ++i) off[i] = off[i] < last ? off[i] : last;
         }
         // read r (0 .. READS-1) of k-slice kk into register set buf: of stage kt, or (Cols) of the stage that src points at
         __device__ __forceinline__ void read(int kt, int kk, int buf, int r) {
@@ -276,8 +310,8 @@ struct Tile {
         return Across ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, a, c, 0, 0, 0) : __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
     }
 
-    // acc += sum over k < kBK * KT of A(m, k) B(n, k) for ONE tile.  lds: LDS_BYTES bytes,
-    // 16-byte aligned.  All threads of the block must call this together.
+    // The main loop over one tile or a run of tiles.  lds: LDS_BYTES bytes, 16-byte aligned.  All threads of the
+    // block must call everything here together.
     // ACols, BCols: how the operands lie (see Operand); Clamp: a last stage may not be whole (k_valid).
     //
     // Schedule of a step: both wavefronts of a SIMD multiply at the same time and each hides its
@@ -288,77 +322,131 @@ struct Tile {
     // stage s+1 landed; after it stage s+1 may be read and the buffer of stage s is refilled with
     // stage s+2 (its DMA instructions spread over the MFMAs).
     template <bool ACols, bool BCols, bool Across = false, bool Clamp = false>
-    __device__ static __forceinline__ void mainloop(const Operand &oa, const Operand &ob, int KT, char *lds, Acc &acc) {
+    struct Loop {  // (a run of tiles is not clamped)
+        Side<BM, FM, ACols> a;
+        Side<BN, FN, BCols> b;
+        static constexpr int NR = Side<BM, FM, ACols>::READS + Side<BN, FN, BCols>::READS, READ_EVERY = NR * 2 <= FM * FN ? 2 : 1;
+        static constexpr int DMA_EVERY = FM * FN / STAGE_LOADS, NEXT_EVERY = FM * FN / (2 * STAGE_LOADS);
         static_assert(KK == 2 && kStages == 2, "two k-slices per stage, two stages");
-        Side<BM, FM, ACols> a(oa, lds, 0, wave_m0());
-        Side<BN, FN, BCols> b(ob, lds, A_BYTES, wave_n0());
-        constexpr int NR = a.READS + b.READS, READ_EVERY = NR * 2 <= FM * FN ? 2 : 1;
-        constexpr int DMA_EVERY = FM * FN / STAGE_LOADS;
-        static_assert(NR * READ_EVERY <= FM * FN && DMA_EVERY >= 2, "reads and DMA fit between the MFMAs of a slice");
-        auto read = [&](int kt, int kk, int buf, int r) {
-            if (r < a.READS) a.read(kt, kk, buf, r);
-            else b.read(kt, kk, buf, r - a.READS);
-        };
-        auto feed = [&](int kt, int buf, int i) {
-            const bool end = Clamp && kt == KT - 1;
-            if (i < A_LOADS) a.template one<Clamp>(kt, buf, i, end);
-            else b.template one<Clamp>(kt, buf, i - A_LOADS, end);
-        };
-        __syncthreads();  // every wave is done with the previous contents of lds
-#pragma unroll
-        for (int i = 0; i < STAGE_LOADS; ++i) feed(0, 0, i);
-        if (KT > 1) {
-#pragma unroll
-            for (int i = 0; i < STAGE_LOADS; ++i) feed(1, 1, i);
-            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(STAGE_LOADS) : "memory");  // loads return in order: stage 0 has landed
-        } else {
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        static_assert(NR * READ_EVERY <= FM * FN && DMA_EVERY >= 2 && NEXT_EVERY >= 1, "reads and DMA fit between the MFMAs of a slice");
+
+        __device__ __forceinline__ Loop(const Operand &oa, const Operand &ob, char *lds) : a(oa, lds, 0, wave_m0()), b(ob, lds, A_BYTES, wave_n0()) {}
+
+        __device__ __forceinline__ void feed(int kt, int i) {
+            if (i < A_LOADS) a.one(kt, kt % kStages, i);
+            else b.one(kt, kt % kStages, i - A_LOADS);
         }
-        fence_barrier();
-#pragma unroll
-        for (int r = 0; r < NR; ++r) read(0, 0, 0, r);
-        int to_other = STAGE_BYTES;  // distance to the stage that column addresses do not point at
-        // One step; MORE: a stage kt+1 exists, FEED: a stage kt+2 exists.  Compile-time flags: a
-        // branch around every read and every DMA instruction costs the wavefront more issue time
-        // than the instruction it guards, so the last two steps are peeled off the loop instead.
-        auto step = [&](int kt, auto more_t, auto feed_t) {
-            constexpr bool MORE = decltype(more_t)::value, FEED = decltype(feed_t)::value;
-            // ---- slice 0 of stage kt, reading its slice 1 between the MFMAs
-#pragma unroll
-            for (int j = 0; j < FM * FN; ++j) {
-                const int fm = j / FN, fn = snake(j);
-                if (j % READ_EVERY == 0 && j / READ_EVERY < NR) {
-                    read(kt, 1, 1, j / READ_EVERY);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-                acc[fm][fn] = mfma<Across>(a.frag(0, fm), b.frag(0, fn), acc[fm][fn]);
-                __builtin_amdgcn_sched_barrier(0);
+        __device__ __forceinline__ void feed_if(int go, int kt, int i) {
+            if (i < A_LOADS) a.one_if(go, kt, kt % kStages, i);
+            else b.one_if(go, kt, kt % kStages, i - A_LOADS);
+        }
+        __device__ __forceinline__ void clamp_if(bool end) {
+            if (Clamp && end) {
+                a.clamp();
+                b.clamp();
             }
-            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        }
+        // Requests the first stages of the tile.  Every wavefront is done with the previous contents of lds.
+        __device__ __forceinline__ void start(int KT) {
+            clamp_if(KT == 1);
+#pragma unroll
+            for (int i = 0; i < STAGE_LOADS; ++i) feed(0, i);
+            clamp_if(KT == 2);
+            if (KT > 1)
+#pragma unroll
+                for (int i = 0; i < STAGE_LOADS; ++i) feed(1, i);
+        }
+        // acc += sum over k < kBK * KT of A(m, k) B(n, k) for the tile whose first stages are on their way.
+        // Younger: vector memory operations that the wavefront has surely issued since they were requested, unless
+        // `fresh` (none); they may be outstanding while the stages are waited for (loads and stores leave in order).
+        // more: there is a next tile (next() gives some tile in any case), whose first stages are requested in the last half step, when both LDS stages and one set
+        // of fragments are free; next(true_type) is its loop, which is made anew when its turn comes (kept across the
+        // work between two tiles, its addresses would not fit the registers).
+        template <int Younger, bool Run, typename Next>
+        __device__ __forceinline__ void run(int KT, Acc &acc, bool fresh, bool more, Next next) {
+            auto read = [&](int kt, int kk, int buf, int r) {
+                if (r < a.READS) a.read(kt, kk, buf, r);
+                else b.read(kt, kk, buf, r - a.READS);
+            };
+            // loads return in order: stage 0 has landed
+            if (Run) {  // (of a tile that follows another; both stages of the first one)
+                const int after = fresh ? 0 : 1;
+                if (KT > 1) wait_for<STAGE_LOADS + Younger>(after);
+                else wait_for<Younger>(after);
+            } else if (KT > 1) {
+                asm volatile("s_waitcnt vmcnt(%0)" ::"n"(STAGE_LOADS) : "memory");
+            } else {
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            }
             fence_barrier();
-            a.turn(to_other);
-            b.turn(to_other);
-            to_other = -to_other;
-            // ---- slice 1, reading slice 0 of stage kt+1 and feeding the DMA of stage kt+2
 #pragma unroll
-            for (int j = 0; j < FM * FN; ++j) {
-                const int fm = j / FN, fn = snake(j);
-                if (j % READ_EVERY == 0 && j / READ_EVERY < NR) {
-                    if (MORE) read(kt + 1, 0, 0, j / READ_EVERY);
+            for (int r = 0; r < NR; ++r) read(0, 0, 0, r);
+            int go = 0, go_on = 0;       // there is a next tile, it has a second stage
+            int to_other = STAGE_BYTES;  // distance to the stage that column addresses do not point at
+            // One step; MORE: a stage kt+1 exists, FEED: a stage kt+2 exists, NEXT: the next tile's first stages are
+            // requested.  Compile-time flags: a
+            // branch around every read and every DMA instruction costs the wavefront more issue time
+            // than the instruction it guards, so the last two steps are peeled off the loop instead.
+            auto step = [&](int kt, auto more_t, auto feed_t, auto next_t) {
+                constexpr bool MORE = decltype(more_t)::value, FEED = decltype(feed_t)::value, NEXT = decltype(next_t)::value;
+                // ---- slice 0 of stage kt, reading its slice 1 between the MFMAs
+#pragma unroll
+                for (int j = 0; j < FM * FN; ++j) {
+                    const int fm = j / FN, fn = snake(j);
+                    if (j % READ_EVERY == 0 && j / READ_EVERY < NR) {
+                        read(kt, 1, 1, j / READ_EVERY);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    acc[fm][fn] = mfma<Across>(a.frag(0, fm), b.frag(0, fn), acc[fm][fn]);
                     __builtin_amdgcn_sched_barrier(0);
                 }
-                if (j % DMA_EVERY == 1 && j / DMA_EVERY < STAGE_LOADS) {
-                    if (FEED) feed(kt + 2, kt % kStages, j / DMA_EVERY);
+                if (Run && Younger > 0) wait_for<Younger>(kt == 0 && !fresh ? 1 : 0);
+                else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+                fence_barrier();
+                a.turn(to_other);
+                b.turn(to_other);
+                to_other = -to_other;
+                if (FEED) clamp_if(kt + 3 == KT);
+                // ---- slice 1, reading slice 0 of stage kt+1 and feeding the DMA of stage kt+2
+                auto following = next(std::integral_constant<bool, NEXT>{});
+#pragma unroll
+                for (int j = 0; j < FM * FN; ++j) {
+                    const int fm = j / FN, fn = snake(j);
+                    if (j % READ_EVERY == 0 && j / READ_EVERY < NR) {
+                        if (MORE) read(kt + 1, 0, 0, j / READ_EVERY);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    if (FEED && j % DMA_EVERY == 1 && j / DMA_EVERY < STAGE_LOADS) {
+                        feed(kt + 2, j / DMA_EVERY);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    if constexpr (NEXT) if (j % NEXT_EVERY == 0) {
+                        const int i = j / NEXT_EVERY;
+                        if (i < STAGE_LOADS) following.feed_if(go, 0, i);
+                        else following.feed_if(go_on, 1, i - STAGE_LOADS);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    acc[fm][fn] = mfma<Across>(a.frag(1, fm), b.frag(1, fn), acc[fm][fn]);
                     __builtin_amdgcn_sched_barrier(0);
                 }
-                acc[fm][fn] = mfma<Across>(a.frag(1, fm), b.frag(1, fn), acc[fm][fn]);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        };
-        int kt = 0;
-        for (; kt + 2 < KT; ++kt) step(kt, std::true_type{}, std::true_type{});
-        if (kt + 1 < KT) step(kt++, std::true_type{}, std::false_type{});
-        step(kt, std::false_type{}, std::false_type{});
+            };
+            using std::true_type, std::false_type;
+            go = more ? 1 : 0;
+            go_on = more && KT > 1 ? 1 : 0;
+            int kt = 0;
+            for (; kt + 2 < KT; ++kt) step(kt, true_type{}, true_type{}, false_type{});
+            if (kt + 1 < KT) step(kt++, true_type{}, false_type{}, false_type{});
+            step(kt, false_type{}, false_type{}, std::integral_constant<bool, Run>{});
+        }
+    };
+
+    // acc += sum over k < kBK * KT of A(m, k) B(n, k) for ONE tile.
+    template <bool ACols, bool BCols, bool Across = false, bool Clamp = false>
+    __device__ static __forceinline__ void mainloop(const Operand &oa, const Operand &ob, int KT, char *lds, Acc &acc) {
+        Loop<ACols, BCols, Across, Clamp> loop(oa, ob, lds);
+        __syncthreads();  // every wave is done with the previous contents of lds
+        loop.start(KT);
+        loop.template run<0, false>(KT, acc, true, false, [](auto) { return 0; });
     }
 
     __device__ static __forceinline__ void zero(Acc &acc) {
