@@ -1816,6 +1816,27 @@ static void launch_gather(const spo_pg_desc *d, const void *X, const int32_t *ac
                                                          zero_bytes);
 }
 
+// The logit gradients of the active ones of Tcp gathered rows X; W: the head as it reads it (cols: [H,V]).
+template <typename TT, bool WCols>
+static int launch_recompute(const spo_pg_desc *d, const void *W, const bf16_t *X, int64_t Kc, int64_t Tcp, const float4 *tok, bf16_t *dZ,
+                            const int32_t *n_act, int64_t row_base, hipStream_t s) {
+    auto *kernel = recompute_dz_kernel<TT, WCols>;
+    if (int rc = allow_lds(kernel, TT::LDS_BYTES)) return rc;
+    const int64_t nVt = ceil_div(d->V, TT::BM), wgs = sweep_blocks_max(Tcp / TT::BN, nVt);
+    ScopedKernelTimer timer(kTimeRecompute, s);
+    kernel<<<static_cast<unsigned>(wgs), TT::NT, TT::LDS_BYTES, s>>>(
+        static_cast<const char *>(W), (WCols ? d->V : Kc) * 2, d->V, reinterpret_cast<const char *>(X), Kc * 2, Tcp,
+        static_cast<int>(Kc / kBK), tok, nVt, dZ, Tcp * kBlockK, n_act, row_base);
+    return SPO_OK;
+}
+static int launch_recompute(const spo_pg_desc *d, const void *W, bool cols, const bf16_t *X, int64_t Kc, int64_t Tcp, bool small,
+                            const float4 *tok, bf16_t *dZ, const int32_t *n_act, int64_t row_base, hipStream_t s) {
+    if (small) return cols ? launch_recompute<TS, true>(d, W, X, Kc, Tcp, tok, dZ, n_act, row_base, s)
+                           : launch_recompute<TS, false>(d, W, X, Kc, Tcp, tok, dZ, n_act, row_base, s);
+    return cols ? launch_recompute<TL, true>(d, W, X, Kc, Tcp, tok, dZ, n_act, row_base, s)
+                : launch_recompute<TL, false>(d, W, X, Kc, Tcp, tok, dZ, n_act, row_base, s);
+}
+
 // dHidden of M rows (of Tcp in the blocks of dZ): every part of the vocabulary, the head as WT, or as it was given (NULL).
 static int launch_dhidden(const spo_pg_desc *d, const bf16_t *dZ, int64_t M, int64_t Tcp, const bf16_t *WT, int64_t V_pad, void *out,
                           int out_dtype, const int32_t *n_act, int64_t row_base, const int32_t *row_map, const float *row_scale,
@@ -1927,19 +1948,7 @@ int fused_bwd(const spo_pg_desc *d, const float *logp, const float *lse, float g
         launch_gather(d, d->hidden, p.act_idx, p.n_act, t0, Tcp, d->target, lse, p.g, d->dtype == SPO_BF16 || d_W ? p.Xc : nullptr,
                       p.Xs, p.tok, c == 0 ? d_hidden : nullptr, d_hidden_dtype, T, s);
         const bf16_t *Xk = d->dtype == SPO_FP32 ? p.Xs : p.Xc, *Xrows = p.Xc;  // operands of the recompute and of dW
-        auto recompute = [&](auto *kernel, auto tile, bool cols) {
-            typedef decltype(tile) TT;
-            if (int rc = allow_lds(kernel, TT::LDS_BYTES)) return rc;
-            const int64_t nVt = ceil_div(V, TT::BM), wgs = sweep_blocks_max(Tcp / TT::BN, nVt);
-            ScopedKernelTimer timer(kTimeRecompute, s);
-            kernel<<<static_cast<unsigned>(wgs), TT::NT, TT::LDS_BYTES, s>>>(
-                static_cast<const char *>(Wk), (cols ? V : p.Kc) * 2, V, reinterpret_cast<const char *>(Xk), p.Kc * 2,
-                Tcp, static_cast<int>(p.Kc / kBK), p.tok, nVt, p.dZ, Tcp * kBlockK, p.n_act, t0);
-            return static_cast<int>(SPO_OK);
-        };
-        if (small) rc = direct && hv ? recompute(recompute_dz_kernel<TS, true>, TS{}, true) : recompute(recompute_dz_kernel<TS, false>, TS{}, false);
-        else rc = direct && hv ? recompute(recompute_dz_kernel<TL, true>, TL{}, true) : recompute(recompute_dz_kernel<TL, false>, TL{}, false);
-        if (rc) return rc;
+        if ((rc = launch_recompute(d, Wk, direct && hv, Xk, p.Kc, Tcp, small, p.tok, p.dZ, p.n_act, t0, s))) return rc;
         if (d_hidden && (rc = launch_dhidden(d, p.dZ, Tcp, Tcp, direct ? nullptr : p.WT, p.V_pad, d_hidden, d_hidden_dtype, p.n_act, t0,
                                              p.act_idx + t0, nullptr, p.part_tiles, s)))
             return rc;
@@ -1963,6 +1972,15 @@ int fused_bwd(const spo_pg_desc *d, const float *logp, const float *lse, float g
 // By default a piece's stored logits stay within kDzBudgetBytes, and so do its gradients.
 // Without a loss mask the pass over the stored logits is left out as well: the sweep stores
 // bf16 scaled probabilities that the contractions read as they are (probs_reference).
+//
+// A batch with a mask stores its logits and turns them into gradients in a pass over them: 2 V bytes written, read and
+// written again per token.  Where a logit is few steps of the contraction, forming it again for the active tokens is
+// cheaper: 11238 tokens (a fifth masked) at V = 151936 with H = 192 3936 -> 3366 us, 384 5728 -> 5488, but 512 6210 -> 6261
+// and 1024 10096 -> 11151; short batches gain more (300 at H = 256 247 -> 192 us) and small vocabularies nothing
+// (8000 at 256 x 3000 120.1 and 119.5).  fp32 heads are three times the steps and gain nothing down to H = 64 (189 -> 201).
+constexpr int64_t kAgainSteps = 6;
+static bool form_again(const spo_pg_desc *d) { return d->mask && d->dtype == SPO_BF16 && ceil_div(d->H, kBK) <= kAgainSteps; }
+
 struct FbPlan {
     bool small;
     int64_t Tz, T_pad, V_pad, V_blk, Kc, nVt, nblk_tok, room;  // room: entries of part_max, part_sum
@@ -1973,7 +1991,7 @@ struct FbPlan {
     uint32_t *done;
     int32_t *act_idx, *n_act;
     float4 *tok;
-    uint16_t *Z;
+    uint16_t *Z;  // (and offs: none where the logits of a masked batch are formed again)
     bf16_t *dZ, *WT, *Xc, *Xs, *Ws;
     void *Wvh;
     size_t bytes;
@@ -2006,14 +2024,15 @@ static FbPlan plan_fb(const spo_pg_desc *d, int64_t chunk_tokens, void *ws, bool
     p.part_max = a.take<float>(static_cast<size_t>(p.room));
     p.part_sum = a.take<float>(static_cast<size_t>(p.room));
     p.dense = d->mask == nullptr;
-    p.offs = a.take<float>(p.dense ? p.T_pad : static_cast<size_t>(p.V_blk / (roomy ? TS::WM : TL::WM)) * p.Tz);
+    const bool stored = !form_again(d);
+    p.offs = p.dense ? a.take<float>(p.T_pad) : stored ? a.take<float>(static_cast<size_t>(p.V_blk / (roomy ? TS::WM : TL::WM)) * p.Tz) : nullptr;
     p.cscale = p.dense ? a.take<float>(p.Tz) : nullptr;
     p.act_idx = a.take<int32_t>(p.Tz);
     p.n_act = a.take<int32_t>(1);
     p.tok = a.take<float4>(p.Tz);
     p.Xc = a.take<bf16_t>(static_cast<size_t>(p.Tz) * d->H);
     p.WT = want_dx ? a.take<bf16_t>(static_cast<size_t>(d->H) * p.V_blk) : nullptr;
-    p.Z = a.take<uint16_t>(static_cast<size_t>(p.Tz) * p.V_blk);
+    p.Z = stored ? a.take<uint16_t>(static_cast<size_t>(p.Tz) * p.V_blk) : nullptr;
     p.dZ = p.dense ? nullptr : a.take<bf16_t>(static_cast<size_t>(p.Tz) * p.V_blk);
     p.Xs = p.Ws = nullptr;
     p.dW_acc = nullptr;
@@ -2086,8 +2105,11 @@ int fused_fwd_bwd(const spo_pg_desc *d, float grad_loss, float *loss, float *log
         const SweepMap map(nTt, nVt, sweep_splits(nTt, nVt, tile_slots(p.small),
                                                   static_cast<uint32_t>(std::min<int64_t>(p.room / Tzp, kNoSplitCap))));
         const Sweep w{Wk, H, V, p.Kc, direct && hv, Xk, Tv, p.part_max, p.part_sum, p.Z, Tzp * kBlockK, p.dense ? p.offs + t0 : p.offs};
-        if ((rc = p.dense ? launch_sweep<kEmitProbs>(w, p.small, map, s) : launch_sweep<kEmitLogits>(w, p.small, map, s))) return rc;
-        const bool back = d_hidden || d_W;
+        const bool back = d_hidden || d_W, again = form_again(d);
+        if ((rc = p.dense  ? launch_sweep<kEmitProbs>(w, p.small, map, s)
+                  : again ? launch_sweep<kEmitNone>(w, p.small, map, s)
+                          : launch_sweep<kEmitLogits>(w, p.small, map, s)))
+            return rc;
         TokenGrad gr{};
         if (back) gr = TokenGrad{p.g + t0, Tzp, p.count, grad_loss, nullptr, nullptr, 0, V, d->target + t0};
         if (back && p.dense) {
@@ -2126,7 +2148,9 @@ int fused_fwd_bwd(const spo_pg_desc *d, float grad_loss, float *loss, float *log
                       d->dtype == SPO_BF16 || d_W ? p.Xc : nullptr, nullptr, p.tok,
                       d_hidden ? static_cast<char *>(d_hidden) + t0 * H * dx_elt : nullptr, d_hidden_dtype, Tv, s);
         const bf16_t *Xrows = p.Xc;
-        {
+        if (again) {
+            if ((rc = launch_recompute(d, Wk, direct && hv, Xrows, p.Kc, Tzp, p.small, p.tok, p.dZ, p.n_act, 0, s))) return rc;
+        } else {
             constexpr int per_wg = 8;
             const int64_t n_blk = p.V_blk / kBlockK;
             ScopedKernelTimer timer(kTimeLogitsToDz, s);

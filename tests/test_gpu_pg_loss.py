@@ -460,6 +460,22 @@ def test_tiles_of_both_sizes(spo, T, H, V, w_layout, mask_frac, one_call):
         assert float((got.double() - ref).abs().max()) <= 2e-2 * float(ref.abs().max())
 
 
+@pytest.mark.parametrize("H", [384, 448])  # logits of the active tokens formed twice; stored and turned into gradients
+@pytest.mark.parametrize("T,chunk", [(713, 0), (2600, 1024)])
+@pytest.mark.parametrize("w_layout", [0, 1])
+def test_masked_batches_with_and_without_stored_logits(spo, T, H, chunk, w_layout):
+    say(f"fused bf16 T={T} H={H} V=3000 layout={w_layout} chunk={chunk}: logits of a masked batch")
+    case = Case(wl.scaled(MID, name="again", H=H, V=3000), [T // 3, T - T // 3], mask_frac=0.2)
+    case.old = np.zeros(T, np.float32)
+    case.old = (torch_reference(case)[1].cpu().numpy() + 0.1 * case.noise).astype(np.float32)  # no ratio near a clip bound
+    loss, logp, gx, gw = torch_reference(case)
+    fwd, dx, dw = run_fwd_bwd(spo, case, w_layout, one_call=True, chunk_tokens=chunk)
+    assert abs(fwd[0].item() - loss) <= 2e-3 * abs(loss) + 1e-7
+    assert (fwd[1].double() - logp).abs().max() < 2e-4
+    for got, ref in ((dx, gx), (dw, gw)):
+        assert float((got.double() - ref).norm() / ref.norm()) < GRAD_TOL
+        assert float((got.double() - ref).abs().max()) <= 2e-2 * float(ref.abs().max())
+
 @pytest.mark.parametrize("T,H,V,mask_frac", [(512, 128, 1000, None), (713, 256, 3000, 0.25)])
 def test_workspaces_down_to_what_large_tiles_need(spo, oracle, T, H, V, mask_frac):
     # small tiles have more partial results; a workspace without that room is served by large ones
