@@ -175,6 +175,14 @@ struct Tile {
     template <int EDGE>
     __device__ static __forceinline__ int ksw(int r) { return ((r & 3) << 1) | (((r >> 3) & (EDGE == 256 ? 3 : 1)) << 3); }
 
+    // The thread index through an empty asm, so that the compiler cannot trace what is derived from it: hoisted out of a
+    // loop over tiles these few cheap values would sit in registers across the main loop, where every register counts.
+    __device__ static __forceinline__ int fresh_thread() {
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        return tid;
+    }
+
     // One operand's side of the main loop: EDGE rows (columns) of the tile, F blocks of 16 of them per wavefront.
     // Global -> LDS: slot q = i*NT + tid of a stage <-> (row q / chunks per row, position q % chunks per row).
     // LDS -> fragments: READS reads per k-slice of 32.
@@ -199,15 +207,11 @@ struct Tile {
         v4s half[Cols ? 2 : 1][Cols ? F : 1][2];  // two halves of the 8 contraction values
 
         // region: where this operand lies inside a stage; row0: the wavefront's first row / column of the tile
-        __device__ __forceinline__ Side(const Operand &o, char *lds, int region, int row0) {
-            // The thread index goes through an empty asm so that the compiler cannot trace what is
-            // derived from it: hoisted out of a loop over tiles these few cheap values would sit
-            // in registers across the main loop, where every register counts.
-            int tid = threadIdx.x;
-            asm volatile("" : "+v"(tid));
+        // tid: fresh_thread()
+        __device__ __forceinline__ Side(const Operand &o, char *lds, int region, int row0, int tid) {
             const int lane = tid & 63;
             lds_wave = lds_address(lds) + region + wave_id() * (kWave * 16);
-            aim(o);
+            aim(o, tid);
             if constexpr (Cols) {
                 // within 16 lanes a transposing read gives lane i element i%4 of the source lanes i/4 + 4e: source lane s
                 // points at row k0 + s/4, columns 4*(s%4).. of a 16-column block, so lane i ends up with rows
@@ -227,9 +231,7 @@ struct Tile {
             }
         }
         // where the transfers of the tile at o.first come from
-        __device__ __forceinline__ void aim(const Operand &o) {
-            int tid = threadIdx.x;
-            asm volatile("" : "+v"(tid));
+        __device__ __forceinline__ void aim(const Operand &o, int tid) {
             // 32-bit byte offsets from the tile's first row (a tile spans < 4 GiB)
             const uint32_t ld = static_cast<uint32_t>(o.ld);
             if constexpr (Cols) {
@@ -330,7 +332,10 @@ struct Tile {
         static_assert(KK == 2 && kStages == 2, "two k-slices per stage, two stages");
         static_assert(NR * READ_EVERY <= FM * FN && DMA_EVERY >= 2 && NEXT_EVERY >= 1, "reads and DMA fit between the MFMAs of a slice");
 
-        __device__ __forceinline__ Loop(const Operand &oa, const Operand &ob, char *lds) : a(oa, lds, 0, wave_m0()), b(ob, lds, A_BYTES, wave_n0()) {}
+        // (what both sides derive from one fresh thread index is formed once; a run has no registers to keep it in)
+        __device__ __forceinline__ Loop(const Operand &oa, const Operand &ob, char *lds, int tid) : Loop(oa, ob, lds, tid, tid) {}
+        __device__ __forceinline__ Loop(const Operand &oa, const Operand &ob, char *lds, int tid_a, int tid_b)
+            : a(oa, lds, 0, wave_m0(), tid_a), b(ob, lds, A_BYTES, wave_n0(), tid_b) {}
 
         __device__ __forceinline__ void feed(int kt, int i) {
             if (i < A_LOADS) a.one(kt, kt % kStages, i);
@@ -443,7 +448,7 @@ struct Tile {
     // acc += sum over k < kBK * KT of A(m, k) B(n, k) for ONE tile.
     template <bool ACols, bool BCols, bool Across = false, bool Clamp = false>
     __device__ static __forceinline__ void mainloop(const Operand &oa, const Operand &ob, int KT, char *lds, Acc &acc) {
-        Loop<ACols, BCols, Across, Clamp> loop(oa, ob, lds);
+        Loop<ACols, BCols, Across, Clamp> loop(oa, ob, lds, fresh_thread());
         __syncthreads();  // every wave is done with the previous contents of lds
         loop.start(KT);
         loop.template run<0, false>(KT, acc, true, false, [](auto) { return 0; });

@@ -823,14 +823,17 @@ fwd_sweep_kernel(const char *__restrict__ W, int64_t ldw_bytes, int64_t V, const
         st[0] = make_float4(m_run[0], m_run[1], m_run[2], m_run[3]);
         st[1] = make_float4(s_run[0], s_run[1], s_run[2], s_run[3]);
     };
-        // Where tiles are stored they are a run: the first stages of the next tile are requested in the last step of this one,
+    // Where tiles are stored they are a run: the first stages of the next tile are requested in the last step of this one,
     // and this one's stores (at least kStores per wavefront) are not waited for before its first step: 8192 tokens at 1024 x
     // 151936 6420 -> 6345 us, 11238 masked ones at 192 x 151936 4101 -> 4022, 20000 at 2048 x 60000 the same.  (Without stores
     // it is 2 % slower, and so no gain for the recompute, whose records would have to wait in LDS.)
     constexpr bool kRun = Emit != kEmitNone;
     constexpr int kStores = kRun ? TT::FN * (TT::FM / 4) * 2 : 0;
     typedef typename TT::template Loop<WCols, false> Tiles;
-    auto tile = [&](int64_t vt) { return Tiles({W, ldw_bytes, vt * TT::BM, V, 0, 0}, {X, ldx_bytes, n0, T, 0, 0}, lds); };
+    auto tile = [&](int64_t vt) {
+        const int tid = TT::fresh_thread();
+        return Tiles({W, ldw_bytes, vt * TT::BM, V, 0, 0}, {X, ldx_bytes, n0, T, 0, 0}, lds, tid, kRun ? TT::fresh_thread() : tid);
+    };
     for (int64_t vt = vt0; vt < vt1; ++vt) {
         typename TT::Acc acc;
         TT::zero(acc);
