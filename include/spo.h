@@ -132,9 +132,10 @@ int spo_sample_prompts_static(const float *alpha, const float *beta, int64_t N, 
  * ws           optional, spo_advantages_workspace_bytes(B) bytes, 256-byte aligned.
  *              Without it one workgroup does all the work (right for the batches
  *              of the paper; from 16385 responses on it reads the batch three times, slow
- *              beyond ~10^5 responses); with it, batches of 16384 responses or more are spread
- *              over the chip (partial sums of 4096 responses each, added in a fixed
- *              order).  Both forms are bitwise reproducible; between them the
+ *              beyond ~10^5 responses); with it, batches of more than 1024 responses are spread
+ *              over the chip (partial sums of 256 responses each, beyond 65536 of 4096, added in a fixed
+ *              order; a workspace that has room for partial sums of 4096 responses only is accepted and
+ *              spreads batches of 16384 or more).  Both forms are bitwise reproducible; between them the
  *              statistics agree to fp64 rounding.
  * Statistics are accumulated in fp64 in a fixed order.
  * Limits: 1 <= B < 2^31.  Errors: ws too small -> SPO_EWORKSPACE.
@@ -327,7 +328,9 @@ int spo_pg_loss_bwd(const spo_pg_desc *d, const float *logp, const float *lse, f
  *    fp16 resolves d * 2^-11: the error this adds to a probability p is at most
  *    p * ln(1/p) * 2^-11.  One pass then turns the stored logits of the tokens with a
  *    non-zero factor into bf16 logit gradients (as much workspace again), and the
- *    contractions run over those tokens only, as in spo_pg_loss_bwd.
+ *    contractions run over those tokens only, as in spo_pg_loss_bwd.  bf16 heads of up
+ *    to 384 hidden units store no logits: those of the tokens with a factor are formed
+ *    again, which costs less there, straight into their gradients.
  * chunk_tokens = 0 lets the library choose: the most tokens, in multiples of 4096,
  * whose stored values stay within 8 GiB (24576 at V = 151936).  Shorter pieces cost
  * more passes over d_W.

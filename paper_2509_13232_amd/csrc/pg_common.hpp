@@ -90,7 +90,7 @@ constexpr int kTokWaves = 16;       // most wavefronts per workgroup
 // How a launch over n_blocks blocks is cut: four splits for each of `ways` wavefronts while the blocks alone do not
 // fill the chip (kTokChipWaves), and from kTokFewBlocks on several blocks per workgroup, more where there would be
 // more than kTokChipGroups workgroups: their counts meet at one address, 11 ns apart.  (200000 tokens of two splits:
-// 19 us, 27 with four blocks per workgroup and 71 with one, of 16 wavefronts.)
+// 19 us, 27 with four blocks per workgroup and 71 with one, of 16 wavefronts, while the count still wrote caches back.)
 constexpr int kTokChipWaves = 2048, kTokChipGroups = 512, kTokFewBlocks = 64;
 struct TokenShape {
     unsigned blocks, threads;

@@ -3,7 +3,7 @@
 // draw of the training loop).  The O(N) part (weights + scans of blocks) streams the tracker
 // once; the draw itself is B searches, of the blocks' sums and of a block's CDF.  Tables of one scan block are
 // handled by a single launch that keeps the CDF in LDS (a step of 16 prompts: 7 launches -> 3,
-// 52 us -> 35 us, what is left being the host's).
+// 52 us -> 35 us, what was left being the host's: 16 us with the plain calls in an extension).
 //
 // Everything that decides an index is integer arithmetic or a single correctly
 // rounded IEEE fp64 operation (add, divide, subtract, multiply, sqrt: no fused

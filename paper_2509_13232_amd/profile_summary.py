@@ -17,12 +17,13 @@ import csv
 import glob
 import json
 import os
+import re
 
 from .build import source_digest
 
 KERNELS = (("fwd_sweep", "fwd_sweep_kernel"), ("bwd_recompute", "recompute_dz_kernel"),
            ("logits_to_dz", "dz_from_logits_kernel"),
-           ("bwd_dhidden", "gemm_store_kernel<false>"), ("bwd_dw", "gemm_store_kernel<true>"))
+           ("bwd_dhidden", "gemm_store_kernel<\\w+, false"), ("bwd_dw", "gemm_store_kernel<\\w+, true"))
 BENCH = "python3 bench.py --no-cpu-baseline --no-small --no-logits-in --no-others"
 
 
@@ -42,7 +43,7 @@ def _one(d, pattern):
 
 
 def _short(name):
-    return name.split("(")[0].replace("void ", "")
+    return re.sub(r"spo::Tile<(\d+), (\d+)[^>]*>", r"\1x\2", name.split("(")[0].replace("void ", ""))
 
 
 def _counters(d):
@@ -55,8 +56,7 @@ def _counters(d):
 
 
 def _of(table, sub):
-    ks = [k for k in table if sub in k]
-    return table[ks[0]] if ks else []
+    return [x for k in table if re.search(sub, k) for x in table[k]]  # (a short last piece may run on smaller tiles)
 
 
 def kernel_trace(args, b):
@@ -85,7 +85,7 @@ def kernel_trace(args, b):
                 continue
         o.append(f"    {_short(r['Name'])[:58]:58s} {int(r['Calls']):6d} {int(r['TotalDurationNs']) / 1e6:11.3f} "
                  f"{float(r['AverageNs']) / 1e6:10.4f} {float(r['Percentage']):7.3f}")
-    o.append("\ngemm_store_kernel<false> is the dHidden contraction, gemm_store_kernel<true> the dW contraction;")
+    o.append("\ngemm_store_kernel<tile, false, ..> is the dHidden contraction, gemm_store_kernel<tile, true, ..> the dW contraction;")
     o.append("fwd_sweep_kernel<0> forms log-sum-exps only, <1> also stores a piece's logits (batches with a loss mask), which")
     o.append("dz_from_logits_kernel turns into logit gradients, <2> its scaled probabilities (without). The batch is walked in")
     o.append("pieces (one call) or the backward in chunks of tokens that carry a gradient (two calls); per-launch averages are")
