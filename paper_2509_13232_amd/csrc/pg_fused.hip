@@ -22,6 +22,7 @@
 #include <algorithm>
 
 #include "gemm_core.hpp"
+#include "head_form.hpp"
 #include "pg_common.hpp"
 #include "timing.hpp"
 
@@ -1490,7 +1491,6 @@ struct TileTimes {
 constexpr TileTimes kSweepTimes{1.30, 8.3, 0.57, 0.85, 0.90, 4.4, 4.6, 5.1, 0.0};
 constexpr TileTimes kDHiddenTimes{1.70, 4.6, 0.34, 0.75, 1.00, 0.0, 17.0, 15.4, 4.1};
 constexpr TileTimes kDWTimes{1.66, 10.7, 0.53, 0.75, 0.90, 7.0, 3.2, 2.1, 19.0};
-constexpr int64_t kHeadInL2 = int64_t(32) << 20;
 static double launch_time(const TileTimes &t, bool small, double rounds, int64_t wgs, int64_t steps, int64_t head_bytes) {
     const double step = !small ? t.step : wgs <= kChipCUs ? t.lone : head_bytes <= kHeadInL2 ? t.in_l2 : t.pair;
     return rounds * (static_cast<double>(steps) * step + (small ? t.ends_s : t.ends)) + (small ? t.rest_s : t.rest);
@@ -1539,23 +1539,9 @@ static bool small_dW(int64_t T, int64_t H, int64_t V) {
     return small_is_faster(time);
 }
 
-// Is a bf16 head read as it was given, or copied into the forms that the main loop reads fastest?  Columns along k
-// (dHidden of a head [V,H], the logits of one [H,V]) and rows that are not blocked cost 2 to 5 % of a contraction, and
-// the target logits of a head [H,V] then come out of its columns, a line of memory per value; the copies take the
-// time of reading the head and writing it once or twice.
-//   [V,H]: only dHidden's form is spared.  8192 tokens at 1024 x 151936 6440 us with the copy, 6374 without; 522 at 2112 x
-//   151936 2058 and 1843; the gain has vanished at 14000 tokens by these figures.
-//   [H,V]: both forms are spared, and a launch: 271 tokens at 3136 x 151936 2035 us with the copies, 1579 without; 4000 at
-//   2048 x 151936 6553 and 6414; 4000 at 4096 x 30000 2614 and 2795; 1100 at 768 x 1000 66 and 65, 4000 of them 82 and 87.
-//   Values out of columns: 14 us per million where the head comes from memory, 4 out of the L2s.
-constexpr int64_t kDirectTokens = 8192;
+static_assert(TL::BN <= kTileRows && TS::BN <= kTileRows && kBK <= 64, "what rows_fit_offsets counts");
 static bool direct_head(const spo_pg_desc *d) {
-    if (d->dtype != SPO_BF16) return false;
-    if (d->w_layout == SPO_W_VH) return d->T <= kDirectTokens;
-    if (d->V % 8 != 0) return false;  // rows of [H,V] on 16-byte boundaries
-    const double T = static_cast<double>(d->T), head = static_cast<double>(d->H) * static_cast<double>(d->V);
-    const double columns = T * static_cast<double>(d->H) * (head * 2 <= static_cast<double>(kHeadInL2 / 4) ? 4e-6 : 14e-6);
-    return columns + T * head * 7e-11 < 8.0 + head * 1.07e-6;
+    return direct_head(d->dtype == SPO_BF16, d->w_layout == SPO_W_HV, d->T, d->H, d->V);
 }
 
 struct FwdPlan {

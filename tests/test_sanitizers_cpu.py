@@ -52,12 +52,21 @@ def test_abi_argument_checks_run_clean_under_asan_and_ubsan(tmp_path):
     assert "ABI host-side sanitizer run ok" in r.stdout
 
 
-def test_claims_of_a_draw_without_replacement_follow_the_sequential_rule(tmp_path):
-    # whatever the order of the claims, and also where a displaced slot has to find its attempt again
-    exe = str(tmp_path / "claims")
+def _run_host_part(tmp_path, name):
+    # a header of csrc/ that needs no GPU, with the program that drives it
+    exe = str(tmp_path / name)
     csrc = os.path.join(ROOT, "paper_2509_13232_amd", "csrc")
     subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all", "-pthread",
-                    "-Wall", "-Wextra", "-I" + csrc, os.path.join(SAN, "claims_driver.cpp"), "-o", exe], check=True)
+                    "-Wall", "-Wextra", "-I" + csrc, os.path.join(SAN, name + "_driver.cpp"), "-o", exe], check=True)
     r = subprocess.run([exe], capture_output=True, text=True, env=ENV, timeout=300)
     assert r.returncode == 0, (r.stdout + r.stderr)[-3000:]
-    assert "claims follow the sequential rule" in r.stdout
+    return r.stdout
+
+
+def test_claims_of_a_draw_without_replacement_follow_the_sequential_rule(tmp_path):
+    # whatever the order of the claims, and also where a displaced slot has to find its attempt again
+    assert "claims follow the sequential rule" in _run_host_part(tmp_path, "claims")
+
+
+def test_heads_read_as_given_fit_the_offsets_of_the_main_loop(tmp_path):
+    assert "heads read as given fit the offsets" in _run_host_part(tmp_path, "head_form")
