@@ -411,7 +411,6 @@ struct Tile {
                 a.turn(to_other);
                 b.turn(to_other);
                 to_other = -to_other;
-                if (FEED) clamp_if(kt + 3 == KT);
                 // ---- slice 1, reading slice 0 of stage kt+1 and feeding the DMA of stage kt+2
                 auto following = next(std::integral_constant<bool, NEXT>{});
 #pragma unroll
@@ -439,7 +438,15 @@ struct Tile {
             go = more ? 1 : 0;
             go_on = more && KT > 1 ? 1 : 0;
             int kt = 0;
-            for (; kt + 2 < KT; ++kt) step(kt, true_type{}, true_type{}, false_type{});
+            if constexpr (Clamp) {  // the step that requests the last stage apart: a condition in the loop spilled 36 registers
+                for (; kt + 3 < KT; ++kt) step(kt, true_type{}, true_type{}, false_type{});
+                if (kt + 2 < KT) {
+                    clamp_if(true);
+                    step(kt++, true_type{}, true_type{}, false_type{});
+                }
+            } else {
+                for (; kt + 2 < KT; ++kt) step(kt, true_type{}, true_type{}, false_type{});
+            }
             if (kt + 1 < KT) step(kt++, true_type{}, false_type{}, false_type{});
             step(kt, false_type{}, false_type{}, std::integral_constant<bool, Run>{});
         }
