@@ -113,12 +113,10 @@ struct Tile {
     // base + (c / kBlockK) * blk + k * ld + (c % kBlockK) * 2 bytes, all columns of the tile readable.
     // first: the tile's first row / column, a whole number of blocks where blk != 0 and Cols.
     // Elements of the last stage past the contraction's end are fetched like the others - the other operand is zero
-    // there - unless k_valid says how many elements of the last stage there are (0: all kBK may be read): what lies past
-    // the operand's last piece is then fetched from that piece.
+    // there - unless the second operand ends inside it (see mainloop).
     struct Operand {
         const char *base;
         int64_t ld, first, count, blk;
-        int k_valid;
     };
 
     // the same in every lane; say so, the DMA wants it in SGPRs
@@ -198,7 +196,6 @@ struct Tile {
         const char *base;            // first row / column of the panel (wave-uniform)
         int64_t step;                // bytes from one stage to the next
         uint32_t off[LOADS];         // this lane's byte offsets inside the panel
-        uint32_t last;               // the last piece that may be read of a last stage that is not whole
         uint32_t lds_wave;           // LDS address of this wave's 1 KiB slice of stage 0
         uint32_t src[Cols ? F : KK];  // Cols: LDS address of this lane's piece of each block, slice 0, of the stage in use;
                                      // otherwise its offset inside 16 rows, per k-slice
@@ -245,7 +242,6 @@ struct Tile {
                     off[i] = o.blk ? static_cast<uint32_t>((c / cpb) * o.blk + row * o.ld + (c % cpb) * 16)
                                    : static_cast<uint32_t>(row) * ld + static_cast<uint32_t>((c < c_last ? c : c_last) * 16);
                 }
-                last = o.k_valid ? static_cast<uint32_t>(o.k_valid - 1) * ld + c_last * 16 : 0xffffffffu;
             } else {
                 base = uniform(o.base + o.first * o.ld);
                 step = o.blk ? o.blk : kRowBytes;
@@ -257,7 +253,6 @@ struct Tile {
                     const uint32_t r = static_cast<uint32_t>(i * (NT / kChunks) + ld_row);
                     off[i] = (r < r_last ? r : r_last) * ld + chunk16;
                 }
-                last = o.k_valid ? r_last * ld + static_cast<uint32_t>(o.k_valid / 8 - 1) * 16 : 0xffffffffu;
             }
         }
         // DMA instruction i of this thread's share of stage kt, into LDS stage buf
@@ -267,10 +262,24 @@ struct Tile {
         __device__ __forceinline__ void one_if(int go, int kt, int buf, int i) const {
             dma_if(go, base + kt * step, off[i], lds_wave + buf * STAGE_BYTES + i * (NT * 16));
         }
-        // from the next stage on, pieces past the last that may be read are fetched from there
-        __device__ __forceinline__ void clamp() {
+        // A last stage of `end` elements (rows along k: a multiple of 8): does piece i of this thread lie past them?
+        __device__ static __forceinline__ bool past(int i, int tid, int end) {
+            return (Cols ? (i * NT + tid) / CHUNKS : ((tid % kChunks) ^ swz(tid / kChunks & 15)) * 8) >= end;
+        }
+        // from the next stage on, pieces past its end are fetched from its first one
+        __device__ __forceinline__ void clamp(int end) {
+            const int tid = fresh_thread();
 #pragma unroll
-            for (int i = 0; i < LOADS; ++i) off[i] = off[i] < last ? off[i] : last;
+            for (int i = 0; i < LOADS; ++i) off[i] = past(i, tid, end) ? 0u : off[i];
+        }
+        // ... and cleared in LDS stage buf.  This thread's transfers have landed.
+        __device__ __forceinline__ void clear(int buf, int end) const {
+            typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+            const int tid = fresh_thread();
+            const uint32_t at = lds_wave + buf * STAGE_BYTES + (tid & 63) * 16;
+#pragma unroll
+            for (int i = 0; i < LOADS; ++i)
+                if (past(i, tid, end)) *(u4 __attribute__((address_space(3))) *)(uintptr_t)(at + i * (NT * 16)) = u4{0, 0, 0, 0};
         }
         // read r (0 .. READS-1) of k-slice kk into register set buf: of stage kt, or (Cols) of the stage that src points at
         __device__ __forceinline__ void read(int kt, int kk, int buf, int r) {
@@ -314,7 +323,7 @@ struct Tile {
 
     // The main loop over one tile or a run of tiles.  lds: LDS_BYTES bytes, 16-byte aligned.  All threads of the
     // block must call everything here together.
-    // ACols, BCols: how the operands lie (see Operand); Clamp: a last stage may not be whole (k_valid).
+    // ACols, BCols: how the operands lie (see Operand); Clamp: B's last stage has `end` elements (0: all).
     //
     // Schedule of a step: both wavefronts of a SIMD multiply at the same time and each hides its
     // own fragment reads between its MFMAs (one read per two MFMAs, or per one where there are more, into a second
@@ -345,18 +354,23 @@ struct Tile {
             if (i < A_LOADS) a.one_if(go, kt, kt % kStages, i);
             else b.one_if(go, kt, kt % kStages, i - A_LOADS);
         }
-        __device__ __forceinline__ void clamp_if(bool end) {
-            if (Clamp && end) {
-                a.clamp();
-                b.clamp();
-            }
+        // What B has past its end is not to be read, and what is fetched in its place must not count: zeros of A times an
+        // infinite weight are NaN (a head that bans a token).  Before the requests of the last stage, and before the barrier that
+        // opens it.
+        __device__ __forceinline__ void clamp_if(bool last, int end) {
+            if (Clamp && last && end) b.clamp(end);
+        }
+        __device__ __forceinline__ void clear_if(int buf, int end) {
+            if (!Clamp || !end) return;
+            b.clear(buf, end);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         }
         // Requests the first stages of the tile.  Every wavefront is done with the previous contents of lds.
-        __device__ __forceinline__ void start(int KT) {
-            clamp_if(KT == 1);
+        __device__ __forceinline__ void start(int KT, int end = 0) {
+            clamp_if(KT == 1, end);
 #pragma unroll
             for (int i = 0; i < STAGE_LOADS; ++i) feed(0, i);
-            clamp_if(KT == 2);
+            clamp_if(KT == 2, end);
             if (KT > 1)
 #pragma unroll
                 for (int i = 0; i < STAGE_LOADS; ++i) feed(1, i);
@@ -368,7 +382,7 @@ struct Tile {
         // of fragments are free; next(true_type) is its loop, which is made anew when its turn comes (kept across the
         // work between two tiles, its addresses would not fit the registers).
         template <int Younger, bool Run, typename Next>
-        __device__ __forceinline__ void run(int KT, Acc &acc, bool fresh, bool more, Next next) {
+        __device__ __forceinline__ void run(int KT, Acc &acc, bool fresh, bool more, Next next, int end = 0) {
             auto read = [&](int kt, int kk, int buf, int r) {
                 if (r < a.READS) a.read(kt, kk, buf, r);
                 else b.read(kt, kk, buf, r - a.READS);
@@ -382,6 +396,7 @@ struct Tile {
                 asm volatile("s_waitcnt vmcnt(%0)" ::"n"(STAGE_LOADS) : "memory");
             } else {
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                clear_if(0, end);
             }
             fence_barrier();
 #pragma unroll
@@ -407,6 +422,7 @@ struct Tile {
                 }
                 if (Run && Younger > 0) wait_for<Younger>(kt == 0 && !fresh ? 1 : 0);
                 else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+                if (MORE && !FEED) clear_if((kt + 1) % kStages, end);
                 fence_barrier();
                 a.turn(to_other);
                 b.turn(to_other);
@@ -441,7 +457,7 @@ struct Tile {
             if constexpr (Clamp) {  // the step that requests the last stage apart: a condition in the loop spilled 36 registers
                 for (; kt + 3 < KT; ++kt) step(kt, true_type{}, true_type{}, false_type{});
                 if (kt + 2 < KT) {
-                    clamp_if(true);
+                    clamp_if(true, end);
                     step(kt++, true_type{}, true_type{}, false_type{});
                 }
             } else {
@@ -452,13 +468,14 @@ struct Tile {
         }
     };
 
-    // acc += sum over k < kBK * KT of A(m, k) B(n, k) for ONE tile.
+    // acc += sum over k < kBK * KT of A(m, k) B(n, k) for ONE tile.  end (Clamp): B's last stage has that many elements, a
+    // multiple of 8 where its rows are along k; past them A is zero.  0: all kBK may be read.
     template <bool ACols, bool BCols, bool Across = false, bool Clamp = false>
-    __device__ static __forceinline__ void mainloop(const Operand &oa, const Operand &ob, int KT, char *lds, Acc &acc) {
+    __device__ static __forceinline__ void mainloop(const Operand &oa, const Operand &ob, int KT, char *lds, Acc &acc, int end = 0) {
         Loop<ACols, BCols, Across, Clamp> loop(oa, ob, lds, fresh_thread());
         __syncthreads();  // every wave is done with the previous contents of lds
-        loop.start(KT);
-        loop.template run<0, false>(KT, acc, true, false, [](auto) { return 0; });
+        loop.start(KT, end);
+        loop.template run<0, false>(KT, acc, true, false, [](auto) { return 0; }, end);
     }
 
     __device__ static __forceinline__ void zero(Acc &acc) {

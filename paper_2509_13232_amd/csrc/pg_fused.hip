@@ -833,7 +833,7 @@ fwd_sweep_kernel(const char *__restrict__ W, int64_t ldw_bytes, int64_t V, const
     typedef typename TT::template Loop<WCols, false> Tiles;
     auto tile = [&](int64_t vt) {
         const int tid = TT::fresh_thread();
-        return Tiles({W, ldw_bytes, vt * TT::BM, V, 0, 0}, {X, ldx_bytes, n0, T, 0, 0}, lds, tid, kRun ? TT::fresh_thread() : tid);
+        return Tiles({W, ldw_bytes, vt * TT::BM, V, 0}, {X, ldx_bytes, n0, T, 0}, lds, tid, kRun ? TT::fresh_thread() : tid);
     };
     for (int64_t vt = vt0; vt < vt1; ++vt) {
         typename TT::Acc acc;
@@ -1001,8 +1001,8 @@ recompute_dz_kernel(const char *__restrict__ W, int64_t ldw_bytes, int64_t V,
     for (int tm = vt0; tm < vt1; ++tm) {
         typename TT::Acc acc;
         TT::zero(acc);
-        TT::template mainloop<WCols, false>({W, ldw_bytes, static_cast<int64_t>(tm) * TT::BM, V, 0, 0},
-                                            {X, ldx_bytes, static_cast<int64_t>(tn) * TT::BN, T_valid, 0, 0}, KT, lds, acc);
+        TT::template mainloop<WCols, false>({W, ldw_bytes, static_cast<int64_t>(tm) * TT::BM, V, 0},
+                                            {X, ldx_bytes, static_cast<int64_t>(tn) * TT::BN, T_valid, 0}, KT, lds, acc);
         emit(acc, tm, tn);
     }
 }
@@ -1254,9 +1254,8 @@ gemm_store_kernel(const char *__restrict__ A, int64_t lda_bytes, int64_t M, cons
         const int64_t sa = ACols ? kBK * lda_bytes : a_blk ? a_blk : kBK * 2, sb = BCols ? kBK * ldb_bytes : b_blk ? b_blk : kBK * 2;
         const int64_t Mr = ACols ? (a_blk ? m0 + TT::BM : (M + 7) & ~int64_t(7)) : M;
         const int64_t Nr = BCols ? (b_blk ? n0 + TT::BN : (N + 7) & ~int64_t(7)) : N;
-        TT::template mainloop<ACols, BCols, true, Clamp>({A + kt0 * sa, lda_bytes, m0, Mr, a_blk, 0},
-                                                         {B + kt0 * sb, ldb_bytes, n0, Nr, b_blk, Clamp && kt0 + KT == KT_all ? k_valid : 0},
-                                                         KT, lds, acc);
+        TT::template mainloop<ACols, BCols, true, Clamp>({A + kt0 * sa, lda_bytes, m0, Mr, a_blk}, {B + kt0 * sb, ldb_bytes, n0, Nr, b_blk}, KT, lds,
+                                                         acc, Clamp && kt0 + KT == KT_all ? k_valid : 0);
     }
     GemmOut o{out, ldo, m0, m_end, static_cast<int>(n0), static_cast<int>(N), out_dtype, accumulate, row_map, row_scale};
     if (nsplit > 1 || tail == kTailCut) {  // a part: fp32, in place, unscaled (parts are scaled when they are added)

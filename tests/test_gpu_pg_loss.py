@@ -476,6 +476,38 @@ def test_masked_batches_with_and_without_stored_logits(spo, T, H, chunk, w_layou
         assert float((got.double() - ref).norm() / ref.norm()) < GRAD_TOL
         assert float((got.double() - ref).abs().max()) <= 2e-2 * float(ref.abs().max())
 
+
+@pytest.mark.parametrize("T,H,V", [
+    (100, 64, 40),          # one stage of 40 entries
+    (300, 128, 104),        # two
+    (713, 256, 3000),       # small tiles, the vocabulary in parts
+    (1000, 2112, 20008),    # large tiles
+    (700, 4096, 8307)])     # rows of a head [H,V] that start anywhere: copied
+@pytest.mark.parametrize("w_layout", [0, 1])
+@pytest.mark.parametrize("mask_frac", [None, 0.2], ids=["no_mask", "masked"])
+def test_infinite_weights_stay_in_their_column(spo, T, H, V, w_layout, mask_frac, one_call):
+    # A head may ban a token: one feature is 1 everywhere and its weight is -inf.  d_hidden of that feature is then NaN (a
+    # probability of 0 times -inf), and so are the banned ids' rows of d_W (rows that pad the batch); all else is what a very
+    # large finite weight gives.  The banned ids are those whose weights lie beside what a last stage that is not whole
+    # reads in place of entries past the vocabulary.
+    say(f"fused bf16 T={T} H={H} V={V} layout={w_layout} mask={mask_frac} one_call={one_call}: infinite weights")
+    case = Case(wl.scaled(MID, name="ban", H=H, V=V), [T // 3, T - T // 3], mask_frac=mask_frac)
+    feature, banned = H - 1, [0, V - 1]
+    case.hidden[:, feature] = 1.0
+    case.target[:] = 1 + case.target % (V - 2)
+    case.W[banned] = 0.0
+    case.old = np.zeros(T, np.float32)
+    case.W[banned, feature] = -3e38
+    case.old = (torch_reference(case)[1].cpu().numpy() + 0.1 * case.noise).astype(np.float32)
+    res = []
+    for ban in (-3e38, -np.inf):
+        case.W[banned, feature] = ban
+        res.append(run_fwd_bwd(spo, case, w_layout, one_call=one_call))
+    (fwd, dx, dw), (fwd_inf, dx_inf, dw_inf) = res
+    assert all(torch.equal(a, b) for a, b in zip(fwd, fwd_inf)) and torch.equal(dw[1:V - 1], dw_inf[1:V - 1])
+    assert torch.isfinite(dx).all() and torch.equal(dx[:, :feature], dx_inf[:, :feature])
+
+
 @pytest.mark.parametrize("T,H,V,mask_frac", [(512, 128, 1000, None), (713, 256, 3000, 0.25)])
 def test_workspaces_down_to_what_large_tiles_need(spo, oracle, T, H, V, mask_frac):
     # small tiles have more partial results; a workspace without that room is served by large ones
