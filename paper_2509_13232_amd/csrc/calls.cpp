@@ -11,6 +11,7 @@
 #include <ATen/PythonTorchFunctionTLS.h>
 #include <ATen/core/TensorBody.h>
 #include <ATen/ops/empty.h>
+#include <c10/core/impl/LocalDispatchKeySet.h>
 #include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
@@ -30,7 +31,17 @@ PyObject *refused(int status, const char *where) {
     return nullptr;
 }
 
-bool plain_context() { return !at::impl::torch_function_mode_enabled() && !c10::impl::TorchDispatchModeTLS::any_modes_set(); }
+// Under a transform (grad, jvp, functionalize, vmap of torch.func), functionalization or a trace, outputs made here are not
+// plain tensors, whatever the inputs are.
+bool plain_context() {
+    using c10::DispatchKey;
+    constexpr c10::DispatchKeySet transforms({DispatchKey::FuncTorchDynamicLayerFrontMode, DispatchKey::FuncTorchDynamicLayerBackMode,
+                                              DispatchKey::FuncTorchVmapMode, DispatchKey::VmapMode, DispatchKey::Functionalize,
+                                              DispatchKey::Tracer, DispatchKey::PreDispatch, DispatchKey::PythonDispatcher,
+                                              DispatchKey::Python, DispatchKey::PythonTLSSnapshot});
+    return !at::impl::torch_function_mode_enabled() && !c10::impl::TorchDispatchModeTLS::any_modes_set() &&
+           !c10::impl::tls_local_dispatch_key_set().included_.has_any(transforms);
+}
 
 // NULL: not a plain tensor
 const at::Tensor *tensor(PyObject *o) {
@@ -77,12 +88,14 @@ spo_stream_t stream() { return reinterpret_cast<spo_stream_t>(c10::hip::getCurre
 template <typename T> T *ptr(const at::Tensor *t) { return t ? static_cast<T *>(t->data_ptr()) : nullptr; }
 template <typename T> T *ptr(const at::Tensor &t) { return static_cast<T *>(t.data_ptr()); }
 
-template <typename F> int unlocked(F call) {  // other threads run meanwhile, as through ctypes
-    int rc;
-    Py_BEGIN_ALLOW_THREADS
-    rc = call();
-    Py_END_ALLOW_THREADS
-    return rc;
+// Other threads run meanwhile, as through ctypes.  The lock is taken again on every way out: an exception (a tensor that has
+// no memory) is turned into Python's by the caller, which needs it.
+template <typename F> int unlocked(F call) {
+    struct Unlocked {
+        PyThreadState *state = PyEval_SaveThread();
+        ~Unlocked() { PyEval_RestoreThread(state); }
+    } lock;
+    return call();
 }
 template <typename... T> PyObject *tuple_of(T &&...t) { return PyTuple_Pack(sizeof...(t), t...); }
 // a tuple of new references

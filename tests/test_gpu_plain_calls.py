@@ -148,3 +148,35 @@ def test_errors_are_those_of_the_general_way(spo, monkeypatch):
                     call()
                 seen.append((type(e.value), str(e.value), getattr(e.value, "status", None)))
         assert seen[0] == seen[1], (i, seen)
+
+
+@pytest.mark.parametrize("under", ["grad", "jvp", "functionalize", "vmap"])
+def test_calls_under_a_transform_take_the_general_way(spo, monkeypatch, under):
+    # outputs made under a transform may have no memory to write to: what then happens (an error, or a result) is the
+    # general way's business
+    say(f"plain calls under {under}")
+    raw, r = torch.linspace(-1, 1, 24, device="cuda"), torch.ones(24, device="cuda")
+    x = torch.ones(2, device="cuda")
+    seen = []
+
+    def f(t):
+        try:
+            d = spo.spo_advantage_diagnostics(raw, r)
+            seen[-1].append("result" if torch._C._functorch.is_functorch_wrapped_tensor(d) else d.cpu().tolist())
+        except Exception as e:
+            seen[-1].append((type(e), str(e), getattr(e, "status", None)))
+        return t.sum()
+
+    F = torch.func
+    run = {"grad": lambda: F.grad(f)(x), "jvp": lambda: F.jvp(f, (x,), (x,)), "functionalize": lambda: F.functionalize(f)(x),
+           "vmap": lambda: F.vmap(f)(x[None])}[under]
+    real = spo._plain_calls()
+    for way in (real, Nothing()):
+        seen.append([])
+        with monkeypatch.context() as m:
+            m.setattr(spo, "_calls", way)
+            run()
+    torch.cuda.synchronize()
+    assert seen[0] and seen[0] == seen[1], seen
+    # afterwards calls are plain again, and other threads run
+    assert real.advantage_diagnostics(raw, r, 1e-4, 0.02) is not None
