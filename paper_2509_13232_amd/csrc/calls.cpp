@@ -69,7 +69,9 @@ bool number(PyObject *o, double &v) {
     if (PyFloat_CheckExact(o)) v = PyFloat_AS_DOUBLE(o);
     else if (PyLong_CheckExact(o)) v = PyLong_AsDouble(o);
     else return false;
-    return !PyErr_Occurred();
+    if (!PyErr_Occurred()) return true;
+    PyErr_Clear();  // an int past the largest double: the general way says so
+    return false;
 }
 bool whole(PyObject *o, int64_t lo, int64_t hi, int64_t &v) {
     if (!PyLong_CheckExact(o)) return false;

@@ -130,6 +130,10 @@ def test_errors_are_those_of_the_general_way(spo, monkeypatch):
         lambda: spo.spo_sample_prompts(a.double(), b, 8, workspace=ws),
         lambda: spo.spo_sample_prompts(a.cpu(), b, 8, workspace=ws),
         lambda: spo.spo_sample_prompts(a, b, 8, 1.5, workspace=ws),
+        lambda: spo.spo_sample_prompts(a, b, 8, 10 ** 400, workspace=ws),             # an int that no double holds
+        lambda: spo.spo_advantages(a, b, idx, r, 0, -10 ** 400),
+        lambda: spo.spo_advantage_diagnostics(r, r, 0, 10 ** 400),
+        lambda: spo.spo_tracker_update(a, b, idx, r, r, 10 ** 400, 0.875, 0.96),
         lambda: spo.spo_advantages(a, b, idx.long(), r),
         lambda: spo.spo_advantages(a, b, idx, r, ddof=2),
         lambda: spo.spo_advantages(a, b, idx, r, workspace=ws[8:]),
