@@ -367,6 +367,14 @@ def spo_pg_loss_fwd(desc, workspace=None, want_stats=True):
     return loss, logp, lse, stats
 
 
+def _want_d_W(d_W, d):
+    """The first V * H elements of a d_W that the caller gives are written, in order: it has to hold them."""
+    if not (d_W.is_cuda or d_W.is_pinned()) or not d_W.is_contiguous():
+        raise TypeError("d_W: expected a contiguous CUDA tensor")
+    if d_W.numel() < d.V * d.H:
+        raise ValueError(f"d_W: expected {d.V * d.H} elements, got {d_W.numel()}")
+
+
 def spo_pg_loss_bwd_workspace_bytes(desc, chunk_tokens=0) -> int:
     return int(lib().spo_pg_loss_bwd_workspace_bytes(C.byref(desc[0]), int(chunk_tokens)))
 
@@ -402,6 +410,8 @@ def spo_pg_loss_bwd(desc, logp, lse, grad_loss=1.0, d_hidden_dtype=None, d_W_dty
         d_W = torch.empty(W.shape, dtype=d_W_dtype, device=dev)
     if not want_d_W:
         d_W = None
+    if d_W is not None:
+        _want_d_W(d_W, d)
     _check(lib().spo_pg_loss_bwd(C.byref(d), _ptr(logp), _ptr(lse), float(grad_loss), _ptr(dx),
                                  _dt(dx.dtype) if dx is not None else 0, _ptr(d_W),
                                  _dt(d_W.dtype) if d_W is not None else 0, int(bool(accumulate_dW)), None,
@@ -439,6 +449,8 @@ def spo_pg_loss_fwd_bwd(desc, grad_loss=1.0, d_hidden_dtype=None, d_W_dtype=torc
         d_W = torch.empty(W.shape, dtype=d_W_dtype, device=dev)
     if not want_d_W:
         d_W = None
+    if d_W is not None:
+        _want_d_W(d_W, d)
     _check(lib().spo_pg_loss_fwd_bwd(C.byref(d), float(grad_loss), _ptr(loss), _ptr(logp), _ptr(lse), _ptr(stats),
                                      _ptr(dx), _dt(dx.dtype) if dx is not None else 0, _ptr(d_W),
                                      _dt(d_W.dtype) if d_W is not None else 0, int(bool(accumulate_dW)),

@@ -208,7 +208,12 @@ bool descriptor(PyObject *address, PyObject *target, const spo_pg_desc *&d, cons
     return d && like && d->T > 0;
 }
 at::ScalarType type_of(int dtype) { return dtype == SPO_FP32 ? at::kFloat : at::kBFloat16; }
-int code_of(const at::Tensor &t) { return t.scalar_type() == at::kFloat ? SPO_FP32 : t.scalar_type() == at::kBFloat16 ? SPO_BF16 : -1; }
+// the caller's d_W: the first V * H of its elements are written, in order
+const at::Tensor *head_gradient(PyObject *o, const spo_pg_desc *d) {
+    const at::Tensor *t = tensor(o);
+    return t && (t->scalar_type() == at::kFloat || t->scalar_type() == at::kBFloat16) && t->is_contiguous() && t->numel() >= d->V * d->H ? t : nullptr;
+}
+int code_of(const at::Tensor &t) { return t.scalar_type() == at::kFloat ? SPO_FP32 : SPO_BF16; }
 
 // (descriptor, target, workspace) -> (loss, logp, lse, stats)
 PyObject *pg_loss_fwd(PyObject *, PyObject *const *a, Py_ssize_t n) {
@@ -251,8 +256,8 @@ PyObject *pg_loss_bwd(PyObject *, PyObject *const *a, Py_ssize_t n) {
         });
         return rc ? refused(rc, "spo_pg_loss_bwd") : wrap(dl);
     }
-    const at::Tensor *dw = tensor(a[5]);
-    if (!dw || code_of(*dw) < 0) return none();
+    const at::Tensor *dw = head_gradient(a[5], d);
+    if (!dw) return none();
     const at::Tensor dx = fresh({d->T, d->H}, type_of(d->dtype), *like);
     const spo_stream_t s = stream();
     const int rc = unlocked([&] {
@@ -271,11 +276,11 @@ PyObject *pg_loss_fwd_bwd(PyObject *, PyObject *const *a, Py_ssize_t n) {
     const spo_pg_desc *d;
     const at::Tensor *like;
     if (n != 7 || !plain_context() || !descriptor(a[0], a[1], d, like) || d->logits) return none();
-    const at::Tensor *dw = tensor(a[3]);
+    const at::Tensor *dw = head_gradient(a[3], d);
     double grad;
     int accumulate;
     int64_t chunk;
-    if (!dw || code_of(*dw) < 0 || !number(a[2], grad) || !flag(a[4], accumulate) || !whole(a[5], INT64_MIN, INT64_MAX, chunk)) return none();
+    if (!dw || !number(a[2], grad) || !flag(a[4], accumulate) || !whole(a[5], INT64_MIN, INT64_MAX, chunk)) return none();
     const at::Tensor *ws = workspace(a[6], spo_pg_loss_fwd_bwd_workspace_bytes(d, chunk));
     if (!ws) return none();
     const at::Tensor loss = fresh({1}, at::kFloat, *like), logp = fresh({d->T}, at::kFloat, *like), lse = fresh({d->T}, at::kFloat, *like),

@@ -143,6 +143,14 @@ def test_errors_are_those_of_the_general_way(spo, monkeypatch):
         lambda: spo.spo_tracker_update(a, b, idx, r, r[::2], 0.25, 0.875, 0.96),
         lambda: spo.spo_tracker_update(a, b, idx, r, r, 0.25, 0.875, 0.96, ids_unique=False, workspace=ws[:0]),
     ]
+    case = Case(wl.scaled(wl.CONFIGS["C2"], name="plain", H=128, V=600), [30, 90])
+    case.old = np.full(case.T, -6.0, np.float32)
+    desc = case.to_gpu(spo)
+    logp = torch.full((case.T,), -6.0, device="cuda")
+    wb, wo = space(spo.spo_pg_loss_bwd_workspace_bytes(desc)), space(spo.spo_pg_loss_fwd_bwd_workspace_bytes(desc))
+    for d_W in (torch.zeros(599, 128, device="cuda"), torch.zeros(128, 600, device="cuda").t(), torch.zeros(600, 128)):  # short, across, on the host
+        calls += [lambda d_W=d_W: spo.spo_pg_loss_bwd(desc, logp, logp, d_W=d_W, workspace=wb),
+                  lambda d_W=d_W: spo.spo_pg_loss_fwd_bwd(desc, d_W=d_W, workspace=wo)]
     for i, call in enumerate(calls):
         seen = []
         for way in (spo._plain_calls(), Nothing()):
