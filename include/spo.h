@@ -335,7 +335,8 @@ int spo_pg_loss_bwd(const spo_pg_desc *d, const float *logp, const float *lse, f
  * whose stored values stay within 8 GiB (24576 at V = 151936).  Shorter pieces cost
  * more passes over d_W.
  * Arguments as in spo_pg_loss_fwd and spo_pg_loss_bwd; d_hidden and d_W may each be
- * NULL.  The workspace size depends on whether the desc has a mask.  Errors as
+ * NULL.  The workspace size depends on whether the desc has a mask; one queried with a
+ * mask also serves the same batch without one.  Errors as
  * there; a desc with logits != NULL -> SPO_EUNSUPPORTED. */
 size_t spo_pg_loss_fwd_bwd_workspace_bytes(const spo_pg_desc *d, int64_t chunk_tokens);
 int spo_pg_loss_fwd_bwd(const spo_pg_desc *d, float grad_loss, float *loss, float *logp,

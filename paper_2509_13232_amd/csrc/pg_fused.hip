@@ -2037,7 +2037,13 @@ static FbPlan plan_fb(const spo_pg_desc *d, int64_t chunk_tokens, void *ws, bool
 
 int fused_fwd_bwd_workspace(const spo_pg_desc *d, int64_t chunk_tokens, size_t *bytes) {
     const FbPlan p = plan_fb(d, chunk_tokens, nullptr, true, true, true);  // sized for the larger case
-    *bytes = p.bytes + room_for_shorter_chunks(d, p.Tz);
+    *bytes = p.bytes;
+    if (d->mask) {  // enough for a batch without one as well: a program that masks some of its batches keeps one workspace
+        spo_pg_desc all = *d;
+        all.mask = nullptr;
+        *bytes = std::max(*bytes, plan_fb(&all, chunk_tokens, nullptr, true, true, true).bytes);
+    }
+    *bytes += room_for_shorter_chunks(d, p.Tz);
     return SPO_OK;
 }
 

@@ -169,3 +169,14 @@ def test_gradient_workspace_of_long_chunks_serves_short_ones(L, dtype, mask):
         for chunk in (0, 256, 4096):
             by_T = [[s[0] for s in sizes(T, V, H, [chunk])] for T in TOKENS]
             assert all(_never_shrinks([s[i] for s in by_T]) for i in (0, 1)), (V, H, chunk)
+
+
+@pytest.mark.parametrize("w_layout", [0, 1])
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_one_call_workspace_of_a_masked_batch_serves_one_without_a_mask(L, dtype, w_layout):
+    size = lambda T, V, H, chunk, mask: L.spo_pg_loss_fwd_bwd_workspace_bytes(_pg_desc(T, V, H, dtype, w_layout, mask), chunk)
+    for H in (64, 128, 384, 448, 4096):   # short rows store no logits, longer ones do
+        for V in (40, 300, 3000, 151936):
+            for chunk in (0, 256, 4096):
+                for T in TOKENS[::4]:
+                    assert size(T, V, H, chunk, True) >= size(T, V, H, chunk, False) > 0, (T, V, H, chunk)
