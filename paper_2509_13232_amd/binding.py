@@ -132,7 +132,8 @@ def _check(status: int, where: str):
 
 # The smallest calls (a step of 16 prompts, a few rows of logits) are bound by the host.  What a training loop calls over
 # and over therefore goes to csrc/calls.cpp first (25 us for the three calls of a prompt step through this file, 16
-# there); the general way below takes every other call and says what is wrong with one.  Pointers and the stream go to
+# there); the general way below takes every other call and says what is wrong with one.  Calls that leave a workspace or
+# d_W to be allocated go there at once.  Pointers and the stream go to
 # ctypes as plain integers, which the argument types turn into pointers, and no output is a slice of a larger tensor.  The raw
 # stream comes from the accessor behind torch.cuda.current_stream, without the Stream object that this builds.
 def _ptr(t):
@@ -180,9 +181,10 @@ def spo_kernel_timing_read():
 # ------------------------------------------------------------------ sampler
 def spo_sample_prompts(alpha, beta, B, eps_explore=0.05, seed=0, iteration=0, replace=False,
                        max_attempts=0, workspace=None, return_info=False):
-    out = _plain_calls().sample_prompts(alpha, beta, B, eps_explore, seed, iteration, replace, max_attempts, workspace)
-    if out is not None:
-        return out if return_info else out[0]
+    if workspace is not None:
+        out = _plain_calls().sample_prompts(alpha, beta, B, eps_explore, seed, iteration, replace, max_attempts, workspace)
+        if out is not None:
+            return out if return_info else out[0]
     N = alpha.numel()
     _want(alpha, torch.float32, "alpha")
     _want(beta, torch.float32, "beta", N)
@@ -277,7 +279,7 @@ def spo_tracker_update(alpha, beta, idx, reward, kl, d_half, rho_min, rho_max, i
                        n_obs=None, want_v_prev=False, info=None, workspace=None, check_repeats=False):
     """Updates alpha and beta IN PLACE; returns v_prev[B] when asked.  info: optional int32[1] tensor
     (bit 1: id out of range, bit 2: repeated id with ids_unique, looked for when check_repeats)."""
-    if n_obs is None and info is None and not (want_v_prev or check_repeats) and \
+    if n_obs is None and info is None and not (want_v_prev or check_repeats) and (workspace is not None or ids_unique) and \
             _plain_calls().tracker_update(alpha, beta, idx, reward, kl, d_half, rho_min, rho_max, ids_unique, workspace):
         return None
     return _tracker_update(lib().spo_tracker_update, "spo_tracker_update", alpha, beta, idx, reward, kl, d_half,
@@ -351,7 +353,7 @@ def _per_token(T, device):
 def spo_pg_loss_fwd(desc, workspace=None, want_stats=True):
     """Returns (loss[1], logp[T], lse[T], stats[4] or None)."""
     d, keep = desc
-    if want_stats is True:
+    if want_stats is True and workspace is not None:
         out = _plain_calls().pg_loss_fwd(C.addressof(d), keep[3], workspace)
         if out is not None:
             return out
@@ -385,7 +387,7 @@ def spo_pg_loss_bwd(desc, logp, lse, grad_loss=1.0, d_hidden_dtype=None, d_W_dty
     """Fused form: returns (d_hidden[T,H] or None, d_W in W's layout or None).
     Logits-in form: returns d_logits[T,V]."""
     d, keep = desc
-    if d_hidden_dtype is None and want_d_hidden is True and want_d_W is True:
+    if workspace is not None and (d_W is not None or d.logits) and d_hidden_dtype is None and want_d_hidden is True and want_d_W is True:
         out = _plain_calls().pg_loss_bwd(C.addressof(d), keep[3], logp, lse, grad_loss, d_W, accumulate_dW, chunk_tokens, workspace)
         if out is not None:
             return out
@@ -404,14 +406,14 @@ def spo_pg_loss_bwd(desc, logp, lse, grad_loss=1.0, d_hidden_dtype=None, d_W_dty
     dx = None
     if want_d_hidden:
         dx = torch.empty((d.T, d.H), dtype=d_hidden_dtype or hidden.dtype, device=dev)
-    if want_d_W and d_W is None:
-        if accumulate_dW:
-            raise ValueError("accumulate_dW needs an existing d_W")
-        d_W = torch.empty(W.shape, dtype=d_W_dtype, device=dev)
     if not want_d_W:
         d_W = None
-    if d_W is not None:
+    elif d_W is not None:
         _want_d_W(d_W, d)
+    elif accumulate_dW:
+        raise ValueError("accumulate_dW needs an existing d_W")
+    else:
+        d_W = torch.empty(W.shape, dtype=d_W_dtype, device=dev)
     _check(lib().spo_pg_loss_bwd(C.byref(d), _ptr(logp), _ptr(lse), float(grad_loss), _ptr(dx),
                                  _dt(dx.dtype) if dx is not None else 0, _ptr(d_W),
                                  _dt(d_W.dtype) if d_W is not None else 0, int(bool(accumulate_dW)), None,
@@ -428,7 +430,7 @@ def spo_pg_loss_fwd_bwd(desc, grad_loss=1.0, d_hidden_dtype=None, d_W_dtype=torc
                         want_stats=True):
     """Fused form only.  Returns (loss[1], logp[T], lse[T], stats[4] or None, d_hidden or None, d_W or None)."""
     d, keep = desc
-    if d_hidden_dtype is None and want_d_hidden is True and want_d_W is True and want_stats is True:
+    if workspace is not None and d_W is not None and d_hidden_dtype is None and want_d_hidden is True and want_d_W is True and want_stats is True:
         out = _plain_calls().pg_loss_fwd_bwd(C.addressof(d), keep[3], grad_loss, d_W, accumulate_dW, chunk_tokens, workspace)
         if out is not None:
             return out
@@ -443,14 +445,14 @@ def spo_pg_loss_fwd_bwd(desc, grad_loss=1.0, d_hidden_dtype=None, d_W_dtype=torc
     dx = None
     if want_d_hidden:
         dx = torch.empty((d.T, d.H), dtype=d_hidden_dtype or hidden.dtype, device=dev)
-    if want_d_W and d_W is None:
-        if accumulate_dW:
-            raise ValueError("accumulate_dW needs an existing d_W")
-        d_W = torch.empty(W.shape, dtype=d_W_dtype, device=dev)
     if not want_d_W:
         d_W = None
-    if d_W is not None:
+    elif d_W is not None:
         _want_d_W(d_W, d)
+    elif accumulate_dW:
+        raise ValueError("accumulate_dW needs an existing d_W")
+    else:
+        d_W = torch.empty(W.shape, dtype=d_W_dtype, device=dev)
     _check(lib().spo_pg_loss_fwd_bwd(C.byref(d), float(grad_loss), _ptr(loss), _ptr(logp), _ptr(lse), _ptr(stats),
                                      _ptr(dx), _dt(dx.dtype) if dx is not None else 0, _ptr(d_W),
                                      _dt(d_W.dtype) if d_W is not None else 0, int(bool(accumulate_dW)),

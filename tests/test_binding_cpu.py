@@ -77,3 +77,33 @@ def test_a_given_d_W_holds_the_head(reached, w_layout, one_call):
     call(OnDevice(torch.zeros(shape[0] + 28, shape[1])))          # and a buffer that is longer
     call(OnDevice(torch.zeros(1)), want_d_W=False)                # not looked at
     assert len(reached) == 4
+
+
+def test_calls_without_a_workspace_do_not_ask_for_a_plain_call(reached, monkeypatch):
+    asked = []
+
+    class Asked:
+        def __getattr__(self, name):
+            return lambda *a: asked.append(name)
+
+    monkeypatch.setattr(spo, "_calls", Asked())
+    f, i = OnDevice(torch.zeros(16)), OnDevice(torch.zeros(4, dtype=torch.int32))
+    r, ws = OnDevice(torch.zeros(4)), OnDevice(torch.zeros(512, dtype=torch.uint8))
+    ws.data_ptr = lambda: 256
+    desc, logp, lse = _desc(spo.SPO_W_VH)
+    d_W = OnDevice(torch.zeros(100, 64))
+    spo.spo_sample_prompts(f, f, 4)
+    spo.spo_tracker_update(f, f, i, r, r, 0.25, 0.875, 0.96, ids_unique=False)
+    spo.spo_pg_loss_fwd(desc)
+    for w, g in ((None, d_W), (ws, None), (None, None)):
+        spo.spo_pg_loss_bwd(desc, logp, lse, d_W=g, workspace=w)
+        spo.spo_pg_loss_fwd_bwd(desc, d_W=g, workspace=w)
+    assert len(reached) == 9 and not asked
+    # those that might be plain do
+    spo.spo_sample_prompts(f, f, 4, workspace=ws)
+    spo.spo_advantages(f, f, i, r)
+    spo.spo_tracker_update(f, f, i, r, r, 0.25, 0.875, 0.96)
+    spo.spo_pg_loss_fwd(desc, workspace=ws)
+    spo.spo_pg_loss_bwd(desc, logp, lse, d_W=d_W, workspace=ws)
+    spo.spo_pg_loss_fwd_bwd(desc, d_W=d_W, workspace=ws)
+    assert asked == ["sample_prompts", "advantages", "tracker_update", "pg_loss_fwd", "pg_loss_bwd", "pg_loss_fwd_bwd"]
