@@ -93,10 +93,12 @@ tracker_update_unique_kernel(float *__restrict__ alpha, float *__restrict__ beta
 // observation of every id per round: 952 us for a prompt step of 40000 responses to 20000 prompts,
 // 84 us now, 30 of them here before the lists were sorted by ranks.)  A list that might overflow is applied and restarted: the ids are read in
 // batch order, so what is applied earlier is earlier in the batch.
-// What is left is latency: the ids come kOwnChunk at a time, all of a thread's in flight together, and are counted before
-// they are filed, so that a list which cannot overflow takes three barriers per chunk (4096 ids requested at a time
-// and a barrier or two per 1024 of them: 26 us for that step, 18.5 now).
-constexpr int kOwnThreads = 512, kOwnCap = 4096, kOwnVecs = 8, kOwnVec = 4 * kOwnThreads, kOwnChunk = kOwnVecs * kOwnVec;
+// What is left is latency: the ids come a chunk of Vecs vectors per thread at a time, all of a thread's in flight together, and are
+// counted before they are filed, so that a list which cannot overflow takes three barriers per chunk (4096 ids
+// requested at a time and a barrier or two per 1024 of them: 26 us for that step, 18.5 now).  Up to kOwnCap ids need no
+// count, and a chunk is no longer than the list: with one length of chunk for all, 16 ids took 5.4 us, 1000 9.5 and
+// 5000 8.2, against 3.1, 6.3 and 7.1.
+constexpr int kOwnThreads = 512, kOwnCap = 4096, kOwnVec = 4 * kOwnThreads;
 static_assert(kOwnVec <= kOwnCap, "the ids of one vector per thread fit an empty list");
 typedef int32_t i32x4u_t __attribute__((ext_vector_type(4), aligned(4)));  // (the list may start anywhere)
 constexpr int kOwnSpan = 2048;          // sorted observations whose rewards and discounts are in LDS at a time
@@ -107,7 +109,7 @@ constexpr int kOwnPerGroup = 128;       // observations per workgroup below that
 // 88 -> 84 us).  The reads grow with n * n: longer lists keep the bitonic sort.
 constexpr int kOwnRank = 256;
 
-template <bool Ema>
+template <bool Ema, int Vecs>
 __global__ void __launch_bounds__(kOwnThreads)
 tracker_update_owned_kernel(float *__restrict__ alpha, float *__restrict__ beta, int64_t N,
                             const int32_t *__restrict__ idx, const float *__restrict__ reward,
@@ -118,7 +120,17 @@ tracker_update_owned_kernel(float *__restrict__ alpha, float *__restrict__ beta,
     __shared__ double rho[kOwnSpan];
     __shared__ float rew[kOwnSpan];
     __shared__ int count, coming;
+    constexpr int kOwnVecs = Vecs, kOwnChunk = Vecs * kOwnVec;
+    constexpr bool kOnce = kOwnChunk <= kOwnCap;  // launched for one chunk at most, which the list holds
     const int tid = threadIdx.x;
+    auto mine = [&](int32_t i) {
+        return static_cast<uint32_t>(i) < static_cast<uint32_t>(N) &&
+               static_cast<uint64_t>(static_cast<uint32_t>(i) * 0x9E3779B1u) >> shift == blockIdx.x;
+    };
+    auto out_of_range = [&](int64_t k) {
+        if (info) atomicOr(&info[0], kInfoRange);
+        if (v_prev) v_prev[k] = __builtin_nanf("");
+    };
     // applies the n observations in key[] (n is the same in every thread)
     auto apply_list = [&](int n) {
         if (n <= kOwnRank) {  // every key counts the smaller ones (keys are distinct)
@@ -175,6 +187,21 @@ tracker_update_owned_kernel(float *__restrict__ alpha, float *__restrict__ beta,
         }
     };
     if (tid == 0) count = 0;
+    if constexpr (kOnce) {
+        int32_t id[4 * Vecs];
+#pragma unroll
+        for (int j = 0; j < 4 * Vecs; ++j) id[j] = j * kOwnThreads + tid < B ? idx[j * kOwnThreads + tid] : 0;
+        __syncthreads();  // the count is set
+#pragma unroll
+        for (int j = 0; j < 4 * Vecs; ++j) {
+            const int k = j * kOwnThreads + tid;
+            if (k >= B) continue;
+            if (mine(id[j])) key[atomicAdd(&count, 1)] = static_cast<uint64_t>(id[j]) << 32 | static_cast<uint32_t>(k);
+            else if (blockIdx.x == 0 && static_cast<uint32_t>(id[j]) >= static_cast<uint32_t>(N)) out_of_range(k);
+        }
+        __syncthreads();
+        return apply_list(count);
+    }
     for (int64_t base = 0; base < B; base += kOwnChunk) {
         i32x4u_t id[kOwnVecs];
         if (tid == 0) coming = 0;
@@ -185,10 +212,6 @@ tracker_update_owned_kernel(float *__restrict__ alpha, float *__restrict__ beta,
 #pragma unroll
                 for (int e = 0; e < 4; ++e) v[e] = k + e < B ? idx[k + e] : 0;
             }
-        };
-        auto mine = [&](int32_t i) {
-            return static_cast<uint32_t>(i) < static_cast<uint32_t>(N) &&
-                   static_cast<uint64_t>(static_cast<uint32_t>(i) * 0x9E3779B1u) >> shift == blockIdx.x;
         };
         auto file = [&](int64_t k) { key[atomicAdd(&count, 1)] = static_cast<uint64_t>(idx[k]) << 32 | static_cast<uint32_t>(k); };
 #pragma unroll
@@ -212,9 +235,7 @@ tracker_update_owned_kernel(float *__restrict__ alpha, float *__restrict__ beta,
 #pragma unroll 1
             for (int j = 0; j < 4 * kOwnVecs; ++j) {
                 const int64_t k = base + (j >> 2) * kOwnVec + tid * 4 + (j & 3);
-                if (k >= B || static_cast<uint32_t>(idx[k]) < static_cast<uint32_t>(N)) continue;
-                if (info) atomicOr(&info[0], kInfoRange);
-                if (v_prev) v_prev[k] = __builtin_nanf("");
+                if (k < B && static_cast<uint32_t>(idx[k]) >= static_cast<uint32_t>(N)) out_of_range(k);
             }
         __syncthreads();  // coming is cleared, the list of the chunk before is complete
         if (own) atomicAdd(&coming, __popc(own));
@@ -575,8 +596,11 @@ static int tracker_update_launch(float *alpha, float *beta, int64_t N, const int
     } else {
         int bits = 0;
         while (1 << bits < kOwnGroups && (static_cast<int64_t>(kOwnPerGroup) << bits) < B) ++bits;
-        tracker_update_owned_kernel<Ema><<<1u << bits, kOwnThreads, 0, s>>>(alpha, beta, N, idx, reward, kl, B, d_half, rho_min,
-                                                                            rho_max, n_obs, v_prev_out, info, 32 - bits);
+        auto *kernel = B <= kOwnVec       ? tracker_update_owned_kernel<Ema, 1>
+                       : B <= 2 * kOwnVec ? tracker_update_owned_kernel<Ema, 2>
+                       : B <= 4 * kOwnVec ? tracker_update_owned_kernel<Ema, 4>
+                                          : tracker_update_owned_kernel<Ema, 8>;
+        kernel<<<1u << bits, kOwnThreads, 0, s>>>(alpha, beta, N, idx, reward, kl, B, d_half, rho_min, rho_max, n_obs, v_prev_out, info, 32 - bits);
     }
     return launch_status();
 }

@@ -555,6 +555,9 @@ def test_diagnostics_kept_in_registers(spo, B):
 
 
 @pytest.mark.parametrize("B,N,hot,offset", [
+    (6, 40, 0.5, 1), (512, 300, 0.0, 0), (2048, 900, 0.0, 1), (2049, 40, 0.5, 2),    # lists that need no count: one length of
+    (4096, 1, 0.0, 1), (4096, 20000, 0.0, 0),                                        # chunk and the next
+    (4097, 20000, 0.9, 3), (8192, 300, 0.0, 0), (8193, 300, 0.9, 1),                 # counted, shorter chunks and the long ones
     (16383, 5000, 0.0, 0), (16385, 5000, 0.0, 1),   # one chunk of ids and a little more, from an odd place on
     (40000, 300, 0.0, 0),                           # few prompts: long lists, sorted by the other sort
     (33000, 20000, 0.9, 3)])                        # one prompt with most of them: lists applied and restarted
