@@ -24,10 +24,15 @@ struct Claims {
 
     // Settles slot k and the slots displaced on the way; returns the highest attempt reached.
     //   draw(k, n)    candidate of attempt n of slot k
+    //   peek(c)       what the claim on c is, or was at any time before
     //   claim(c, v)   atomic minimum of the claim on c and v, returning what was there
     //   fail(k)       slot k has run out of attempts
-    template <typename Draw, typename Claim, typename Fail>
-    __host__ __device__ __forceinline__ static uint32_t settle(uint32_t k, uint32_t max_attempts, Draw draw, Claim claim, Fail fail) {
+    // Claims only fall, so a slot that finds a lower one where it looks is turned away for good, without an atomic.
+    // From attempt kLookFirst on it looks before it claims: few slots come so far while prompts are free, and where
+    // nearly all are taken the atomics of all slots would meet at the same addresses.
+    static constexpr uint32_t kLookFirst = 4;
+    template <typename Draw, typename Peek, typename Claim, typename Fail>
+    __host__ __device__ __forceinline__ static uint32_t settle(uint32_t k, uint32_t max_attempts, Draw draw, Peek peek, Claim claim, Fail fail) {
         uint32_t attempt = 0, most = 0;
         for (;;) {
             most = attempt > most ? attempt : most;
@@ -35,7 +40,12 @@ struct Claims {
                 fail(k);
                 return most;
             }
-            const int32_t c = draw(k, attempt), mine = filed(k, attempt), was = claim(c, mine);
+            const int32_t c = draw(k, attempt), mine = filed(k, attempt);
+            if (attempt >= kLookFirst && peek(c) < mine) {
+                ++attempt;
+                continue;
+            }
+            const int32_t was = claim(c, mine);
             if (was == kNoOwner) return most;
             if (was > mine) {  // displaced (a slot never meets a claim of its own)
                 k = slot(was);

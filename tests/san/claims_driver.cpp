@@ -64,12 +64,28 @@ static uint64_t run(std::mt19937 &rng, bool threads) {
     std::vector<std::atomic<int32_t>> failed(t.B);
     for (auto &f : failed) f = 0;
     std::atomic<uint32_t> most{0};
+    // claims of a prompt as they were, for looks that see the past
+    std::vector<std::unique_ptr<std::atomic<int32_t>[]>> past(2);
+    for (auto &p : past) {
+        p.reset(new std::atomic<int32_t>[t.N]);
+        for (uint32_t c = 0; c < t.N; ++c) p[c] = kNoOwner;
+    }
+    const bool current = rng() % 2;  // looks see the claims as they are, or some as they were
+    std::atomic<uint32_t> wasted{0};  // late claims that a look would have spared
     auto settle = [&](uint32_t k) {
         const uint32_t m = C::settle(
             k, t.max_attempts, [&](uint32_t s, uint32_t n) { return t.draw(s, n); },
+            [&](int32_t c) {
+                if (threads) std::this_thread::yield();
+                const uint32_t how = (k + c) % 3;
+                return !current && how ? past[how - 1][c].load() : owner[c].load();
+            },
             [&](int32_t c, int32_t v) {
                 if (threads) std::this_thread::yield();
                 int32_t was = owner[c].load();
+                wasted += was < v && (static_cast<uint32_t>(v) & ((1u << Bits) - 1)) >= C::kLookFirst;
+                past[1][c] = past[0][c].load();
+                past[0][c] = was;
                 while (!owner[c].compare_exchange_weak(was, std::min(was, v))) {}
                 return was;
             },
@@ -98,6 +114,10 @@ static uint64_t run(std::mt19937 &rng, bool threads) {
         }
     if (most != want_most) {
         std::fprintf(stderr, "bits %d: highest attempt %u, rule %u\n", Bits, most.load(), want_most);
+        std::exit(1);
+    }
+    if (current && !threads && wasted) {
+        std::fprintf(stderr, "bits %d: %u claims from attempt %u on where a lower one stands\n", Bits, wasted.load(), C::kLookFirst);
         std::exit(1);
     }
     return saturated;
