@@ -132,8 +132,8 @@ int spo_sample_prompts_static(const float *alpha, const float *beta, int64_t N, 
  * ws           optional, spo_advantages_workspace_bytes(B) bytes, 256-byte aligned.
  *              Without it one workgroup does all the work (right for the batches
  *              of the paper; from 16385 responses on it reads the batch three times, slow
- *              beyond ~10^5 responses); with it, batches of more than 1024 responses are spread
- *              over the chip (partial sums of 256 responses each, beyond 65536 of 4096, added in a fixed
+ *              beyond ~10^5 responses); with it, batches of more than 1024 to 3072 responses, by
+ *              the table's size, are spread over the chip (partial sums of 256 responses each, beyond 65536 of 4096, added in a fixed
  *              order; a workspace that has room for partial sums of 4096 responses only is accepted and
  *              spreads batches of 16384 or more).  Both forms are bitwise reproducible; between them the
  *              statistics agree to fp64 rounding.

@@ -637,9 +637,12 @@ extern "C" int spo_tracker_init(const float *v0, int64_t N, float rho_min, float
     return launch_status();
 }
 
-// Batches of one response per thread are as fast in one workgroup (kAdvThreads; 4096 responses there 15.4 us, one
-// compute unit fetching as many lines, in 16 workgroups of two launches 4.6 + 4.5); up to kAdvNarrowMost workgroups of
-// kAdvNarrow responses follow, then ones of kAdvSpan.
+// Responses that one workgroup takes although there is a workspace: what two launches cost is gained back where a compute unit
+// waits for lines of memory, later where they come from the L2, latest where the table is a few lines per response or there is
+// none.  (us in one workgroup and in two launches: 1025 responses to 2^20 prompts 7.8 and 6.6, 4096 15.1 and 7.6; 2048 to 2^18
+// prompts 6.9 and 6.6, 1300 6.05 and 6.1; 2500 to 20000 6.6 and 6.6, 1025 5.8 and 6.3; 3000 to 1000 6.4 and 6.6.)
+static int adv_one_workgroup(int64_t N) { return (N > int64_t(1) << 18 ? 1 : N > int64_t(1) << 15 ? 2 : 3) * kAdvThreads; }
+// Above, up to kAdvNarrowMost workgroups of kAdvNarrow responses, then ones of kAdvSpan.
 constexpr int kAdvNarrowMost = 256;
 static size_t adv_parts_bytes(int B, int span) { return static_cast<size_t>(2 * ceil_div(B, span)) * sizeof(double); }
 
@@ -669,7 +672,7 @@ extern "C" int spo_advantages(const float *alpha, const float *beta, int64_t N, 
         second<<<nb, threads, 0, s>>>(alpha, beta, idx, reward, B, ddof, eps_norm, use_baseline, adv_raw, adv_norm, stats, N, info, part);
         return launch_status();
     };
-    if (ws && B > kAdvThreads && B <= kAdvNarrowMost * kAdvNarrow && ws_bytes >= adv_parts_bytes(B, kAdvNarrow))
+    if (ws && B > adv_one_workgroup(use_baseline ? N : 0) && B <= kAdvNarrowMost * kAdvNarrow && ws_bytes >= adv_parts_bytes(B, kAdvNarrow))
         return two(advantages_wide_kernel<0, kAdvNarrow, 1>, advantages_wide_kernel<1, kAdvNarrow, 1>, kAdvNarrow, kAdvNarrow);
     if (ws && B >= 4 * kAdvSpan)
         return two(advantages_wide_kernel<0, kAdvThreads, kAdvPer>, advantages_wide_kernel<1, kAdvThreads, kAdvPer>, kAdvSpan, kAdvThreads);

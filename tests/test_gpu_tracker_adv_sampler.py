@@ -542,6 +542,26 @@ def test_advantages_spread_from_small_batches_on(spo, oracle, B):
         np.testing.assert_allclose(st.cpu().numpy(), [mu, sigma], rtol=RTOL, atol=1e-7)
 
 
+@pytest.mark.parametrize("N,most", [(0, 3072), (1000, 3072), (1 << 15, 3072), (40000, 2048), (300000, 1024)])   # 0: no baseline
+@pytest.mark.parametrize("more", [0, 1])
+def test_advantages_of_small_tables_stay_in_one_workgroup(spo, oracle, N, most, more):
+    # which shows in the workspace: only launches over several workgroups write to it
+    B = most + more
+    say(f"advantages of {B} responses to {N} prompts")
+    rng = np.random.default_rng([N, B])
+    a, b = (rng.uniform(0.5, 50, max(N, 1)).astype(np.float32) for _ in range(2))
+    idx = rng.integers(0, max(N, 1), B).astype(np.int32)
+    r = (rng.random(B) < 0.4).astype(np.float32)
+    eraw, enrm, (mu, sigma) = oracle.advantages(a, b, idx, r, 0, 0.0, N > 0)
+    ws = torch.full((spo.lib().spo_advantages_workspace_bytes(B),), 255, dtype=torch.uint8, device="cuda")
+    raw, nrm, st = spo.spo_advantages(dev(a), dev(b), dev(idx), dev(r), use_baseline=N > 0, workspace=ws)
+    torch.cuda.synchronize()
+    assert bool((ws == 255).all()) == (more == 0)
+    np.testing.assert_allclose(raw.cpu().numpy(), eraw, rtol=RTOL, atol=1e-7)
+    np.testing.assert_allclose(nrm.cpu().numpy(), enrm, rtol=RTOL, atol=1e-6)
+    np.testing.assert_allclose(st.cpu().numpy(), [mu, sigma], rtol=RTOL, atol=1e-7)
+
+
 @pytest.mark.parametrize("B", [1, 8192, 8193, 24576, 24577, 40960, 40961])   # 8, 24, 40 responses per thread, any number
 def test_diagnostics_kept_in_registers(spo, B):
     say(f"diagnostics, B={B}")
