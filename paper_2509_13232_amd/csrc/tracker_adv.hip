@@ -475,7 +475,8 @@ advantages_wide_kernel(const float *__restrict__ alpha, const float *__restrict_
 // Diagnostics of the unnormalised advantages (one workgroup, fp64, fixed order).  Bound by the latency
 // of a thread's loads and by its fp64 instructions: up to PER responses per thread stay in registers for both passes, all
 // loads in flight together, a thread adds up its own in two chains (40000 responses: 14.5 us with eight
-// requested at a time and a second pass over memory, 11.9 now).  PER = 0 is the form without a limit: kDiagAhead responses
+// requested at a time and a second pass over memory, 11.9 now; 8 and
+// 8193 of them 6.4 and 7.7 us then, 6.6 and 7.9 by the kernels of 8 and 24 per thread, 6.3 and 7.4 by those of 1 and 12).  PER = 0 is the form without a limit: kDiagAhead responses
 // requested at a time, and only a thread's last group asks which of its responses exist (10^6 responses: 275 us if every
 // group does, 194).
 constexpr int kDiagAhead = 8;
@@ -563,7 +564,9 @@ extern "C" int spo_advantage_diagnostics(const float *adv_raw, const float *rewa
                                          float tau_loose, float *diag, spo_stream_t stream) {
     if (!adv_raw || !reward || !diag) return SPO_ENULL;
     if (B < 1 || !(tau_tight >= 0.0f) || !(tau_loose >= tau_tight)) return SPO_EINVAL;
-    auto *kernel = B <= 8 * kAdvThreads    ? advantage_diagnostics_kernel<8>
+    auto *kernel = B <= kAdvThreads        ? advantage_diagnostics_kernel<1>
+                   : B <= 8 * kAdvThreads  ? advantage_diagnostics_kernel<8>
+                   : B <= 12 * kAdvThreads ? advantage_diagnostics_kernel<12>
                    : B <= 24 * kAdvThreads ? advantage_diagnostics_kernel<24>
                    : B <= 40 * kAdvThreads ? advantage_diagnostics_kernel<40>
                                            : advantage_diagnostics_kernel<0>;

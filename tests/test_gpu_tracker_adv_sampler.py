@@ -562,7 +562,7 @@ def test_advantages_of_small_tables_stay_in_one_workgroup(spo, oracle, N, most, 
     np.testing.assert_allclose(st.cpu().numpy(), [mu, sigma], rtol=RTOL, atol=1e-7)
 
 
-@pytest.mark.parametrize("B", [1, 8192, 8193, 24576, 24577, 40960, 40961])   # 8, 24, 40 responses per thread, any number
+@pytest.mark.parametrize("B", [1, 1024, 1025, 8192, 8193, 12288, 12289, 24576, 24577, 40960, 40961])   # 1, 8, 12, 24, 40 per thread, any number
 def test_diagnostics_kept_in_registers(spo, B):
     say(f"diagnostics, B={B}")
     rng = np.random.default_rng([B, 4])
