@@ -1,4 +1,5 @@
-// Which form of the LM head the contractions read: sizes alone decide, so this runs on any host.
+// Which form of the LM head the contractions read, and what the 32-bit offsets inside a tile bound: sizes alone decide, so
+// this runs on any host.
 #pragma once
 
 #include <stdint.h>
@@ -16,6 +17,11 @@ static inline bool rows_fit_offsets(int64_t H, int64_t V) {
     const int64_t rows = H < kTileRows ? H : kTileRows;  // H is a multiple of 64
     return rows * 2 * V < int64_t(1) << 32;
 }
+
+// The logit gradients of a chunk of tokens lie in blocks of 64 vocabulary entries, 128 bytes per token; d_W reads kTileRows / 64
+// blocks side by side, 64 tokens at a time.  Chunks are no longer than those offsets allow (11.2 million tokens; only
+// vocabularies of a few hundred entries would otherwise have longer ones by default).
+constexpr int64_t kMostChunkTokens = ((int64_t(1) << 32) - 64 * 128) / ((kTileRows / 64 - 1) * 128) / 256 * 256;
 
 // Is a bf16 head read as it was given, or copied into the forms that the main loop reads fastest?  Columns along k
 // (dHidden of a head [V,H], the logits of one [H,V]) and rows that are not blocked cost 2 to 5 % of a contraction, and

@@ -1538,7 +1538,7 @@ static bool small_dW(int64_t T, int64_t H, int64_t V) {
     return small_is_faster(time);
 }
 
-static_assert(TL::BN <= kTileRows && TS::BN <= kTileRows && kBK <= 64, "what rows_fit_offsets counts");
+static_assert(TL::BN <= kTileRows && TS::BN <= kTileRows && kBK <= 64 && kBlockK == 64 && kMostChunkTokens % TL::BN == 0, "what head_form.hpp counts");
 static bool direct_head(const spo_pg_desc *d) {
     return direct_head(d->dtype == SPO_BF16, d->w_layout == SPO_W_HV, d->T, d->H, d->V);
 }
@@ -1695,7 +1695,7 @@ static BwdPlan plan_bwd(const spo_pg_desc *d, int64_t chunk_tokens, void *ws, bo
     p.V_pad = round_up(d->V, kBK);
     p.V_blk = round_up(d->V, TL::BM);
     const int64_t tc = chunk_tokens > 0 ? round_up(chunk_tokens, TL::BN) : default_chunk_tokens(d->H, p.V_blk);
-    p.Tc = std::min(tc, Tmax);
+    p.Tc = std::min({tc, Tmax, kMostChunkTokens});
     p.Kc = d->dtype == SPO_FP32 ? kSplitTerms * d->H : d->H;
     Arena a(ws);
     p.count = a.take<double>(1);
@@ -1997,7 +1997,7 @@ static FbPlan plan_fb(const spo_pg_desc *d, int64_t chunk_tokens, void *ws, bool
     // logit gradients likewise
     int64_t tz = chunk_tokens > 0 ? round_up(chunk_tokens, TL::BN) : kDzBudgetBytes / (2 * p.V_blk) / 4096 * 4096;
     if (tz < TL::BN) tz = TL::BN;
-    p.Tz = std::min(tz, p.T_pad);
+    p.Tz = std::min({tz, p.T_pad, kMostChunkTokens});
     p.small = roomy && small_sweep(std::min(p.Tz, d->T), d->V, p.Kc);
     p.room = sweep_splits(p.Tz / TL::BN, p.nVt, kSlots<TL>) * p.Tz;
     if (roomy) p.room = std::max(p.room, sweep_room(p.Tz, d->V, true));

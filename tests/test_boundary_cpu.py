@@ -180,3 +180,16 @@ def test_one_call_workspace_of_a_masked_batch_serves_one_without_a_mask(L, dtype
             for chunk in (0, 256, 4096):
                 for T in TOKENS[::4]:
                     assert size(T, V, H, chunk, True) >= size(T, V, H, chunk, False) > 0, (T, V, H, chunk)
+
+
+@pytest.mark.parametrize("mask", [False, True])
+def test_chunks_are_as_long_as_offsets_inside_a_tile_allow(L, mask):
+    # blocks of 64 entries of a chunk's logit gradients lie 128 bytes per token apart, a tile reads four of them: 3 blocks,
+    # 63 tokens and the last piece of a row stay below 2^32 bytes
+    most = 11184640
+    assert 3 * most * 128 + 63 * 128 + 112 < 1 << 32 <= 3 * (most + 256) * 128 + 63 * 128 + 112
+    for q in (L.spo_pg_loss_bwd_workspace_bytes, L.spo_pg_loss_fwd_bwd_workspace_bytes):
+        size = lambda T, chunk: q(_pg_desc(T, 250, 64, 1, 0, mask), chunk)
+        for chunk in (0, 1 << 24, (1 << 31) - 1):
+            assert size(1 << 24, chunk) == size(1 << 24, most)
+            assert size(most, chunk) == size(most, most) > size(most, most - 256)
