@@ -477,6 +477,29 @@ def test_masked_batches_with_and_without_stored_logits(spo, T, H, chunk, w_layou
         assert float((got.double() - ref).abs().max()) <= 2e-2 * float(ref.abs().max())
 
 
+@pytest.mark.parametrize("T,H,V,dtype,mask_frac", [
+    (1000, 64, 17904, "bf16", None),    # small tiles, a contraction of one step: three tiles per workgroup
+    (1000, 128, 17904, "bf16", None),   # of two steps
+    (300, 448, 33000, "bf16", 0.2),     # logits stored from small tiles, two of them per workgroup
+    (300, 64, 40000, "fp32", 0.2),      # the same, six steps of a split contraction
+    (713, 128, 40000, "bf16", None),    # large tiles, two steps, two tiles
+    (1000, 512, 60000, "bf16", 0.2)])   # logits stored from large tiles, several of them
+@pytest.mark.parametrize("w_layout", [0, 1])
+def test_runs_of_tiles_that_are_stored(spo, T, H, V, dtype, mask_frac, w_layout):
+    # the next tile's operands are requested in the last step of a tile, whose stores are still on their way then
+    say(f"one call, {dtype} T={T} H={H} V={V} mask={mask_frac} layout={w_layout}: runs of tiles")
+    case = Case(wl.scaled(MID, name="runs", H=H, V=V, dtype=dtype), [T // 3, T - T // 3], mask_frac=mask_frac)
+    case.old = np.zeros(T, np.float32)
+    case.old = (torch_reference(case)[1].cpu().numpy() + 0.1 * case.noise).astype(np.float32)  # no ratio near a clip bound
+    loss, logp, gx, gw = torch_reference(case)
+    fwd, dx, dw = run_fwd_bwd(spo, case, w_layout, one_call=True)
+    assert abs(fwd[0].item() - loss) <= 2e-3 * abs(loss) + 1e-7
+    assert (fwd[1].double() - logp).abs().max() < 2e-4
+    for got, ref in ((dx, gx), (dw, gw)):
+        assert float((got.double() - ref).norm() / ref.norm()) < GRAD_TOL
+        assert float((got.double() - ref).abs().max()) <= 2e-2 * float(ref.abs().max())
+
+
 @pytest.mark.parametrize("T,H,V", [
     (100, 64, 40),          # one stage of 40 entries
     (300, 128, 104),        # two
