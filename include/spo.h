@@ -322,8 +322,8 @@ int spo_pg_loss_bwd(const spo_pg_desc *d, const float *logp, const float *lse, f
  *    grows with the square of the ratio: an unclipped token whose ratio exceeds
  *    about e^40 overflows it (spo_pg_loss_bwd, whose factor is linear in the ratio,
  *    reaches e^80).
- *  - mask != NULL: fp16 of the logit minus an offset per (token, 128 vocabulary
- *    entries), the largest logit the sweep has met for that token up to there.  An
+ *  - mask != NULL: fp16 of the logit minus an offset per (token, 64 or 128
+ *    vocabulary entries), the largest logit that one wavefront of the sweep has met for that token up to there.  An
  *    entry within d of its row's largest logit is stored within d of zero, where
  *    fp16 resolves d * 2^-11: the error this adds to a probability p is at most
  *    p * ln(1/p) * 2^-11.  One pass then turns the stored logits of the tokens with a

@@ -90,8 +90,6 @@ struct Tile {
         return wave_n0() + fn * MI + (threadIdx.x & (MI - 1));
     }
     static constexpr int GROUPS = kWave / MI;  // lane groups that hold different rows of the same column
-    static constexpr int RUNS = ACC_R / 4;     // runs of four consecutive rows per block and lane
-    __device__ static __forceinline__ int lane_group() { return (threadIdx.x & 63) / MI; }
     // Row d of the wavefront's part of the tile (0 <= d < WM) lives in block fm, register r of
     // the lanes of group g.
     __device__ static __forceinline__ void locate(int d, int &fm, int &r, int &g) {

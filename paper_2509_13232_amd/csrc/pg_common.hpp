@@ -89,8 +89,9 @@ constexpr int kTokWaves = 16;       // most wavefronts per workgroup
 
 // How a launch over n_blocks blocks is cut: four splits for each of `ways` wavefronts while the blocks alone do not
 // fill the chip (kTokChipWaves), and from kTokFewBlocks on several blocks per workgroup, more where there would be
-// more than kTokChipGroups workgroups: their counts meet at one address, 11 ns apart.  (200000 tokens of two splits:
-// 19 us, 27 with four blocks per workgroup and 71 with one, of 16 wavefronts, while the count still wrote caches back.)
+// more than kTokChipGroups workgroups: their counts meet at one address.  (200000 tokens of two splits: 19 us, 27 with four
+// blocks per workgroup and 71 with one, of 16 wavefronts.  Fitted while a count still wrote caches back, 11 ns each, and
+// not again since it does not: it may be cheaper now.)
 constexpr int kTokChipWaves = 2048, kTokChipGroups = 512, kTokFewBlocks = 64;
 struct TokenShape {
     unsigned blocks, threads;
@@ -199,8 +200,10 @@ token_loss_kernel(const float *__restrict__ part_max, const float *__restrict__ 
     if (threadIdx.x == 0) {
         const int mine = static_cast<int>(n_blocks - first < per_wg ? n_blocks - first : per_wg);
         // Stores and loads that every XCD sees, and a wait for them before the count: a count that releases and acquires
-        // would write back and invalidate whole caches for these 32 bytes (with what is requested first above: forward,
-        // 100000 tokens at 64 x 128 39.1 -> 35.2 us, 8192 at 128 x 3000 29.1 -> 27.5, 25 at 384 x 30471 21.0 -> 20.3).
+        // would write back and invalidate whole caches for these 32 bytes.  That the sums are seen where the count is seen
+        // is a property of gfx950, not of the language's memory model: relaxed stores and loads at agent scope go past the
+        // caches of the XCD, and a store counts as done (vmcnt) when it is there.  (With what is requested first above: forward,
+        // 100000 tokens at 64 x 128 39.1 -> 35.2 us, 8192 at 128 x 3000 29.1 -> 27.5, 25 at 384 x 30471 21.0 -> 20.3.)
         for (int b = 0; b < mine; ++b) {
             FwdPartial *p = partials + (in.t_base / kTokThreads + first + b);
             __hip_atomic_store(&p->sum_obj, block_part[b].sum_obj, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

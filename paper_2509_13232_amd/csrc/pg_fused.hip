@@ -10,11 +10,11 @@
 //             walks the batch in pieces: the sweep of a piece also stores, at two
 //             bytes per logit, what the two contractions of that piece then
 //             read, so the logits are formed once.
-// The logits and dHidden run through the main loop of gemm_core.hpp in the form
-// D[m][n] = sum_k A[m][k] B[n][k] (a transposition kernel provides the head with
-// the vocabulary contiguous for dHidden); dW contracts over tokens, the row index
-// of both dZ and the hidden states, through the loop's second form
-// D[m][n] = sum_k A[k][m] B[k][n], so neither is copied.
+// The main loop of gemm_core.hpp takes every operand with the contraction index either contiguous or
+// as its row index.  dW contracts over tokens, the row index of both dZ and the hidden states, so
+// neither is copied.  The head is read as it was given by short bf16 batches (direct_head); otherwise a
+// preparation kernel provides it with one row per vocabulary entry for the logits and in
+// blocks along the vocabulary for dHidden.
 //
 // fp32 inputs use the same bf16 main loop: every value is split into three bf16
 // parts (x = x0 + x1 + x2) and the six leading cross products are laid side by
@@ -692,9 +692,9 @@ __device__ __forceinline__ uint32_t pack_f16x2_rn(float lo, float hi) {
 // written out, in the blocked layout of the logit gradients (token n of this launch, vocabulary
 // entry v at Z + (v / 64) * z_blk + n * 64 + v % 64).
 // Emit = kEmitLogits: fp16 of (logit - offset).  The offset is the running maximum of the token
-// over the 128 vocabulary rows per tile that the wavefront has seen so far in its sweep, this
-// tile included: one value per (vocabulary tile, half of the tile, token), written to
-// offs[(tile * 2 + half) * T_pad + n].  Stored values are <= 0, and an entry within d of the
+// over the TT::WM vocabulary rows per tile (128 of large tiles, 64 of small ones) that the wavefront has seen so far in its
+// sweep, this tile included: one value per (vocabulary tile, part of WM rows, token), written to
+// offs[(tile * WGM + part) * T_pad + n].  Stored values are <= 0, and an entry within d of the
 // row's largest logit is stored within d of zero, where fp16 resolves 2^-11 * d: the entries
 // that carry the softmax are the most exact ones.  Rows past the vocabulary are stored as -inf.
 // Emit = kEmitProbs: bf16 of exp(logit - r_n), with r_n a per-token reference known before the
@@ -776,7 +776,7 @@ fwd_sweep_kernel(const char *__restrict__ W, int64_t ldw_bytes, int64_t V, const
             const float c = -nm * kLog2e;
             // what is stored of an entry: a * value + b, with value the exponential (kEmitProbs: times
             // exp(nm - r), capped) or the logit itself (kEmitLogits: minus the offset, the largest logit the
-            // wavefront's 128 rows have shown for this token so far)
+            // wavefront's WM rows have shown for this token so far)
             float a = 0.0f, off = 0.0f;
             if (Emit == kEmitProbs) a = __builtin_amdgcn_exp2f(fminf(fmaf(nm, kLog2e, -ref[fn]), 126.0f));
             if (Emit == kEmitLogits) {
@@ -827,7 +827,10 @@ fwd_sweep_kernel(const char *__restrict__ W, int64_t ldw_bytes, int64_t V, const
     // Where tiles are stored they are a run: the first stages of the next tile are requested in the last step of this one,
     // and this one's stores (at least kStores per wavefront) are not waited for before its first step: 8192 tokens at 1024 x
     // 151936 6420 -> 6345 us, 11238 masked ones at 192 x 151936 4101 -> 4022, 20000 at 2048 x 60000 the same.  (Without stores
-    // it is 2 % slower, and so no gain for the recompute, whose records would have to wait in LDS.)
+    // it is 2 % slower, and so no gain for the recompute, whose records would have to wait in LDS.)  Large tiles then have more
+    // values between two tiles than registers: scaled probabilities spill 4 of them (a head [H,V] read as it is 20, its logits
+    // 13; without stores 8, the recompute 3), which come back in up to 10 four-byte loads per tile, none inside the loop over the
+    // steps.
     constexpr bool kRun = Emit != kEmitNone;
     constexpr int kStores = kRun ? TT::FN * (TT::FM / 4) * 2 : 0;
     typedef typename TT::template Loop<WCols, false> Tiles;
@@ -890,8 +893,8 @@ fwd_sweep_kernel(const char *__restrict__ W, int64_t ldw_bytes, int64_t V, const
 // dz[t][v] = g[t] * ([v == target[t]] - exp(z[t][v] - lse[t])), written once, in blocks
 // of kBlockK = 64 vocabulary entries: dz[t][v] at dZ + (v / 64) * dz_blk + t * 64 + v % 64
 // (dz_blk elements per block = rows of the chunk * 64).  dHidden reads the blocks as a
-// k-blocked operand (contraction over v: one block per k-step), dW reads four neighbouring
-// blocks as a matrix with the tokens as rows (contraction over t).  Entries with v >= V and
+// k-blocked operand (contraction over v: one block per k-step), dW reads the BM / 64
+// blocks of a tile as a matrix with the tokens as rows (contraction over t).  Entries with v >= V and
 // tokens past the active rows of their tile are written as zeros.  Token tiles that start at
 // or after the number of active rows of this chunk (device value n_act[0] - row_base) are
 // skipped altogether.
@@ -1036,13 +1039,11 @@ constexpr int kTailNone = 0, kTailWhole = 1, kTailCut = 2;  // what a launch doe
 // ----------------------------------------------------------------------------
 // backward, steps 2 and 3: plain contraction with a store / accumulate epilogue
 // ----------------------------------------------------------------------------
-// out[row(m)*ldo + n] (=|+=) sum_k A[m][k] B[n][k], or with KMajor
-// sum_k A[k][m] B[k][n] (rows of A and B are then readable up to the next multiple
-// of 8 elements past M and N).  An operand with a_blk / b_blk != 0 is stored in blocks
-// of kBlockK = 64 elements of its contiguous index, blk bytes apart, rows 128 bytes
-// apart inside a block: for the plain form that index is k (see Dma), for KMajor it is
-// m (n), and tile tm (tn) of the operand is made of the four blocks from 4 tm (4 tn) on
-// (see DmaK).
+// out[row(m)*ldo + n] (=|+=) sum_k A(m,k) B(n,k).  ACols, BCols: the operand has the contraction index as its row index
+// (rows then readable up to the next multiple of 8 elements past M or N), otherwise contiguous.  An operand with
+// a_blk / b_blk != 0 is stored in blocks of kBlockK = 64 elements of its contiguous index, blk bytes apart, rows
+// 128 bytes apart inside a block: that index is k, or (Cols) m or n, of which a tile takes BM / 64 blocks (see
+// Tile::Operand).
 // With n_act != NULL the extent that holds active tokens is read on the device
 // (rows = active_rows(n_act, row_base, .)): limit == kLimitRows keeps only the first
 // `rows` rows of A and stores row m at out row row_map[m] (dHidden: scatter back to the
@@ -1051,7 +1052,7 @@ constexpr int kTailNone = 0, kTailWhole = 1, kTailCut = 2;  // what a launch doe
 // do not add to the output): row m of the product is multiplied by row_scale[m] on its way out.
 constexpr int kLimitRows = 1, kLimitK = 2;
 
-// With nsplit > 1 (plain form only) the contraction is cut into nsplit equal runs of k-steps;
+// With nsplit > 1 (k contiguous in A only) the contraction is cut into nsplit equal runs of k-steps;
 // workgroup (tile, part) writes its fp32 partial tile to partials[part][m][n] (leading
 // dimension N) and reduce_split_kernel adds the parts in a fixed order: shapes with fewer
 // tiles than the chip has compute units still fill it, and the result does not depend on timing.
@@ -1367,10 +1368,10 @@ reduce_tail_kernel(const float *__restrict__ partials, int64_t M, int64_t N, int
 // ----------------------------------------------------------------------------
 // dZ[j][v] = g * ([v == target] - exp(z[v] - lse)) for the active tokens j of a piece of the
 // batch, from the fp16 offsets written by fwd_sweep_kernel<kEmitLogits> (z = stored value + offset of
-// the entry's half tile), into the blocked bf16 layout the two contractions read.
+// the entry's part of a tile, bph blocks of 64), into the blocked bf16 layout the two contractions read.
 // Row j of the output is token act_idx[j] of the piece; tok[j] is its record (see
-// gather_chunk_kernel); rows from the number of active tokens up to the next multiple of 256
-// are written as zeros, rows beyond are left alone (no contraction reads them).  A wavefront
+// gather_chunk_kernel); rows from the number of active tokens up to the next multiple of `edge`
+// (a tile's tokens) are written as zeros, rows beyond are left alone (no contraction reads them).  A wavefront
 // moves 8 rows x 128 bytes of one 64-entry block per step (16 bytes per lane), a workgroup 32
 // rows, over `per_wg` consecutive blocks.
 __global__ void __launch_bounds__(256)
@@ -1606,7 +1607,7 @@ int fused_fwd_workspace(const spo_pg_desc *d, size_t *bytes) {
 // The sweep of one piece of T tokens on tiles TT; W: the head as the sweep reads it (cols: [H,V]).
 struct Sweep {
     const void *W;
-    int64_t H, V, Kc;
+    int64_t V, Kc;
     bool cols;
     const void *X;
     int64_t T;
@@ -1646,7 +1647,6 @@ int fused_fwd(const spo_pg_desc *d, float *loss, float *logp, float *lse, float 
         launch_prep_with_targets(d, jobs, p.z_target, nullptr, 0, p.done, s);
         Sweep w{};
         w.W = fp32 ? p.Ws : direct || !p.Wvh ? d->W : p.Wvh;
-        w.H = d->H;
         w.V = d->V;
         w.Kc = p.Kc;
         w.cols = direct && hv;
@@ -2098,7 +2098,7 @@ int fused_fwd_bwd(const spo_pg_desc *d, float grad_loss, float *loss, float *log
         const int64_t nTt = Tzp / edge, nVt = ceil_div(V, edge);
         const SweepMap map(nTt, nVt, sweep_splits(nTt, nVt, tile_slots(p.small),
                                                   static_cast<uint32_t>(std::min<int64_t>(p.room / Tzp, kNoSplitCap))));
-        const Sweep w{Wk, H, V, p.Kc, direct && hv, Xk, Tv, p.part_max, p.part_sum, p.Z, Tzp * kBlockK, p.dense ? p.offs + t0 : p.offs};
+        const Sweep w{Wk, V, p.Kc, direct && hv, Xk, Tv, p.part_max, p.part_sum, p.Z, Tzp * kBlockK, p.dense ? p.offs + t0 : p.offs};
         const bool back = d_hidden || d_W, again = form_again(d);
         if ((rc = p.dense  ? launch_sweep<kEmitProbs>(w, p.small, map, s)
                   : again ? launch_sweep<kEmitNone>(w, p.small, map, s)
