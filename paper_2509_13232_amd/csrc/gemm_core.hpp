@@ -311,7 +311,7 @@ struct Tile {
     // Column of the j-th block of a slice: along a row of blocks and back along the next, so that every instruction
     // shares an operand with the one before.  What changes hands costs power, which is what bounds large batches
     // (register-only loops 1985 -> 1995 TFLOP/s; 17043 tokens at 4096 x 151936 62.05 -> 61.84 ms, 46511 with a mask
-    // 108.07 -> 107.57).
+    // 108.07 -> 107.57, of which two runs of one side differ by half).
     __device__ static constexpr int snake(int j) { return (j / FN) & 1 ? FN - 1 - j % FN : j % FN; }
 
     template <bool Across>

@@ -24,6 +24,7 @@
 #include "gemm_core.hpp"
 #include "head_form.hpp"
 #include "pg_common.hpp"
+#include "tile_choice.hpp"
 #include "timing.hpp"
 
 namespace spo {
@@ -42,8 +43,9 @@ constexpr int kSweepSplits = 16;  // vocabulary splits of the forward sweep on l
 // partly filled round of tiles, so larger chunks (the caller's choice) are a little faster:
 // at H = 4096, V = 151936 the step takes about 1 % longer with 8 GiB than with 40 GB.
 constexpr int64_t kDzBudgetBytes = int64_t(8) << 30;
-constexpr int kChipCUs = 256;
 template <typename T> constexpr int kSlots = kChipCUs * 512 / T::NT;  // workgroups that the chip holds at a time
+static_assert(TS::BM == kSmallEdge && TL::BM == kLargeEdge && kSlots<TS> == 2 * kChipCUs && kSlots<TL> == kChipCUs && kBK == kStep,
+              "what tile_choice.hpp counts");
 constexpr int kTailTiles = kChipCUs;  // fp32 tiles of room for the parts of cut contractions (see launch_gemm)
 
 static int64_t gcd64(int64_t a, int64_t b) { return b ? gcd64(b, a % b) : a; }
@@ -1010,30 +1012,7 @@ recompute_dz_kernel(const char *__restrict__ W, int64_t ldw_bytes, int64_t V,
     }
 }
 
-// A launch ends in a partly filled round of tiles when its tile count is no multiple of the chip's
-// compute units.  A short last round (at most half of the units busy) is cut off: the tiles
-// before it run as they are, in whole rounds, and the `rem` tiles after them are each cut along the
-// contraction into `parts` runs whose partial results are added in a fixed order afterwards.  Host
-// and device code ask the same function, so the number of tiles may be known on the device only.
-// Tiles count in the order in which they are launched (TileOrder): the tiles that run are then whole rounds.  (Counted
-// row by row, the tiles left out were spread over the last patches, and where a band of patches is no divisor of a
-// round the rest took a round more: dHidden of 5000 x 3648 x 151936, 256 + 44 tiles, 6667 us, half of that now.)
-// k_steps: the contraction's length before it is limited on the device.  The steps that a cut saves have to be worth its
-// two launches and the parts' way through memory, 19 us together (a step of small tiles takes about half as long).
-constexpr int kCutSteps = 12;
-struct TailCut {
-    int64_t whole;  // tiles that run in whole rounds (all of them when nothing is cut)
-    int rem, parts;
-    __host__ __device__ __forceinline__ TailCut(int64_t tiles, int64_t k_steps, int slots) : whole(tiles), rem(0), parts(1) {
-        const int r = static_cast<int>(tiles % slots);
-        const int most = r > 0 ? (slots / r < 8 ? slots / r : 8) : 1;
-        if (most > 1 && (k_steps - k_steps / most) * kChipCUs >= kCutSteps * slots) {
-            whole = tiles - r;
-            rem = r;
-            parts = most;
-        }
-    }
-};
+// Host and device ask TailCut (tile_choice.hpp) what is cut off a launch's end.
 constexpr int kTailNone = 0, kTailWhole = 1, kTailCut = 2;  // what a launch does about a short last round
 
 // ----------------------------------------------------------------------------
@@ -1474,42 +1453,6 @@ static int allow_lds(K kernel, int bytes) {
 static inline int64_t round_up(int64_t x, int64_t a) { return ceil_div(x, a) * a; }
 static inline unsigned grid1(int64_t n, int per = 256) { return static_cast<unsigned>(ceil_div(n, per)); }
 
-// Small or large tiles?  A launch takes about
-//   rounds of workgroups on the chip x (steps of a tile x time of a step + time of a tile's ends) + the rest, in us,
-// with times fitted to 24 to 8000 tokens, H = 192 to 4096, V = 1000 to 151936.  What this chooses is within 1 % of the
-// better of the two on average (large tiles always: 25 to 30 % behind, small ones: 3 %), and within 25 % where it errs.
-// Up to kChipCUs small tiles have a compute unit each, above two share one; their steps take longer where the head does
-// not fit the L2s (kHeadInL2).  In the limit of long launches 128 x 128 x 2 per compute unit take 0.55 to 0.75 of the time of
-// 256 x 256: twice the bytes per product.  (Loss and gradients of 512 fp32 tokens at 128 x 1000: 97 us on large tiles,
-// 68 on small; 31 bf16 tokens at 1024 x 151936 438 and 381; 4000 at 4096 x 30000 2406 and 2875.)
-struct TileTimes {
-    double step, ends;             // large tiles
-    double lone, in_l2, pair;      // a step of small ones: with a compute unit to itself, two on it with the head in the L2s or not
-    double ends_s;
-    double rest, rest_s, cut;      // of a launch, large and small; a cut tail
-};
-constexpr TileTimes kSweepTimes{1.30, 8.3, 0.57, 0.85, 0.90, 4.4, 4.6, 5.1, 0.0};
-constexpr TileTimes kDHiddenTimes{1.70, 4.6, 0.34, 0.75, 1.00, 0.0, 17.0, 15.4, 4.1};
-constexpr TileTimes kDWTimes{1.66, 10.7, 0.53, 0.75, 0.90, 7.0, 3.2, 2.1, 19.0};
-static double launch_time(const TileTimes &t, bool small, double rounds, int64_t wgs, int64_t steps, int64_t head_bytes) {
-    const double step = !small ? t.step : wgs <= kChipCUs ? t.lone : head_bytes <= kHeadInL2 ? t.in_l2 : t.pair;
-    return rounds * (static_cast<double>(steps) * step + (small ? t.ends_s : t.ends)) + (small ? t.rest_s : t.rest);
-}
-// the same of contractions whose short last round may be cut
-static double launch_time_cut(const TileTimes &t, bool small, int64_t tiles, int64_t steps, bool may_cut, int64_t head_bytes) {
-    const int slots = small ? kSlots<TS> : kSlots<TL>;
-    const TailCut cut(may_cut ? tiles : 0, steps, slots);
-    if (!cut.rem) return launch_time(t, small, static_cast<double>(ceil_div(tiles, slots)), tiles, steps, head_bytes);
-    return launch_time(t, small, static_cast<double>(cut.whole / slots) + 1.0 / cut.parts,
-                       cut.whole ? tiles : cut.rem * cut.parts, steps, head_bytes) + t.cut;
-}
-// Long launches run at the power cap, where the smaller tiles' extra traffic costs more than fitted: they have to be ahead
-// by an eighth there (dW of 40485 tokens at 512 x 86540: the whole call 11.38 ms on large tiles, 11.97 on small).
-static bool small_is_faster(const double (&time)[2]) { return time[1] < time[0] * (time[0] > 500.0 ? 0.875 : 1.0); }
-static int64_t tile_edge(bool small) { return small ? TS::BM : TL::BM; }
-static int tile_slots(bool small) { return small ? kSlots<TS> : kSlots<TL>; }
-static int dhidden_parts(int64_t Tc, int64_t H, int64_t V_pad, bool small);
-
 // the logits of T tokens, Kc values long each (forward sweep, recompute)
 static bool small_sweep(int64_t T, int64_t V, int64_t Kc) {
     double time[2];
@@ -1518,27 +1461,8 @@ static bool small_sweep(int64_t T, int64_t V, int64_t Kc) {
         const int64_t ns = sweep_splits(nTt, nVt, tile_slots(small)), rounds = ceil_div(nTt * ns, tile_slots(small)) * ceil_div(nVt, ns);
         time[small] = launch_time(kSweepTimes, small, static_cast<double>(rounds), nTt * ns, Kc / kBK, V * Kc * 2);
     }
-    return small_is_faster(time);
+    return small_is_faster(kSweepTimes, time);
 }
-static bool small_dhidden(int64_t T, int64_t H, int64_t V_pad) {
-    // large tiles that fill the chip by themselves: long steps of a vocabulary, where they are faster than fitted (16000
-    // tokens at 256 x 40000 343 and 432 us, 17497 at 640 x 35002 767 and 816, 11238 at 192 x 151936 743 and 1098)
-    if (dhidden_parts(T, H, V_pad, false) == 1) return false;
-    double time[2];
-    for (int small = 0; small < 2; ++small) {
-        const int64_t parts = dhidden_parts(T, H, V_pad, small), tiles = ceil_div(T, tile_edge(small)) * ceil_div(H, tile_edge(small));
-        time[small] = launch_time_cut(kDHiddenTimes, small, tiles * parts, ceil_div(V_pad / kBK, parts), parts == 1, H * V_pad * 2);
-    }
-    return small_is_faster(time);
-}
-static bool small_dW(int64_t T, int64_t H, int64_t V) {
-    double time[2];
-    for (int small = 0; small < 2; ++small)
-        time[small] = launch_time_cut(kDWTimes, small, ceil_div(V, tile_edge(small)) * ceil_div(H, tile_edge(small)), ceil_div(T, kBK), true,
-                                      H * V * 2);
-    return small_is_faster(time);
-}
-
 static_assert(TL::BN <= kTileRows && TS::BN <= kTileRows && kBK <= 64 && kBlockK == 64 && kMostChunkTokens % TL::BN == 0, "what head_form.hpp counts");
 static bool direct_head(const spo_pg_desc *d) {
     return direct_head(d->dtype == SPO_BF16, d->w_layout == SPO_W_HV, d->T, d->H, d->V);
@@ -1661,19 +1585,6 @@ int fused_fwd(const spo_pg_desc *d, float *loss, float *logp, float *lse, float 
         p.part_max, p.part_sum, p.nsplit, tok.ways, p.T_pad, p.z_target, token_inputs(d, 0, d->T), logp, lse, p.partials,
         TokenGrad{}, p.nblk_tok, p.nblk_tok, p.done, loss, stats);
     return launch_status();
-}
-
-// Parts that the contraction of dHidden over the vocabulary is cut into, for a chunk of Tc tokens: its
-// (Tc / 256) * ceil(H / 256) tiles leave more than a quarter of the chip idle.  A part takes some 1.4 us per
-// step of 64 entries and adds its tile to what reduce_split_kernel reads (64 MB for a chip full of parts,
-// 15 us): up to eight parts in any case, more while a part keeps kPartSteps steps.  (Loss then gradients
-// of 17 tokens at 896 x 151936, 4 tiles, 2374 steps: 948 us in 8 parts, 642 in 64; of 85 tokens at
-// 3264 x 15635, 13 tiles, 245 steps: 19 parts gain what 8 leave of the chip idle.)
-constexpr int64_t kPartSteps = 16;
-static int dhidden_parts(int64_t Tc, int64_t H, int64_t V_pad, bool small) {
-    const int64_t tiles = ceil_div(Tc, tile_edge(small)) * ceil_div(H, tile_edge(small)), slots = tile_slots(small);
-    if (tiles * 4 >= slots * 3) return 1;
-    return static_cast<int>(std::min<int64_t>(slots / tiles, std::max<int64_t>(8, V_pad / kBK / kPartSteps)));
 }
 
 struct BwdPlan {

@@ -70,3 +70,8 @@ def test_claims_of_a_draw_without_replacement_follow_the_sequential_rule(tmp_pat
 
 def test_heads_read_as_given_fit_the_offsets_of_the_main_loop(tmp_path):
     assert "heads read as given fit the offsets" in _run_host_part(tmp_path, "head_form")
+
+
+def test_shapes_get_the_tiles_that_are_well_ahead(tmp_path):
+    # what a launch on one kind of tiles takes is estimated; the estimates once missed where the operands come from
+    assert "tiles are the faster ones" in _run_host_part(tmp_path, "tile_choice")
