@@ -80,7 +80,7 @@ const char *spo_status_string(int status);
  *               and every v_i is 0 or 1) nothing can be drawn: all entries are
  *               -1 and info[0] = 1.
  * max_attempts  bound on attempts per slot (0 selects 65536).  Without replacement the
- *               slots draw side by side, 4 to 8 us per attempt (up to 190 where 16384 of
+ *               slots draw side by side, 1.4 to 8 us per attempt (9 where 16384 of
  *               them want the same prompt): a batch that takes most of the prompts with
  *               non-zero weight needs many attempts for its last slots (about N ln N
  *               draws to collect the last of N equal weights), so such a call can take
